@@ -201,6 +201,9 @@ bool mfma_linear_supported(int32_t M, int32_t N, int32_t K);
 int32_t launch_linear_mfma(const bf16_t* A, const bf16_t* W, const float* bias, int32_t M, int32_t N,
                            int32_t K, int32_t epi, bf16_t* out, float* resid, RowVec gate, hipStream_t s, int cu_share = 1,
                            const LnFold* ln = nullptr);
+// gemm_pipe.hip: the same product for many rows, K a multiple of 64 (called by launch_linear_mfma)
+int32_t launch_linear_pipe(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, int cu_share, const LnFold* ln);
 // shapes the folded-LayerNorm epilogues cover: M rows of width D normalised, rows_per_sample tokens per sample
 bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample);
 // the same kernel on fp32 operands (v_mfma_f32_32x32x2_f32), fp32 output

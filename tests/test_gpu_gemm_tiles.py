@@ -1,0 +1,71 @@
+"""The bf16 GEMM kernels at the sizes where their tiles and K loops can go wrong: remainders in rows and columns, one,
+two and three K slices, column halves of a tile that are all padding.  Reference: the same product in fp32 by
+torch on the bf16 values."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# A bf16 result is within 2^-9 of the value it rounds, so the 2-norm error is below 2^-9 = 2.0e-3 of the result; the fp32 sums
+# add K 2^-24 at worst (2.7e-4 for K = 4608, sqrt(K) 2^-24 = 4e-6 where errors are independent).
+BF16_TOL = 2.0e-3 + 3e-4
+# fp32 residual: sums in another order only, sqrt(4608) 2^-24 = 4e-6, five times that
+F32_TOL = 2e-5
+
+
+def _case(M, N, K, seed=0):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed + M + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    return (rnd(M, K).to(torch.bfloat16), (rnd(N, K) / K ** 0.5).to(torch.bfloat16), rnd(N),
+            rnd(M, N), rnd(1, N))
+
+
+def _rel(a, b):
+    return ((a.double() - b.double()).norm() / b.double().norm()).item()
+
+
+def check_linear(M, N, K):
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, resid, gate = _case(M, N, K)
+    ref = x.float() @ w.float().T + bias
+    out = binding.op_linear(x, w, bias, "bf16", binding.EPI_BIAS)
+    assert _rel(out, ref) < BF16_TOL
+    row = (out.float() - ref).norm(dim=1).max() / ref.norm(dim=1).mean()
+    assert row.item() < 2 * BF16_TOL                           # no single row is off
+    out = binding.op_linear(x, w, bias, "bf16", binding.EPI_BIAS_GELU)
+    assert _rel(out, torch.nn.functional.gelu(ref, approximate="tanh")) < BF16_TOL
+    got = resid.clone()
+    binding.op_linear(x, w, bias, "bf16", binding.EPI_GATE_RESID, resid=got, gate=gate, rows_per_sample=M)
+    ref = resid + gate * ref
+    assert _rel(got, ref) < F32_TOL
+    assert ((got - ref).norm(dim=1).max() / ref.norm(dim=1).mean()).item() < 5 * F32_TOL
+
+
+# gemm_pipe.hip: 384 x 192 tiles with one, two and three slices; 256 x 192; 256 x 256 with a column tile half of padding;
+# 192 x 256; a full and a ragged last round
+@pytest.mark.parametrize("M,N,K", [(4100, 4104, 64), (4100, 4104, 128), (4100, 4104, 192), (7000, 1160, 320),
+                                   (8190, 4608, 128), (12100, 1160, 256), (12200, 1024, 128)])
+def test_many_rows(M, N, K):
+    check_linear(M, N, K)
+
+
+@pytest.mark.parametrize("M,rows", [(8192, 256), (7680, 480), (12288, 1024)])
+def test_residual_update_with_row_sums(M, rows):
+    """z and the 128-column sums of the prepared LayerNorm from both tiles that write them (192 x 256 and 256 x 256)."""
+    import torch
+    from paper_2511_20390_amd import binding
+    N, K = 1152, 192
+    x, w, bias, resid, _ = _case(M, N, K, seed=1)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    mod = torch.randn(M // rows, 2 * N, generator=g, device="cuda")
+    gate, scale = mod[:, :N], mod[:, N:]
+    got = resid.clone()
+    z, stats = binding.op_linear_resid_prep(x, w, bias, got, gate, scale, rows)
+    ref = resid + gate.repeat_interleave(rows, 0) * (x.float() @ w.float().T + bias)
+    assert _rel(got, ref) < F32_TOL
+    assert _rel(z, got * (1 + scale.repeat_interleave(rows, 0))) < BF16_TOL
+    parts = got.double().view(M, N // 128, 128)
+    # sums of 128 fp32 values: 128 2^-24 of the sum of magnitudes at worst
+    assert (stats[..., 0] - parts.sum(-1)).abs().max().item() < 128 * 2 ** -24 * parts.abs().sum(-1).max().item()
+    assert _rel(stats[..., 1], (parts ** 2).sum(-1)) < 128 * 2 ** -24
