@@ -201,9 +201,17 @@ bool mfma_linear_supported(int32_t M, int32_t N, int32_t K);
 int32_t launch_linear_mfma(const bf16_t* A, const bf16_t* W, const float* bias, int32_t M, int32_t N,
                            int32_t K, int32_t epi, bf16_t* out, float* resid, RowVec gate, hipStream_t s, int cu_share = 1,
                            const LnFold* ln = nullptr);
-// gemm_pipe.hip: the same product for many rows, K a multiple of 64 (called by launch_linear_mfma)
+// the same product, K a whole number of slices, by two kernels that launch_linear_mfma chooses between:
+// gemm_pipe.hip (many rows; bf16, all epilogues) ...
+enum PipeTile { PIPE_256x256, PIPE_384x192, PIPE_256x192, PIPE_192x256, PIPE_192x128, PIPE_160x128, PIPE_128x128 };
 int32_t launch_linear_pipe(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, int cu_share, const LnFold* ln);
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, PipeTile tile, const LnFold* ln);
+// ... and gemm_rows.hip (few rows; N % 8 == 0 and 16-byte aligned operands, checked by linear_rows_covers)
+enum RowsTile { ROWS_64x64, ROWS_128x64, ROWS_128x128 };
+int32_t launch_linear_rows(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
+bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* bias, const void* out, const float* resid,
+                        const RowVec& gate);
 // shapes the folded-LayerNorm epilogues cover: M rows of width D normalised, rows_per_sample tokens per sample
 bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample);
 // the same kernel on fp32 operands (v_mfma_f32_32x32x2_f32), fp32 output

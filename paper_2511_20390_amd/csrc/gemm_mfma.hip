@@ -5,8 +5,8 @@
 // v_mfma_f32_32x32x16_bf16 (lane l: row/col l%32, 8 consecutive k at 8*(l/32)).
 //
 // Design for gfx950 (64-wide wavefronts, 160 KB LDS per CU, 512 registers per lane):
-//  * used for fp32 operands, for bf16 with K no multiple of the slice, and for bf16 problems of few rows; the large bf16
-//    problems are the pipelined kernel's (gemm_pipe.hip).
+//  * used for fp32 operands and for bf16 with K no multiple of the slice; bf16 problems of whole slices are chosen between
+//    the tiles of gemm_pipe.hip and gemm_rows.hip at the end of this file.
 //  * workgroup = 4 or 8 wavefronts in a WGM x WGN grid, macro tile BM x BN (256x256 and
 //    384x192 with 8 wavefronts - two per SIMD, so one wavefront's memory instructions issue
 //    under the other's MFMAs - 256x128 / 128x128 / 96x128 / 160x128 with 4 for small problems), K slices of
@@ -326,8 +326,8 @@ int32_t launch_one(const T* X, const T* W, const float* bias, int32_t M, int32_t
 template <typename T, int BM, int BN, int WGM, int WGN>
 int32_t launch_cfg(const T* X, const T* W, const float* bias, int32_t M, int32_t N, int32_t K,
                    int32_t epi, T* out, float* resid, RowVec gate, hipStream_t s) {
-    // (bf16 problems of whole slices that want an eight-wavefront tile go to gemm_pipe.hip)
-    constexpr bool kRaggedOnly = std::is_same<T, bf16_t>::value && WGM * WGN == 8;
+    // (bf16 problems of whole slices go to gemm_pipe.hip and gemm_rows.hip)
+    constexpr bool kRaggedOnly = std::is_same<T, bf16_t>::value;
     const bool even = !kRaggedOnly && (K % (kRowBytes / static_cast<int>(sizeof(T)))) == 0;
 #define FREE_GEMM_CASE(E)                                                                                              \
     case E:                                                                                                            \
@@ -370,7 +370,7 @@ double small_tile_time(int M, int N, int nk, double sc, int cus) {
 // is cut, never the order in which a dot product is summed, so the result does not depend on it.
 template <typename T>
 int32_t choose_and_launch(const T* X, const T* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                          T* out, float* resid, RowVec gate, hipStream_t s, int cu_share, const LnFold* ln) {
+                          T* out, float* resid, RowVec gate, hipStream_t s, int cu_share) {
     if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
     constexpr int kSliceElems = kRowBytes / static_cast<int>(sizeof(T));
     const double sc = sizeof(T) == 4 ? 4.4 : 1.0;
@@ -378,16 +378,6 @@ int32_t choose_and_launch(const T* X, const T* W, const float* bias, int32_t M, 
     const int cus = std::max(1, device_cus() / std::max(1, cu_share));
     const double t256 = cfg_time(M, N, nk, 256, 256, 1.83 * sc, 9.0, cus);
     const double t384 = cfg_time(M, N, nk, 384, 192, 2.06 * sc, 10.0, cus);
-    // bf16 with whole slices: the large tiles and the folded-LayerNorm epilogues are the pipelined kernel's (gemm_pipe.hip)
-    const bool pipe = std::is_same<T, bf16_t>::value && K % kSliceElems == 0;
-    auto launch_pipe = [&]() -> int32_t {
-        if constexpr (std::is_same<T, bf16_t>::value)
-            return launch_linear_pipe(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share, ln);
-        else
-            return FREE_ERR_SHAPE;
-    };
-    if (epi == FREE_EPI_LN_BIAS || epi == FREE_EPI_LN_BIAS_GELU || epi == FREE_EPI_GATE_RESID_PREP)
-        return pipe && ln != nullptr ? launch_pipe() : FREE_ERR_SHAPE;
     const double t2x1 = cfg_time(M, N, nk, 256, 128, 1.31 * sc, 6.0, cus);
     const double t128 = M <= 4096 ? small_tile_time(M, N, nk, sc, cus) : cfg_time(M, N, nk, 128, 128, 0.80 * sc, 4.0, cus);
     // 96 x 128 (one row of four wavefronts, each 96 x 32): for problems of few rows and few columns, where
@@ -409,11 +399,62 @@ int32_t choose_and_launch(const T* X, const T* W, const float* bias, int32_t M, 
     const double best = std::fmin(std::fmin(std::fmin(t256, t384), std::fmin(t2x1, t128)), std::fmin(t96, t160));
     if (best == t160) return launch_cfg<T, 160, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
     if (best == t96) return launch_cfg<T, 96, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    if (pipe && (best == t384 || best == t256)) return launch_pipe();
     if (best == t384) return launch_cfg<T, 384, 192, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
     if (best == t256) return launch_cfg<T, 256, 256, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
     if (best == t2x1) return launch_cfg<T, 256, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
     return launch_cfg<T, 128, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+}
+
+// Tile choice for bf16 problems of whole slices.  Time of a launch: `f` + per round of workgroups (nk slices + `e`), with
+// `a` us per slice for a workgroup that has its CU to itself and `b` each for two that share one (tiles of at most 80 KB of
+// LDS; `b` unused otherwise).  Fitted to the times of every tile at 40 values of M from 64 to 12288 and the four layer shapes
+// at widths 384, 768 and 1152, weights from HBM and from the caches in equal parts (rms error 10-16 % per tile); the tile
+// chosen is within 0.5 % of the best one on average, 11 % at worst (2048 x 4608 x 1152: 29.8 us for 26.9).  Tiles change how
+// the output is cut, never the order in which a dot product is summed, so the result does not depend on the choice.
+struct TileTime {
+    bool rows;                    // gemm_rows.hip / gemm_pipe.hip
+    int tile, bm, bn;
+    bool paired;                  // two workgroups fit a CU
+    double f, e, a, b;
+};
+constexpr TileTime kTiles[] = {
+    {true, ROWS_64x64, 64, 64, true, 2.1, 1.2, 0.231, 0.472},
+    {true, ROWS_128x64, 128, 64, true, 1.3, 2.5, 0.347, 0.731},
+    {true, ROWS_128x128, 128, 128, false, 0.5, 4.8, 0.453, 0.0},
+    {false, PIPE_128x128, 128, 128, true, 0.5, 3.7, 0.546, 1.053},
+    {false, PIPE_160x128, 160, 128, true, 4.2, 1.6, 0.643, 1.360},
+    {false, PIPE_192x128, 192, 128, true, 0.5, 4.7, 0.646, 1.400},
+    {false, PIPE_256x192, 256, 192, false, 0.5, 8.5, 1.058, 0.0},
+    {false, PIPE_192x256, 192, 256, false, 0.5, 8.3, 1.044, 0.0},
+    {false, PIPE_256x256, 256, 256, false, 0.5, 10.0, 1.278, 0.0},
+    {false, PIPE_384x192, 384, 192, false, 0.5, 10.9, 1.451, 0.0},
+};
+
+// cu_share: how many launches of this size are expected to run side by side (the parts of a packed batch on several
+// streams); the tile is chosen for that share of the compute units.
+const TileTime& choose_tile(int32_t M, int32_t N, int32_t K, int32_t epi, bool rows_ok, int cu_share) {
+    const double cus = std::max(1, device_cus() / std::max(1, cu_share));
+    const int nk = K / BK;
+    const TileTime* best = nullptr;
+    double t_best = 0.0;
+    for (const TileTime& t : kTiles) {
+        if (t.rows && (!rows_ok || epi > FREE_EPI_GATE_RESID)) continue;
+        if (epi == FREE_EPI_GATE_RESID_PREP && t.bn != 256) continue;        // whole 128-column slots of row sums
+        const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) / cus;
+        const double alone = nk * t.a + t.e, shared = nk * t.b + t.e;
+        double time = t.f;
+        if (t.paired) {
+            const double full = std::floor(u / 2.0), rest = u - 2.0 * full;
+            time += full * shared + (rest <= 0.0 ? 0.0 : rest <= 1.0 ? alone : shared);
+        } else {
+            time += std::ceil(u) * alone;
+        }
+        if (best == nullptr || time < t_best) {
+            best = &t;
+            t_best = time;
+        }
+    }
+    return *best;
 }
 
 }  // namespace
@@ -447,7 +488,12 @@ int32_t launch_linear_mfma(const bf16_t* X, const bf16_t* W, const float* bias, 
                 return FREE_ERR_SHAPE;
         }
     }
-    return choose_and_launch<bf16_t>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share, ln);
+    if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
+    if (K % BK != 0) return ln ? FREE_ERR_SHAPE : choose_and_launch<bf16_t>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share);
+    if (ln == nullptr && epi > FREE_EPI_GATE_RESID) return FREE_ERR_SHAPE;
+    const TileTime& t = choose_tile(M, N, K, epi, linear_rows_covers(N, K, 2, bias, out, resid, gate), cu_share);
+    return t.rows ? launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(t.tile))
+                  : launch_linear_pipe(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<PipeTile>(t.tile), ln);
 }
 
 bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample) {
@@ -458,7 +504,7 @@ bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample) {
 int32_t launch_linear_mfma_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K,
                                int32_t epi, float* out, float* resid, RowVec gate, hipStream_t s, int cu_share) {
     if (!mfma_linear_f32_supported(M, N, K)) return FREE_ERR_SHAPE;
-    return choose_and_launch<float>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share, nullptr);
+    return choose_and_launch<float>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share);
 }
 
 }  // namespace freemi

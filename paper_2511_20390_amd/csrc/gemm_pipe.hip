@@ -24,7 +24,6 @@
 // reaches its power limit and lowers its clock; whole verification rounds (12 x 1024 tokens: 14.11 -> 13.85 ms, 32 x 256
 // tokens: 10.25 -> 9.36 ms) gain accordingly less than single launches where the chip is full.
 #include <algorithm>
-#include <cmath>
 
 #include "free_internal.h"
 #include "gemm_dma.h"
@@ -342,39 +341,28 @@ int32_t launch_tile(const Args& a, int32_t epi, const LnFold& ln) {
         case FREE_EPI_LN_BIAS: return launch_one<BM, BN, WGM, WGN, FREE_EPI_LN_BIAS>(a, ln);
         case FREE_EPI_LN_BIAS_GELU: return launch_one<BM, BN, WGM, WGN, FREE_EPI_LN_BIAS_GELU>(a, ln);
         case FREE_EPI_GATE_RESID_PREP:
-            if constexpr (BN / WGN == 64) return launch_one<BM, BN, WGM, WGN, FREE_EPI_GATE_RESID_PREP>(a, ln);
+            if constexpr (BN == 256) return launch_one<BM, BN, WGM, WGN, FREE_EPI_GATE_RESID_PREP>(a, ln);
+            return FREE_ERR_RANGE;
         default: return FREE_ERR_RANGE;
     }
 }
 
 }  // namespace
 
-// Tile choice.  At these sizes the chip works at its power limit, so a round of workgroups that does not fill it is
-// faster than a full one: measured times over M = 8192 and 12288 and the four layer shapes follow
-// flops / sqrt(share of the products that are useful * share of the CU-rounds in use) within 4 % with one factor per tile.
-//                       QKV        out-proj      MLP-1        MLP-2        (us; M = 8192 | 12288)
-//   256 x 256        71 |  98    40 | 45.5   108 | 141    105 | 126
-//   384 x 192        72 | 105    44 | 48     111 | 134    107 | 125
-//   256 x 192        81 | 101    34 | 60     100 | 143     90 | 162
-//   192 x 256        75 | 110    35 | 63     110 | 152     93 | 167
 int32_t launch_linear_pipe(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, int cu_share, const LnFold* ln) {
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, PipeTile tile, const LnFold* ln) {
     const Args a{X, W, bias, M, N, K, out, resid, gate, s};
     const LnFold f = ln ? *ln : LnFold{};
-    const double cus = std::max(1, device_cus() / std::max(1, cu_share));
-    auto score = [&](int bm, int bn, double q) {
-        const double tiles = static_cast<double>((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        return q * std::sqrt(static_cast<double>(M) * N / (std::ceil(tiles / cus) * cus * bm * bn));
-    };
-    const double s256 = score(256, 256, 1.0), s384 = score(384, 192, 1.04), s2x192 = score(256, 192, 1.0), s192 = score(192, 256, 0.97);
-    if (epi == FREE_EPI_GATE_RESID_PREP)
-        // (tiles of whole 128-column slots only)
-        return s192 > s256 ? launch_tile<192, 256, 2, 4>(a, epi, f) : launch_tile<256, 256, 2, 4>(a, epi, f);
-    const double best = std::max(std::max(s256, s384), std::max(s2x192, s192));
-    if (best == s256) return launch_tile<256, 256, 2, 4>(a, epi, f);
-    if (best == s384) return launch_tile<384, 192, 4, 2>(a, epi, f);
-    if (best == s2x192) return launch_tile<256, 192, 4, 2>(a, epi, f);
-    return launch_tile<192, 256, 2, 4>(a, epi, f);
+    switch (tile) {
+        case PIPE_256x256: return launch_tile<256, 256, 2, 4>(a, epi, f);
+        case PIPE_384x192: return launch_tile<384, 192, 4, 2>(a, epi, f);
+        case PIPE_256x192: return launch_tile<256, 192, 4, 2>(a, epi, f);
+        case PIPE_192x256: return launch_tile<192, 256, 2, 4>(a, epi, f);
+        case PIPE_192x128: return launch_tile<192, 128, 2, 4>(a, epi, f);
+        case PIPE_160x128: return launch_tile<160, 128, 1, 4>(a, epi, f);
+        case PIPE_128x128: return launch_tile<128, 128, 2, 4>(a, epi, f);
+    }
+    return FREE_ERR_RANGE;
 }
 
 }  // namespace freemi

@@ -42,11 +42,19 @@ def check_linear(M, N, K):
     assert ((got - ref).norm(dim=1).max() / ref.norm(dim=1).mean()).item() < 5 * F32_TOL
 
 
-# gemm_pipe.hip: 384 x 192 tiles with one, two and three slices; 256 x 192; 256 x 256 with a column tile half of padding;
-# 192 x 256; a full and a ragged last round
-@pytest.mark.parametrize("M,N,K", [(4100, 4104, 64), (4100, 4104, 128), (4100, 4104, 192), (7000, 1160, 320),
-                                   (8190, 4608, 128), (12100, 1160, 256), (12200, 1024, 128)])
+# every tile of gemm_pipe.hip with ragged rows and columns, one to three slices and more; 1150 columns: element-wise epilogue
+@pytest.mark.parametrize("M,N,K", [(700, 3464, 192), (6000, 1160, 320), (1000, 4600, 192), (8190, 1160, 128), (3000, 4600, 64),
+                                   (8190, 4600, 320), (2040, 4600, 1152), (3000, 4600, 320), (8190, 4600, 1152),
+                                   (12100, 4600, 1152), (300, 1150, 128)])
 def test_many_rows(M, N, K):
+    check_linear(M, N, K)
+
+
+# the tiles of gemm_rows.hip: single rows and columns groups, fewer slices than stages, as many, one more and many
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (65, 72, 128), (130, 200, 192), (63, 1152, 256), (190, 328, 320), (500, 1160, 384),
+                                   (257, 1152, 4608), (390, 3464, 128), (390, 3464, 192), (390, 3464, 256), (300, 3464, 1152),
+                                   (500, 4600, 1152), (1000, 3464, 2304)])
+def test_few_rows(M, N, K):
     check_linear(M, N, K)
 
 
