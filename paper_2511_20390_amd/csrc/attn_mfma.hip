@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "free_internal.h"
+#include "prefetch.h"
 
 namespace freemi {
 
@@ -50,7 +51,12 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) { return pack_bf16_pa
 template <int DH, int QT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 72 ? 3 : 2, DH <= 72 ? 3 : 2))) void attn_mfma_kernel(const bf16_t* __restrict__ qkv, int32_t N,
                                                              int32_t heads, float scale_log2,
-                                                             bf16_t* __restrict__ out) {
+                                                             bf16_t* __restrict__ out, int32_t n_blocks, Prefetch pf) {
+    const int first_prefetch = (n_blocks + 7) & ~7;
+    if (static_cast<int>(blockIdx.x) >= n_blocks) {
+        if (static_cast<int>(blockIdx.x) >= first_prefetch) prefetch_lines(pf, first_prefetch);
+        return;
+    }
     constexpr int KSTEPS = (DH + 15) / 16;            // MFMA k-steps over the head dim (S^T)
     constexpr int DCH = DH / 8;                       // 16-byte chunks per Q/K/V row
     constexpr int DT = (DH + 31) / 32;                // 32-row tiles of O^T
@@ -73,7 +79,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     // tiles of one (sample, head) re-read the same K and V, so they are placed on ONE XCD,
     // back to back: id L -> XCD L % 8; pair index = L % 8 + 8 * (L / (8 nq)), tile = (L / 8) % nq.
     const int nq = (N + BQ - 1) / BQ;
-    const int n_pairs = static_cast<int>(gridDim.x) / nq;       // (sample, head) pairs
+    const int n_pairs = n_blocks / nq;       // (sample, head) pairs
     int pair_idx, q_tile;
     if (n_pairs % 8 == 0) {
         const int L = blockIdx.x;
@@ -360,14 +366,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
 }
 
 template <int DH>
-int32_t launch_dh(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, bf16_t* out, hipStream_t s) {
+int32_t launch_dh(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, bf16_t* out, hipStream_t s, const Prefetch& pf) {
     const float scale_log2 = 1.4426950408889634f / std::sqrt(static_cast<float>(DH));
     // one 32-query tile per wavefront: 128 queries per workgroup, two or three workgroups per CU
     // (measured faster than two query tiles per wavefront at one workgroup per CU)
     const int64_t total = static_cast<int64_t>((N + 127) / 128) * heads * B;
-    if (total > 0x7fffffff) return FREE_ERR_SHAPE;
-    dim3 grid(static_cast<unsigned>(total));
-    hipLaunchKernelGGL((attn_mfma_kernel<DH, 1>), grid, dim3(kThreads), 0, s, qkv, N, heads, scale_log2, out);
+    if (total > 0x7fff0000) return FREE_ERR_SHAPE;
+    const int n = static_cast<int>(total), np = pf.blocks();
+    hipLaunchKernelGGL((attn_mfma_kernel<DH, 1>), dim3(np ? (n + 7) / 8 * 8 + np : n), dim3(kThreads), 0, s, qkv, N, heads,
+                       scale_log2, out, n, pf);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 
@@ -378,16 +385,16 @@ bool mfma_attention_supported(int32_t N, int32_t dh) {
 }
 
 int32_t launch_attention_mfma(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh, bf16_t* out,
-                              hipStream_t s) {
+                              hipStream_t s, const Prefetch& pf) {
     if (reinterpret_cast<uintptr_t>(qkv) & 15u) return FREE_ERR_SHAPE;
     if (B > 65535 || heads > 65535) return FREE_ERR_SHAPE;
     // one sample's rows are addressed through a buffer descriptor with 32-bit byte offsets
     if (static_cast<int64_t>(N) * 3 * heads * dh * 2 >= (1ll << 31)) return FREE_ERR_SHAPE;
     switch (dh) {
-        case 16: return launch_dh<16>(qkv, B, N, heads, out, s);
-        case 64: return launch_dh<64>(qkv, B, N, heads, out, s);
-        case 72: return launch_dh<72>(qkv, B, N, heads, out, s);
-        case 128: return launch_dh<128>(qkv, B, N, heads, out, s);
+        case 16: return launch_dh<16>(qkv, B, N, heads, out, s, pf);
+        case 64: return launch_dh<64>(qkv, B, N, heads, out, s, pf);
+        case 72: return launch_dh<72>(qkv, B, N, heads, out, s, pf);
+        case 128: return launch_dh<128>(qkv, B, N, heads, out, s, pf);
         default: return FREE_ERR_SHAPE;
     }
 }

@@ -6,6 +6,7 @@
 // holds the plain (non-MFMA) linear and attention kernels used by the fp32 mode
 // and as the shape fallback of the bf16 mode.
 #include "free_internal.h"
+#include "prefetch.h"
 
 namespace freemi {
 
@@ -401,7 +402,12 @@ __global__ __launch_bounds__(kThreads) void ln_modulate_kernel(
 // through the L1 - and the next row is requested before the current one is reduced.
 template <typename OT, int NV, int kLnRows>
 __global__ __launch_bounds__(kThreads) void ln_modulate_vec_kernel(
-    const float* __restrict__ x, RowVec shift, RowVec scale, int32_t M, int32_t D, OT* __restrict__ out) {
+    const float* __restrict__ x, RowVec shift, RowVec scale, int32_t M, int32_t D, OT* __restrict__ out, Prefetch pf,
+    int32_t first_prefetch) {
+    if (static_cast<int>(blockIdx.x) >= first_prefetch) {
+        prefetch_lines(pf, first_prefetch);
+        return;
+    }
     const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * kWaves + (threadIdx.x >> 6)) * kLnRows;
     const int lane = threadIdx.x & 63;
     if (row0 >= M) return;
@@ -996,24 +1002,24 @@ int32_t launch_patch_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, 
 }
 
 int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t D, int32_t dtype,
-                           void* out, hipStream_t s) {
+                           void* out, hipStream_t s, const Prefetch& pf) {
     const int blocks = (M + kWaves - 1) / kWaves;
     auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     const bool vec = (D % 4 == 0) && D <= 2048 && al16(x) && al16(out) && al16(shift.base) && al16(scale.base) &&
                      (shift.stride % 4 == 0) && (scale.stride % 4 == 0);
     if (vec) {
         const int nv = (D / 4 + 63) / 64;
-#define FREE_LN_CASE(OT, NV)                                                                                   \
-    do {                                                                                                       \
-        if (rows_per_wave == 4)                                                                                \
-            hipLaunchKernelGGL((ln_modulate_vec_kernel<OT, NV, 4>), dim3((blocks + 3) / 4), dim3(kThreads), 0, s, x, \
-                               shift, scale, M, D, static_cast<OT*>(out));                                     \
-        else if (rows_per_wave == 2)                                                                           \
-            hipLaunchKernelGGL((ln_modulate_vec_kernel<OT, NV, 2>), dim3((blocks + 1) / 2), dim3(kThreads), 0, s, x, \
-                               shift, scale, M, D, static_cast<OT*>(out));                                     \
-        else                                                                                                   \
-            hipLaunchKernelGGL((ln_modulate_vec_kernel<OT, NV, 1>), dim3(blocks), dim3(kThreads), 0, s, x, shift, \
-                               scale, M, D, static_cast<OT*>(out));                                            \
+#define FREE_LN_LAUNCH(OT, NV, ROWS)                                                                              \
+    do {                                                                                                          \
+        const int n = (blocks + ROWS - 1) / ROWS, np = pf.blocks(), first = (n + 7) / 8 * 8;                      \
+        hipLaunchKernelGGL((ln_modulate_vec_kernel<OT, NV, ROWS>), dim3(np ? first + np : n), dim3(kThreads), 0, s, x, shift, \
+                           scale, M, D, static_cast<OT*>(out), pf, first);                                        \
+    } while (0)
+#define FREE_LN_CASE(OT, NV)                                      \
+    do {                                                          \
+        if (rows_per_wave == 4) FREE_LN_LAUNCH(OT, NV, 4);        \
+        else if (rows_per_wave == 2) FREE_LN_LAUNCH(OT, NV, 2);   \
+        else FREE_LN_LAUNCH(OT, NV, 1);                           \
     } while (0)
         // measured at D = 1152: 12288 rows 19.3 / 16.2 / 15.8 us with 1 / 2 / 4 rows per wavefront, 6144 rows
         // 10.4 / 9.1 / 10.0 us; with few rows the chain of one row's latencies is what counts
@@ -1030,6 +1036,7 @@ int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M
             else FREE_LN_CASE(float, 8);
         }
 #undef FREE_LN_CASE
+#undef FREE_LN_LAUNCH
         return launch_ok() ? FREE_OK : FREE_ERR_HIP;
     }
     if (dtype == FREE_BF16)

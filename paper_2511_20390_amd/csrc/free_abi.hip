@@ -231,10 +231,10 @@ int32_t linear_dispatch(const Dims& d, const void* A, const void* W, const float
     return launch_linear_simple(A, W, bias, M, N, K, d.mode, epi, out, resid, gate, s);
 }
 
-int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s) {
+int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, const Prefetch& pf) {
     if (d.mode == FREE_BF16 && mfma_attention_supported(d.ntok, d.dh))
         return launch_attention_mfma(static_cast<const bf16_t*>(qkv), B, d.ntok, d.heads, d.dh,
-                                     static_cast<bf16_t*>(out), s);
+                                     static_cast<bf16_t*>(out), s, pf);
     if (d.mode == FREE_FP32 && mfma_attention_f32_supported(d.ntok, d.dh))
         return launch_attention_mfma_f32(static_cast<const float*>(qkv), B, d.ntok, d.heads, d.dh,
                                          static_cast<float*>(out), s);
@@ -260,6 +260,8 @@ struct ActBufs {
 // `nblk` adaLN-Zero blocks on samples [b0, b0 + nb) of a batch.  blkw holds 10 pointers per block
 // (B_* order); block l's six modulation vectors of sample b are mod[b * mod_rows + l * 6D ..].
 // cu_share: number of such stacks running side by side on different streams (tile choice of the GEMMs).
+// weights_far: the weights of a block are not in the caches when the stack gets to it (the target: 0.9 GB per forward; the
+// drafter's one or two blocks stay in the 256 MB Infinity Cache from one step of a chain to the next).
 // fold_ready (nullable): event after which fold->vec is complete; waited for on `s` before the first use.
 // fold (nullable): the LayerNorms are folded into the GEMMs around them (all but the first one of block 0, whose
 // input no GEMM of this stack produced): fold->vec holds the fold vectors of all samples of the batch, fold->stats the
@@ -272,7 +274,7 @@ struct FoldBufs {
 };
 int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const float* mod, int32_t mod_rows,
                         const ActBufs& a, int b0, int nb, hipStream_t s, Profiler* pf, int cu_share = 1,
-                        const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr) {
+                        const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool weights_far = true) {
     const size_t esz = d.mode == FREE_BF16 ? 2 : 4;
     const int32_t M = nb * d.ntok;
     const int64_t r0 = static_cast<int64_t>(b0) * d.ntok;
@@ -312,6 +314,20 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         f.slots = fold->slots;
         return f;
     };
+    // Few rows: the GEMMs are bound by how fast a CU gets its weights, so the short kernels in front of them pull the weights
+    // of this block into the caches.  (fp32 GEMMs are bound by the matrix cores: no gain, 0.4 % lost on 2 x 256 tokens.)
+    const bool few_rows = weights_far && d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
+    auto ahead = [&](int l, int w0, int64_t n0, int w1, int64_t n1) {
+        Prefetch p;
+        if (few_rows) {
+            p.p[0] = W(l, w0);
+            p.bytes[0] = n0 * static_cast<int64_t>(esz);
+            p.p[1] = W(l, w1);
+            p.bytes[1] = n1 * static_cast<int64_t>(esz);
+        }
+        return p;
+    };
+    const int64_t DD = static_cast<int64_t>(d.D) * d.D, DF = static_cast<int64_t>(d.D) * d.F;
     for (int l = 0; l < nblk; ++l) {
         // x += gate1 * Proj(Attn(LN(x)(1+scale1)+shift1))
         if (fold && l > 0) {
@@ -322,7 +338,8 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         } else {
             {
                 ProfScope prof(pf, PROF_LN_MOD, s);
-                FREE_TRY(launch_ln_modulate(xres_h, vec(l, 0), vec(l, 1), M, d.D, d.mode, xn_h, s));
+                FREE_TRY(launch_ln_modulate(xres_h, vec(l, 0), vec(l, 1), M, d.D, d.mode, xn_h, s,
+                                            ahead(l, B_QKV_W, 3 * DD, B_PROJ_W, DD)));
             }
             ProfScope prof(pf, PROF_GEMM_QKV, s);
             FREE_TRY(linear_dispatch(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_BIAS, qkv_h,
@@ -330,7 +347,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         {
             ProfScope prof(pf, PROF_ATTN, s);
-            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s));
+            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(l, B_FC1_W, DF, B_FC2_W, DF)));
         }
         if (fold) {
             // the out-projection also prepares the second LayerNorm: z = x (1 + scale2), partial row sums
@@ -1006,7 +1023,7 @@ int32_t free_op_attention(const void* qkv, int32_t B, int32_t N, int32_t heads, 
     d.ntok = N;
     d.heads = heads;
     d.dh = dh;
-    return attention_dispatch(d, qkv, B, out, static_cast<hipStream_t>(stream));
+    return attention_dispatch(d, qkv, B, out, static_cast<hipStream_t>(stream), Prefetch{});
 }
 
 int32_t free_op_ln_modulate(const float* x, const float* shift, const float* scale, int32_t mod_stride, int32_t M,
@@ -1102,7 +1119,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     FREE_TRY(linear_dispatch(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
                              2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, RowVec{dr->ones, 0, 1}, s));
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};
-    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof));
+    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, nullptr, nullptr, false));
     RowVec fsh{mod + static_cast<int64_t>(dr->depth) * 6 * d.D, mod_stride, d.ntok};
     RowVec fsc{mod + static_cast<int64_t>(dr->depth) * 6 * d.D + d.D, mod_stride, d.ntok};
     return launch_final_layer(f_out, fsh, fsc, B, d.gh, d.gw, d.p, d.c_out, d.D, dr->fin(F_W),

@@ -94,6 +94,18 @@ struct LnFold {
     float inv_width = 0.f;                 // 1 / width of the normalised rows
 };
 
+// Weight matrices that the launches after the next one read: the launch of a short kernel carries extra workgroups that
+// load them, so that the GEMMs find them in the L2 of their XCD or in the Infinity Cache (prefetch.h).
+struct Prefetch {
+    const void* p[2] = {nullptr, nullptr};
+    int64_t bytes[2] = {0, 0};
+    int blocks() const {                                     // workgroups of 256 threads, a multiple of 8
+        const int64_t n = (bytes[0] + bytes[1] + kPrefetchBlockBytes - 1) / kPrefetchBlockBytes;
+        return static_cast<int>((n + 7) / 8 * 8);
+    }
+    static constexpr int64_t kPrefetchBlockBytes = 64 << 10;
+};
+
 // Thread-local HIP error memo (free_last_hip_error).
 void note_hip_error(hipError_t e);
 inline bool hip_ok(hipError_t e) {
@@ -154,7 +166,7 @@ int32_t launch_patch_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, 
                            int32_t p, int32_t D, const float* pw, const float* pb, const float* pos,
                            float* out, hipStream_t s);
 int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t D,
-                           int32_t dtype, void* out, hipStream_t s);
+                           int32_t dtype, void* out, hipStream_t s, const Prefetch& pf = Prefetch{});
 int32_t launch_linear_simple(const void* A, const void* W, const float* bias, int32_t M, int32_t N,
                              int32_t K, int32_t dtype, int32_t epi, void* out, float* resid,
                              RowVec gate, hipStream_t s);
@@ -226,7 +238,7 @@ int32_t launch_ln_fold(const float* mod, int32_t B, int32_t D, int32_t mod_strid
                        int64_t fold_stride, hipStream_t s);
 bool mfma_attention_supported(int32_t N, int32_t dh);
 int32_t launch_attention_mfma(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
-                              bf16_t* out, hipStream_t s);
+                              bf16_t* out, hipStream_t s, const Prefetch& pf = Prefetch{});
 // fp32 operands and softmax on the matrix cores (attn_f32_mfma.hip); qkv and out 16-byte aligned
 bool mfma_attention_f32_supported(int32_t N, int32_t dh);
 int32_t launch_attention_mfma_f32(const float* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
