@@ -222,6 +222,8 @@ int32_t launch_linear_pipe(const bf16_t* X, const bf16_t* W, const float* bias, 
 enum RowsTile { ROWS_64x64, ROWS_128x64, ROWS_128x128 };
 int32_t launch_linear_rows(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
                            bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
+int32_t launch_linear_rows(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                           float* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
 bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* bias, const void* out, const float* resid,
                         const RowVec& gate);
 // shapes the folded-LayerNorm epilogues cover: M rows of width D normalised, rows_per_sample tokens per sample

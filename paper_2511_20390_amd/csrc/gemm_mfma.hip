@@ -430,6 +430,15 @@ constexpr TileTime kTiles[] = {
     {false, PIPE_384x192, 384, 192, false, 0.5, 10.9, 1.451, 0.0},
 };
 
+// Time of a launch of `u` workgroups per CU.  last_alone: up to this many workgroups per CU left over after the full pairs
+// run as if they had a CU each.
+double launch_time(const TileTime& t, double u, int nk, double last_alone) {
+    const double alone = nk * t.a + t.e, shared = nk * t.b + t.e;
+    if (!t.paired) return t.f + std::ceil(u) * alone;
+    const double full = std::floor(u / 2.0), rest = u - 2.0 * full;
+    return t.f + full * shared + (rest <= 0.0 ? 0.0 : rest <= (full > 0.0 ? last_alone : 1.0) ? alone : shared);
+}
+
 // cu_share: how many launches of this size are expected to run side by side (the parts of a packed batch on several
 // streams); the tile is chosen for that share of the compute units.
 const TileTime& choose_tile(int32_t M, int32_t N, int32_t K, int32_t epi, bool rows_ok, int cu_share) {
@@ -441,14 +450,42 @@ const TileTime& choose_tile(int32_t M, int32_t N, int32_t K, int32_t epi, bool r
         if (t.rows && (!rows_ok || epi > FREE_EPI_GATE_RESID)) continue;
         if (epi == FREE_EPI_GATE_RESID_PREP && t.bn != 256) continue;        // whole 128-column slots of row sums
         const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) / cus;
-        const double alone = nk * t.a + t.e, shared = nk * t.b + t.e;
-        double time = t.f;
-        if (t.paired) {
-            const double full = std::floor(u / 2.0), rest = u - 2.0 * full;
-            time += full * shared + (rest <= 0.0 ? 0.0 : rest <= 1.0 ? alone : shared);
-        } else {
-            time += std::ceil(u) * alone;
+        const double time = launch_time(t, u, nk, 1.0);
+        if (best == nullptr || time < t_best) {
+            best = &t;
+            t_best = time;
         }
+    }
+    return *best;
+}
+
+// The same for fp32 (slices of 32, whole ones).  A slice of a 32 x 32 block is 16 products of 64 cycles, so the matrix cores
+// decide as soon as every SIMD has a wavefront, and below that the number of tiles does: 512 x 1152 x 4608 is 54 tiles of
+// 96 x 128 (217 us) or 144 of 64 x 64 (89 us).  Fitted to every tile at 18 values of M from 64 to 4096 and the four layer
+// shapes at widths 384, 768 and 1152 (rms error 2-5 %); the chosen tile is within 1 % of the best one on average, 5 % at
+// worst, up to kFewRowsF32 rows.  Above that the rule of choose_and_launch is as good.  us, old rule -> this one, at width
+// 1152 (QKV, out-projection, MLP-1, MLP-2):  64 rows 57 56 56 208 -> 24 24 23 82;  512 rows 61 59 64 217 -> 44 26 64 89;
+// 1024 rows 77 60 96 218 -> 75 44 96 153;  2048 rows 142 63 179 229 -> 141 63 179 229.
+constexpr int kFewRowsF32 = 2048;
+enum { F32_96x128 = 100, F32_128x128, F32_160x128, F32_256x256 };
+constexpr TileTime kTilesF32[] = {
+    {true, ROWS_64x64, 64, 64, true, 2.0, 2.3, 0.572, 1.082},
+    {true, ROWS_128x64, 128, 64, true, 3.9, 1.7, 1.038, 2.043},
+    {false, F32_96x128, 96, 128, true, 3.5, 2.8, 1.455, 2.872},
+    {false, F32_128x128, 128, 128, true, 8.0, 0.0, 1.881, 3.739},
+    {false, F32_160x128, 160, 128, true, 0.0, 8.6, 2.329, 4.623},
+    {false, F32_256x256, 256, 256, false, 0.6, 9.9, 7.039, 0.0},
+};
+
+const TileTime& choose_tile_f32(int32_t M, int32_t N, int32_t K, bool rows_ok, int cu_share) {
+    const double cus = std::max(1, device_cus() / std::max(1, cu_share));
+    const int nk = K / (kRowBytes / 4);
+    const TileTime* best = nullptr;
+    double t_best = 0.0;
+    for (const TileTime& t : kTilesF32) {
+        if (t.rows && !rows_ok) continue;
+        const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) / cus;
+        const double time = launch_time(t, u, nk, 0.75);
         if (best == nullptr || time < t_best) {
             best = &t;
             t_best = time;
@@ -504,7 +541,17 @@ bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample) {
 int32_t launch_linear_mfma_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K,
                                int32_t epi, float* out, float* resid, RowVec gate, hipStream_t s, int cu_share) {
     if (!mfma_linear_f32_supported(M, N, K)) return FREE_ERR_SHAPE;
-    return choose_and_launch<float>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share);
+    if (K % (kRowBytes / 4) != 0 || M > kFewRowsF32 || epi > FREE_EPI_GATE_RESID)
+        return choose_and_launch<float>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share);
+    if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
+    const TileTime& t = choose_tile_f32(M, N, K, linear_rows_covers(N, K, 4, bias, out, resid, gate), cu_share);
+    if (t.rows) return launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(t.tile));
+    switch (t.tile) {
+        case F32_96x128: return launch_cfg<float, 96, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case F32_128x128: return launch_cfg<float, 128, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case F32_160x128: return launch_cfg<float, 160, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        default: return launch_cfg<float, 256, 256, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+    }
 }
 
 }  // namespace freemi

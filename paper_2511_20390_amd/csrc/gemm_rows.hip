@@ -17,6 +17,8 @@
 // MLP-1, MLP-2):   256 rows 13.3, 15.8, 14.5, 43.8 -> 8.2, 8.7, 11.2, 23.2
 //                  512 rows 14.3, 16.0, 16.1, 44.3 -> 10.5, 8.8, 15.0, 23.3
 //                 1024 rows 16.6, 16.4, 20.0, 44.7 -> 14.1, 11.2, 20.0, 31.7
+// fp32 is bound by the matrix cores (0.43 us for the 16 products of a wavefront's slice; measured 0.57 with its waits), and
+// what the small tiles buy is wavefronts: 512 rows 61, 59, 64, 217 -> 44, 26, 64, 89 (MLP-1 keeps its 96 x 128).
 #include <algorithm>
 
 #include "free_internal.h"
@@ -307,16 +309,26 @@ bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* b
            aligned(gate.base) && gate.stride % 4 == 0;
 }
 
-int32_t launch_linear_rows(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile) {
-    const Args<bf16_t> a{X, W, bias, M, N, K, out, resid, gate, s};
-    if (!linear_rows_covers(N, K, sizeof(bf16_t), bias, out, resid, gate)) return FREE_ERR_SHAPE;
-    switch (tile) {
-        case ROWS_64x64: return launch_tile<bf16_t, 64, 64, 2, 2, 4>(a, epi);
-        case ROWS_128x64: return launch_tile<bf16_t, 128, 64, 2, 2, 3>(a, epi);
-        case ROWS_128x128: return launch_tile<bf16_t, 128, 128, 2, 4, 4>(a, epi);
+template <typename T>
+static int32_t launch_rows(const Args<T>& a, int32_t epi, RowsTile tile) {
+    if (!linear_rows_covers(a.N, a.K, sizeof(T), a.bias, a.out, a.resid, a.gate)) return FREE_ERR_SHAPE;
+    if (tile == ROWS_64x64) return launch_tile<T, 64, 64, 2, 2, 4>(a, epi);
+    if (tile == ROWS_128x64) return launch_tile<T, 128, 64, 2, 2, 3>(a, epi);
+    // (fp32: as fast as the 128 x 128 tile of gemm_mfma.hip where either is the best one, so there is only that)
+    if constexpr (!std::is_same<T, float>::value) {
+        if (tile == ROWS_128x128) return launch_tile<T, 128, 128, 2, 4, 4>(a, epi);
     }
     return FREE_ERR_RANGE;
+}
+
+int32_t launch_linear_rows(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile) {
+    return launch_rows(Args<bf16_t>{X, W, bias, M, N, K, out, resid, gate, s}, epi, tile);
+}
+
+int32_t launch_linear_rows(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                           float* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile) {
+    return launch_rows(Args<float>{X, W, bias, M, N, K, out, resid, gate, s}, epi, tile);
 }
 
 }  // namespace freemi

@@ -1,6 +1,6 @@
-"""The bf16 GEMM kernels at the sizes where their tiles and K loops can go wrong: remainders in rows and columns, one,
-two and three K slices, column halves of a tile that are all padding.  Reference: the same product in fp32 by
-torch on the bf16 values."""
+"""The GEMM kernels at the sizes where their tiles and K loops can go wrong: remainders in rows and columns, one,
+two and three K slices, column halves of a tile that are all padding.  Reference: the same product by torch, in fp32 on the bf16
+values or in fp64 on the fp32 values."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -56,6 +56,27 @@ def test_many_rows(M, N, K):
                                    (500, 4600, 1152), (1000, 3464, 2304)])
 def test_few_rows(M, N, K):
     check_linear(M, N, K)
+
+
+# fp32: the tiles of gemm_rows.hip and each of the larger ones; slices of 32, fewer than the ring's stages and more
+@pytest.mark.parametrize("M,N,K", [(1, 8, 32), (65, 72, 64), (130, 200, 96), (63, 1152, 160), (257, 1152, 4608), (450, 3464, 1152),
+                                   (512, 4600, 1152), (900, 3464, 1152), (1200, 2304, 768), (1000, 4600, 384), (1500, 4600, 256),
+                                   (2048, 3080, 192), (2049, 1160, 64)])
+def test_few_rows_fp32(M, N, K):
+    import torch
+    from paper_2511_20390_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, w, bias, resid, gate = rnd(M, K), rnd(N, K) / K ** 0.5, rnd(N), rnd(M, N), rnd(1, N)
+    ref = x.double() @ w.double().T + bias
+    assert _rel(binding.op_linear(x, w, bias, "fp32", binding.EPI_BIAS), ref) < F32_TOL
+    out = binding.op_linear(x, w, bias, "fp32", binding.EPI_BIAS_GELU)
+    assert _rel(out, torch.nn.functional.gelu(ref, approximate="tanh")) < F32_TOL
+    got = resid.clone()
+    binding.op_linear(x, w, bias, "fp32", binding.EPI_GATE_RESID, resid=got, gate=gate, rows_per_sample=M)
+    ref = resid + gate * ref
+    assert _rel(got, ref) < F32_TOL
+    assert ((got - ref).norm(dim=1).max() / ref.norm(dim=1).mean()).item() < 5 * F32_TOL
 
 
 @pytest.mark.parametrize("M,rows", [(8192, 256), (7680, 480), (12288, 1024)])
