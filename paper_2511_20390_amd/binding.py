@@ -163,8 +163,8 @@ def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
-def _dev(t, dtype, name, shape=None, optional=False):
-    """Pointer of a device tensor handed to the library, after the checks the C side cannot make: the
+def _addr(t, dtype, name, shape=None, optional=False):
+    """Address of a device tensor handed to the library, after the checks the C side cannot make: the
     library reads raw memory, so a tensor of another element type (torch integers default to int64), a
     strided view or a host tensor would give wrong results or out-of-bounds device reads, not an error."""
     if t is None:
@@ -177,14 +177,22 @@ def _dev(t, dtype, name, shape=None, optional=False):
         raise FreeError(FREE_ERR_DTYPE, f"{name}: element type {t.dtype}, expected {dtype}")
     if not t.is_contiguous():
         raise FreeError(FREE_ERR_SHAPE, f"{name}: not contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise FreeError(FREE_ERR_SHAPE, f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _dev(t, dtype, name, shape=None, optional=False):
+    """_addr as a ctypes pointer."""
+    a = _addr(t, dtype, name, shape, optional)
+    return None if a is None else C.c_void_p(a)
 
 
 def _stream():
+    """Handle of the current stream of the current device.  A verification call is bound by its submission (15 us
+    against 6 us of kernels on one trajectory), and a torch stream object made for its handle alone was 3 us of that."""
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def make_config(cfg: dict, mode: str) -> FreeDitConfig:
@@ -261,14 +269,14 @@ def spec_verify(m_target, m_draft, x_draft, sigma, u, lam=None, out=None, worksp
     out = _verify_out(out, n_traj, K, d, dev)
     if workspace is None:
         workspace = torch.empty(max(256, spec_verify_workspace_bytes(n_traj, K, d)), dtype=torch.uint8, device=dev)
-    args = [_dev(m_target, f32, "m_target"), _dev(m_draft, f32, "m_draft", (n_traj, K, d)),
-            _dev(x_draft, f32, "x_draft", (n_traj, K, d)), _dev(sigma, f32, "sigma", (n_traj, K)),
-            _dev(u, f32, "u", (n_traj, K)), _dev(lam, f32, "lambda", (n_traj, K), optional=True),
-            n_traj, K, d, _dev(out["log_ratio"], f32, "log_ratio", (n_traj, K)),
-            _dev(out["accept"], torch.uint8, "accept", (n_traj, K)),
-            _dev(out["n_accept"], torch.int32, "n_accept", (n_traj,)),
-            _dev(out["x_out"], f32, "x_out", (n_traj, d)),
-            _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()]
+    args = [_addr(m_target, f32, "m_target"), _addr(m_draft, f32, "m_draft", (n_traj, K, d)),
+            _addr(x_draft, f32, "x_draft", (n_traj, K, d)), _addr(sigma, f32, "sigma", (n_traj, K)),
+            _addr(u, f32, "u", (n_traj, K)), _addr(lam, f32, "lambda", (n_traj, K), optional=True),
+            n_traj, K, d, _addr(out["log_ratio"], f32, "log_ratio", (n_traj, K)),
+            _addr(out["accept"], torch.uint8, "accept", (n_traj, K)),
+            _addr(out["n_accept"], torch.int32, "n_accept", (n_traj,)),
+            _addr(out["x_out"], f32, "x_out", (n_traj, d)),
+            _addr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()]
     if timed:
         a, b = C.c_float(0.0), C.c_float(0.0)
         _check(load().spec_verify_timed(*args, C.addressof(a), C.addressof(b)), "spec_verify_timed")
@@ -288,12 +296,12 @@ def spec_verify_diag(m_target, m_draft, x_draft, sigma_elem, u, lam=None, out=No
     if workspace is None:
         workspace = torch.empty(max(256, spec_verify_workspace_bytes(n_traj, K, d)), dtype=torch.uint8, device=dev)
     _check(load().spec_verify_diag(
-        _dev(m_target, f32, "m_target"), _dev(m_draft, f32, "m_draft", (n_traj, K, d)),
-        _dev(x_draft, f32, "x_draft", (n_traj, K, d)), _dev(sigma_elem, f32, "sigma_elem", (n_traj, K, d)),
-        _dev(u, f32, "u", (n_traj, K)), _dev(lam, f32, "lambda", (n_traj, K), optional=True), n_traj, K, d,
-        _dev(out["log_ratio"], f32, "log_ratio", (n_traj, K)), _dev(out["accept"], torch.uint8, "accept", (n_traj, K)),
-        _dev(out["n_accept"], torch.int32, "n_accept", (n_traj,)), _dev(out["x_out"], f32, "x_out", (n_traj, d)),
-        _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()), "spec_verify_diag")
+        _addr(m_target, f32, "m_target"), _addr(m_draft, f32, "m_draft", (n_traj, K, d)),
+        _addr(x_draft, f32, "x_draft", (n_traj, K, d)), _addr(sigma_elem, f32, "sigma_elem", (n_traj, K, d)),
+        _addr(u, f32, "u", (n_traj, K)), _addr(lam, f32, "lambda", (n_traj, K), optional=True), n_traj, K, d,
+        _addr(out["log_ratio"], f32, "log_ratio", (n_traj, K)), _addr(out["accept"], torch.uint8, "accept", (n_traj, K)),
+        _addr(out["n_accept"], torch.int32, "n_accept", (n_traj,)), _addr(out["x_out"], f32, "x_out", (n_traj, d)),
+        _addr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()), "spec_verify_diag")
     return out
 
 
@@ -305,11 +313,11 @@ def spec_verify_static(m_target, m_draft, x_draft, sigma, u, lam=None, out=None)
     n_traj, K, d = m_target.shape
     out = _verify_out(out, n_traj, K, d, m_target.device)
     _check(load().spec_verify_static(
-        _dev(m_target, f32, "m_target"), _dev(m_draft, f32, "m_draft", (n_traj, K, d)),
-        _dev(x_draft, f32, "x_draft", (n_traj, K, d)), _dev(sigma, f32, "sigma", (n_traj, K)),
-        _dev(u, f32, "u", (n_traj, K)), _dev(lam, f32, "lambda", (n_traj, K), optional=True), n_traj, K, d,
-        _dev(out["log_ratio"], f32, "log_ratio", (n_traj, K)), _dev(out["accept"], torch.uint8, "accept", (n_traj, K)),
-        _dev(out["n_accept"], torch.int32, "n_accept", (n_traj,)), _dev(out["x_out"], f32, "x_out", (n_traj, d)),
+        _addr(m_target, f32, "m_target"), _addr(m_draft, f32, "m_draft", (n_traj, K, d)),
+        _addr(x_draft, f32, "x_draft", (n_traj, K, d)), _addr(sigma, f32, "sigma", (n_traj, K)),
+        _addr(u, f32, "u", (n_traj, K)), _addr(lam, f32, "lambda", (n_traj, K), optional=True), n_traj, K, d,
+        _addr(out["log_ratio"], f32, "log_ratio", (n_traj, K)), _addr(out["accept"], torch.uint8, "accept", (n_traj, K)),
+        _addr(out["n_accept"], torch.int32, "n_accept", (n_traj,)), _addr(out["x_out"], f32, "x_out", (n_traj, d)),
         _stream()), "spec_verify_static")
     return out
 
