@@ -29,13 +29,13 @@ namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 typedef short v8s_t __attribute__((ext_vector_type(8)));
 
 constexpr int kThreads = 256;
+constexpr int BKV = 64;                   // keys per LDS tile
 
 __device__ inline int swap_bits_2_3(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
@@ -48,20 +48,10 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) { return pack_bf16_pa
 // O^T on the matrix pipe - are serial inside a wavefront, so what overlaps them is the number of
 // wavefronts per SIMD; the third one is worth more (measured 4.5 %) than the second set of K/V staging
 // registers it costs.
-//
-// KS: wavefronts that share a block of 32 queries.  KS = 1 (four query blocks per workgroup) is the throughput form.  With few
-// (sample, head, query block) triples there is less than one workgroup per CU and one wavefront per SIMD, whose serial phases
-// - 704 cycles of products, 512 of exponentials, about 450 of other VALU work per 64-key tile - nothing overlaps.  KS = 2
-// gives each of two wavefronts one 32-key block of every tile and twice the workgroups; the partial results (maximum, sum,
-// O^T) are joined through LDS at the end.  us at 16 heads of 72, KS = 1 -> 2: 1 x 256 tokens 8.8 -> 7.7, 2 x 256 9.1 -> 8.1,
-// 1 x 1024 20.7 -> 16.4, 2 x 1024 22.8 -> 21.6; 6 x 256 10.2 -> 10.6.
-template <int DH, int KS>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 72 ? 3 : 2, DH <= 72 ? 3 : 2))) void attn_mfma_kernel(
-    const bf16_t* __restrict__ qkv, int32_t N, int32_t heads, float scale_log2, bf16_t* __restrict__ out, int32_t n_blocks,
-    Prefetch pf) {
-    constexpr int QT = 1;                             // query blocks per wavefront
-    constexpr int BKV = 64;                           // keys per LDS tile
-    constexpr int KB = BKV / 32 / KS;                 // 32-key blocks per wavefront and tile
+template <int DH, int QT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 72 ? 3 : 2, DH <= 72 ? 3 : 2))) void attn_mfma_kernel(const bf16_t* __restrict__ qkv, int32_t N,
+                                                             int32_t heads, float scale_log2,
+                                                             bf16_t* __restrict__ out, int32_t n_blocks, Prefetch pf) {
     const int first_prefetch = (n_blocks + 7) & ~7;
     if (static_cast<int>(blockIdx.x) >= n_blocks) {
         if (static_cast<int>(blockIdx.x) >= first_prefetch) prefetch_lines(pf, first_prefetch);
@@ -73,20 +63,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     constexpr int kSets = DH <= 72 ? 1 : 2;           // K/V register sets: tiles in flight from global memory
     constexpr bool kSumByMfma = (DH % 32) != 0;       // a spare row of O^T can carry the softmax denominator
     constexpr int KROW = ((2 * KSTEPS) | 1) * 16;     // bytes per K row in LDS (odd # of chunks)
-    constexpr int BQ = 4 / KS * 32 * QT;              // queries per workgroup
+    constexpr int BQ = 4 * 32 * QT;                   // queries per workgroup
     constexpr int NLD = (BKV * DCH + kThreads - 1) / kThreads;   // 16-byte loads per thread per tile
     // V stays row-major in LDS ([key][d]) and is read with the transposing LDS load; a row stride of
     // 64 or 192 (mod 256) bytes puts the 4 keys x 64 bytes that 32 lanes of such a load touch on
     // disjoint banks
     constexpr int VROW = DT == 1 ? 64 : (DT <= 3 ? 192 : 320);
     constexpr int kKBytes = BKV * KROW, kVBytes = BKV * VROW;
-    __shared__ __attribute__((aligned(16))) char smem[2 * (kKBytes + kVBytes)];      // two stages: tile t is multiplied
-    char* const sKbuf = smem;                                                        // while tile t+1 is written
-    char* const sVbuf = smem + 2 * kKBytes;
+    __shared__ __attribute__((aligned(16))) char sKbuf[2 * kKBytes];      // two stages: tile t is multiplied
+    __shared__ __attribute__((aligned(16))) char sVbuf[2 * kVBytes];      // while tile t+1 is written
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, g = lane >> 5;
-    const int kg = wave % KS, kb0 = kg * KB;          // this wavefront's share of every tile's keys
     // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  All query
     // tiles of one (sample, head) re-read the same K and V, so they are placed on ONE XCD,
     // back to back: id L -> XCD L % 8; pair index = L % 8 + 8 * (L / (8 nq)), tile = (L / 8) % nq.
@@ -104,7 +92,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     const int h = pair_idx % heads, b = pair_idx / heads;
     const int D = heads * DH;
     const int64_t row0 = static_cast<int64_t>(b) * N;
-    const int q_base = q_tile * BQ + wave / KS * 32 * QT;
+    const int q_base = q_tile * BQ + wave * 32 * QT;
     const size_t row_bytes = static_cast<size_t>(3) * D * 2;
     const char* qkv_b = reinterpret_cast<const char*>(qkv);
 
@@ -221,23 +209,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         const char* sK = sKbuf + (t & 1) * kKBytes;
         const char* sV = sVbuf + (t & 1) * kVBytes;
 
-        // ---- S^T = K Q^T for this wavefront's 32-key blocks of the tile
+        // ---- S^T = K Q^T for the two 32-key blocks of the tile
         __builtin_amdgcn_s_setprio(kPrioMfma);
-        f32x16_t st[KB][QT];
+        f32x16_t st[2][QT];
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) st[kb][qt][e] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
-            bf16x8_t kf[KB];
+            bf16x8_t kf[2];
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-                kf[kb] = *reinterpret_cast<const bf16x8_t*>(sK + ((kb0 + kb) * 32 + l32) * KROW + (2 * ks + g) * 16);
+            for (int kb = 0; kb < 2; ++kb)
+                kf[kb] = *reinterpret_cast<const bf16x8_t*>(sK + (kb * 32 + l32) * KROW + (2 * ks + g) * 16);
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int qt = 0; qt < QT; ++qt)
                     st[kb][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[qt][ks], st[kb][qt], 0, 0, 0);
@@ -252,10 +240,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         // kv0 + 32 kb + 16 (e/8) + 8 g + 4 ((e/4)%2) + e%4   (LDS rows were permuted on the way in)
         if (kRagged) {
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int kv = kv0 + 32 * (kb0 + kb) + 16 * (e >> 3) + 8 * g + 4 * ((e >> 2) & 1) + (e & 3);
+                    const int kv = kv0 + 32 * kb + 16 * (e >> 3) + 8 * g + 4 * ((e >> 2) & 1) + (e & 3);
                     if (kv >= N) {
 #pragma unroll
                         for (int qt = 0; qt < QT; ++qt) st[kb][qt][e] = -INFINITY;
@@ -264,12 +252,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         }
 
         // ---- online softmax per query column, probabilities packed straight into MFMA operands
-        bf16x8_t pr[QT][KB][2];
+        bf16x8_t pf[QT][2][2];
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
             float mx = st[0][qt][0];
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[kb][qt][e]);
             {   // both half-waves of a column agree: v_permlane32_swap leaves {own, partner} in the two
@@ -292,7 +280,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
             const float mb = m_ref[qt] * scale_log2;
             [[maybe_unused]] float sum = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh) {
                     float p[8];
@@ -303,7 +291,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
                     }
                     u32x4_t pk = {pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]),
                                   pack_bf16x2(p[6], p[7])};
-                    pr[qt][kb][hh] = __builtin_bit_cast(bf16x8_t, pk);
+                    pf[qt][kb][hh] = __builtin_bit_cast(bf16x8_t, pk);
                 }
             if constexpr (!kSumByMfma) l_run[qt] += sum;
         }
@@ -311,20 +299,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         // ---- O^T += V^T P^T
         __builtin_amdgcn_s_setprio(kPrioMfma);
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
                     using lds_v4 = __attribute__((address_space(3))) v4s_t*;
-                    const char* vp = sV + ((kb0 + kb) * 32 + hh * 16) * VROW + dt * 64 + vtr_off;
+                    const char* vp = sV + (kb * 32 + hh * 16) * VROW + dt * 64 + vtr_off;
                     const v4s_t vlo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(vp));
                     const v4s_t vhi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(vp + 4 * VROW));
                     const v8s_t v8 = __builtin_shufflevector(vlo, vhi, 0, 1, 2, 3, 4, 5, 6, 7);
                     const bf16x8_t vf = __builtin_bit_cast(bf16x8_t, v8);
 #pragma unroll
                     for (int qt = 0; qt < QT; ++qt)
-                        o[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pr[qt][kb][hh], o[dt][qt], 0, 0, 0);
+                        o[dt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[qt][kb][hh], o[dt][qt], 0, 0, 0);
                 }
             }
         __builtin_amdgcn_s_setprio(0);
@@ -344,53 +332,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     if (t < ntiles) {
         if (t & 1) tile(t, std::true_type{}, set0);
         else tile(t, std::true_type{}, set1);
-    }
-
-    if constexpr (KS > 1) {
-        // ---- join the key groups of a query block (the last tile ended with a barrier: the tiles are idle).  Every group has
-        // seen a whole 32-key block, so its maximum is finite.
-        constexpr int kPart = (DT * 4 + 1) * 1024;            // O^T in 16-byte pieces per lane, then maximum and sum
-        static_assert((4 - 4 / KS) * kPart <= 2 * (kKBytes + kVBytes), "partial results must fit in the tiles");
-        char* part = smem + (wave / KS * (KS - 1) + kg - 1) * kPart + lane * 16;
-        if (kg > 0) {
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4_t v = {o[dt][0][4 * q], o[dt][0][4 * q + 1], o[dt][0][4 * q + 2], o[dt][0][4 * q + 3]};
-                    *reinterpret_cast<f32x4_t*>(part + (dt * 4 + q) * 1024) = v;
-                }
-            *reinterpret_cast<f32x4_t*>(part + DT * 4096) = f32x4_t{m_ref[0], l_run[0], 0.f, 0.f};
-        }
-        __syncthreads();
-        if (kg > 0) return;
-        const char* parts = smem + wave / KS * (KS - 1) * kPart + lane * 16;
-        f32x4_t ml[KS - 1];
-        float m_all = m_ref[0];
-#pragma unroll
-        for (int k = 0; k < KS - 1; ++k) {
-            ml[k] = *reinterpret_cast<const f32x4_t*>(parts + k * kPart + DT * 4096);
-            m_all = fmaxf(m_all, ml[k][0]);
-        }
-        const float own = __builtin_amdgcn_exp2f((m_ref[0] - m_all) * scale_log2);
-        l_run[0] *= own;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) o[dt][0][e] *= own;
-#pragma unroll
-        for (int k = 0; k < KS - 1; ++k) {
-            const float a = __builtin_amdgcn_exp2f((ml[k][0] - m_all) * scale_log2);
-            l_run[0] = fmaf(a, ml[k][1], l_run[0]);
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(parts + k * kPart + (dt * 4 + q) * 1024);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) o[dt][0][4 * q + c] = fmaf(a, v[c], o[dt][0][4 * q + c]);
-                }
-        }
     }
 
     // ---- normalise and store: register e of O^T tile dt is row d = 32 dt + 8 (e/4) + 4 g + e%4, column l32
@@ -424,25 +365,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     }
 }
 
-template <int DH, int KS>
-int32_t launch_ks(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, bf16_t* out, hipStream_t s, const Prefetch& pf) {
+template <int DH>
+int32_t launch_dh(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, bf16_t* out, hipStream_t s, const Prefetch& pf) {
     const float scale_log2 = 1.4426950408889634f / std::sqrt(static_cast<float>(DH));
-    constexpr int BQ = 128 / KS;
-    const int64_t total = static_cast<int64_t>((N + BQ - 1) / BQ) * heads * B;
+    // one 32-query tile per wavefront: 128 queries per workgroup, two or three workgroups per CU
+    // (measured faster than two query tiles per wavefront at one workgroup per CU)
+    const int64_t total = static_cast<int64_t>((N + 127) / 128) * heads * B;
     if (total > 0x7fff0000) return FREE_ERR_SHAPE;
     const int n = static_cast<int>(total), np = pf.blocks();
-    hipLaunchKernelGGL((attn_mfma_kernel<DH, KS>), dim3(np ? (n + 7) / 8 * 8 + np : n), dim3(kThreads), 0, s, qkv, N, heads,
+    hipLaunchKernelGGL((attn_mfma_kernel<DH, 1>), dim3(np ? (n + 7) / 8 * 8 + np : n), dim3(kThreads), 0, s, qkv, N, heads,
                        scale_log2, out, n, pf);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
-}
-
-template <int DH>
-int32_t launch_dh(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, bf16_t* out, hipStream_t s, bool few_rows,
-                  const Prefetch& pf) {
-    const int64_t n1 = static_cast<int64_t>((N + 127) / 128) * heads * B;            // workgroups with KS = 1
-    // two wavefronts per query block where that leaves at most one workgroup per CU, or two of a long key loop
-    if (few_rows && N >= 64 && (n1 <= 128 || (n1 <= 256 && N >= 512))) return launch_ks<DH, 2>(qkv, B, N, heads, out, s, pf);
-    return launch_ks<DH, 1>(qkv, B, N, heads, out, s, pf);
 }
 
 }  // namespace
@@ -452,16 +385,16 @@ bool mfma_attention_supported(int32_t N, int32_t dh) {
 }
 
 int32_t launch_attention_mfma(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh, bf16_t* out,
-                              hipStream_t s, bool few_rows, const Prefetch& pf) {
+                              hipStream_t s, const Prefetch& pf) {
     if (reinterpret_cast<uintptr_t>(qkv) & 15u) return FREE_ERR_SHAPE;
     if (B > 65535 || heads > 65535) return FREE_ERR_SHAPE;
     // one sample's rows are addressed through a buffer descriptor with 32-bit byte offsets
     if (static_cast<int64_t>(N) * 3 * heads * dh * 2 >= (1ll << 31)) return FREE_ERR_SHAPE;
     switch (dh) {
-        case 16: return launch_dh<16>(qkv, B, N, heads, out, s, few_rows, pf);
-        case 64: return launch_dh<64>(qkv, B, N, heads, out, s, few_rows, pf);
-        case 72: return launch_dh<72>(qkv, B, N, heads, out, s, few_rows, pf);
-        case 128: return launch_dh<128>(qkv, B, N, heads, out, s, few_rows, pf);
+        case 16: return launch_dh<16>(qkv, B, N, heads, out, s, pf);
+        case 64: return launch_dh<64>(qkv, B, N, heads, out, s, pf);
+        case 72: return launch_dh<72>(qkv, B, N, heads, out, s, pf);
+        case 128: return launch_dh<128>(qkv, B, N, heads, out, s, pf);
         default: return FREE_ERR_SHAPE;
     }
 }

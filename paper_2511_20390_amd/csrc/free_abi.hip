@@ -231,11 +231,10 @@ int32_t linear_dispatch(const Dims& d, const void* A, const void* W, const float
     return launch_linear_simple(A, W, bias, M, N, K, d.mode, epi, out, resid, gate, s);
 }
 
-int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, bool few_rows,
-                           const Prefetch& pf) {
+int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, const Prefetch& pf) {
     if (d.mode == FREE_BF16 && mfma_attention_supported(d.ntok, d.dh))
         return launch_attention_mfma(static_cast<const bf16_t*>(qkv), B, d.ntok, d.heads, d.dh,
-                                     static_cast<bf16_t*>(out), s, few_rows, pf);
+                                     static_cast<bf16_t*>(out), s, pf);
     if (d.mode == FREE_FP32 && mfma_attention_f32_supported(d.ntok, d.dh))
         return launch_attention_mfma_f32(static_cast<const float*>(qkv), B, d.ntok, d.heads, d.dh,
                                          static_cast<float*>(out), s);
@@ -317,11 +316,10 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     };
     // Few rows: the GEMMs are bound by how fast a CU gets its weights, so the short kernels in front of them pull the weights
     // of this block into the caches.  (fp32 GEMMs are bound by the matrix cores: no gain, 0.4 % lost on 2 x 256 tokens.)
-    const bool few_rows = M < kMinFoldRows && cu_share == 1;       // (never the part of a larger batch)
-    const bool pull = few_rows && weights_far && d.mode == FREE_BF16;
+    const bool few_rows = weights_far && d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
     auto ahead = [&](int l, int w0, int64_t n0, int w1, int64_t n1) {
         Prefetch p;
-        if (pull) {
+        if (few_rows) {
             p.p[0] = W(l, w0);
             p.bytes[0] = n0 * static_cast<int64_t>(esz);
             p.p[1] = W(l, w1);
@@ -349,7 +347,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         {
             ProfScope prof(pf, PROF_ATTN, s);
-            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, few_rows, ahead(l, B_FC1_W, DF, B_FC2_W, DF)));
+            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(l, B_FC1_W, DF, B_FC2_W, DF)));
         }
         if (fold) {
             // the out-projection also prepares the second LayerNorm: z = x (1 + scale2), partial row sums
@@ -1025,8 +1023,7 @@ int32_t free_op_attention(const void* qkv, int32_t B, int32_t N, int32_t heads, 
     d.ntok = N;
     d.heads = heads;
     d.dh = dh;
-    return attention_dispatch(d, qkv, B, out, static_cast<hipStream_t>(stream),
-                              static_cast<int64_t>(B) * N < kMinFoldRows, Prefetch{});
+    return attention_dispatch(d, qkv, B, out, static_cast<hipStream_t>(stream), Prefetch{});
 }
 
 int32_t free_op_ln_modulate(const float* x, const float* shift, const float* scale, int32_t mod_stride, int32_t M,

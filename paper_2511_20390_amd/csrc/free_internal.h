@@ -239,9 +239,8 @@ int32_t launch_ln_fold(const float* mod, int32_t B, int32_t D, int32_t mod_strid
                        int32_t rows_fc1, const void* const* w_tab, const float* const* b_tab, float* fold,
                        int64_t fold_stride, hipStream_t s);
 bool mfma_attention_supported(int32_t N, int32_t dh);
-// few_rows: the batch never runs cut in parts, so the kernel may be chosen by B (its forms differ in rounding)
 int32_t launch_attention_mfma(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
-                              bf16_t* out, hipStream_t s, bool few_rows, const Prefetch& pf = Prefetch{});
+                              bf16_t* out, hipStream_t s, const Prefetch& pf = Prefetch{});
 // fp32 operands and softmax on the matrix cores (attn_f32_mfma.hip); qkv and out 16-byte aligned
 bool mfma_attention_f32_supported(int32_t N, int32_t dh);
 int32_t launch_attention_mfma_f32(const float* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
