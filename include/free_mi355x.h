@@ -451,6 +451,11 @@ int32_t free_op_linear(const void* A, const void* W, const float* bias, int32_t 
                        int32_t Kdim, int32_t dtype, int32_t epilogue, void* out,
                        float* resid, const float* gate, int32_t gate_stride,
                        int32_t rows_per_sample, void* stream);
+/* The matrix-core kernel and tile free_op_linear (epilogue 0 to 2), free_op_linear_ln (3: plain, 4: GELU) or
+ * free_op_linear_resid_prep (5) launches for operands that are 16-byte aligned: 1000000 * kernel (0: staged through
+ * registers, 1: few rows, 2: many rows) + 1000 * rows + columns of the tile.  Host only: no device call but the count of
+ * compute units (256 where there is no device).  FREE_ERR_SHAPE where no such kernel covers the shape. */
+int32_t free_linear_tile(int32_t M, int32_t N, int32_t Kdim, int32_t dtype, int32_t epilogue);
 /* out[b, n, h*dh + :] = softmax(q k^T / sqrt(dh)) v per (sample, head);
  * qkv [B*N, 3*heads*dh] rows ordered q | k | v, out [B*N, heads*dh]; dh <= 128. */
 int32_t free_op_attention(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,

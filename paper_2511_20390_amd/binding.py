@@ -32,7 +32,7 @@ EXPORTED_SYMBOLS = [
     "free_drafter_weight_count", "free_drafter_create", "free_drafter_destroy", "free_drafter_workspace_bytes",
     "drafter_forward", "draft_round", "free_sample_workspace_bytes", "free_sample",
     "free_self_speculative_workspace_bytes", "free_self_speculative", "free_lambda_profile",
-    "free_op_linear", "free_op_attention", "free_op_ln_modulate",
+    "free_op_linear", "free_linear_tile", "free_op_attention", "free_op_ln_modulate",
     "free_dit_set_ln_fold", "free_dit_ln_fold_active", "free_op_ln_fold_vectors", "free_op_linear_resid_prep",
     "free_op_linear_ln",
     "free_profile_begin", "free_profile_end", "free_profile_category_name", "free_mfma_ceiling", "free_validate_inputs",
@@ -126,6 +126,8 @@ def load():
     lib.free_lambda_profile.argtypes = [vp, i32, i32, vp]
     lib.free_op_linear.restype = i32
     lib.free_op_linear.argtypes = [vp, vp, vp, i32, i32, i32, i32, i32, vp, vp, vp, i32, i32, vp]
+    lib.free_linear_tile.restype = i32
+    lib.free_linear_tile.argtypes = [i32] * 5
     lib.free_op_attention.restype = i32
     lib.free_op_attention.argtypes = [vp, i32, i32, i32, i32, i32, vp, vp]
     lib.free_op_ln_modulate.restype = i32

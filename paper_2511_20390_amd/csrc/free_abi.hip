@@ -946,6 +946,12 @@ int32_t free_op_linear(const void* A, const void* W, const float* bias, int32_t 
     return linear_dispatch(d, A, W, bias, M, N, Kdim, epilogue, out, resid, g, static_cast<hipStream_t>(stream));
 }
 
+int32_t free_linear_tile(int32_t M, int32_t N, int32_t Kdim, int32_t dtype, int32_t epilogue) {
+    if (dtype != FREE_FP32 && dtype != FREE_BF16) return FREE_ERR_DTYPE;
+    if (epilogue < FREE_EPI_BIAS || epilogue > FREE_EPI_GATE_RESID_PREP) return FREE_ERR_RANGE;
+    return mfma_linear_tile(M, N, Kdim, dtype, epilogue);
+}
+
 int32_t free_op_ln_fold_vectors(const float* mod, int32_t B, int32_t hidden, int32_t ffn, int32_t mod_stride,
                                 int32_t depth, const void* const* w_qkv, const float* const* b_qkv,
                                 const void* const* w_fc1, const float* const* b_fc1, float* fold,

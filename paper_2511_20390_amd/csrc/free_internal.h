@@ -233,6 +233,9 @@ bool mfma_linear_f32_supported(int32_t M, int32_t N, int32_t K);
 int32_t launch_linear_mfma_f32(const float* A, const float* W, const float* bias, int32_t M, int32_t N,
                                int32_t K, int32_t epi, float* out, float* resid, RowVec gate, hipStream_t s,
                                int cu_share = 1);
+// the kernel and tile the two launches above pick for a problem with aligned operands that has the device to itself, encoded
+// as free_linear_tile returns it; negative: not theirs
+int32_t mfma_linear_tile(int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epi);
 // fold vectors of all blocks in one launch (lnfold_mfma.hip); see LnFold
 bool ln_fold_supported(int32_t D, int32_t rows_qkv, int32_t rows_fc1);
 int32_t launch_ln_fold(const float* mod, int32_t B, int32_t D, int32_t mod_stride, int32_t depth, int32_t rows_qkv,

@@ -365,17 +365,11 @@ double small_tile_time(int M, int N, int nk, double sc, int cus) {
     return full * shared + (rest == 0.0 ? 0.0 : (rest <= cus ? alone : shared));
 }
 
-// cu_share: how many launches of this size are expected to run side by side (the halves of a packed batch on two
-// streams); the tile configuration is chosen for that share of the compute units.  Tiles change how the output
-// is cut, never the order in which a dot product is summed, so the result does not depend on it.
-template <typename T>
-int32_t choose_and_launch(const T* X, const T* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                          T* out, float* resid, RowVec gate, hipStream_t s, int cu_share) {
-    if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
-    constexpr int kSliceElems = kRowBytes / static_cast<int>(sizeof(T));
-    const double sc = sizeof(T) == 4 ? 4.4 : 1.0;
-    const int nk = (K + kSliceElems - 1) / kSliceElems;
-    const int cus = std::max(1, device_cus() / std::max(1, cu_share));
+enum StagedTile { STAGED_96x128, STAGED_128x128, STAGED_160x128, STAGED_256x128, STAGED_256x256, STAGED_384x192 };
+
+// cus: compute units this launch can count on.  Tiles change how the output is cut, never the order in which a dot product is
+// summed, so the result does not depend on the choice.
+StagedTile choose_staged(int32_t M, int32_t N, int nk, double sc, int cus) {
     const double t256 = cfg_time(M, N, nk, 256, 256, 1.83 * sc, 9.0, cus);
     const double t384 = cfg_time(M, N, nk, 384, 192, 2.06 * sc, 10.0, cus);
     const double t2x1 = cfg_time(M, N, nk, 256, 128, 1.31 * sc, 6.0, cus);
@@ -397,101 +391,124 @@ int32_t choose_and_launch(const T* X, const T* W, const float* bias, int32_t M, 
         else if (tiles <= 2.0 * cus) t160 = nk * 1.40 * sc + 4.0;
     }
     const double best = std::fmin(std::fmin(std::fmin(t256, t384), std::fmin(t2x1, t128)), std::fmin(t96, t160));
-    if (best == t160) return launch_cfg<T, 160, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    if (best == t96) return launch_cfg<T, 96, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    if (best == t384) return launch_cfg<T, 384, 192, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    if (best == t256) return launch_cfg<T, 256, 256, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    if (best == t2x1) return launch_cfg<T, 256, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    return launch_cfg<T, 128, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+    if (best == t160) return STAGED_160x128;
+    if (best == t96) return STAGED_96x128;
+    if (best == t384) return STAGED_384x192;
+    if (best == t256) return STAGED_256x256;
+    if (best == t2x1) return STAGED_256x128;
+    return STAGED_128x128;
 }
+
+template <typename T>
+int32_t launch_staged(StagedTile tile, const T* X, const T* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                      T* out, float* resid, RowVec gate, hipStream_t s) {
+    switch (tile) {
+        case STAGED_96x128: return launch_cfg<T, 96, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case STAGED_128x128: return launch_cfg<T, 128, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case STAGED_160x128: return launch_cfg<T, 160, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case STAGED_256x128: return launch_cfg<T, 256, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case STAGED_256x256: return launch_cfg<T, 256, 256, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+        case STAGED_384x192: return launch_cfg<T, 384, 192, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
+    }
+    return FREE_ERR_RANGE;
+}
+
+// A tile of one of the three kernels and the constants of its time.
+enum TileFamily { TILE_STAGED, TILE_ROWS, TILE_PIPE };     // this file, gemm_rows.hip, gemm_pipe.hip
+struct TileTime {
+    TileFamily family;
+    int tile, bm, bn;
+    bool paired, paired_resid;    // two workgroups fit a CU (80 KB of LDS and the registers): bias epilogues, residual update
+    double f;                     // per launch
+    double e_bias, e_gelu, e_resid;    // per round of workgroups, by epilogue
+    double a, b, d;               // per slice alone; per slice and per round for each of two that share a CU
+};
 
 // Tile choice for bf16 problems of whole slices.  Time of a launch: `f` + per round of workgroups (nk slices + `e`), with
-// `a` us per slice for a workgroup that has its CU to itself and `b` each for two that share one (tiles of at most 80 KB of
-// LDS; `b` unused otherwise).  Fitted to the times of every tile at 40 values of M from 64 to 12288 and the four layer shapes
-// at widths 384, 768 and 1152, weights from HBM and from the caches in equal parts (rms error 10-16 % per tile); the tile
-// chosen is within 0.5 % of the best one on average, 11 % at worst (2048 x 4608 x 1152: 29.8 us for 26.9).  Tiles change how
-// the output is cut, never the order in which a dot product is summed, so the result does not depend on the choice.
-struct TileTime {
-    bool rows;                    // gemm_rows.hip / gemm_pipe.hip
-    int tile, bm, bn;
-    bool paired;                  // two workgroups fit a CU
-    double f, e, a, b;
-};
+// `a` us per slice for a workgroup that has its CU to itself, and `b` per slice and `d` more per round for each of two that
+// share one.  Constants fitted to the times of every tile at 50 values of M from 64 to 12288 and the layer shapes at widths 384,
+// 768 and 1152, weights from HBM and from the caches in equal parts, so that the tile chosen is close to the best one (a tile
+// within some 3 % of the best counts in part: no choice hangs on the last digit); the times themselves are met to 14 % rms.
+// The tile chosen is 0.2 % behind the best one on average, 15 % at worst (4095 x 384 x 768: 11.6 us for 10.1).  One `e` for all
+// epilogues and both kinds of round, as the table had before, was 1.0 % behind on average and a third at worst (4000 x 768 x
+// 768 with the residual update 15.2 us, now 11.3; 2048 x 4608 x 1152 with GELU 28.5 us, now 26.2): the epilogue of a
+// residual update moves eight bytes per element where the others move two.
+// Tiles change how the output is cut, never the order in which a dot product is summed, so the result does not depend on the
+// choice.
 constexpr TileTime kTiles[] = {
-    {true, ROWS_64x64, 64, 64, true, 2.1, 1.2, 0.231, 0.472},
-    {true, ROWS_128x64, 128, 64, true, 1.3, 2.5, 0.347, 0.731},
-    {true, ROWS_128x128, 128, 128, false, 0.5, 4.8, 0.453, 0.0},
-    {false, PIPE_128x128, 128, 128, true, 0.5, 3.7, 0.546, 1.053},
-    {false, PIPE_160x128, 160, 128, true, 4.2, 1.6, 0.643, 1.360},
-    {false, PIPE_192x128, 192, 128, true, 0.5, 4.7, 0.646, 1.400},
-    {false, PIPE_256x192, 256, 192, false, 0.5, 8.5, 1.058, 0.0},
-    {false, PIPE_192x256, 192, 256, false, 0.5, 8.3, 1.044, 0.0},
-    {false, PIPE_256x256, 256, 256, false, 0.5, 10.0, 1.278, 0.0},
-    {false, PIPE_384x192, 384, 192, false, 0.5, 10.9, 1.451, 0.0},
+    {TILE_ROWS, ROWS_64x64, 64, 64, true, true, 1.1, 1.2, 1.6, 1.7, 0.215, 0.449, 0.0},
+    {TILE_ROWS, ROWS_128x64, 128, 64, true, true, 0.9, 2.0, 2.4, 3.6, 0.256, 0.717, 0.7},
+    {TILE_ROWS, ROWS_128x128, 128, 128, false, false, 0.1, 5.1, 5.8, 11.3, 0.318, 0.0, 0.0},
+    {TILE_PIPE, PIPE_128x128, 128, 128, true, true, 0.0, 3.0, 3.7, 2.8, 0.567, 0.811, 1.1},
+    {TILE_PIPE, PIPE_160x128, 160, 128, true, false, 1.0, 4.3, 6.0, 10.2, 0.475, 0.829, 1.8},
+    {TILE_PIPE, PIPE_192x128, 192, 128, true, true, 0.0, 3.9, 4.6, 4.4, 0.627, 0.981, 3.8},
+    {TILE_PIPE, PIPE_256x192, 256, 192, false, false, 1.7, 1.6, 4.7, 4.2, 1.188, 0.0, 0.0},
+    {TILE_PIPE, PIPE_192x256, 192, 256, false, false, 0.0, 7.6, 10.7, 9.6, 0.958, 0.0, 0.0},
+    {TILE_PIPE, PIPE_256x256, 256, 256, false, false, 1.4, 5.7, 8.5, 12.4, 1.135, 0.0, 0.0},
+    {TILE_PIPE, PIPE_384x192, 384, 192, false, false, 1.8, 6.9, 9.9, 12.6, 1.300, 0.0, 0.0},
 };
-
-// Time of a launch of `u` workgroups per CU.  last_alone: up to this many workgroups per CU left over after the full pairs
-// run as if they had a CU each.
-double launch_time(const TileTime& t, double u, int nk, double last_alone) {
-    const double alone = nk * t.a + t.e, shared = nk * t.b + t.e;
-    if (!t.paired) return t.f + std::ceil(u) * alone;
-    const double full = std::floor(u / 2.0), rest = u - 2.0 * full;
-    return t.f + full * shared + (rest <= 0.0 ? 0.0 : rest <= (full > 0.0 ? last_alone : 1.0) ? alone : shared);
-}
-
-// cu_share: how many launches of this size are expected to run side by side (the parts of a packed batch on several
-// streams); the tile is chosen for that share of the compute units.
-const TileTime& choose_tile(int32_t M, int32_t N, int32_t K, int32_t epi, bool rows_ok, int cu_share) {
-    const double cus = std::max(1, device_cus() / std::max(1, cu_share));
-    const int nk = K / BK;
-    const TileTime* best = nullptr;
-    double t_best = 0.0;
-    for (const TileTime& t : kTiles) {
-        if (t.rows && (!rows_ok || epi > FREE_EPI_GATE_RESID)) continue;
-        if (epi == FREE_EPI_GATE_RESID_PREP && t.bn != 256) continue;        // whole 128-column slots of row sums
-        const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) / cus;
-        const double time = launch_time(t, u, nk, 1.0);
-        if (best == nullptr || time < t_best) {
-            best = &t;
-            t_best = time;
-        }
-    }
-    return *best;
-}
 
 // The same for fp32 (slices of 32, whole ones).  A slice of a 32 x 32 block is 16 products of 64 cycles, so the matrix cores
 // decide as soon as every SIMD has a wavefront, and below that the number of tiles does: 512 x 1152 x 4608 is 54 tiles of
 // 96 x 128 (217 us) or 144 of 64 x 64 (89 us).  Fitted to every tile at 18 values of M from 64 to 4096 and the four layer
 // shapes at widths 384, 768 and 1152 (rms error 2-5 %); the chosen tile is within 1 % of the best one on average, 5 % at
-// worst, up to kFewRowsF32 rows.  Above that the rule of choose_and_launch is as good.  us, old rule -> this one, at width
+// worst, up to kFewRowsF32 rows.  Above that the rule of choose_staged is as good.  us, old rule -> this one, at width
 // 1152 (QKV, out-projection, MLP-1, MLP-2):  64 rows 57 56 56 208 -> 24 24 23 82;  512 rows 61 59 64 217 -> 44 26 64 89;
 // 1024 rows 77 60 96 218 -> 75 44 96 153;  2048 rows 142 63 179 229 -> 141 63 179 229.
 constexpr int kFewRowsF32 = 2048;
-enum { F32_96x128 = 100, F32_128x128, F32_160x128, F32_256x256 };
 constexpr TileTime kTilesF32[] = {
-    {true, ROWS_64x64, 64, 64, true, 2.0, 2.3, 0.572, 1.082},
-    {true, ROWS_128x64, 128, 64, true, 3.9, 1.7, 1.038, 2.043},
-    {false, F32_96x128, 96, 128, true, 3.5, 2.8, 1.455, 2.872},
-    {false, F32_128x128, 128, 128, true, 8.0, 0.0, 1.881, 3.739},
-    {false, F32_160x128, 160, 128, true, 0.0, 8.6, 2.329, 4.623},
-    {false, F32_256x256, 256, 256, false, 0.6, 9.9, 7.039, 0.0},
+    {TILE_ROWS, ROWS_64x64, 64, 64, true, true, 2.0, 2.3, 2.3, 2.3, 0.572, 1.082, 0.0},
+    {TILE_ROWS, ROWS_128x64, 128, 64, true, true, 3.9, 1.7, 1.7, 1.7, 1.038, 2.043, 0.0},
+    {TILE_STAGED, STAGED_96x128, 96, 128, true, true, 3.5, 2.8, 2.8, 2.8, 1.455, 2.872, 0.0},
+    {TILE_STAGED, STAGED_128x128, 128, 128, true, true, 8.0, 0.0, 0.0, 0.0, 1.881, 3.739, 0.0},
+    {TILE_STAGED, STAGED_160x128, 160, 128, true, true, 0.0, 8.6, 8.6, 8.6, 2.329, 4.623, 0.0},
+    {TILE_STAGED, STAGED_256x256, 256, 256, false, false, 0.6, 9.9, 9.9, 9.9, 7.039, 0.0, 0.0},
 };
 
-const TileTime& choose_tile_f32(int32_t M, int32_t N, int32_t K, bool rows_ok, int cu_share) {
-    const double cus = std::max(1, device_cus() / std::max(1, cu_share));
-    const int nk = K / (kRowBytes / 4);
+// Time of a launch of `u` workgroups per CU.  last_alone: up to this many workgroups per CU left over after the full pairs
+// run as if they had a CU each.
+double launch_time(const TileTime& t, int32_t epi, double u, int nk, double last_alone) {
+    const bool resid = epi == FREE_EPI_GATE_RESID || epi == FREE_EPI_GATE_RESID_PREP;
+    const bool gelu = epi == FREE_EPI_BIAS_GELU || epi == FREE_EPI_LN_BIAS_GELU;
+    const double e = resid ? t.e_resid : gelu ? t.e_gelu : t.e_bias;
+    const double alone = nk * t.a + e, shared = nk * t.b + e + t.d;
+    if (!(resid ? t.paired_resid : t.paired)) return t.f + std::ceil(u) * alone;
+    const double full = std::floor(u / 2.0), rest = u - 2.0 * full;
+    return t.f + full * shared + (rest <= 0.0 ? 0.0 : rest <= (full > 0.0 ? last_alone : 1.0) ? alone : shared);
+}
+
+// What a problem is launched on.  rows_ok: linear_rows_covers holds.  cu_share: how many launches of this size are expected to
+// run side by side (the parts of a packed batch on several streams); the tile is chosen for that share of the compute units.
+struct Choice {
+    TileFamily family;
+    int tile, bm, bn;
+};
+Choice choose(int32_t M, int32_t N, int32_t K, int elem_bytes, int32_t epi, bool rows_ok, int cu_share) {
+    const int cus = std::max(1, device_cus() / std::max(1, cu_share));
+    const int slice = kRowBytes / elem_bytes, nk = (K + slice - 1) / slice;
+    const bool f32 = elem_bytes == 4;
+    if (K % slice != 0 || (f32 && M > kFewRowsF32)) {
+        static constexpr int dims[][2] = {{96, 128}, {128, 128}, {160, 128}, {256, 128}, {256, 256}, {384, 192}};
+        const StagedTile t = choose_staged(M, N, nk, f32 ? 4.4 : 1.0, cus);
+        return {TILE_STAGED, t, dims[t][0], dims[t][1]};
+    }
     const TileTime* best = nullptr;
     double t_best = 0.0;
-    for (const TileTime& t : kTilesF32) {
-        if (t.rows && !rows_ok) continue;
+    auto consider = [&](const TileTime& t, double last_alone) {
+        if (t.family == TILE_ROWS && (!rows_ok || epi > FREE_EPI_GATE_RESID)) return;
+        if (epi == FREE_EPI_GATE_RESID_PREP && t.bn != 256) return;          // whole 128-column slots of row sums
         const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) / cus;
-        const double time = launch_time(t, u, nk, 0.75);
+        const double time = launch_time(t, epi, u, nk, last_alone);
         if (best == nullptr || time < t_best) {
             best = &t;
             t_best = time;
         }
-    }
-    return *best;
+    };
+    if (f32)
+        for (const TileTime& t : kTilesF32) consider(t, 0.75);
+    else
+        for (const TileTime& t : kTiles) consider(t, 1.0);
+    return {best->family, best->tile, best->bm, best->bn};
 }
 
 }  // namespace
@@ -526,11 +543,13 @@ int32_t launch_linear_mfma(const bf16_t* X, const bf16_t* W, const float* bias, 
         }
     }
     if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
-    if (K % BK != 0) return ln ? FREE_ERR_SHAPE : choose_and_launch<bf16_t>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share);
-    if (ln == nullptr && epi > FREE_EPI_GATE_RESID) return FREE_ERR_SHAPE;
-    const TileTime& t = choose_tile(M, N, K, epi, linear_rows_covers(N, K, 2, bias, out, resid, gate), cu_share);
-    return t.rows ? launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(t.tile))
-                  : launch_linear_pipe(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<PipeTile>(t.tile), ln);
+    if (ln != nullptr ? K % BK != 0 : epi > FREE_EPI_GATE_RESID) return FREE_ERR_SHAPE;
+    const Choice c = choose(M, N, K, 2, epi, linear_rows_covers(N, K, 2, bias, out, resid, gate), cu_share);
+    switch (c.family) {
+        case TILE_ROWS: return launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(c.tile));
+        case TILE_PIPE: return launch_linear_pipe(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<PipeTile>(c.tile), ln);
+        default: return launch_staged(static_cast<StagedTile>(c.tile), X, W, bias, M, N, K, epi, out, resid, gate, s);
+    }
 }
 
 bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample) {
@@ -541,17 +560,20 @@ bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample) {
 int32_t launch_linear_mfma_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K,
                                int32_t epi, float* out, float* resid, RowVec gate, hipStream_t s, int cu_share) {
     if (!mfma_linear_f32_supported(M, N, K)) return FREE_ERR_SHAPE;
-    if (K % (kRowBytes / 4) != 0 || M > kFewRowsF32 || epi > FREE_EPI_GATE_RESID)
-        return choose_and_launch<float>(X, W, bias, M, N, K, epi, out, resid, gate, s, cu_share);
     if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
-    const TileTime& t = choose_tile_f32(M, N, K, linear_rows_covers(N, K, 4, bias, out, resid, gate), cu_share);
-    if (t.rows) return launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(t.tile));
-    switch (t.tile) {
-        case F32_96x128: return launch_cfg<float, 96, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-        case F32_128x128: return launch_cfg<float, 128, 128, 2, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-        case F32_160x128: return launch_cfg<float, 160, 128, 1, 4>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-        default: return launch_cfg<float, 256, 256, 4, 2>(X, W, bias, M, N, K, epi, out, resid, gate, s);
-    }
+    if (epi > FREE_EPI_GATE_RESID) return FREE_ERR_RANGE;
+    const Choice c = choose(M, N, K, 4, epi, linear_rows_covers(N, K, 4, bias, out, resid, gate), cu_share);
+    if (c.family == TILE_ROWS)
+        return launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(c.tile));
+    return launch_staged(static_cast<StagedTile>(c.tile), X, W, bias, M, N, K, epi, out, resid, gate, s);
+}
+
+int32_t mfma_linear_tile(int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epi) {
+    const int es = dtype == FREE_BF16 ? 2 : 4;
+    if (!(es == 2 ? mfma_linear_supported(M, N, K) : mfma_linear_f32_supported(M, N, K))) return FREE_ERR_SHAPE;
+    if (epi > FREE_EPI_GATE_RESID && (es == 4 || K % BK != 0)) return FREE_ERR_SHAPE;
+    const Choice c = choose(M, N, K, es, epi, linear_rows_covers(N, K, es, nullptr, nullptr, nullptr, RowVec{nullptr, 0, 1}), 1);
+    return c.family * 1000000 + c.bm * 1000 + c.bn;
 }
 
 }  // namespace freemi
