@@ -192,9 +192,13 @@ def _dev(t, dtype, name, shape=None, optional=False):
 
 def _stream():
     """Handle of the current stream of the current device.  A verification call is bound by its submission (15 us
-    against 6 us of kernels on one trajectory), and a torch stream object made for its handle alone was 3 us of that."""
+    against 6 us of kernels on one trajectory), and a torch stream object made for its handle alone was 3 us of that:
+    torch's function for the bare handle is used where there is one (it is not part of torch's public interface)."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def make_config(cfg: dict, mode: str) -> FreeDitConfig:

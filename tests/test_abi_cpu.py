@@ -282,3 +282,15 @@ def test_binding_refuses_tensors_the_library_would_misread():
         with pytest.raises(binding.FreeError) as e:
             binding._dev(bad, torch.int32 if bad.dtype == torch.int64 else torch.float32, "x", (4, 6))
         assert e.value.status == status
+
+
+def test_stream_handle_without_the_private_torch_function(monkeypatch):
+    """The handle of the current stream, by the short way where torch has it and by a stream object where not."""
+    import types
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 40 + dev, raising=False)
+    assert binding._stream() == 43
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._stream() == 77
