@@ -12,9 +12,12 @@ namespace {
 // matrix read as zero).  Inline assembly, because the compiler lets every LDS read wait for all such loads of the builtin
 // form (it cannot tell the stages apart); wait_vm counts them by hand.  The compiler's own counts stay right: it knows of
 // fewer loads in flight than there are and so waits for more.
+// No memory clobber, though it writes LDS: the products and fragment reads around it stay free to move, and what keeps an LDS
+// read from crossing the write of its stage are the clobbers of the two waits below alone - every stage is read between
+// the wait_vm_barrier that says it has arrived and the wait_lds_barrier (or next wait_vm_barrier) that hands it back.
 __device__ __forceinline__ void dma_1k(uint32_t lds_addr, int voff, u32x4_t rsrc, int soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff));
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "{m0}"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff));
 }
 
 // at most N of this wavefront's loads still in flight and all its LDS reads returned, then the workgroup's barrier

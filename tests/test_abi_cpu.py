@@ -294,3 +294,18 @@ def test_stream_handle_without_the_private_torch_function(monkeypatch):
     assert binding._stream() == 43
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
     assert binding._stream() == 77
+
+
+def test_inline_assembly_declares_m0():
+    """A load to LDS takes its LDS address from m0.  Where inline assembly issues one, the address is an operand in m0 - written
+    inside the assembly instead, it would overwrite what the compiler keeps there without its knowledge."""
+    csrc = os.path.join(ROOT, "paper_2511_20390_amd", "csrc")
+    seen = 0
+    for name in sorted(os.listdir(csrc)):
+        if not name.endswith((".hip", ".h")):
+            continue
+        for asm in re.findall(r"asm volatile\((.*?)\);", open(os.path.join(csrc, name)).read(), re.S):
+            if re.search(r'offen lds|\bm0\b', asm):
+                seen += 1
+                assert '"{m0}"(' in asm and not re.search(r"s_\w+ m0,", asm), (name, asm)
+    assert seen
