@@ -13,6 +13,9 @@ namespace freemi {
 // attention kernel (idle CUs at few rows) those of the MLP.  512 rows at width 1152, us per launch without -> with: QKV 10.7
 // -> 8.5, out-projection 8.9 -> 7.0, MLP-1 15.0 -> 11.6, MLP-2 23.5 -> 17.0 against LayerNorm 5.1 -> 6.0 and attention
 // 8.9 -> 11.6; forward 2.30 -> 1.99 ms.  1024 rows: round 2.99 -> 2.69 ms.
+// From some 1500 rows on QKV and MLP-1 run on tiles whose order gives every XCD all of the weights: what the read-ahead brings
+// then is in the Infinity Cache rather than in the right L2, and buys 6 to 9 % of the forward instead of 11 to 14 (2560 to 3840
+// against 256 to 1024 rows).  LayerNorm and attention each contribute: 4 and 8 % of those 11 to 14.
 __device__ inline void prefetch_lines(const Prefetch& pf, int first) {
     const int xcd = blockIdx.x & 7, rank = (blockIdx.x - first) >> 3, n = (gridDim.x - first) >> 3;
     uint32_t acc = 0;

@@ -26,3 +26,25 @@ def test_alone_or_packed_same_bits(hidden, heads, lat_h, lat_w, B, mode):
         assert torch.equal(eps1.reshape(-1), eps[b].reshape(-1)), b
         assert torch.equal(feat1.reshape(-1), feat.reshape(B, -1)[b]), b
     model.close()
+
+
+@pytest.mark.parametrize("hidden,heads,depth", [(512, 8, 44), (1152, 16, 5), (2048, 16, 3)])
+def test_reading_weights_ahead_changes_no_bit(hidden, heads, depth):
+    """Models whose weights do not stay in the caches have them read ahead by the LayerNorm and attention launches of small
+    packs; the same states in a pack of 17, too large for that, without folded LayerNorms, give the same bits."""
+    import torch
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("small", hidden=hidden, heads=heads, mlp_hidden=4 * hidden, depth=depth, lat_h=32, lat_w=32)
+    assert depth * 18 * hidden * hidden * 2 >= 192 << 20 and 17 * synth.n_tokens(cfg) >= 4096
+    model = binding.FreeDit(cfg, pu.weights_for(cfg, "bf16", 13), "bf16")
+    model.set_ln_fold(binding.LN_FOLD_OFF)
+    rng = np.random.default_rng(14)
+    x = pu.to_dev(rng.standard_normal((17, cfg["in_ch"], 32, 32)).astype(np.float32))
+    t, y = (pu.to_dev(rng.integers(0, n, 17).astype(np.int32)) for n in (1000, cfg["num_classes"] + 1))
+    eps, feat = (v.clone() for v in model.dit_forward_packed(x, t, y, want_feat=True))
+    for lo, hi in ((0, 1), (1, 4), (4, 17)):
+        part = [v[lo:hi].contiguous() for v in (x, t, y)]
+        eps1, feat1 = model.dit_forward_packed(*part, want_feat=True)
+        assert torch.equal(eps1.reshape(-1), eps[lo:hi].reshape(-1)), lo
+        assert torch.equal(feat1.reshape(-1), feat.reshape(17, -1)[lo:hi].reshape(-1)), lo
+    model.close()
