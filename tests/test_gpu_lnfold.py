@@ -93,6 +93,26 @@ def test_residual_update_that_prepares_the_next_layer_norm(M, N, K, rows):
                                              (12288, 3456, 1152, 1024, 0.3), (12288, 4608, 1152, 1024, 0.0),
                                              (6144, 4608, 1152, 1024, 1.0), (1000, 392, 384, 96, 0.2)])
 def test_linear_after_a_folded_layer_norm(M, N, K, rows, mean, gelu):
+    check_linear_after_a_folded_layer_norm(M, N, K, rows, mean, gelu)
+
+
+# every tile: a ragged last tile in both directions, samples that end inside a wavefront's rows (96 and 160 in blocks of 64 to
+# 160), and one sample per wavefront (192 x 256 is never taken with GELU)
+@pytest.mark.parametrize("tile,gelu,M,N,K,rows", [
+    (128128, False, 1000, 392, 384, 96), (128128, True, 1000, 392, 384, 160),
+    (160128, False, 9000, 392, 768, 96), (160128, True, 5000, 1544, 768, 96), (160128, True, 9000, 392, 1152, 480),
+    (192128, False, 9000, 392, 256, 96), (192128, True, 9000, 392, 256, 480), (192128, True, 8190, 520, 1152, 160),
+    (192256, False, 11000, 1000, 256, 96), (192256, False, 11000, 1000, 1152, 480),
+    (256192, False, 5000, 1544, 256, 96), (256192, True, 5000, 1544, 256, 160), (256192, False, 12100, 776, 1152, 480),
+    (256256, False, 5000, 2312, 256, 160), (256256, True, 5000, 2312, 768, 96),
+    (384192, False, 6500, 2312, 256, 96), (384192, True, 10000, 1544, 256, 160)])
+def test_linear_after_a_folded_layer_norm_by_tile(tile, gelu, M, N, K, rows):
+    from paper_2511_20390_amd import binding
+    assert binding.load().free_linear_tile(M, N, K, binding.FREE_BF16, 4 if gelu else 3) == 2000000 + tile
+    check_linear_after_a_folded_layer_norm(M, N, K, rows, 0.3, gelu)
+
+
+def check_linear_after_a_folded_layer_norm(M, N, K, rows, mean, gelu):
     """act((LN(x) (1 + scale) + shift) W^T + b) from z = bf16(x (1 + scale)), the row sums and the fold vectors,
     against the oracle's layer_norm / linear / gelu_tanh on the same x."""
     from paper_2511_20390_amd import binding
