@@ -209,6 +209,8 @@ int32_t launch_adaln_mfma(const float* sc, int32_t B, int32_t D, const void* con
                           int32_t total_rows, int32_t mode, float* mod, hipStream_t s);
 
 // ---- MFMA kernels, bf16 only (gemm_mfma.hip, attn_mfma.hip) ------------------------
+// compute units of the device (256 where there is none): asked once
+int device_cus();
 bool mfma_linear_supported(int32_t M, int32_t N, int32_t K);
 int32_t launch_linear_mfma(const bf16_t* A, const bf16_t* W, const float* bias, int32_t M, int32_t N,
                            int32_t K, int32_t epi, bf16_t* out, float* resid, RowVec gate, hipStream_t s, int cu_share = 1,

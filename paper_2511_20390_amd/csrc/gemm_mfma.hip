@@ -5,8 +5,9 @@
 // v_mfma_f32_32x32x16_bf16 (lane l: row/col l%32, 8 consecutive k at 8*(l/32)).
 //
 // Design for gfx950 (64-wide wavefronts, 160 KB LDS per CU, 512 registers per lane):
-//  * used for fp32 operands and for bf16 with K no multiple of the slice; bf16 problems of whole slices are chosen between
-//    the tiles of gemm_pipe.hip and gemm_rows.hip at the end of this file.
+//  * used for fp32 operands and for bf16 with K no multiple of the slice (no model of this library has such a layer; the
+//    operator entry takes them); bf16 problems of whole slices are chosen between the tiles of gemm_pipe.hip and
+//    gemm_rows.hip at the end of this file.  Rates quoted below for bf16 were measured when this kernel took those as well.
 //  * workgroup = 4 or 8 wavefronts in a WGM x WGN grid, macro tile BM x BN (256x256 and
 //    384x192 with 8 wavefronts - two per SIMD, so one wavefront's memory instructions issue
 //    under the other's MFMAs - 256x128 / 128x128 / 96x128 / 160x128 with 4 for small problems), K slices of
@@ -55,6 +56,17 @@
 #include "gemm_tile.h"
 
 namespace freemi {
+
+int device_cus() {
+    static int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
 
 namespace {
 
@@ -277,17 +289,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(
                             lds + wave * kWaveStage, LnFold{}, ln_scale);
 }
 
-int device_cus() {
-    static int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 template <typename T, int BM, int BN, int WGM, int WGN, int EPI, bool EVEN_K>
 int32_t launch_one(const T* X, const T* W, const float* bias, int32_t M, int32_t N, int32_t K, T* out,
                    float* resid, RowVec gate, hipStream_t s) {
@@ -355,8 +356,7 @@ double cfg_time(int M, int N, int nk, int bm, int bn, double us_per_slice, doubl
 
 // The 128x128 configuration is small enough for two workgroups per CU: measured 0.6 us per slice for a
 // workgroup that has its CU to itself and 1.05 us each for two that share one.  Used for problems of
-// few rows (the drafter, single-state steps), where it decides between half-empty rounds of large
-// tiles and fuller rounds of small ones.
+// few rows, where it decides between half-empty rounds of large tiles and fuller rounds of small ones.
 double small_tile_time(int M, int N, int nk, double sc, int cus) {
     const double tiles = static_cast<double>((M + 127) / 128) * ((N + 127) / 128);
     const double shared = nk * 1.05 * sc + 4.0, alone = nk * 0.6 * sc + 4.0;

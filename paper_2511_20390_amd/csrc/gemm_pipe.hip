@@ -19,10 +19,11 @@
 // the registers of three k-steps of fragments, as many as the staging registers of the register-staged loop take.
 // Measured in one process, launches back to back, against the register-staged loop of gemm_mfma.hip (us, weights from HBM):
 //   12288 rows: QKV 106 -> 98, out-projection 46.6 -> 45.5, MLP-1 (384 x 192) 141 -> 134, MLP-2 134 -> 123
-//   8192 rows:  QKV 75 -> 69, out-projection 41 -> 34, MLP-1 114 -> 100, MLP-2 113 -> 90 (256 x 192 tiles)
-// With 160 of 256 CUs at work MLP-2 takes 1.27 us per slice, the bound above; with 240 it takes 1.55 because the chip
-// reaches its power limit and lowers its clock; whole verification rounds (12 x 1024 tokens: 14.11 -> 13.85 ms, 32 x 256
-// tokens: 10.25 -> 9.36 ms) gain accordingly less than single launches where the chip is full.
+//   8192 rows:  QKV 75 -> 69, out-projection 41 -> 34, MLP-1 114 -> 100, MLP-2 113 -> 90 (192 x 256 tiles)
+// The bound of 1.25 us per slice is reached while part of the chip is idle.  Counters of MLP-2 on 256 x 256 tiles inside
+// verification rounds: 80 workgroups 96 us at 2.4 GHz, 120 workgroups 101 us at 2.4 GHz, 240 workgroups 130 us at 2.0 GHz - with
+// every CU at work the same launch takes 8 % more cycles and the chip, at its power limit, 20 % longer cycles.  Whole rounds
+// (12 x 1024 tokens: 14.01 -> 13.74 ms, 32 x 256 tokens: 10.20 -> 9.31 ms) gain accordingly less than single launches.
 #include <algorithm>
 
 #include "free_internal.h"
@@ -278,17 +279,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_pipe_kernel(
             if (gm < M && gs < ln.slots) ln.stats[(static_cast<int64_t>(gm) * ln.slots + gs) * 2 + k] = h[0] + h[2];
         }
     }
-}
-
-int device_cus() {
-    static int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return n;
-    }();
-    return cus;
 }
 
 struct Args {
