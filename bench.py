@@ -45,18 +45,18 @@ def forward_flops(cfg, B):
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "spec_round_xl2_512_hbm_traffic.md")
 # (epilogue codes in the kernel names: 0 bias, 1 bias + GELU, 2 gated residual update; with the LayerNorms folded
 # into the GEMMs 3 / 4 = the same two after a folded LayerNorm, 5 = residual update that prepares the next one)
-CATEGORY_SYMBOL = {"gemm_fc1": "gemm_bf16_kernel<bf16_t, 384, 192, 4, 2, 4, true>`",
-                   "gemm_qkv": "gemm_bf16_kernel<bf16_t, 256, 256, 4, 2, 3, true>`",
-                   "gemm_fc2": "gemm_bf16_kernel<bf16_t, 256, 256, 4, 2, 5, true>` FC2",
-                   "gemm_proj": "gemm_bf16_kernel<bf16_t, 256, 256, 4, 2, 5, true>` out-projection",
+CATEGORY_SYMBOL = {"gemm_fc1": "gemm_pipe_kernel<384, 192, 4, 2, 4>`",
+                   "gemm_qkv": "gemm_pipe_kernel<256, 256, 2, 4, 3>`",
+                   "gemm_fc2": "gemm_pipe_kernel<256, 256, 2, 4, 5>` FC2",
+                   "gemm_proj": "gemm_pipe_kernel<256, 256, 2, 4, 5>` out-projection",
                    "attention": "attn_mfma_kernel<72, 1>`",
                    "verify_partial": "verify_partial_kernel<256, 4, true, true, false>`"}
 
 
-CATEGORY_SYMBOL_PLAIN = {"gemm_fc1": "gemm_bf16_kernel<bf16_t, 384, 192, 4, 2, 1, true>`",
-                         "gemm_qkv": "gemm_bf16_kernel<bf16_t, 256, 256, 4, 2, 0, true>`",
-                         "gemm_fc2": "gemm_bf16_kernel<bf16_t, 256, 256, 4, 2, 2, true>` FC2",
-                         "gemm_proj": "gemm_bf16_kernel<bf16_t, 256, 256, 4, 2, 2, true>` out-projection"}
+CATEGORY_SYMBOL_PLAIN = {"gemm_fc1": "gemm_pipe_kernel<384, 192, 4, 2, 1>`",
+                         "gemm_qkv": "gemm_pipe_kernel<256, 256, 2, 4, 0>`",
+                         "gemm_fc2": "gemm_pipe_kernel<256, 256, 2, 4, 2>` FC2",
+                         "gemm_proj": "gemm_pipe_kernel<256, 256, 2, 4, 2>` out-projection"}
 
 
 def measured_traffic(category, folded=True):

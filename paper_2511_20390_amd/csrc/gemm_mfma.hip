@@ -5,9 +5,9 @@
 // v_mfma_f32_32x32x16_bf16 (lane l: row/col l%32, 8 consecutive k at 8*(l/32)).
 //
 // Design for gfx950 (64-wide wavefronts, 160 KB LDS per CU, 512 registers per lane):
-//  * used for fp32 operands and for bf16 with K no multiple of the slice (no model of this library has such a layer; the
-//    operator entry takes them); bf16 problems of whole slices are chosen between the tiles of gemm_pipe.hip and
-//    gemm_rows.hip at the end of this file.  Rates quoted below for bf16 were measured when this kernel took those as well.
+//  * used for fp32 operands and for bf16 with K no multiple of the slice; bf16 problems of whole slices are chosen between
+//    the tiles of gemm_pipe.hip and gemm_rows.hip at the end of this file.  Rates quoted below for bf16 were measured when
+//    this kernel took those as well.
 //  * workgroup = 4 or 8 wavefronts in a WGM x WGN grid, macro tile BM x BN (256x256 and
 //    384x192 with 8 wavefronts - two per SIMD, so one wavefront's memory instructions issue
 //    under the other's MFMAs - 256x128 / 128x128 / 96x128 / 160x128 with 4 for small problems), K slices of

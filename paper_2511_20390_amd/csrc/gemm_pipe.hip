@@ -22,7 +22,7 @@
 //   8192 rows:  QKV 75 -> 69, out-projection 41 -> 34, MLP-1 114 -> 100, MLP-2 113 -> 90 (192 x 256 tiles)
 // The bound of 1.25 us per slice is reached while part of the chip is idle.  Counters of MLP-2 on 256 x 256 tiles inside
 // verification rounds: 80 workgroups 96 us at 2.4 GHz, 120 workgroups 101 us at 2.4 GHz, 240 workgroups 130 us at 2.0 GHz - with
-// every CU at work the same launch takes 8 % more cycles and the chip, at its power limit, 20 % longer cycles.  Whole rounds
+// every CU at work the same launch takes 8 % more cycles and the chip, at its power limit, a quarter longer cycles.  Whole rounds
 // (12 x 1024 tokens: 14.01 -> 13.74 ms, 32 x 256 tokens: 10.20 -> 9.31 ms) gain accordingly less than single launches.
 #include <algorithm>
 

@@ -36,3 +36,24 @@ def test_tile_query_errors():
     assert tile(64, 64, 60, binding.FREE_BF16, BIAS) == binding.FREE_ERR_SHAPE      # no whole 16-byte chunks
     assert tile(64, 64, 96, binding.FREE_BF16, 3) == binding.FREE_ERR_SHAPE         # folded LayerNorm: whole slices only
     assert tile(64, 64, 64, binding.FREE_FP32, 3) == binding.FREE_ERR_SHAPE         # and bf16 only
+
+
+@pytest.mark.parametrize("folded", [True, False])
+def test_measured_traffic_belongs_to_the_kernels_of_the_benchmark(folded):
+    """The kernel names under which bench.py looks measured HBM traffic up are those of the kernels its round launches (12288
+    rows of width 1152), and the committed summary has a line for each."""
+    import re
+
+    import bench
+    layers = {"gemm_qkv": (3456, 1152, 3 if folded else BIAS), "gemm_proj": (1152, 1152, 5 if folded else RESID),
+              "gemm_fc1": (4608, 1152, 4 if folded else GELU), "gemm_fc2": (1152, 4608, 5 if folded else RESID)}
+    names = bench.CATEGORY_SYMBOL if folded else bench.CATEGORY_SYMBOL_PLAIN
+    for cat, (N, K, epi) in layers.items():
+        m = re.match(r"gemm_pipe_kernel<(\d+), (\d+), \d, \d, (\d)>`", names[cat])
+        assert m, names[cat]
+        tile = PIPE + 1000 * int(m[1]) + int(m[2])
+        assert (tile, int(m[3])) == (binding.load().free_linear_tile(12288, N, K, binding.FREE_BF16, epi), epi), cat
+        t = bench.measured_traffic(cat, folded)
+        assert t and 0 < t["write_MB"] <= t["fetch_MB"], cat
+    for cat in ("attention", "verify_partial"):
+        assert bench.measured_traffic(cat, folded), cat
