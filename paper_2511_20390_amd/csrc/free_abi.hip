@@ -36,8 +36,9 @@ constexpr int kTuneSlots = 8;                 // batch sizes a handle remembers 
 constexpr int64_t kMinSplitRows = 2048;       // token rows per part below which the split does not pay
 // token rows from which the folded-LayerNorm path is taken by default: its residual updates run on the 256-column tiles only
 constexpr int64_t kMinFoldRows = 4096;
-// Weights of a block stack from which they are read ahead below kMinFoldRows rows: three quarters of the Infinity Cache.
-constexpr int64_t kReadAheadBytes = 192ll << 20;
+// Weights of a block stack from which its LayerNorms read them ahead below kMinFoldRows rows: the line between 221 MB, where that
+// costs up to 1 % of the forward, and 234 MB, where it gains as much (the Infinity Cache holds 256 MB).
+constexpr int64_t kReadAheadBytes = 220ll << 20;
 constexpr size_t kMaxProfSlots = 8192;
 }  // namespace
 
@@ -262,6 +263,7 @@ struct ActBufs {
 // `nblk` adaLN-Zero blocks on samples [b0, b0 + nb) of a batch.  blkw holds 10 pointers per block
 // (B_* order); block l's six modulation vectors of sample b are mod[b * mod_rows + l * 6D ..].
 // cu_share: number of such stacks running side by side on different streams (tile choice of the GEMMs).
+// chained: the stack runs again at once on the same weights (the steps of a drafting chain).
 // fold_ready (nullable): event after which fold->vec is complete; waited for on `s` before the first use.
 // fold (nullable): the LayerNorms are folded into the GEMMs around them (all but the first one of block 0, whose
 // input no GEMM of this stack produced): fold->vec holds the fold vectors of all samples of the batch, fold->stats the
@@ -274,7 +276,7 @@ struct FoldBufs {
 };
 int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const float* mod, int32_t mod_rows,
                         const ActBufs& a, int b0, int nb, hipStream_t s, Profiler* pf, int cu_share = 1,
-                        const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr) {
+                        const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool chained = false) {
     const size_t esz = d.mode == FREE_BF16 ? 2 : 4;
     const int32_t M = nb * d.ntok;
     const int64_t r0 = static_cast<int64_t>(b0) * d.ntok;
@@ -315,18 +317,27 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         return f;
     };
     // Few rows: the GEMMs are bound by how fast a CU gets its weights, so the short kernels in front of them pull the weights
-    // of this block into the caches - unless the weights of the whole stack (with the adaLN matrices of its blocks, read once
-    // in front of it) stay in the 256 MB Infinity Cache from one pass to the next, as those of a small model or of a drafter do:
-    // then there is nothing to bring nearer, and the extra workgroups cost 0.5 to 1 %.  Forward with / without, 64 to 3840
-    // rows: 64 MB (width 384, 12 blocks) 1.00-1.01, 177 MB (640, 12) 1.00-1.01, 191 MB (768, 9) 0.95-1.005 but (384, 36)
-    // 1.00-1.01, 212 MB (768, 10) 0.92-0.97, 221 MB (640, 15) 0.95-0.99, 255 MB (768, 12) 0.85-0.95, 1.3 GB (1152, 28) 0.82-0.94.
+    // of this block into the caches.  The LayerNorm, which nothing hides, only where the weights of the whole stack (with the
+    // adaLN matrices of its blocks, read once in front of it) do not stay in the 256 MB Infinity Cache from one pass to the
+    // next; the attention kernel, which leaves CUs idle, in smaller models too, but not in a drafter, whose next step follows at
+    // once on the same weights.  Forward against none, 64 to 3840 rows:
+    //   1.3 GB (width 1152, 28 blocks) LayerNorm 0.95-0.98, attention 0.87-0.97, both 0.82-0.94
+    //   255 MB (768, 12)               LayerNorm 0.97-0.99, attention 0.88-0.97, both 0.85-0.95
+    //   212 MB (768, 10)               LayerNorm 0.99-1.01, attention 0.93-0.97, both 0.92-0.97
+    //   191 MB (768, 9), (384, 36)     LayerNorm 1.00-1.01, attention 0.95-1.00, both 0.95-1.01
+    //   177 MB (640, 12)               LayerNorm 1.01,      attention 0.97-1.01, both 0.97-1.01
+    //   64 MB (384, 12)                LayerNorm 1.005-1.01, attention 0.99-1.00, both 1.00-1.01
+    // and with the forwards of three models of 64 MB in turn attention 0.99 (5 x 450 tokens 649 us, none 655, both 652); a
+    // drafting round of one block (48 MB) 1.01 at 256^2 and 512^2.
     // (fp32 GEMMs are bound by the matrix cores: no gain, 0.4 % lost on 2 x 256 tokens.)
     const int64_t DD = static_cast<int64_t>(d.D) * d.D, DF = static_cast<int64_t>(d.D) * d.F;
     const int64_t stack_bytes = nblk * (10 * DD + 2 * DF) * static_cast<int64_t>(esz);
-    const bool read_ahead = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1 && stack_bytes >= kReadAheadBytes;
-    auto ahead = [&](int l, int w0, int64_t n0, int w1, int64_t n1) {
+    const bool few_rows = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
+    const bool ln_ahead = few_rows && stack_bytes >= kReadAheadBytes;
+    const bool attn_ahead = few_rows && (!chained || stack_bytes >= kReadAheadBytes);
+    auto ahead = [&](bool on, int l, int w0, int64_t n0, int w1, int64_t n1) {
         Prefetch p;
-        if (read_ahead) {
+        if (on) {
             p.p[0] = W(l, w0);
             p.bytes[0] = n0 * static_cast<int64_t>(esz);
             p.p[1] = W(l, w1);
@@ -345,7 +356,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
             {
                 ProfScope prof(pf, PROF_LN_MOD, s);
                 FREE_TRY(launch_ln_modulate(xres_h, vec(l, 0), vec(l, 1), M, d.D, d.mode, xn_h, s,
-                                            ahead(l, B_QKV_W, 3 * DD, B_PROJ_W, DD)));
+                                            ahead(ln_ahead, l, B_QKV_W, 3 * DD, B_PROJ_W, DD)));
             }
             ProfScope prof(pf, PROF_GEMM_QKV, s);
             FREE_TRY(linear_dispatch(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_BIAS, qkv_h,
@@ -353,7 +364,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         {
             ProfScope prof(pf, PROF_ATTN, s);
-            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(l, B_FC1_W, DF, B_FC2_W, DF)));
+            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(attn_ahead, l, B_FC1_W, DF, B_FC2_W, DF)));
         }
         if (fold) {
             // the out-projection also prepares the second LayerNorm: z = x (1 + scale2), partial row sums
@@ -1131,7 +1142,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     FREE_TRY(linear_dispatch(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
                              2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, RowVec{dr->ones, 0, 1}, s));
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};
-    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof));
+    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, nullptr, nullptr, true));
     RowVec fsh{mod + static_cast<int64_t>(dr->depth) * 6 * d.D, mod_stride, d.ntok};
     RowVec fsc{mod + static_cast<int64_t>(dr->depth) * 6 * d.D + d.D, mod_stride, d.ntok};
     return launch_final_layer(f_out, fsh, fsc, B, d.gh, d.gw, d.p, d.c_out, d.D, dr->fin(F_W),

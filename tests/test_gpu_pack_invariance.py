@@ -35,7 +35,7 @@ def test_reading_weights_ahead_changes_no_bit(hidden, heads, depth):
     import torch
     from paper_2511_20390_amd import binding
     cfg = synth.dit_config("small", hidden=hidden, heads=heads, mlp_hidden=4 * hidden, depth=depth, lat_h=32, lat_w=32)
-    assert depth * 18 * hidden * hidden * 2 >= 192 << 20 and 17 * synth.n_tokens(cfg) >= 4096
+    assert depth * 18 * hidden * hidden * 2 >= 220 << 20 and 17 * synth.n_tokens(cfg) >= 4096
     model = binding.FreeDit(cfg, pu.weights_for(cfg, "bf16", 13), "bf16")
     model.set_ln_fold(binding.LN_FOLD_OFF)
     rng = np.random.default_rng(14)
