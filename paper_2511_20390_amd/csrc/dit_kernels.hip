@@ -5,6 +5,8 @@
 // final layer + unpatchify, guidance + eps->mean (Eq. ddpm_update).  It also
 // holds the plain (non-MFMA) linear and attention kernels used by the fp32 mode
 // and as the shape fallback of the bf16 mode.
+#include <type_traits>
+
 #include "free_internal.h"
 #include "prefetch.h"
 
@@ -298,29 +300,23 @@ __global__ __launch_bounds__(kThreads) void patch_embed16_kernel(
 // registers.  A workgroup takes kPeTok consecutive tokens of up to kPeSamples samples: the position vectors are
 // loaded once and reused for every sample, all latent values it needs are gathered into LDS up front, and a
 // two-sample launch (the drafter's) still covers every CU.
+// FT (bf16_t or float, not void): the drafter's form.  out is then [emb | feat] per token in the compute type FT: the thread
+// that embeds four columns also converts the same columns of feat, and clears them in zero_out (nullable, may be feat).  One
+// launch less per drafting step, and the embedding is not written and read back in fp32: 256 tokens 5.8 + 3.1 -> 5.7 us, 2 x 1024
+// tokens 7.2 + 7.4 -> 12.3 us.
 constexpr int kPeThreads = 320;            // 288 of them carry columns at D = 1152
 constexpr int kPeTok = 4;
 constexpr int kPeSamples = 16;
+template <typename FT>
 __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
     const float* __restrict__ x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p, int32_t D,
     const float* __restrict__ pw, const float* __restrict__ pb, const float* __restrict__ pos,
-    float* __restrict__ out, int32_t ntok) {
+    void* __restrict__ out, int32_t ntok, const float* feat, float* zero_out) {
+    constexpr bool kFuse = !std::is_same<FT, void>::value;
     __shared__ __attribute__((aligned(16))) float patch[kPeSamples][kPeTok][16];
     const int gw = W / p;
     const int n0 = blockIdx.x * kPeTok, b0 = blockIdx.y * kPeSamples;
     const int nb = B - b0 < kPeSamples ? B - b0 : kPeSamples;
-    for (int e = threadIdx.x; e < nb * kPeTok * 16; e += kPeThreads) {
-        const int sb = e / (kPeTok * 16), tk = (e >> 4) % kPeTok, q = e & 15;
-        const int n = n0 + tk;
-        float v = 0.f;
-        if (n < ntok) {
-            const float* xb = x + static_cast<int64_t>((b0 + sb) % x_mod) * C * H * W;
-            const int gi = n / gw, gj = n % gw;
-            const int c = q / (p * p), ph = (q / p) % p, pq = q % p;
-            v = xb[(static_cast<int64_t>(c) * H + gi * p + ph) * W + gj * p + pq];
-        }
-        patch[sb][tk][q] = v;
-    }
     const int j0 = 4 * static_cast<int>(threadIdx.x);
     const bool col_on = j0 < D;
     const int jc = col_on ? j0 : 0;                     // idle lanes re-read column 0 and store nothing
@@ -336,11 +332,47 @@ __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
         const int n = n0 + u < ntok ? n0 + u : ntok - 1;
         pe[u] = *reinterpret_cast<const float4*>(pos + static_cast<int64_t>(n) * D + jc);
     }
+    for (int e = threadIdx.x; e < nb * kPeTok * 16; e += kPeThreads) {
+        const int sb = e / (kPeTok * 16), tk = (e >> 4) % kPeTok, q = e & 15;
+        const int n = n0 + tk;
+        float v = 0.f;
+        if (n < ntok) {
+            const float* xb = x + static_cast<int64_t>((b0 + sb) % x_mod) * C * H * W;
+            const int gi = n / gw, gj = n % gw;
+            const int c = q / (p * p), ph = (q / p) % p, pq = q % p;
+            v = xb[(static_cast<int64_t>(c) * H + gi * p + ph) * W + gj * p + pq];
+        }
+        patch[sb][tk][q] = v;
+    }
+    float4 fv[kPeTok];                                  // kFuse: this thread's columns of feat, a sample ahead
+    auto load_feat = [&](int sb) {
+        if constexpr (kFuse) {
+#pragma unroll
+            for (int u = 0; u < kPeTok; ++u) {
+                const int n = n0 + u < ntok ? n0 + u : ntok - 1;
+                fv[u] = *reinterpret_cast<const float4*>(feat + (static_cast<int64_t>(b0 + sb) * ntok + n) * D + jc);
+            }
+        }
+    };
+    load_feat(0);
     __syncthreads();
     for (int sb = 0; sb < nb; ++sb) {
+        if constexpr (kFuse) {
+#pragma unroll
+            for (int u = 0; u < kPeTok; ++u) {
+                if (!col_on || n0 + u >= ntok) continue;
+                const int64_t row = static_cast<int64_t>(b0 + sb) * ntok + n0 + u;
+                FT* dst = static_cast<FT*>(out) + row * 2 * D + D + j0;
+                if constexpr (sizeof(FT) == 2)
+                    *reinterpret_cast<uint2*>(dst) = uint2{pack_bf16_pair(fv[u].x, fv[u].y), pack_bf16_pair(fv[u].z, fv[u].w)};
+                else
+                    *reinterpret_cast<float4*>(dst) = fv[u];
+                if (zero_out) *reinterpret_cast<float4*>(zero_out + row * D + j0) = float4{0.f, 0.f, 0.f, 0.f};
+            }
+            load_feat(sb + 1 < nb ? sb + 1 : sb);
+        }
 #pragma unroll
         for (int u = 0; u < kPeTok; ++u) {
-            const int n = n0 + u;
             float4 pv[4];
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) pv[q4] = reinterpret_cast<const float4*>(patch[sb][u])[q4];
@@ -357,9 +389,18 @@ __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
                 }
                 o[c] = acc;
             }
-            if (col_on && n < ntok)
-                *reinterpret_cast<float4*>(out + (static_cast<int64_t>(b0 + sb) * ntok + n) * D + j0) =
-                    make_float4(o[0] + pe[u].x, o[1] + pe[u].y, o[2] + pe[u].z, o[3] + pe[u].w);
+            if (!col_on || n0 + u >= ntok) continue;
+            const float4 r = make_float4(o[0] + pe[u].x, o[1] + pe[u].y, o[2] + pe[u].z, o[3] + pe[u].w);
+            const int64_t row = static_cast<int64_t>(b0 + sb) * ntok + n0 + u;
+            if constexpr (!kFuse) {
+                *reinterpret_cast<float4*>(static_cast<float*>(out) + row * D + j0) = r;
+            } else {
+                FT* dst = static_cast<FT*>(out) + row * 2 * D + j0;
+                if constexpr (sizeof(FT) == 2)
+                    *reinterpret_cast<uint2*>(dst) = uint2{pack_bf16_pair(r.x, r.y), pack_bf16_pair(r.z, r.w)};
+                else
+                    *reinterpret_cast<float4*>(dst) = r;
+            }
         }
     }
 }
@@ -403,13 +444,14 @@ __global__ __launch_bounds__(kThreads) void ln_modulate_kernel(
 template <typename OT, int NV, int kLnRows>
 __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, const RowVec& shift, const RowVec& scale,
                                                  int32_t M, int32_t D, OT* __restrict__ out) {
-    const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * kWaves + (threadIdx.x >> 6)) * kLnRows;
+    // (the row as a scalar of 32 bits: the divisions by the rows per sample are a dozen scalar instructions, not 130 of 64 bits)
+    const int row0 = (blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kLnRows;
     const int lane = threadIdx.x & 63;
     if (row0 >= M) return;
-    const int nrows = M - row0 < kLnRows ? static_cast<int>(M - row0) : kLnRows;
+    const int nrows = M - row0 < kLnRows ? M - row0 : kLnRows;
     const int nvec = D >> 2;
-    auto load_row = [&](float4 (&dst)[NV], int64_t row) {
-        const float4* xr = reinterpret_cast<const float4*>(x + row * D);
+    auto load_row = [&](float4 (&dst)[NV], int row) {
+        const float4* xr = reinterpret_cast<const float4*>(x + static_cast<int64_t>(row) * D);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const int v = lane + 64 * k;
@@ -417,21 +459,22 @@ __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, co
         }
     };
     float4 xv[NV], xn[NV], shv[NV], scv[NV];
-    int64_t sh_smp = -1, sc_smp = -1;
+    int sh_smp = -1, sc_smp = -1;
     load_row(xv, row0);
     for (int r = 0; r < nrows; ++r) {
-        const int64_t row = row0 + r;
+        const int row = row0 + r;
         if (r + 1 < nrows) load_row(xn, row + 1);
-        const int64_t s_sh = row / shift.rows_per_sample, s_sc = row / scale.rows_per_sample;
+        const int s_sh = static_cast<uint32_t>(row) / static_cast<uint32_t>(shift.rows_per_sample);
+        const int s_sc = static_cast<uint32_t>(row) / static_cast<uint32_t>(scale.rows_per_sample);
         if (s_sh != sh_smp) {                                  // wave-uniform
-            const float4* sh = reinterpret_cast<const float4*>(shift.base + s_sh * shift.stride);
+            const float4* sh = reinterpret_cast<const float4*>(shift.base + static_cast<int64_t>(s_sh) * shift.stride);
 #pragma unroll
             for (int k = 0; k < NV; ++k)
                 if (lane + 64 * k < nvec) shv[k] = sh[lane + 64 * k];
             sh_smp = s_sh;
         }
         if (s_sc != sc_smp) {
-            const float4* sc = reinterpret_cast<const float4*>(scale.base + s_sc * scale.stride);
+            const float4* sc = reinterpret_cast<const float4*>(scale.base + static_cast<int64_t>(s_sc) * scale.stride);
 #pragma unroll
             for (int k = 0; k < NV; ++k)
                 if (lane + 64 * k < nvec) scv[k] = sc[lane + 64 * k];
@@ -463,9 +506,9 @@ __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, co
                     uint2 pk;
                     pk.x = pack_bf16_pair(o0, o1);
                     pk.y = pack_bf16_pair(o2, o3);
-                    reinterpret_cast<uint2*>(out + row * D)[v] = pk;
+                    reinterpret_cast<uint2*>(out + static_cast<int64_t>(row) * D)[v] = pk;
                 } else {
-                    reinterpret_cast<float4*>(out + row * D)[v] = make_float4(o0, o1, o2, o3);
+                    reinterpret_cast<float4*>(out + static_cast<int64_t>(row) * D)[v] = make_float4(o0, o1, o2, o3);
                 }
             }
         }
@@ -986,16 +1029,28 @@ int32_t launch_adaln(const float* sc, int32_t B, int32_t D, const void* const* w
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 
+static bool patch_embed16v_covers(int32_t C, int32_t p, int32_t D, const float* pw, const float* pb, const float* pos,
+                                  const void* out) {
+    auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
+    return C * p * p == 16 && D % 4 == 0 && D <= 4 * kPeThreads && al16(pw) && al16(pb) && al16(pos) && al16(out);
+}
+
+template <typename FT>
+static int32_t launch_patch_embed16v(const float* x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p,
+                                     int32_t D, const float* pw, const float* pb, const float* pos, void* out, const float* feat,
+                                     float* zero_out, hipStream_t s) {
+    const int ntok = (H / p) * (W / p);
+    hipLaunchKernelGGL(patch_embed16v_kernel<FT>, dim3((ntok + kPeTok - 1) / kPeTok, (B + kPeSamples - 1) / kPeSamples),
+                       dim3(kPeThreads), 0, s, x, x_mod, B, C, H, W, p, D, pw, pb, pos, out, ntok, feat, zero_out);
+    return launch_ok() ? FREE_OK : FREE_ERR_HIP;
+}
+
 int32_t launch_patch_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W,
                            int32_t p, int32_t D, const float* pw, const float* pb, const float* pos,
                            float* out, hipStream_t s) {
     const int ntok = (H / p) * (W / p);
-    auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-    if (C * p * p == 16 && D % 4 == 0 && D <= 4 * kPeThreads && al16(pw) && al16(pb) && al16(pos) && al16(out)) {
-        hipLaunchKernelGGL(patch_embed16v_kernel, dim3((ntok + kPeTok - 1) / kPeTok, (B + kPeSamples - 1) / kPeSamples),
-                           dim3(kPeThreads), 0, s, x, x_mod, B, C, H, W, p, D, pw, pb, pos, out, ntok);
-        return launch_ok() ? FREE_OK : FREE_ERR_HIP;
-    }
+    if (patch_embed16v_covers(C, p, D, pw, pb, pos, out))
+        return launch_patch_embed16v<void>(x, x_mod, B, C, H, W, p, D, pw, pb, pos, out, nullptr, nullptr, s);
     if (C * p * p == 16 && D <= 8 * kThreads && (reinterpret_cast<uintptr_t>(pw) & 15u) == 0) {
         const dim3 grid((ntok + kPatchTok - 1) / kPatchTok, B);
         const int nr = (D + kThreads - 1) / kThreads;
@@ -1015,6 +1070,10 @@ int32_t launch_patch_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, 
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 
+// Threads per workgroup of a LayerNorm with one row per wavefront.  A CU takes in some 100 KB/us and a row with its shift and
+// scale is 14 KB at width 1152: few rows go to as many CUs as there are (512 rows 4.63 -> 4.43 us with the scalar row above).
+static int ln_threads(int32_t M) { return M <= 512 ? 64 : kThreads; }
+
 int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t D, int32_t dtype,
                            void* out, hipStream_t s, const Prefetch& pf) {
     const int blocks = (M + kWaves - 1) / kWaves;
@@ -1022,9 +1081,9 @@ int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M
     const bool vec = (D % 4 == 0) && D <= 2048 && al16(x) && al16(out) && al16(shift.base) && al16(scale.base) &&
                      (shift.stride % 4 == 0) && (scale.stride % 4 == 0);
     if (vec) {
-        const int nv = (D / 4 + 63) / 64;
+        const int nv = (D / 4 + 63) / 64, threads = ln_threads(M), vblocks = (M + threads / 64 - 1) / (threads / 64);
 #define FREE_LN_LAUNCH(OT, NV, ROWS)                                                                                   \
-    hipLaunchKernelGGL((ln_modulate_vec_kernel<OT, NV, ROWS>), dim3((blocks + ROWS - 1) / ROWS), dim3(kThreads), 0, s, x, shift, \
+    hipLaunchKernelGGL((ln_modulate_vec_kernel<OT, NV, ROWS>), dim3((vblocks + ROWS - 1) / ROWS), dim3(threads), 0, s, x, shift, \
                        scale, M, D, static_cast<OT*>(out))
 #define FREE_LN_CASE(OT, NV)                                      \
     do {                                                          \
@@ -1033,9 +1092,9 @@ int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M
         else FREE_LN_LAUNCH(OT, NV, 1);                           \
     } while (0)
 #define FREE_LN_AHEAD(NV)                                                                                                    \
-    hipLaunchKernelGGL((ln_modulate_ahead_kernel<bf16_t, NV>), dim3(first_ahead + ahead_blocks), dim3(kThreads), 0, s, x, shift, \
+    hipLaunchKernelGGL((ln_modulate_ahead_kernel<bf16_t, NV>), dim3(first_ahead + ahead_blocks), dim3(threads), 0, s, x, shift, \
                        scale, M, D, static_cast<bf16_t*>(out), pf, first_ahead)
-        const int ahead_blocks = pf.blocks(), first_ahead = (blocks + 7) / 8 * 8;
+        const int ahead_blocks = pf.blocks(threads), first_ahead = (vblocks + 7) / 8 * 8;
         // measured at D = 1152: 12288 rows 19.3 / 16.2 / 15.8 us with 1 / 2 / 4 rows per wavefront, 6144 rows
         // 10.4 / 9.1 / 10.0 us; with few rows the chain of one row's latencies is what counts
         const int rows_per_wave = M >= 8192 ? 4 : (M >= 4096 ? 2 : 1);
@@ -1199,17 +1258,15 @@ int32_t launch_final_layer(const float* x, RowVec shift, RowVec scale, int32_t B
 }
 
 // ---- drafter helpers (Sec. 3.2: FC layer on [embedding | propagated feature]; Alg. 1 drafting loop) ----
-// fin[m, 0:D] = emb[m, :], fin[m, D:2D] = feat[m, :] in the compute type; 4 elements per thread (D % 4 == 0).
+// fin[m, 0:D] = emb[m, :], fin[m, D:2D] = feat[m, :] in the compute type; a row per blockIdx.x, 4 elements per thread (D % 4 == 0).
 // zero_out (nullable, [M, D], may be feat itself): cleared on the way - the stream the fusion GEMM then
 // accumulates into; the thread that clears an element of feat is the one that has just read it.
 template <typename OT>
-__global__ __launch_bounds__(256) void fuse_pack_kernel(const float* __restrict__ emb, const float* feat, int64_t M,
-                                                        int32_t D, OT* __restrict__ fin, float* zero_out) {
-    const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;       // group of 4 output elements
-    const int32_t per_row = 2 * D / 4;
-    if (q >= M * per_row) return;
-    const int64_t m = q / per_row;
-    const int32_t c = static_cast<int32_t>(q % per_row) * 4;
+__global__ __launch_bounds__(256) void fuse_pack_kernel(const float* __restrict__ emb, const float* feat, int32_t D,
+                                                        OT* __restrict__ fin, float* zero_out) {
+    const int64_t m = blockIdx.x;
+    const int32_t c = (blockIdx.y * 256 + threadIdx.x) * 4;
+    if (c >= 2 * D) return;
     const float4 v = c < D ? *reinterpret_cast<const float4*>(emb + m * D + c)
                            : *reinterpret_cast<const float4*>(feat + m * D + (c - D));
     if (zero_out && c >= D) *reinterpret_cast<float4*>(zero_out + m * D + (c - D)) = float4{0.f, 0.f, 0.f, 0.f};
@@ -1306,15 +1363,25 @@ int32_t launch_pack_cond(const int32_t* t, int32_t y, int32_t null_label, int32_
 int32_t launch_fuse_pack(const float* emb, const float* feat, int64_t M, int32_t D, int32_t dtype, void* fin,
                          float* zero_out, hipStream_t s) {
     if (D % 4) return FREE_ERR_SHAPE;
-    const int64_t groups = M * (2 * D / 4);
-    const unsigned blocks = static_cast<unsigned>((groups + 255) / 256);
+    if (M > INT32_MAX) return FREE_ERR_SHAPE;
+    const dim3 grid(static_cast<unsigned>(M), (2 * D / 4 + 255) / 256);
     if (dtype == FREE_BF16)
-        hipLaunchKernelGGL(fuse_pack_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, emb, feat, M, D,
-                           static_cast<bf16_t*>(fin), zero_out);
+        hipLaunchKernelGGL(fuse_pack_kernel<bf16_t>, grid, dim3(256), 0, s, emb, feat, D, static_cast<bf16_t*>(fin), zero_out);
     else
-        hipLaunchKernelGGL(fuse_pack_kernel<float>, dim3(blocks), dim3(256), 0, s, emb, feat, M, D,
-                           static_cast<float*>(fin), zero_out);
+        hipLaunchKernelGGL(fuse_pack_kernel<float>, grid, dim3(256), 0, s, emb, feat, D, static_cast<float*>(fin), zero_out);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
+}
+
+int32_t launch_draft_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p, int32_t D,
+                           const float* pw, const float* pb, const float* pos, const float* feat, int32_t dtype, void* fin,
+                           float* zero_out, float* emb_buf, hipStream_t s) {
+    if (patch_embed16v_covers(C, p, D, pw, pb, pos, fin))
+        return dtype == FREE_BF16
+                   ? launch_patch_embed16v<bf16_t>(x, x_mod, B, C, H, W, p, D, pw, pb, pos, fin, feat, zero_out, s)
+                   : launch_patch_embed16v<float>(x, x_mod, B, C, H, W, p, D, pw, pb, pos, fin, feat, zero_out, s);
+    const int32_t st = launch_patch_embed(x, x_mod, B, C, H, W, p, D, pw, pb, pos, emb_buf, s);
+    if (st != FREE_OK) return st;
+    return launch_fuse_pack(emb_buf, feat, static_cast<int64_t>(B) * (H / p) * (W / p), D, dtype, fin, zero_out, s);
 }
 
 int32_t run_validate(const int32_t* t, int64_t n_t, int32_t T, const float* sigma, const float* u,

@@ -1134,11 +1134,10 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     }
     float* emb = reinterpret_cast<float*>(ws + L.emb);
     void* fin = ws + L.fin;
-    FREE_TRY(launch_patch_embed(x, x_mod, B, d.C, d.H, d.W, d.p, d.D, static_cast<const float*>(h->w[W_PATCH_W]),
-                                static_cast<const float*>(h->w[W_PATCH_B]), h->pos, emb, s));
     // z = fuse_w [emb | f_prev] + fuse_b, accumulated in fp32 straight into the residual stream:
     // residual epilogue on a zeroed stream with a gate of ones
-    FREE_TRY(launch_fuse_pack(emb, f_prev, M, d.D, d.mode, fin, f_out, s));
+    FREE_TRY(launch_draft_embed(x, x_mod, B, d.C, d.H, d.W, d.p, d.D, static_cast<const float*>(h->w[W_PATCH_W]),
+                                static_cast<const float*>(h->w[W_PATCH_B]), h->pos, f_prev, d.mode, fin, f_out, emb, s));
     FREE_TRY(linear_dispatch(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
                              2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, RowVec{dr->ones, 0, 1}, s));
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};

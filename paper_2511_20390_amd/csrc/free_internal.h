@@ -99,11 +99,10 @@ struct LnFold {
 struct Prefetch {
     const void* p[2] = {nullptr, nullptr};
     int64_t bytes[2] = {0, 0};
-    int blocks() const {                                     // workgroups of 256 threads, a multiple of 8
-        const int64_t n = (bytes[0] + bytes[1] + kPrefetchBlockBytes - 1) / kPrefetchBlockBytes;
-        return static_cast<int>((n + 7) / 8 * 8);
+    int blocks(int threads = 256) const {                    // workgroups of that many threads, a multiple of 8
+        const int64_t per_block = static_cast<int64_t>(threads) << 8;
+        return static_cast<int>(((bytes[0] + bytes[1] + per_block - 1) / per_block + 7) / 8 * 8);
     }
-    static constexpr int64_t kPrefetchBlockBytes = 64 << 10;
 };
 
 // Thread-local HIP error memo (free_last_hip_error).
@@ -182,7 +181,12 @@ int32_t launch_eps_to_mean(const float* eps_out, const float* x_states, const fl
 int32_t launch_pack_cond(const int32_t* t, int32_t y, int32_t null_label, int32_t K, int32_t dup,
                          int32_t* t_out, int32_t* y_out, hipStream_t s);
 
-// drafter helper: fin = [emb | feat] in the compute type, zero_out (nullable) cleared
+// drafter: fin = [emb | feat] in the compute type with emb the patch embedding, zero_out (nullable, may be feat) cleared.  One
+// launch where the patch embedding has its 16-byte form, else emb goes through `emb_buf`.
+int32_t launch_draft_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p, int32_t D,
+                           const float* pw, const float* pb, const float* pos, const float* feat, int32_t dtype, void* fin,
+                           float* zero_out, float* emb_buf, hipStream_t s);
+// fin = [emb | feat], zero_out (nullable) cleared
 int32_t launch_fuse_pack(const float* emb, const float* feat, int64_t M, int32_t D, int32_t dtype, void* fin,
                          float* zero_out, hipStream_t s);
 // blocking range check of device-resident inputs (any pointer may be null); bit mask of violations

@@ -42,6 +42,28 @@ def test_drafter_forward_parity(name, B, depth, mode):
     target.close()
 
 
+@pytest.mark.parametrize("mode", ["fp32", "bf16"])
+@pytest.mark.parametrize("lat_h,lat_w,B,hidden", [(18, 22, 17, 64), (2, 6, 1, 64), (6, 10, 3, 1280)])
+def test_drafter_embedding_edges(lat_h, lat_w, B, hidden, mode):
+    """The patch embedding and the features go to the fusion layer in one launch: token counts that are no multiple of the tokens
+    of a workgroup, more samples than one workgroup takes, the widest rows.  The forward's tolerance."""
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("tiny", lat_h=lat_h, lat_w=lat_w, hidden=hidden, heads=hidden // 64 or 1, mlp_hidden=2 * hidden, depth=1)
+    w, wd = pu.weights_for(cfg, mode, seed=6), synth.make_drafter_weights(cfg, 1, seed=7, bf16_values=(mode == "bf16"))
+    target = binding.FreeDit(cfg, w, mode)
+    drafter = binding.FreeDrafter(target, wd, 1)
+    rng = np.random.default_rng(8)
+    x = rng.standard_normal((B, cfg["in_ch"], lat_h, lat_w)).astype(np.float32)
+    f = rng.standard_normal((B, synth.n_tokens(cfg), hidden)).astype(np.float32)
+    t, y = (rng.integers(0, n, B).astype(np.int32) for n in (1000, cfg["num_classes"] + 1))
+    eps, feat = drafter.drafter_forward(*(pu.to_dev(v) for v in (x, f, t, y)))
+    ref_eps, ref_feat = fo.drafter_forward(wd, w, dict(cfg, drafter_depth=1), x, f, t, y)
+    assert pu.rel_l2(eps.cpu().numpy(), ref_eps) <= pu.DIT_REL_L2[mode]
+    assert pu.rel_l2(feat.cpu().numpy(), ref_feat) <= pu.DIT_REL_L2[mode]
+    drafter.close()
+    target.close()
+
+
 def _draft_inputs(cfg, K, seed, cfg_scale):
     sched = fo.ddpm_schedule()
     di = synth.make_draft_inputs(cfg, K, seed, cfg_scale)
