@@ -34,7 +34,7 @@ EXPORTED_SYMBOLS = [
     "free_self_speculative_workspace_bytes", "free_self_speculative", "free_lambda_profile",
     "free_op_linear", "free_linear_tile", "free_op_attention", "free_op_ln_modulate",
     "free_dit_set_ln_fold", "free_dit_ln_fold_active", "free_op_ln_fold_vectors", "free_op_linear_resid_prep",
-    "free_op_linear_ln",
+    "free_op_linear_ln", "free_op_linear_f32",
     "free_profile_begin", "free_profile_end", "free_profile_category_name", "free_mfma_ceiling", "free_validate_inputs",
 ]
 PROF_NCAT = 12
@@ -138,6 +138,8 @@ def load():
     lib.free_dit_ln_fold_active.argtypes = [vp, i32]
     lib.free_op_ln_fold_vectors.restype = i32
     lib.free_op_ln_fold_vectors.argtypes = [vp, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, i64, vp]
+    lib.free_op_linear_f32.restype = i32
+    lib.free_op_linear_f32.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, vp, i32, i32, vp]
     lib.free_op_linear_resid_prep.restype = i32
     lib.free_op_linear_resid_prep.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp, i32, i32, vp, vp, vp]
     lib.free_op_linear_ln.restype = i32
@@ -621,6 +623,19 @@ def op_linear(A, W, bias, mode: str, epilogue: int = EPI_BIAS, resid=None, gate=
     _check(load().free_op_linear(_ptr(A), _ptr(W), _ptr(bias), M, N, K, MODES[mode], epilogue, _ptr(out),
                                  _ptr(resid), _ptr(gate), 0 if gate is None else gate.stride(0),
                                  rows_per_sample, _stream()), "free_op_linear")
+    return resid if epilogue == EPI_GATE_RESID else out
+
+
+def op_linear_f32(A, W, bias, epilogue: int = EPI_BIAS, resid=None, gate=None, rows_per_sample: int = 1):
+    """A linear layer of a model in fp32 mode (three bf16 parts per value on the matrix cores); arguments as op_linear's."""
+    import torch
+    M, K = A.shape
+    N = W.shape[0]
+    out = None
+    if epilogue != EPI_GATE_RESID:
+        out = torch.empty(M, N, dtype=torch.float32, device=A.device)
+    _check(load().free_op_linear_f32(_ptr(A), _ptr(W), _ptr(bias), M, N, K, epilogue, _ptr(out), _ptr(resid), _ptr(gate),
+                                     0 if gate is None else gate.stride(0), rows_per_sample, _stream()), "free_op_linear_f32")
     return resid if epilogue == EPI_GATE_RESID else out
 
 

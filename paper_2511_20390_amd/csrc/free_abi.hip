@@ -234,6 +234,15 @@ int32_t linear_dispatch(const Dims& d, const void* A, const void* W, const float
     return launch_linear_simple(A, W, bias, M, N, K, d.mode, epi, out, resid, gate, s);
 }
 
+// A linear layer of a model: in fp32 mode with whole slices of K on the bf16 matrix instructions (three parts per value).
+int32_t model_linear(const Dims& d, const void* A, const void* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                     void* out, float* resid, RowVec gate, hipStream_t s, int cu_share = 1, const LnFold* ln = nullptr) {
+    const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
+    if (d.mode == FREE_FP32 && ln == nullptr && linear_f32_covers(a, w, M, N, K))
+        return launch_linear_f32(a, w, bias, M, N, K, epi, static_cast<float*>(out), resid, gate, s, cu_share);
+    return linear_dispatch(d, A, W, bias, M, N, K, epi, out, resid, gate, s, cu_share, ln);
+}
+
 int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, const Prefetch& pf) {
     if (d.mode == FREE_BF16 && mfma_attention_supported(d.ntok, d.dh))
         return launch_attention_mfma(static_cast<const bf16_t*>(qkv), B, d.ntok, d.heads, d.dh,
@@ -350,7 +359,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         if (fold && l > 0) {
             ProfScope prof(pf, PROF_GEMM_QKV, s);
             const LnFold f = consumer(l, 0);
-            FREE_TRY(linear_dispatch(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_LN_BIAS, qkv_h,
+            FREE_TRY(model_linear(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_LN_BIAS, qkv_h,
                                      nullptr, RowVec{nullptr, 0, 1}, s, cu_share, &f));
         } else {
             {
@@ -359,7 +368,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
                                             ahead(ln_ahead, l, B_QKV_W, 3 * DD, B_PROJ_W, DD)));
             }
             ProfScope prof(pf, PROF_GEMM_QKV, s);
-            FREE_TRY(linear_dispatch(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_BIAS, qkv_h,
+            FREE_TRY(model_linear(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_BIAS, qkv_h,
                                      nullptr, RowVec{nullptr, 0, 1}, s, cu_share));
         }
         {
@@ -370,11 +379,11 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
             // the out-projection also prepares the second LayerNorm: z = x (1 + scale2), partial row sums
             ProfScope prof(pf, PROF_GEMM_PROJ, s);
             const LnFold f = producer(vec(l, 4));
-            FREE_TRY(linear_dispatch(d, att_h, W(l, B_PROJ_W), Bv(l, B_PROJ_B), M, d.D, d.D, FREE_EPI_GATE_RESID_PREP,
+            FREE_TRY(model_linear(d, att_h, W(l, B_PROJ_W), Bv(l, B_PROJ_B), M, d.D, d.D, FREE_EPI_GATE_RESID_PREP,
                                      nullptr, xres_h, vec(l, 2), s, cu_share, &f));
         } else {
             ProfScope prof(pf, PROF_GEMM_PROJ, s);
-            FREE_TRY(linear_dispatch(d, att_h, W(l, B_PROJ_W), Bv(l, B_PROJ_B), M, d.D, d.D, FREE_EPI_GATE_RESID,
+            FREE_TRY(model_linear(d, att_h, W(l, B_PROJ_W), Bv(l, B_PROJ_B), M, d.D, d.D, FREE_EPI_GATE_RESID,
                                      nullptr, xres_h, vec(l, 2), s, cu_share));
         }
         // x += gate2 * FC2(gelu(FC1(LN(x)(1+scale2)+shift2)))
@@ -383,7 +392,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
             if (l == 0 && fold_ready && !hip_ok(hipStreamWaitEvent(s, fold_ready, 0))) return FREE_ERR_HIP;
             ProfScope prof(pf, PROF_GEMM_FC1, s);
             const LnFold f = consumer(l, 1);
-            FREE_TRY(linear_dispatch(d, xn_h, W(l, B_FC1_W), Bv(l, B_FC1_B), M, d.F, d.D, FREE_EPI_LN_BIAS_GELU, hmid_h,
+            FREE_TRY(model_linear(d, xn_h, W(l, B_FC1_W), Bv(l, B_FC1_B), M, d.F, d.D, FREE_EPI_LN_BIAS_GELU, hmid_h,
                                      nullptr, RowVec{nullptr, 0, 1}, s, cu_share, &f));
         } else {
             {
@@ -391,18 +400,18 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
                 FREE_TRY(launch_ln_modulate(xres_h, vec(l, 3), vec(l, 4), M, d.D, d.mode, xn_h, s));
             }
             ProfScope prof(pf, PROF_GEMM_FC1, s);
-            FREE_TRY(linear_dispatch(d, xn_h, W(l, B_FC1_W), Bv(l, B_FC1_B), M, d.F, d.D, FREE_EPI_BIAS_GELU, hmid_h,
+            FREE_TRY(model_linear(d, xn_h, W(l, B_FC1_W), Bv(l, B_FC1_B), M, d.F, d.D, FREE_EPI_BIAS_GELU, hmid_h,
                                      nullptr, RowVec{nullptr, 0, 1}, s, cu_share));
         }
         if (fold && l + 1 < nblk) {
             // the MLP's second layer prepares the first LayerNorm of the next block
             ProfScope prof(pf, PROF_GEMM_FC2, s);
             const LnFold f = producer(vec(l + 1, 1));
-            FREE_TRY(linear_dispatch(d, hmid_h, W(l, B_FC2_W), Bv(l, B_FC2_B), M, d.D, d.F, FREE_EPI_GATE_RESID_PREP,
+            FREE_TRY(model_linear(d, hmid_h, W(l, B_FC2_W), Bv(l, B_FC2_B), M, d.D, d.F, FREE_EPI_GATE_RESID_PREP,
                                      nullptr, xres_h, vec(l, 5), s, cu_share, &f));
         } else {
             ProfScope prof(pf, PROF_GEMM_FC2, s);
-            FREE_TRY(linear_dispatch(d, hmid_h, W(l, B_FC2_W), Bv(l, B_FC2_B), M, d.D, d.F, FREE_EPI_GATE_RESID,
+            FREE_TRY(model_linear(d, hmid_h, W(l, B_FC2_W), Bv(l, B_FC2_B), M, d.D, d.F, FREE_EPI_GATE_RESID,
                                      nullptr, xres_h, vec(l, 5), s, cu_share));
         }
     }
@@ -943,11 +952,8 @@ int32_t spec_round(free_dit_t h, const float* x_states, const float* x_last, con
     return launch_verify(a, ws + L.vpart, L.vpart_bytes, s);
 }
 
-int32_t free_op_linear(const void* A, const void* W, const float* bias, int32_t M, int32_t N, int32_t Kdim,
-                       int32_t dtype, int32_t epilogue, void* out, float* resid, const float* gate,
-                       int32_t gate_stride, int32_t rows_per_sample, void* stream) {
-    if (!A || !W || !bias) return FREE_ERR_NULL;
-    if (dtype != FREE_FP32 && dtype != FREE_BF16) return FREE_ERR_DTYPE;
+static int32_t check_op_linear(int32_t M, int32_t N, int32_t Kdim, int32_t epilogue,
+                               const void* out, const float* resid, const float* gate, int32_t rows_per_sample) {
     if (M < 1 || N < 1 || Kdim < 1) return FREE_ERR_SHAPE;
     if (epilogue == FREE_EPI_GATE_RESID) {
         if (!resid || !gate) return FREE_ERR_NULL;
@@ -957,10 +963,29 @@ int32_t free_op_linear(const void* A, const void* W, const float* bias, int32_t 
     } else {
         return FREE_ERR_RANGE;
     }
+    return FREE_OK;
+}
+
+int32_t free_op_linear(const void* A, const void* W, const float* bias, int32_t M, int32_t N, int32_t Kdim,
+                       int32_t dtype, int32_t epilogue, void* out, float* resid, const float* gate,
+                       int32_t gate_stride, int32_t rows_per_sample, void* stream) {
+    if (!A || !W || !bias) return FREE_ERR_NULL;
+    if (dtype != FREE_FP32 && dtype != FREE_BF16) return FREE_ERR_DTYPE;
+    FREE_TRY(check_op_linear(M, N, Kdim, epilogue, out, resid, gate, rows_per_sample));
     Dims d{};
     d.mode = dtype;
     RowVec g{gate, gate_stride, rows_per_sample > 0 ? rows_per_sample : 1};
     return linear_dispatch(d, A, W, bias, M, N, Kdim, epilogue, out, resid, g, static_cast<hipStream_t>(stream));
+}
+
+int32_t free_op_linear_f32(const float* A, const float* W, const float* bias, int32_t M, int32_t N, int32_t Kdim, int32_t epilogue,
+                           float* out, float* resid, const float* gate, int32_t gate_stride, int32_t rows_per_sample,
+                           void* stream) {
+    if (!A || !W || !bias) return FREE_ERR_NULL;
+    FREE_TRY(check_op_linear(M, N, Kdim, epilogue, out, resid, gate, rows_per_sample));
+    if (!linear_f32_covers(A, W, M, N, Kdim)) return FREE_ERR_SHAPE;
+    RowVec g{gate, gate_stride, rows_per_sample > 0 ? rows_per_sample : 1};
+    return launch_linear_f32(A, W, bias, M, N, Kdim, epilogue, out, resid, g, static_cast<hipStream_t>(stream));
 }
 
 int32_t free_linear_tile(int32_t M, int32_t N, int32_t Kdim, int32_t dtype, int32_t epilogue) {
@@ -1138,7 +1163,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     // residual epilogue on a zeroed stream with a gate of ones
     FREE_TRY(launch_draft_embed(x, x_mod, B, d.C, d.H, d.W, d.p, d.D, static_cast<const float*>(h->w[W_PATCH_W]),
                                 static_cast<const float*>(h->w[W_PATCH_B]), h->pos, f_prev, d.mode, fin, f_out, emb, s));
-    FREE_TRY(linear_dispatch(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
+    FREE_TRY(model_linear(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
                              2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, RowVec{dr->ones, 0, 1}, s));
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};
     FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, nullptr, nullptr, true));

@@ -232,6 +232,10 @@ int32_t launch_linear_rows(const float* X, const float* W, const float* bias, in
                            float* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
 bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* bias, const void* out, const float* resid,
                         const RowVec& gate);
+// fp32 operands and results, K a multiple of 32, products on the bf16 matrix instructions (gemm_f32.hip)
+bool linear_f32_covers(const float* X, const float* W, int32_t M, int32_t N, int32_t K);
+int32_t launch_linear_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
+                          float* out, float* resid, RowVec gate, hipStream_t s, int cu_share = 1);
 // shapes the folded-LayerNorm epilogues cover: M rows of width D normalised, rows_per_sample tokens per sample
 bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample);
 // the same kernel on fp32 operands (v_mfma_f32_32x32x2_f32), fp32 output

@@ -1,0 +1,78 @@
+"""The linear layers of fp32 models (three bf16 parts per value on the matrix cores) at the sizes where their tiles and K loop can go
+wrong, against the product in 64 bits and against the fp32 instructions."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# three parts carry all 24 bits and the products left out are below 3 * 2^-22 of each: what remains are fp32 sums, sqrt(K) 2^-24 of
+# the result where errors are independent (4e-6 at K = 4608); five times that, as for the fp32 instructions
+F32_TOL = 2e-5
+
+
+def _data(M, N, K, seed=0):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed + M + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    return rnd(M, K), rnd(N, K) / K ** 0.5, rnd(N), rnd(M, N), rnd(1, N)
+
+
+def _rel(a, b):
+    return ((a.double() - b.double()).norm() / b.double().norm()).item()
+
+
+# one row, one column group, one to 144 slices (the loop takes four per pass), ragged rows and columns of both tiles (64 x 64 up to
+# some 500 rows, 128 x 128 above), 1150 columns: element-wise epilogue
+@pytest.mark.parametrize("M,N,K", [(1, 8, 32), (65, 72, 64), (130, 200, 96), (63, 1152, 128), (64, 64, 160), (257, 1152, 4608),
+                                   (450, 1150, 384), (512, 4608, 1152), (600, 3464, 1152), (2050, 1160, 32), (3000, 4600, 224)])
+def test_parts(M, N, K):
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, resid, gate = _data(M, N, K)
+    ref = x.double() @ w.double().T + bias
+    out = binding.op_linear_f32(x, w, bias)
+    err = _rel(out, ref)
+    assert err < F32_TOL
+    if M * N >= 4096:                                    # no further off than the fp32 instructions
+        assert err <= 1.02 * _rel(binding.op_linear(x, w, bias, "fp32"), ref)
+    assert ((out - ref).norm(dim=1).max() / ref.norm(dim=1).mean()).item() < 5 * F32_TOL
+    out = binding.op_linear_f32(x, w, bias, binding.EPI_BIAS_GELU)
+    assert _rel(out, torch.nn.functional.gelu(ref, approximate="tanh")) < F32_TOL
+    got = resid.clone()
+    binding.op_linear_f32(x, w, bias, binding.EPI_GATE_RESID, resid=got, gate=gate, rows_per_sample=M)
+    ref = resid + gate * ref
+    assert _rel(got, ref) < F32_TOL
+    assert ((got - ref).norm(dim=1).max() / ref.norm(dim=1).mean()).item() < 5 * F32_TOL
+
+
+def test_rows_do_not_depend_on_the_pack():
+    """Both tiles add in the same order: 70 rows alone (64 x 64) are those of 3000 (128 x 128), bit for bit."""
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, _, _ = _data(3000, 1152, 352)
+    assert torch.equal(binding.op_linear_f32(x[:70].contiguous(), w, bias), binding.op_linear_f32(x, w, bias)[:70])
+
+
+@pytest.mark.parametrize("M,N", [(100, 72), (3000, 1160)])
+def test_values_without_three_parts(M, N):
+    """Infinities, NaN, magnitudes near both ends of fp32: what fp32 products give."""
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, _, _ = _data(M, N, 64, seed=1)
+    x[3, 5], x[40, 7], x[70, 0], x[71, :], w[9, 1] = float("inf"), float("nan"), 3e38, 1e-42, float("-inf")
+    out, ref = binding.op_linear_f32(x, w, bias), x @ w.T + bias
+    assert torch.equal(out.isnan(), ref.isnan()) and torch.equal(out.isinf(), ref.isinf())
+    assert torch.equal(out[ref.isinf()], ref[ref.isinf()])
+    ok = ref.isfinite()
+    # 64 products: errors of 64 2^-24 of the largest partial sum at worst
+    assert ((out - ref).abs()[ok] <= 64 * 2 ** -24 * (x.abs() @ w.abs().T + bias.abs())[ok]).all()
+
+
+def test_refused():
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, _, _ = _data(4, 8, 64)
+    lib, p = binding.load(), lambda t: t.data_ptr()
+    call = lambda a, k, epi: lib.free_op_linear_f32(a, p(w), p(bias), 4, 8, k, epi, p(x), None, None, 0, 1, None)
+    assert call(p(x), 36, 0) == binding.FREE_ERR_SHAPE and call(p(x) + 4, 64, 0) == binding.FREE_ERR_SHAPE
+    assert call(p(x), 64, 3) == binding.FREE_ERR_RANGE and call(None, 64, 0) == binding.FREE_ERR_NULL
+    assert call(p(x), 64, 2) == binding.FREE_ERR_NULL
