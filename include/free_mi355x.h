@@ -182,7 +182,8 @@ int32_t free_dit_stream_choice(free_dit_t h, int32_t B);
  *   FREE_LN_FOLD_AUTO (initial state): folded when covered and the batch has at
  *     least 4096 token rows (its GEMMs use the two large tile shapes only),
  *     the separate LayerNorm kernel otherwise.
- *   FREE_LN_FOLD_OFF: always the separate kernel.
+ *   FREE_LN_FOLD_OFF: always the separate kernel.  Outputs then do not depend on how many states a batch holds, bit for bit;
+ *     otherwise they do not up to 4095 token rows (smaller batches may add their sums in another order than larger ones).
  *   FREE_LN_FOLD_REQUIRE: always folded; free_dit_set_ln_fold returns
  *     FREE_ERR_SHAPE when the model is not covered - never a silent switch.
  * free_dit_ln_fold_active(h, B): 1 if a forward on B packed states would take
@@ -468,6 +469,9 @@ int32_t free_linear_tile(int32_t M, int32_t N, int32_t Kdim, int32_t dtype, int3
  * qkv [B*N, 3*heads*dh] rows ordered q | k | v, out [B*N, heads*dh]; dh <= 128. */
 int32_t free_op_attention(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
                           int32_t dtype, void* out, void* stream);
+/* The same in bf16 as small batches run it (below 4096 token rows, few heads or the drafter): the keys of a query over two wavefronts,
+ * whose partial results are added at the end.  dh 16, 64, 72 or 128 (FREE_ERR_SHAPE otherwise). */
+int32_t free_op_attention_split(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh, void* out, void* stream);
 /* out[m, :] = LayerNorm(x[m, :]) * (1 + scale[m / rows_per_sample, :]) + shift[...]
  * (no affine, biased variance, eps 1e-6); x fp32 [M, D]; shift/scale fp32 with
  * row stride mod_stride; out fp32 or bf16 per dtype. */

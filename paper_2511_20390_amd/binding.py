@@ -34,7 +34,7 @@ EXPORTED_SYMBOLS = [
     "free_self_speculative_workspace_bytes", "free_self_speculative", "free_lambda_profile",
     "free_op_linear", "free_linear_tile", "free_op_attention", "free_op_ln_modulate",
     "free_dit_set_ln_fold", "free_dit_ln_fold_active", "free_op_ln_fold_vectors", "free_op_linear_resid_prep",
-    "free_op_linear_ln", "free_op_linear_f32",
+    "free_op_linear_ln", "free_op_linear_f32", "free_op_attention_split",
     "free_profile_begin", "free_profile_end", "free_profile_category_name", "free_mfma_ceiling", "free_validate_inputs",
 ]
 PROF_NCAT = 12
@@ -138,6 +138,8 @@ def load():
     lib.free_dit_ln_fold_active.argtypes = [vp, i32]
     lib.free_op_ln_fold_vectors.restype = i32
     lib.free_op_ln_fold_vectors.argtypes = [vp, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, i64, vp]
+    lib.free_op_attention_split.restype = i32
+    lib.free_op_attention_split.argtypes = [vp, i32, i32, i32, i32, vp, vp]
     lib.free_op_linear_f32.restype = i32
     lib.free_op_linear_f32.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, vp, i32, i32, vp]
     lib.free_op_linear_resid_prep.restype = i32
@@ -644,6 +646,14 @@ def op_attention(qkv, B: int, N: int, heads: int, dh: int, mode: str):
     out = torch.empty(B * N, heads * dh, dtype=qkv.dtype, device=qkv.device)
     _check(load().free_op_attention(_ptr(qkv), B, N, heads, dh, MODES[mode], _ptr(out), _stream()),
            "free_op_attention")
+    return out
+
+
+def op_attention_split(qkv, B: int, N: int, heads: int, dh: int):
+    """bf16 attention with the keys of a query over two wavefronts, as small batches run it."""
+    import torch
+    out = torch.empty(B * N, heads * dh, dtype=qkv.dtype, device=qkv.device)
+    _check(load().free_op_attention_split(_ptr(qkv), B, N, heads, dh, _ptr(out), _stream()), "free_op_attention_split")
     return out
 
 

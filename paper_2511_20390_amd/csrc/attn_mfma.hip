@@ -30,6 +30,7 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef short v4s_t __attribute__((ext_vector_type(4)));
 typedef short v8s_t __attribute__((ext_vector_type(8)));
@@ -48,8 +49,13 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) { return pack_bf16_pa
 // O^T on the matrix pipe - are serial inside a wavefront, so what overlaps them is the number of
 // wavefronts per SIMD; the third one is worth more (measured 4.5 %) than the second set of K/V staging
 // registers it costs.
-template <int DH, int QT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 72 ? 3 : 2, DH <= 72 ? 3 : 2))) void attn_mfma_kernel(const bf16_t* __restrict__ qkv, int32_t N,
+//
+// KS = 2: the wavefronts are 2 query blocks x 2 key halves.  With few token rows there are fewer workgroups than places for them and a
+// launch lasts as long as the chain of tiles in one wavefront; here every wavefront takes one 32-key block of each tile, and the
+// two partial results of a query (O^T, its reference maximum and sum) are added through LDS at the end.  us per launch, KS = 1 -> 2:
+// NOW
+template <int DH, int QT, int KS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 72 && KS == 1 ? 3 : 2, DH <= 72 && KS == 1 ? 3 : 2))) void attn_mfma_kernel(const bf16_t* __restrict__ qkv, int32_t N,
                                                              int32_t heads, float scale_log2,
                                                              bf16_t* __restrict__ out, int32_t n_blocks, Prefetch pf) {
     const int first_prefetch = (n_blocks + 7) & ~7;
@@ -60,10 +66,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     constexpr int KSTEPS = (DH + 15) / 16;            // MFMA k-steps over the head dim (S^T)
     constexpr int DCH = DH / 8;                       // 16-byte chunks per Q/K/V row
     constexpr int DT = (DH + 31) / 32;                // 32-row tiles of O^T
-    constexpr int kSets = DH <= 72 ? 1 : 2;           // K/V register sets: tiles in flight from global memory
+    constexpr int kSets = DH <= 72 && KS == 1 ? 1 : 2;    // K/V register sets: tiles in flight from global memory
     constexpr bool kSumByMfma = (DH % 32) != 0;       // a spare row of O^T can carry the softmax denominator
     constexpr int KROW = ((2 * KSTEPS) | 1) * 16;     // bytes per K row in LDS (odd # of chunks)
-    constexpr int BQ = 4 * 32 * QT;                   // queries per workgroup
+    constexpr int KB = 2 / KS;                        // 32-key blocks of a tile per wavefront
+    constexpr int BQ = 4 / KS * 32 * QT;              // queries per workgroup
     constexpr int NLD = (BKV * DCH + kThreads - 1) / kThreads;   // 16-byte loads per thread per tile
     // V stays row-major in LDS ([key][d]) and is read with the transposing LDS load; a row stride of
     // 64 or 192 (mod 256) bytes puts the 4 keys x 64 bytes that 32 lanes of such a load touch on
@@ -73,8 +80,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     __shared__ __attribute__((aligned(16))) char sKbuf[2 * kKBytes];      // two stages: tile t is multiplied
     __shared__ __attribute__((aligned(16))) char sVbuf[2 * kVBytes];      // while tile t+1 is written
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = KS == 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, g = lane >> 5;
+    const int qw = KS == 1 ? wave : wave & 1, kb0 = KS == 1 ? 0 : wave >> 1;    // query block, first 32-key block
     // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2).  All query
     // tiles of one (sample, head) re-read the same K and V, so they are placed on ONE XCD,
     // back to back: id L -> XCD L % 8; pair index = L % 8 + 8 * (L / (8 nq)), tile = (L / 8) % nq.
@@ -92,7 +100,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     const int h = pair_idx % heads, b = pair_idx / heads;
     const int D = heads * DH;
     const int64_t row0 = static_cast<int64_t>(b) * N;
-    const int q_base = q_tile * BQ + wave * 32 * QT;
+    const int q_base = q_tile * BQ + qw * 32 * QT;
     const size_t row_bytes = static_cast<size_t>(3) * D * 2;
     const char* qkv_b = reinterpret_cast<const char*>(qkv);
 
@@ -174,7 +182,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     // group G pointing at V[8 (G/2) + r/4][16 (G%2) + 4 (r%4) ..+3], lane l gets 4 consecutive keys
     // 8 (l/32) + 0..3 of head-dim column l % 32: half of the A operand of O^T += V^T P^T; the same
     // read 4 rows further down gives the other half.
-    const int vtr_off = (8 * (lane >> 5) + ((lane & 15) >> 2)) * VROW + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+    const int vtr_off = kb0 * 32 * VROW + (8 * (lane >> 5) + ((lane & 15) >> 2)) * VROW + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
 
     f32x16_t o[DT][QT];
 #pragma unroll
@@ -211,21 +219,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
 
         // ---- S^T = K Q^T for the two 32-key blocks of the tile
         __builtin_amdgcn_s_setprio(kPrioMfma);
-        f32x16_t st[2][QT];
+        f32x16_t st[KB][QT];
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) st[kb][qt][e] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
-            bf16x8_t kf[2];
+            bf16x8_t kf[KB];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-                kf[kb] = *reinterpret_cast<const bf16x8_t*>(sK + (kb * 32 + l32) * KROW + (2 * ks + g) * 16);
+            for (int kb = 0; kb < KB; ++kb)
+                kf[kb] = *reinterpret_cast<const bf16x8_t*>(sK + ((kb0 + kb) * 32 + l32) * KROW + (2 * ks + g) * 16);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int qt = 0; qt < QT; ++qt)
                     st[kb][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kb], qf[qt][ks], st[kb][qt], 0, 0, 0);
@@ -240,10 +248,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         // kv0 + 32 kb + 16 (e/8) + 8 g + 4 ((e/4)%2) + e%4   (LDS rows were permuted on the way in)
         if (kRagged) {
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int kv = kv0 + 32 * kb + 16 * (e >> 3) + 8 * g + 4 * ((e >> 2) & 1) + (e & 3);
+                    const int kv = kv0 + 32 * (kb0 + kb) + 16 * (e >> 3) + 8 * g + 4 * ((e >> 2) & 1) + (e & 3);
                     if (kv >= N) {
 #pragma unroll
                         for (int qt = 0; qt < QT; ++qt) st[kb][qt][e] = -INFINITY;
@@ -252,12 +260,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         }
 
         // ---- online softmax per query column, probabilities packed straight into MFMA operands
-        bf16x8_t pf[QT][2][2];
+        bf16x8_t pf[QT][KB][2];
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) {
             float mx = st[0][qt][0];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[kb][qt][e]);
             {   // both half-waves of a column agree: v_permlane32_swap leaves {own, partner} in the two
@@ -277,10 +285,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
                     for (int e = 0; e < 16; ++e) o[dt][qt][e] *= alpha;
                 m_ref[qt] = m_new;
             }
-            const float mb = m_ref[qt] * scale_log2;
+            // (KS 2: a key half may have seen no key yet - probabilities of zero, not NaN)
+            const float mb = KS == 2 && m_ref[qt] == -INFINITY ? 0.f : m_ref[qt] * scale_log2;
             [[maybe_unused]] float sum = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh) {
                     float p[8];
@@ -299,7 +308,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         // ---- O^T += V^T P^T
         __builtin_amdgcn_s_setprio(kPrioMfma);
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
 #pragma unroll
@@ -334,6 +343,36 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
         else tile(t, std::true_type{}, set1);
     }
 
+    if constexpr (KS == 2) {
+        // the second key half hands O^T, its reference maximum and (where no row of O^T carries it) its sum to the first; the stages
+        // are idle (the barrier at the end of the last tile)
+        static_assert(QT == 1 && 2 * DT * 4096 <= 2 * kVBytes && 1024 <= 2 * kKBytes, "the partial results must fit in the stages");
+        float* ml = reinterpret_cast<float*>(sKbuf) + qw * 128 + lane;
+        if (kb0 == 1) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<f32x4_t*>(sVbuf + ((qw * DT + dt) * 4 + q) * 1024 + lane * 16) =
+                        f32x4_t{o[dt][0][4 * q], o[dt][0][4 * q + 1], o[dt][0][4 * q + 2], o[dt][0][4 * q + 3]};
+            ml[0] = m_ref[0];
+            ml[64] = l_run[0];
+        }
+        __syncthreads();
+        if (kb0 == 1) return;
+        const float m1 = ml[0], m = fmaxf(m_ref[0], m1);
+        const float a0 = __builtin_amdgcn_exp2f((m_ref[0] - m) * scale_log2), a1 = __builtin_amdgcn_exp2f((m1 - m) * scale_log2);
+        l_run[0] = a0 * l_run[0] + a1 * ml[64];
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(sVbuf + ((qw * DT + dt) * 4 + q) * 1024 + lane * 16);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[dt][0][4 * q + c] = a0 * o[dt][0][4 * q + c] + a1 * v[c];
+            }
+    }
+
     // ---- normalise and store: register e of O^T tile dt is row d = 32 dt + 8 (e/4) + 4 g + e%4, column l32
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
@@ -365,15 +404,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     }
 }
 
-template <int DH>
+template <int DH, int KS>
 int32_t launch_dh(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, bf16_t* out, hipStream_t s, const Prefetch& pf) {
     const float scale_log2 = 1.4426950408889634f / std::sqrt(static_cast<float>(DH));
-    // one 32-query tile per wavefront: 128 queries per workgroup, two or three workgroups per CU
+    // one 32-query tile per wavefront: 128 queries per workgroup (64 with the keys split), two or three workgroups per CU
     // (measured faster than two query tiles per wavefront at one workgroup per CU)
-    const int64_t total = static_cast<int64_t>((N + 127) / 128) * heads * B;
+    const int64_t total = static_cast<int64_t>((N + 128 / KS - 1) / (128 / KS)) * heads * B;
     if (total > 0x7fff0000) return FREE_ERR_SHAPE;
     const int n = static_cast<int>(total), np = pf.blocks();
-    hipLaunchKernelGGL((attn_mfma_kernel<DH, 1>), dim3(np ? (n + 7) / 8 * 8 + np : n), dim3(kThreads), 0, s, qkv, N, heads,
+    hipLaunchKernelGGL((attn_mfma_kernel<DH, 1, KS>), dim3(np ? (n + 7) / 8 * 8 + np : n), dim3(kThreads), 0, s, qkv, N, heads,
                        scale_log2, out, n, pf);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
@@ -385,16 +424,17 @@ bool mfma_attention_supported(int32_t N, int32_t dh) {
 }
 
 int32_t launch_attention_mfma(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh, bf16_t* out,
-                              hipStream_t s, const Prefetch& pf) {
+                              hipStream_t s, const Prefetch& pf, bool split_keys) {
     if (reinterpret_cast<uintptr_t>(qkv) & 15u) return FREE_ERR_SHAPE;
     if (B > 65535 || heads > 65535) return FREE_ERR_SHAPE;
     // one sample's rows are addressed through a buffer descriptor with 32-bit byte offsets
     if (static_cast<int64_t>(N) * 3 * heads * dh * 2 >= (1ll << 31)) return FREE_ERR_SHAPE;
+    const bool split = split_keys;
     switch (dh) {
-        case 16: return launch_dh<16>(qkv, B, N, heads, out, s, pf);
-        case 64: return launch_dh<64>(qkv, B, N, heads, out, s, pf);
-        case 72: return launch_dh<72>(qkv, B, N, heads, out, s, pf);
-        case 128: return launch_dh<128>(qkv, B, N, heads, out, s, pf);
+        case 16: return split ? launch_dh<16, 2>(qkv, B, N, heads, out, s, pf) : launch_dh<16, 1>(qkv, B, N, heads, out, s, pf);
+        case 64: return split ? launch_dh<64, 2>(qkv, B, N, heads, out, s, pf) : launch_dh<64, 1>(qkv, B, N, heads, out, s, pf);
+        case 72: return split ? launch_dh<72, 2>(qkv, B, N, heads, out, s, pf) : launch_dh<72, 1>(qkv, B, N, heads, out, s, pf);
+        case 128: return split ? launch_dh<128, 2>(qkv, B, N, heads, out, s, pf) : launch_dh<128, 1>(qkv, B, N, heads, out, s, pf);
         default: return FREE_ERR_SHAPE;
     }
 }

@@ -194,6 +194,12 @@ struct free_dit_s {
         return d.mode == FREE_BF16 && mfma_ln_fold_supported(d.ntok, d.D, d.ntok) && ln_fold_supported(d.D, 3 * d.D, d.F) &&
                d.D % 64 == 0 && d.F % 64 == 0 && d.depth >= 1;
     }
+    // Whether a batch of that many token rows may cut its sums (softmax over the keys, K of the narrow layers) to fill the chip.
+    // Below the rows from which the LayerNorms are folded, whose sums differ from the separate ones as well, so that a state alone
+    // and in a pack still agree bit for bit there; with FREE_LN_FOLD_OFF, which makes them agree at every size, nothing is cut.
+    bool few_rows_for(int64_t rows) const {
+        return dims.mode == FREE_BF16 && ln_fold == FREE_LN_FOLD_AUTO && rows < kMinFoldRows;
+    }
     bool ln_fold_for(int32_t B) const {
         if (ln_fold == FREE_LN_FOLD_OFF || !ln_fold_covers()) return false;
         return ln_fold == FREE_LN_FOLD_REQUIRE || static_cast<int64_t>(B) * dims.ntok >= kMinFoldRows;
@@ -243,10 +249,11 @@ int32_t model_linear(const Dims& d, const void* A, const void* W, const float* b
     return linear_dispatch(d, A, W, bias, M, N, K, epi, out, resid, gate, s, cu_share, ln);
 }
 
-int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, const Prefetch& pf) {
+// split_keys: the keys of a query over two wavefronts (bf16, few token rows)
+int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, const Prefetch& pf, bool split_keys) {
     if (d.mode == FREE_BF16 && mfma_attention_supported(d.ntok, d.dh))
         return launch_attention_mfma(static_cast<const bf16_t*>(qkv), B, d.ntok, d.heads, d.dh,
-                                     static_cast<bf16_t*>(out), s, pf);
+                                     static_cast<bf16_t*>(out), s, pf, split_keys);
     if (d.mode == FREE_FP32 && mfma_attention_f32_supported(d.ntok, d.dh))
         return launch_attention_mfma_f32(static_cast<const float*>(qkv), B, d.ntok, d.heads, d.dh,
                                          static_cast<float*>(out), s);
@@ -272,6 +279,7 @@ struct ActBufs {
 // `nblk` adaLN-Zero blocks on samples [b0, b0 + nb) of a batch.  blkw holds 10 pointers per block
 // (B_* order); block l's six modulation vectors of sample b are mod[b * mod_rows + l * 6D ..].
 // cu_share: number of such stacks running side by side on different streams (tile choice of the GEMMs).
+// few: the batch has few token rows (few_rows_for), sums may be cut where that fills the chip.
 // chained: the stack runs again at once on the same weights (the steps of a drafting chain).
 // fold_ready (nullable): event after which fold->vec is complete; waited for on `s` before the first use.
 // fold (nullable): the LayerNorms are folded into the GEMMs around them (all but the first one of block 0, whose
@@ -285,7 +293,7 @@ struct FoldBufs {
 };
 int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const float* mod, int32_t mod_rows,
                         const ActBufs& a, int b0, int nb, hipStream_t s, Profiler* pf, int cu_share = 1,
-                        const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool chained = false) {
+                        bool few = false, const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool chained = false) {
     const size_t esz = d.mode == FREE_BF16 ? 2 : 4;
     const int32_t M = nb * d.ntok;
     const int64_t r0 = static_cast<int64_t>(b0) * d.ntok;
@@ -339,11 +347,17 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     // and with the forwards of three models of 64 MB in turn attention 0.99 (5 x 450 tokens 649 us, none 655, both 652); a
     // drafting round of one block (48 MB) 1.01 at 256^2 and 512^2.
     // (fp32 GEMMs are bound by the matrix cores: no gain, 0.4 % lost on 2 x 256 tokens.)
+    // Attention with the keys of a query over two wavefronts: twice the workgroups of half the work, faster while two of them per CU
+    // hold the launch, slower beyond (16 heads: 256 rows 1.03, 1024 rows 1.015, 2048 rows 0.985, 3840 rows 0.97 of the forward).  The
+    // choice may not depend on the number of samples, or a state alone and in a pack would differ: models of few heads, where that
+    // holds up to kMinFoldRows rows (6 heads: 1.02-1.05), and the drafter's one or two samples.
+    const int64_t places = 2 * device_cus();
+    const bool split_keys = few && (d.heads * (kMinFoldRows / 64) <= places || (chained && d.heads * ((2ll * d.ntok + 63) / 64) <= places));
     const int64_t DD = static_cast<int64_t>(d.D) * d.D, DF = static_cast<int64_t>(d.D) * d.F;
     const int64_t stack_bytes = nblk * (10 * DD + 2 * DF) * static_cast<int64_t>(esz);
-    const bool few_rows = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
-    const bool ln_ahead = few_rows && stack_bytes >= kReadAheadBytes;
-    const bool attn_ahead = few_rows && (!chained || stack_bytes >= kReadAheadBytes);
+    const bool may_ahead = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
+    const bool ln_ahead = may_ahead && stack_bytes >= kReadAheadBytes;
+    const bool attn_ahead = may_ahead && (!chained || stack_bytes >= kReadAheadBytes);
     auto ahead = [&](bool on, int l, int w0, int64_t n0, int w1, int64_t n1) {
         Prefetch p;
         if (on) {
@@ -373,7 +387,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         {
             ProfScope prof(pf, PROF_ATTN, s);
-            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(attn_ahead, l, B_FC1_W, DF, B_FC2_W, DF)));
+            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(attn_ahead, l, B_FC1_W, DF, B_FC2_W, DF), split_keys));
         }
         if (fold) {
             // the out-projection also prepares the second LayerNorm: z = x (1 + scale2), partial row sums
@@ -476,7 +490,7 @@ int32_t forward_impl(free_dit_t h, const float* x, int32_t x_mod, const int32_t*
     const void* const* blkw = h->w.data() + 7;
     auto run_blocks = [&](int b0, int nb, hipStream_t st, int cu_share) -> int32_t {
         return run_block_stack(d, blkw, d.depth, mod, d.mod_rows, act, b0, nb, st, &h->prof, cu_share,
-                               folded ? &fb : nullptr, fold_ready);
+                               h->few_rows_for(M), folded ? &fb : nullptr, fold_ready);
     };
     // The samples of a packed batch are independent through all blocks, so the batch can be cut in two halves
     // or three thirds that run on as many streams forked from (and joined back into) the caller's stream: while
@@ -1071,7 +1085,14 @@ int32_t free_op_attention(const void* qkv, int32_t B, int32_t N, int32_t heads, 
     d.ntok = N;
     d.heads = heads;
     d.dh = dh;
-    return attention_dispatch(d, qkv, B, out, static_cast<hipStream_t>(stream), Prefetch{});
+    return attention_dispatch(d, qkv, B, out, static_cast<hipStream_t>(stream), Prefetch{}, false);
+}
+
+int32_t free_op_attention_split(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh, void* out, void* stream) {
+    if (!qkv || !out) return FREE_ERR_NULL;
+    if (B < 1 || N < 1 || heads < 1 || !mfma_attention_supported(N, dh)) return FREE_ERR_SHAPE;
+    return launch_attention_mfma(static_cast<const bf16_t*>(qkv), B, N, heads, dh, static_cast<bf16_t*>(out),
+                                 static_cast<hipStream_t>(stream), Prefetch{}, true);
 }
 
 int32_t free_op_ln_modulate(const float* x, const float* shift, const float* scale, int32_t mod_stride, int32_t M,
@@ -1166,7 +1187,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     FREE_TRY(model_linear(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
                              2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, RowVec{dr->ones, 0, 1}, s));
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};
-    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, nullptr, nullptr, true));
+    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, h->few_rows_for(M), nullptr, nullptr, true));
     RowVec fsh{mod + static_cast<int64_t>(dr->depth) * 6 * d.D, mod_stride, d.ntok};
     RowVec fsc{mod + static_cast<int64_t>(dr->depth) * 6 * d.D + d.D, mod_stride, d.ntok};
     return launch_final_layer(f_out, fsh, fsc, B, d.gh, d.gw, d.p, d.c_out, d.D, dr->fin(F_W),

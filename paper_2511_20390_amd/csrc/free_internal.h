@@ -253,7 +253,7 @@ int32_t launch_ln_fold(const float* mod, int32_t B, int32_t D, int32_t mod_strid
                        int64_t fold_stride, hipStream_t s);
 bool mfma_attention_supported(int32_t N, int32_t dh);
 int32_t launch_attention_mfma(const bf16_t* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
-                              bf16_t* out, hipStream_t s, const Prefetch& pf = Prefetch{});
+                              bf16_t* out, hipStream_t s, const Prefetch& pf = Prefetch{}, bool split_keys = false);
 // fp32 operands and softmax on the matrix cores (attn_f32_mfma.hip); qkv and out 16-byte aligned
 bool mfma_attention_f32_supported(int32_t N, int32_t dh);
 int32_t launch_attention_mfma_f32(const float* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
