@@ -441,9 +441,18 @@ __global__ __launch_bounds__(kThreads) void ln_modulate_kernel(
 // A wavefront walks kLnRows consecutive rows (4 when there are enough rows to fill the chip that way, else 1): the shift / scale vectors of a sample (as many bytes as the row
 // itself, each) stay in registers while the sample does not change - read per row they triple the traffic
 // through the L1 - and the next row is requested before the current one is reduced.
-template <typename OT, int NV, int kLnRows>
+// four elements of a residual update whose sums over K are still in parts (ResidJoin)
+__device__ __forceinline__ float4 join4(const float4 (&p)[kSplitParts], const float4& b, const float4& g, const float4& x) {
+    static_assert(kSplitParts == 3, "the sum of the parts is written out");
+    return make_float4(fmaf(g.x, ((p[0].x + p[1].x) + p[2].x) + b.x, x.x), fmaf(g.y, ((p[0].y + p[1].y) + p[2].y) + b.y, x.y),
+                       fmaf(g.z, ((p[0].z + p[1].z) + p[2].z) + b.z, x.z), fmaf(g.w, ((p[0].w + p[1].w) + p[2].w) + b.w, x.w));
+}
+
+// kJoin (one row per wavefront): the rows are those of x_join after `join`, and are written back there.
+template <typename OT, int NV, int kLnRows, bool kJoin = false>
 __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, const RowVec& shift, const RowVec& scale,
-                                                 int32_t M, int32_t D, OT* __restrict__ out) {
+                                                 int32_t M, int32_t D, OT* __restrict__ out, const ResidJoin* join = nullptr,
+                                                 float* x_join = nullptr) {
     // (the row as a scalar of 32 bits: the divisions by the rows per sample are a dozen scalar instructions, not 130 of 64 bits)
     const int row0 = (blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kLnRows;
     const int lane = threadIdx.x & 63;
@@ -451,11 +460,11 @@ __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, co
     const int nrows = M - row0 < kLnRows ? M - row0 : kLnRows;
     const int nvec = D >> 2;
     auto load_row = [&](float4 (&dst)[NV], int row) {
-        const float4* xr = reinterpret_cast<const float4*>(x + static_cast<int64_t>(row) * D);
+        const float4* xr = reinterpret_cast<const float4*>((kJoin ? x_join : x) + static_cast<int64_t>(row) * D);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const int v = lane + 64 * k;
-            dst[k] = (v < nvec) ? xr[v] : make_float4(0.f, 0.f, 0.f, 0.f);
+            dst[k] = (v < nvec && !(kJoin && join->from_zero)) ? xr[v] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     };
     float4 xv[NV], xn[NV], shv[NV], scv[NV];
@@ -479,6 +488,29 @@ __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, co
             for (int k = 0; k < NV; ++k)
                 if (lane + 64 * k < nvec) scv[k] = sc[lane + 64 * k];
             sc_smp = s_sc;
+        }
+        if constexpr (kJoin) {
+            // (every load of the row is in flight before the first is used)
+            const float4* bias = reinterpret_cast<const float4*>(join->bias);
+            const float4* gate = reinterpret_cast<const float4*>(
+                join->gate.base + static_cast<int64_t>(static_cast<uint32_t>(row) / static_cast<uint32_t>(join->gate.rows_per_sample)) * join->gate.stride);
+            float4 p[NV][kSplitParts], bv[NV], gv[NV];
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                const int v = lane + 64 * k < nvec ? lane + 64 * k : 0;
+#pragma unroll
+                for (int c = 0; c < kSplitParts; ++c)
+                    p[k][c] = reinterpret_cast<const float4*>(join->part + (static_cast<int64_t>(c) * M + row) * D)[v];
+                bv[k] = bias[v];
+                gv[k] = gate[v];
+            }
+            float4* xw = reinterpret_cast<float4*>(x_join + static_cast<int64_t>(row) * D);
+#pragma unroll
+            for (int k = 0; k < NV; ++k)
+                if (lane + 64 * k < nvec) {
+                    xv[k] = join4(p[k], bv[k], gv[k], xv[k]);
+                    xw[lane + 64 * k] = xv[k];
+                }
         }
         float s = 0.f;
 #pragma unroll
@@ -534,6 +566,32 @@ __global__ __launch_bounds__(kThreads) void ln_modulate_ahead_kernel(
         return;
     }
     ln_modulate_rows<OT, NV, 1>(x, shift, scale, M, D, out);
+}
+
+// The same on the residual stream after a residual update whose sums over K are still in parts: 512 rows of 1152 6.0 -> 8.2 us, what
+// the parts cost to read.
+template <int NV>
+__global__ __launch_bounds__(kThreads) void ln_modulate_join_kernel(
+    float* x, ResidJoin join, RowVec shift, RowVec scale, int32_t M, int32_t D, bf16_t* __restrict__ out, Prefetch pf,
+    int32_t first_prefetch) {
+    if (static_cast<int>(blockIdx.x) >= first_prefetch) {
+        prefetch_lines(pf, first_prefetch);
+        return;
+    }
+    ln_modulate_rows<bf16_t, NV, 1, true>(nullptr, shift, scale, M, D, out, &join, x);
+}
+
+// The residual update alone, where no LayerNorm follows: a row per blockIdx.x, four elements per thread.
+__global__ __launch_bounds__(kThreads) void resid_join_kernel(float* x, ResidJoin join, int32_t M, int32_t D) {
+    const int row = blockIdx.x, v = blockIdx.y * kThreads + threadIdx.x;
+    if (4 * v >= D) return;
+    const int64_t gate_off = static_cast<int64_t>(row / join.gate.rows_per_sample) * join.gate.stride;
+    float4 p[kSplitParts];
+#pragma unroll
+    for (int c = 0; c < kSplitParts; ++c) p[c] = reinterpret_cast<const float4*>(join.part + (static_cast<int64_t>(c) * M + row) * D)[v];
+    float4* xr = reinterpret_cast<float4*>(x + static_cast<int64_t>(row) * D) + v;
+    const float4 old = join.from_zero ? make_float4(0.f, 0.f, 0.f, 0.f) : *xr;
+    *xr = join4(p, reinterpret_cast<const float4*>(join.bias)[v], reinterpret_cast<const float4*>(join.gate.base + gate_off)[v], old);
 }
 
 // ---------------------------------------------------------------------------
@@ -1125,6 +1183,35 @@ int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M
     else
         hipLaunchKernelGGL(ln_modulate_kernel<float>, dim3(blocks), dim3(kThreads), 0, s, x, shift, scale, M, D,
                            static_cast<float*>(out));
+    return launch_ok() ? FREE_OK : FREE_ERR_HIP;
+}
+
+static bool join_covers(const float* x, const ResidJoin& join, int32_t D) {
+    auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+    return D % 4 == 0 && D <= 2048 && join.gate.stride % 4 == 0 && al16(x) && al16(join.part) && al16(join.bias) && al16(join.gate.base);
+}
+
+int32_t launch_ln_modulate_join(float* x, const ResidJoin& join, RowVec shift, RowVec scale, int32_t M, int32_t D, bf16_t* out,
+                                hipStream_t s, const Prefetch& pf) {
+    auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+    if (!join_covers(x, join, D) || shift.stride % 4 || scale.stride % 4 || !al16(out) || !al16(shift.base) || !al16(scale.base))
+        return FREE_ERR_SHAPE;
+    const int threads = ln_threads(M), blocks = (M + threads / 64 - 1) / (threads / 64), nv = (D / 4 + 63) / 64;
+    const int ahead_blocks = pf.blocks(threads), first_ahead = (blocks + 7) / 8 * 8;
+    const dim3 grid(ahead_blocks > 0 ? first_ahead + ahead_blocks : blocks);
+#define FREE_LN_JOIN(NV) \
+    hipLaunchKernelGGL(ln_modulate_join_kernel<NV>, grid, dim3(threads), 0, s, x, join, shift, scale, M, D, out, pf, first_ahead)
+    if (nv <= 1) FREE_LN_JOIN(1);
+    else if (nv <= 2) FREE_LN_JOIN(2);
+    else if (nv <= 5) FREE_LN_JOIN(5);
+    else FREE_LN_JOIN(8);
+#undef FREE_LN_JOIN
+    return launch_ok() ? FREE_OK : FREE_ERR_HIP;
+}
+
+int32_t launch_resid_join(float* x, const ResidJoin& join, int32_t M, int32_t D, hipStream_t s) {
+    if (!join_covers(x, join, D)) return FREE_ERR_SHAPE;
+    hipLaunchKernelGGL(resid_join_kernel, dim3(M, (D / 4 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, x, join, M, D);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 

@@ -97,11 +97,18 @@ bool make_dims(const free_dit_config* c, Dims* o) {
 
 // Workspace carve-up for a forward on B packed states (offsets in bytes).
 struct WsLayout {
-    size_t cond_h, sc, mod, tpack, ypack, xres, xn, qkv, att, hmid, eps, mtarget, vpart, vpart_bytes, fold, stats, total;
+    size_t cond_h, sc, mod, tpack, ypack, xres, xn, qkv, att, hmid, eps, mtarget, vpart, vpart_bytes, fold, stats, part, total;
 };
 
 // floats per sample of the fold vectors: c1 of every block's QKV and MLP-1 rows, then c0 of the same
 int64_t fold_stride(const Dims& d) { return 2 * static_cast<int64_t>(d.depth) * (3 * d.D + d.F); }
+
+// Sums over the parts of K that a split linear layer (of that many inputs) leaves to the kernel behind it (ResidJoin): fewer than
+// kMinFoldRows rows.  (Larger batches, which use none, reserve as much: a workspace for some B serves every smaller one.)
+size_t split_bytes(const Dims& d, int32_t k, size_t rows) {
+    if (d.mode != FREE_BF16 || !linear_split_covers(d.D, k)) return 0;
+    return kSplitParts * std::min(rows, static_cast<size_t>(kMinFoldRows - 1)) * d.D * 4;
+}
 
 WsLayout make_layout(const Dims& d, int32_t B) {
     WsLayout L;
@@ -127,6 +134,7 @@ WsLayout make_layout(const Dims& d, int32_t B) {
     // folded LayerNorm (bf16): c1 | c0 of both folded layers of every block per sample, partial row sums per token row
     L.fold = take(d.mode == FREE_BF16 ? static_cast<size_t>(B) * fold_stride(d) * 4 : 0);
     L.stats = take(d.mode == FREE_BF16 ? M * ((d.D + kLnSlotCols - 1) / kLnSlotCols) * 2 * 4 : 0);
+    L.part = take(split_bytes(d, d.F, M));
     L.total = off;
     return L;
 }
@@ -279,7 +287,8 @@ struct ActBufs {
 // `nblk` adaLN-Zero blocks on samples [b0, b0 + nb) of a batch.  blkw holds 10 pointers per block
 // (B_* order); block l's six modulation vectors of sample b are mod[b * mod_rows + l * 6D ..].
 // cu_share: number of such stacks running side by side on different streams (tile choice of the GEMMs).
-// few: the batch has few token rows (few_rows_for), sums may be cut where that fills the chip.
+// few: the batch has few token rows (few_rows_for): sums over the keys and over K may be cut where that fills the chip; part then
+// is room for the sums of split linear layers, [kSplitParts, B*ntok, D] fp32, and join what such a layer in front of the stack left.
 // chained: the stack runs again at once on the same weights (the steps of a drafting chain).
 // fold_ready (nullable): event after which fold->vec is complete; waited for on `s` before the first use.
 // fold (nullable): the LayerNorms are folded into the GEMMs around them (all but the first one of block 0, whose
@@ -293,7 +302,8 @@ struct FoldBufs {
 };
 int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const float* mod, int32_t mod_rows,
                         const ActBufs& a, int b0, int nb, hipStream_t s, Profiler* pf, int cu_share = 1,
-                        bool few = false, const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool chained = false) {
+                        bool few = false, float* part = nullptr, ResidJoin join = ResidJoin{},
+                        const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool chained = false) {
     const size_t esz = d.mode == FREE_BF16 ? 2 : 4;
     const int32_t M = nb * d.ntok;
     const int64_t r0 = static_cast<int64_t>(b0) * d.ntok;
@@ -350,9 +360,10 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     // Attention with the keys of a query over two wavefronts: twice the workgroups of half the work, faster while two of them per CU
     // hold the launch, slower beyond (16 heads: 256 rows 1.03, 1024 rows 1.015, 2048 rows 0.985, 3840 rows 0.97 of the forward).  The
     // choice may not depend on the number of samples, or a state alone and in a pack would differ: models of few heads, where that
-    // holds up to kMinFoldRows rows (6 heads: 1.02-1.05), and the drafter's one or two samples.
+    // holds up to kMinFoldRows rows, from five tiles of keys on (6 heads, 450 and 1024 tokens: 1.035-1.045; 100 and 256 tokens 1.02-1.03,
+    // left as it is), and the drafter's one or two samples.
     const int64_t places = 2 * device_cus();
-    const bool split_keys = few && (d.heads * (kMinFoldRows / 64) <= places || (chained && d.heads * ((2ll * d.ntok + 63) / 64) <= places));
+    const bool split_keys = few && ((d.ntok > 256 && d.heads * (kMinFoldRows / 64) <= places) || (chained && d.heads * ((2ll * d.ntok + 63) / 64) <= places));
     const int64_t DD = static_cast<int64_t>(d.D) * d.D, DF = static_cast<int64_t>(d.D) * d.F;
     const int64_t stack_bytes = nblk * (10 * DD + 2 * DF) * static_cast<int64_t>(esz);
     const bool may_ahead = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
@@ -368,6 +379,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         return p;
     };
+    const bool split_fc2 = few && linear_split_covers(d.D, d.F);
     for (int l = 0; l < nblk; ++l) {
         // x += gate1 * Proj(Attn(LN(x)(1+scale1)+shift1))
         if (fold && l > 0) {
@@ -378,8 +390,13 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         } else {
             {
                 ProfScope prof(pf, PROF_LN_MOD, s);
-                FREE_TRY(launch_ln_modulate(xres_h, vec(l, 0), vec(l, 1), M, d.D, d.mode, xn_h, s,
-                                            ahead(ln_ahead, l, B_QKV_W, 3 * DD, B_PROJ_W, DD)));
+                const Prefetch pre = ahead(ln_ahead, l, B_QKV_W, 3 * DD, B_PROJ_W, DD);
+                if (join.part) {
+                    FREE_TRY(launch_ln_modulate_join(xres_h, join, vec(l, 0), vec(l, 1), M, d.D, static_cast<bf16_t*>(xn_h), s, pre));
+                    join = ResidJoin{};
+                } else {
+                    FREE_TRY(launch_ln_modulate(xres_h, vec(l, 0), vec(l, 1), M, d.D, d.mode, xn_h, s, pre));
+                }
             }
             ProfScope prof(pf, PROF_GEMM_QKV, s);
             FREE_TRY(model_linear(d, xn_h, W(l, B_QKV_W), Bv(l, B_QKV_B), M, 3 * d.D, d.D, FREE_EPI_BIAS, qkv_h,
@@ -423,6 +440,13 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
             const LnFold f = producer(vec(l + 1, 1));
             FREE_TRY(model_linear(d, hmid_h, W(l, B_FC2_W), Bv(l, B_FC2_B), M, d.D, d.F, FREE_EPI_GATE_RESID_PREP,
                                      nullptr, xres_h, vec(l, 5), s, cu_share, &f));
+        } else if (split_fc2) {
+            // (the last block has no LayerNorm behind it: a launch adds the parts up)
+            ProfScope prof(pf, PROF_GEMM_FC2, s);
+            const bool last = l + 1 == nblk;
+            FREE_TRY(launch_linear_split(static_cast<const bf16_t*>(hmid_h), static_cast<const bf16_t*>(W(l, B_FC2_W)),
+                                         Bv(l, B_FC2_B), M, d.D, d.F, xres_h, vec(l, 5), part, last, &join, s));
+            if (last && join.part) FREE_TRY(launch_resid_join(xres_h, join, M, d.D, s));
         } else {
             ProfScope prof(pf, PROF_GEMM_FC2, s);
             FREE_TRY(model_linear(d, hmid_h, W(l, B_FC2_W), Bv(l, B_FC2_B), M, d.D, d.F, FREE_EPI_GATE_RESID,
@@ -490,7 +514,7 @@ int32_t forward_impl(free_dit_t h, const float* x, int32_t x_mod, const int32_t*
     const void* const* blkw = h->w.data() + 7;
     auto run_blocks = [&](int b0, int nb, hipStream_t st, int cu_share) -> int32_t {
         return run_block_stack(d, blkw, d.depth, mod, d.mod_rows, act, b0, nb, st, &h->prof, cu_share,
-                               h->few_rows_for(M), folded ? &fb : nullptr, fold_ready);
+                               h->few_rows_for(M), reinterpret_cast<float*>(ws + L.part), ResidJoin{}, folded ? &fb : nullptr, fold_ready);
     };
     // The samples of a packed batch are independent through all blocks, so the batch can be cut in two halves
     // or three thirds that run on as many streams forked from (and joined back into) the caller's stream: while
@@ -1113,7 +1137,7 @@ namespace {
 constexpr int kHoistRows = 16;          // samples of one adaLN pass
 
 struct DraftLayout {
-    size_t cond_h, sc, mod, tpack, ypack, emb, fin, xn, qkv, att, hmid, eps, feat, total;
+    size_t cond_h, sc, mod, tpack, ypack, emb, fin, xn, qkv, att, hmid, eps, feat, part, total;
 };
 
 DraftLayout make_draft_layout(const Dims& d, int32_t mod_rows, int32_t B) {
@@ -1138,6 +1162,7 @@ DraftLayout make_draft_layout(const Dims& d, int32_t mod_rows, int32_t B) {
     L.hmid = take(M * d.F * es);
     L.eps = take(static_cast<size_t>(B) * d.c_out * d.H * d.W * 4);
     L.feat = take(M * d.D * 4);
+    L.part = take(std::max(split_bytes(d, d.F, M), split_bytes(d, 2 * d.D, M)));
     L.total = off;
     return L;
 }
@@ -1180,14 +1205,27 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     }
     float* emb = reinterpret_cast<float*>(ws + L.emb);
     void* fin = ws + L.fin;
-    // z = fuse_w [emb | f_prev] + fuse_b, accumulated in fp32 straight into the residual stream:
-    // residual epilogue on a zeroed stream with a gate of ones
+    // z = fuse_w [emb | f_prev] + fuse_b, accumulated in fp32 straight into the residual stream: residual epilogue on a
+    // zeroed stream with a gate of ones; in parts of K, added up by the first block's LayerNorm, there is nothing to clear
+    const int32_t rows = static_cast<int32_t>(M);
+    const RowVec ones{dr->ones, 0, 1};
+    const float* fuse_b = static_cast<const float*>(dr->w[1]);
+    float* part = reinterpret_cast<float*>(ws + L.part);
+    const bool few = h->few_rows_for(M);
+    const bool split = few && linear_split_covers(d.D, 2 * d.D), left = split && linear_split_pays(rows, d.D, 2 * d.D, false);
+    ResidJoin join;
     FREE_TRY(launch_draft_embed(x, x_mod, B, d.C, d.H, d.W, d.p, d.D, static_cast<const float*>(h->w[W_PATCH_W]),
-                                static_cast<const float*>(h->w[W_PATCH_B]), h->pos, f_prev, d.mode, fin, f_out, emb, s));
-    FREE_TRY(model_linear(d, fin, dr->w[0], static_cast<const float*>(dr->w[1]), static_cast<int32_t>(M), d.D,
-                             2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, RowVec{dr->ones, 0, 1}, s));
+                                static_cast<const float*>(h->w[W_PATCH_B]), h->pos, f_prev, d.mode, fin, left ? nullptr : f_out, emb, s));
+    if (split) {
+        FREE_TRY(launch_linear_split(static_cast<const bf16_t*>(fin), static_cast<const bf16_t*>(dr->w[0]), fuse_b, rows, d.D, 2 * d.D,
+                                     f_out, ones, part, false, &join, s));
+        join.from_zero = left;
+    } else {
+        FREE_TRY(model_linear(d, fin, dr->w[0], fuse_b, rows, d.D, 2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, ones, s));
+    }
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};
-    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, h->few_rows_for(M), nullptr, nullptr, true));
+    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, few, part, join, nullptr, nullptr,
+                             true));
     RowVec fsh{mod + static_cast<int64_t>(dr->depth) * 6 * d.D, mod_stride, d.ntok};
     RowVec fsc{mod + static_cast<int64_t>(dr->depth) * 6 * d.D + d.D, mod_stride, d.ntok};
     return launch_final_layer(f_out, fsh, fsc, B, d.gh, d.gw, d.p, d.c_out, d.D, dr->fin(F_W),

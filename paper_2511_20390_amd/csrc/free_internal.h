@@ -78,6 +78,12 @@ struct RowVec {
 // its epilogue.  No separate pass over the residual stream, no atomics: every partial sum has one writer
 // and the consumer adds the slots of a row in a fixed order.
 constexpr int FREE_EPI_LN_BIAS = 3, FREE_EPI_LN_BIAS_GELU = 4, FREE_EPI_GATE_RESID_PREP = 5;
+// sums over one part of K, no bias, fp32 to resid[part][M][N] (gemm_rows.hip); see ResidJoin
+constexpr int FREE_EPI_PARTIAL = 6;
+// the residual update of FREE_EPI_GATE_RESID with the sums over those parts of K added in the same order in one workgroup; tiles
+// of up to kSegTileArea elements (a second set of accumulators)
+constexpr int FREE_EPI_GATE_RESID_SEG = 7;
+constexpr int kSegTileArea = 192 * 128;
 constexpr int kLnSlotCols = 128;           // columns of the residual stream per partial-sum slot
 struct LnFold {
     // producer: scale vector of the NEXT LayerNorm (indexed like the gate: same stride and rows per sample),
@@ -92,6 +98,18 @@ struct LnFold {
     int64_t fold_stride = 0;
     int32_t rows_per_sample = 1;
     float inv_width = 0.f;                 // 1 / width of the normalised rows
+};
+
+// Few rows, bf16: a linear layer of long K and few columns sums K in kSplitParts parts, always in this order, so that it can be
+// one workgroup per tile (FREE_EPI_GATE_RESID_SEG) or one per tile and part (FREE_EPI_PARTIAL).  In the second case the residual
+// update is left to the next kernel:
+//   x = gate (((part 0 + part 1) + part 2) + bias) + x        (x taken as zero with from_zero).
+constexpr int kSplitParts = 3;
+struct ResidJoin {
+    const float* part = nullptr;           // [kSplitParts, M, D]; nullptr: nothing to add
+    const float* bias = nullptr;
+    RowVec gate{nullptr, 0, 1};
+    int32_t from_zero = 0;
 };
 
 // Weight matrices that the launches after the next one read: the launch of a short kernel carries extra workgroups that
@@ -166,6 +184,11 @@ int32_t launch_patch_embed(const float* x, int32_t x_mod, int32_t B, int32_t C, 
                            float* out, hipStream_t s);
 int32_t launch_ln_modulate(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t D,
                            int32_t dtype, void* out, hipStream_t s, const Prefetch& pf = Prefetch{});
+// the same in bf16 on the residual stream after `join`, which it writes back to x; and the join alone.  D % 4 == 0, D <= 2048,
+// 16-byte aligned rows
+int32_t launch_ln_modulate_join(float* x, const ResidJoin& join, RowVec shift, RowVec scale, int32_t M, int32_t D, bf16_t* out,
+                                hipStream_t s, const Prefetch& pf);
+int32_t launch_resid_join(float* x, const ResidJoin& join, int32_t M, int32_t D, hipStream_t s);
 int32_t launch_linear_simple(const void* A, const void* W, const float* bias, int32_t M, int32_t N,
                              int32_t K, int32_t dtype, int32_t epi, void* out, float* resid,
                              RowVec gate, hipStream_t s);
@@ -232,6 +255,13 @@ int32_t launch_linear_rows(const float* X, const float* W, const float* bias, in
                            float* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
 bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* bias, const void* out, const float* resid,
                         const RowVec& gate);
+// resid = gate (X W^T + bias) + resid with K summed in kSplitParts parts (shapes: linear_split_covers, whatever M is).  Either at
+// once, or, where that is faster (linear_split_pays), the parts go to part[kSplitParts][M][N] and *join is set for the next kernel.
+// own_launch: the join has a launch of its own.
+bool linear_split_covers(int32_t N, int32_t K);
+bool linear_split_pays(int32_t M, int32_t N, int32_t K, bool own_launch);
+int32_t launch_linear_split(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, float* resid,
+                            RowVec gate, float* part, bool own_launch, ResidJoin* join, hipStream_t s);
 // fp32 operands and results, K a multiple of 32, products on the bf16 matrix instructions (gemm_f32.hip)
 bool linear_f32_covers(const float* X, const float* W, int32_t M, int32_t N, int32_t K);
 int32_t launch_linear_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,

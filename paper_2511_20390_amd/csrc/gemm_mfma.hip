@@ -468,7 +468,8 @@ constexpr TileTime kTilesF32[] = {
 // Time of a launch of `u` workgroups per CU.  last_alone: up to this many workgroups per CU left over after the full pairs
 // run as if they had a CU each.
 double launch_time(const TileTime& t, int32_t epi, double u, int nk, double last_alone) {
-    const bool resid = epi == FREE_EPI_GATE_RESID || epi == FREE_EPI_GATE_RESID_PREP;
+    const bool resid = epi == FREE_EPI_GATE_RESID || epi == FREE_EPI_GATE_RESID_PREP || epi == FREE_EPI_PARTIAL ||
+                       epi == FREE_EPI_GATE_RESID_SEG;       // (fp32 sums out: as many bytes per element as a residual update's)
     const bool gelu = epi == FREE_EPI_BIAS_GELU || epi == FREE_EPI_LN_BIAS_GELU;
     const double e = resid ? t.e_resid : gelu ? t.e_gelu : t.e_bias;
     const double alone = nk * t.a + e, shared = nk * t.b + e + t.d;
@@ -483,7 +484,7 @@ struct Choice {
     TileFamily family;
     int tile, bm, bn;
 };
-Choice choose(int32_t M, int32_t N, int32_t K, int elem_bytes, int32_t epi, bool rows_ok, int cu_share) {
+Choice choose(int32_t M, int32_t N, int32_t K, int elem_bytes, int32_t epi, bool rows_ok, int cu_share, double* time = nullptr) {
     const int cus = std::max(1, device_cus() / std::max(1, cu_share));
     const int slice = kRowBytes / elem_bytes, nk = (K + slice - 1) / slice;
     const bool f32 = elem_bytes == 4;
@@ -495,19 +496,21 @@ Choice choose(int32_t M, int32_t N, int32_t K, int elem_bytes, int32_t epi, bool
     const TileTime* best = nullptr;
     double t_best = 0.0;
     auto consider = [&](const TileTime& t, double last_alone) {
-        if (t.family == TILE_ROWS && (!rows_ok || epi > FREE_EPI_GATE_RESID)) return;
+        if (t.family == TILE_ROWS && (!rows_ok || (epi > FREE_EPI_GATE_RESID && epi != FREE_EPI_GATE_RESID_SEG))) return;
+        if (epi == FREE_EPI_GATE_RESID_SEG && t.bm * t.bn > kSegTileArea) return;
         if (epi == FREE_EPI_GATE_RESID_PREP && t.bn != 256) return;          // whole 128-column slots of row sums
         const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) / cus;
-        const double time = launch_time(t, epi, u, nk, last_alone);
-        if (best == nullptr || time < t_best) {
+        const double t_launch = launch_time(t, epi, u, nk, last_alone);
+        if (best == nullptr || t_launch < t_best) {
             best = &t;
-            t_best = time;
+            t_best = t_launch;
         }
     };
     if (f32)
         for (const TileTime& t : kTilesF32) consider(t, 0.75);
     else
         for (const TileTime& t : kTiles) consider(t, 1.0);
+    if (time) *time = t_best;
     return {best->family, best->tile, best->bm, best->bn};
 }
 
@@ -543,13 +546,68 @@ int32_t launch_linear_mfma(const bf16_t* X, const bf16_t* W, const float* bias, 
         }
     }
     if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
-    if (ln != nullptr ? K % BK != 0 : epi > FREE_EPI_GATE_RESID) return FREE_ERR_SHAPE;
+    if (ln != nullptr ? K % BK != 0 || epi > FREE_EPI_GATE_RESID_PREP : epi > FREE_EPI_GATE_RESID) return FREE_ERR_SHAPE;
     const Choice c = choose(M, N, K, 2, epi, linear_rows_covers(N, K, 2, bias, out, resid, gate), cu_share);
     switch (c.family) {
         case TILE_ROWS: return launch_linear_rows(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<RowsTile>(c.tile));
         case TILE_PIPE: return launch_linear_pipe(X, W, bias, M, N, K, epi, out, resid, gate, s, static_cast<PipeTile>(c.tile), ln);
         default: return launch_staged(static_cast<StagedTile>(c.tile), X, W, bias, M, N, K, epi, out, resid, gate, s);
     }
+}
+
+// A part has at least twelve slices: below that a workgroup is all prologue and epilogue, and with one part less to wait for there
+// is little to gain (K = 1536 to 384 columns 8.6 -> 7.6 us at 2250 rows, which the LayerNorm behind gives back).  And an even number:
+// gemm_rows_kernel takes two per pass.
+bool linear_split_covers(int32_t N, int32_t K) {
+    return N % 8 == 0 && N <= 2048 && K % (kSplitParts * 2 * BK) == 0 && K >= kSplitParts * 12 * BK;
+}
+
+namespace {
+
+const TileTime* best_split_tile(int32_t M, int32_t N, int32_t K, double* t_best) {
+    const TileTime* best = nullptr;
+    for (const TileTime& t : kTiles) {
+        if (t.family != TILE_ROWS) continue;
+        const double u = static_cast<double>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * kSplitParts / device_cus();
+        const double time = launch_time(t, FREE_EPI_PARTIAL, u, K / BK / kSplitParts, 1.0);
+        if (best == nullptr || time < *t_best) {
+            best = &t;
+            *t_best = time;
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
+// The next kernel reads the parts and updates the residual stream, out of the caches at 8.5 TB/s, and takes a microsecond longer; a
+// launch of its own takes three more.  Second layer of the MLP at width 1152, one launch -> parts, and the LayerNorm behind it (us):
+// 256 rows 17 -> 8.4, 4.2 -> 6.2; 512 rows 16.6 -> 11.8, 6.0 -> 8.2; 2048 rows 36 -> 36, 5.6 -> 10.8 (not taken).
+bool linear_split_pays(int32_t M, int32_t N, int32_t K, bool own_launch) {
+    double t_split = 0.0, t_one = 0.0;
+    best_split_tile(M, N, K, &t_split);
+    choose(M, N, K, 2, FREE_EPI_GATE_RESID_SEG, true, 1, &t_one);
+    const double t_join = (own_launch ? 4.0 : 1.0) + 16.0 * M * N / 8.5e6;
+    return t_split + t_join < t_one;
+}
+
+int32_t launch_linear_split(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, float* resid,
+                            RowVec gate, float* part, bool own_launch, ResidJoin* join, hipStream_t s) {
+    if (!mfma_linear_supported(M, N, K) || !linear_split_covers(N, K) || !linear_rows_covers(N, K, 2, bias, part, resid, gate))
+        return FREE_ERR_SHAPE;
+    if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
+    if (linear_split_pays(M, N, K, own_launch)) {
+        double t;
+        const TileTime* tile = best_split_tile(M, N, K, &t);
+        *join = ResidJoin{part, bias, gate, 0};
+        return launch_linear_rows(X, W, nullptr, M, N, K, FREE_EPI_PARTIAL, nullptr, part, RowVec{nullptr, 0, 1}, s,
+                                  static_cast<RowsTile>(tile->tile));
+    }
+    const Choice c = choose(M, N, K, 2, FREE_EPI_GATE_RESID_SEG, true, 1);
+    if (c.family == TILE_ROWS)
+        return launch_linear_rows(X, W, bias, M, N, K, FREE_EPI_GATE_RESID_SEG, nullptr, resid, gate, s, static_cast<RowsTile>(c.tile));
+    return launch_linear_pipe(X, W, bias, M, N, K, FREE_EPI_GATE_RESID_SEG, nullptr, resid, gate, s, static_cast<PipeTile>(c.tile),
+                              nullptr);
 }
 
 bool mfma_ln_fold_supported(int32_t M, int32_t D, int32_t rows_per_sample) {
@@ -571,7 +629,7 @@ int32_t launch_linear_mfma_f32(const float* X, const float* W, const float* bias
 int32_t mfma_linear_tile(int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epi) {
     const int es = dtype == FREE_BF16 ? 2 : 4;
     if (!(es == 2 ? mfma_linear_supported(M, N, K) : mfma_linear_f32_supported(M, N, K))) return FREE_ERR_SHAPE;
-    if (epi > FREE_EPI_GATE_RESID && (es == 4 || K % BK != 0)) return FREE_ERR_SHAPE;
+    if (epi > FREE_EPI_GATE_RESID && (es == 4 || K % BK != 0 || epi > FREE_EPI_GATE_RESID_PREP)) return FREE_ERR_SHAPE;
     const Choice c = choose(M, N, K, es, epi, linear_rows_covers(N, K, es, nullptr, nullptr, nullptr, RowVec{nullptr, 0, 1}), 1);
     return c.family * 1000000 + c.bm * 1000 + c.bn;
 }

@@ -46,6 +46,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_pipe_kernel(
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0 && (NW == 8 || WGM == 1), "whole blocks per wavefront");
     constexpr bool kLnEpi = EPI == FREE_EPI_LN_BIAS || EPI == FREE_EPI_LN_BIAS_GELU;
     constexpr bool kPrep = EPI == FREE_EPI_GATE_RESID_PREP;
+    constexpr bool kSeg = EPI == FREE_EPI_GATE_RESID_SEG;
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
     int tile_m, tile_n;
@@ -87,6 +88,35 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_pipe_kernel(
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    // kSeg: the sums over the first parts of K (ResidJoin's order); the last part is added to them at the end
+    [[maybe_unused]] f32x16_t sum[kSeg ? TM : 1][kSeg ? TN : 1];
+    [[maybe_unused]] const int seg = nk / kSplitParts;
+    [[maybe_unused]] int seg_end = seg;
+    auto add_part = [&](bool last) {
+        if constexpr (kSeg) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        if (last) {
+                            acc[i][j][e] = sum[i][j][e] + acc[i][j][e];
+                        } else {
+                            sum[i][j][e] += acc[i][j][e];
+                            acc[i][j][e] = 0.f;
+                        }
+                    }
+        }
+    };
+    if constexpr (kSeg) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum[i][j][e] = 0.f;
+    }
     auto mma = [&](int ks, int t) {
         const int i = t / TN, j = t % TN;
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, f[ks][TM + j]),
@@ -247,25 +277,34 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_pipe_kernel(
             __builtin_amdgcn_sched_barrier(0);
         }
         int kt = 0;
-        for (; kt + 2 < nk; ++kt) slice(kt, on, yes, yes);
+        for (; kt + 2 < nk; ++kt) {
+            if constexpr (kSeg && decltype(on)::value) {
+                if (kt == seg_end) {
+                    add_part(false);
+                    seg_end += seg;
+                }
+            }
+            slice(kt, on, yes, yes);
+        }
         if (kt + 1 < nk) {
             slice(kt, on, yes, no);
             ++kt;
         }
         slice(kt, on, no, no);
+        if constexpr (decltype(on)::value) add_part(true);
     };
     if (n0 + wn * TN * 32 < N && m0 + wm * TM * 32 < M) k_loop(yes);
     else k_loop(no);
 
     // ---- epilogue: the stages are idle now, each wavefront transposes its output in a private piece of them
     __syncthreads();
-    constexpr bool kResidEpi = EPI == FREE_EPI_GATE_RESID || kPrep;
+    constexpr bool kResidEpi = EPI == FREE_EPI_GATE_RESID || kPrep || kSeg;
     constexpr int kWaveStage = kResidEpi ? 32 * (((TN % 2 == 0 ? 2 : 1) * 8 + 1) * 16)   // fp32 groups
                                          : 32 * (TN * 64 + 16);                          // bf16 rows
     constexpr int kSumBytes = kPrep ? BM * WGN * 2 * 4 : 0;
     static_assert(NW * kWaveStage + kSumBytes <= 2 * kStageBytes, "output staging must fit in the K-loop stages");
     float* row_sums = reinterpret_cast<float*>(lds + NW * kWaveStage);                   // kPrep: [BM][WGN][2]
-    write_tile<bf16_t, TM, TN, EPI, (NW == 8 ? 4 : 0)>(acc, m0 + wm * TM * 32 + l32, n0 + wn * TN * 32, lane, M, N, vec_ok, bias,
+    write_tile<bf16_t, TM, TN, (kSeg ? FREE_EPI_GATE_RESID : EPI), (NW == 8 ? 4 : 0)>(acc, m0 + wm * TM * 32 + l32, n0 + wn * TN * 32, lane, M, N, vec_ok, bias,
                                                        out, resid, gate, lds + wave * kWaveStage, ln, ln_a,
                                                        row_sums + (wm * TM * 32 * WGN + wn) * 2, WGN * 2);
     if constexpr (kPrep) {
@@ -306,7 +345,7 @@ int32_t launch_one(const Args& a, const LnFold& ln) {
     // the vector epilogue needs 16-byte aligned rows of out / resid / bias / gate
     auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     const bool vec = ((a.N & 7) == 0) && al16(a.bias) && al16(a.out) && al16(a.resid) && al16(a.gate.base) && ((a.gate.stride & 3) == 0);
-    if (EPI >= FREE_EPI_LN_BIAS && !vec) return FREE_ERR_SHAPE;     // the folded-LayerNorm epilogues have no element-wise form
+    if (EPI >= FREE_EPI_LN_BIAS && EPI <= FREE_EPI_GATE_RESID_PREP && !vec) return FREE_ERR_SHAPE;     // the folded-LayerNorm epilogues have no element-wise form
     // Row tiles per group of the tile order.  Several rounds of workgroups: the 32 that run together on an XCD should cover
     // a x b tiles with a BM ~ b BN, the shape that needs the fewest distinct X and W panels (first-touch misses of that
     // XCD's L2).  A single round: every XCD holds total / 8 tiles for the whole kernel, and a group of exactly that many
@@ -332,6 +371,9 @@ int32_t launch_tile(const Args& a, int32_t epi, const LnFold& ln) {
         case FREE_EPI_LN_BIAS_GELU: return launch_one<BM, BN, WGM, WGN, FREE_EPI_LN_BIAS_GELU>(a, ln);
         case FREE_EPI_GATE_RESID_PREP:
             if constexpr (BN == 256) return launch_one<BM, BN, WGM, WGN, FREE_EPI_GATE_RESID_PREP>(a, ln);
+            return FREE_ERR_RANGE;
+        case FREE_EPI_GATE_RESID_SEG:
+            if constexpr (BM * BN <= kSegTileArea) return launch_one<BM, BN, WGM, WGN, FREE_EPI_GATE_RESID_SEG>(a, ln);
             return FREE_ERR_RANGE;
         default: return FREE_ERR_RANGE;
     }

@@ -33,7 +33,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
     const T* __restrict__ X, const T* __restrict__ W, const float* __restrict__ bias, int32_t M, int32_t N, int32_t K,
     int32_t tiles_m, int32_t tiles_n, T* __restrict__ out, float* __restrict__ resid, RowVec gate) {
     constexpr bool kF32 = std::is_same<T, float>::value;
-    constexpr bool kResid = EPI == FREE_EPI_GATE_RESID, kGelu = EPI == FREE_EPI_BIAS_GELU;
+    constexpr bool kSeg = EPI == FREE_EPI_GATE_RESID_SEG, kResid = EPI == FREE_EPI_GATE_RESID || kSeg;
+    constexpr bool kGelu = EPI == FREE_EPI_BIAS_GELU, kPart = EPI == FREE_EPI_PARTIAL;
+    constexpr int kParts = kPart ? kSplitParts : 1;
     constexpr int ES = static_cast<int>(sizeof(T)), NW = WGM * WGN;
     constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
     constexpr int LA = BM / 8 / NW, NL = (BM + BN) / 8 / NW;            // 1 KB blocks per wavefront and slice: of X, of both
@@ -43,12 +45,14 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
     int tile_m, tile_n;
-    tile_coords(tiles_m, blockIdx.x, tiles_m, tiles_n, &tile_m, &tile_n);
+    tile_coords(tiles_m, blockIdx.x, tiles_m, tiles_n * kParts, &tile_m, &tile_n);
+    const int part = tile_n % kParts;                                   // (an XCD keeps whole rows of W: what was read ahead for it)
+    tile_n /= kParts;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
     const int l32 = lane & 31, lhi = lane >> 5;
-    const int nk = K / (kRowBytes / ES);
+    const int nk = K / (kRowBytes / ES) / kParts;
 
     // ---- what the epilogue needs: register e of acc[i][j] is row gm_lane + 32 i, column gn_lane + 32 j + 8 (e / 4) + e % 4
     const int gm_lane = m0 + wm * TM * 32 + l32, gn_lane = n0 + wn * TN * 32 + 4 * lhi;
@@ -69,19 +73,24 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
                     pre_g[i][j][q] = ok ? *reinterpret_cast<const f32x4_t*>(gate.base + static_cast<int64_t>(gm / gate.rows_per_sample) * gate.stride + gn) : zero4;
                 }
     };
+    auto load_bias = [&]() {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int gn = gn_lane + j * 32 + 8 * q;                     // N % 8 == 0: four columns are all in or all out
-            pre_b[j][q] = gn < N ? *reinterpret_cast<const f32x4_t*>(bias + gn) : zero4;
-        }
+            for (int q = 0; q < 4; ++q) {
+                const int gn = gn_lane + j * 32 + 8 * q;                 // N % 8 == 0: four columns are all in or all out
+                pre_b[j][q] = gn < N ? *reinterpret_cast<const f32x4_t*>(bias + gn) : zero4;
+            }
+    };
+    constexpr bool kPreBias = !kPart && !(kSeg && !kPreResid);           // (nor for the bias beside two sets of accumulators)
+    if constexpr (kPreBias) load_bias();
     if constexpr (kPreResid) load_resid();
 
     // ---- loads: block u holds tile rows 8 u .. 8 u + 7; lane -> row 8 u + lane / 8, LDS chunk lane % 8, which receives the
     // global 16-byte chunk (lane % 8) ^ ((row / 2) % 8); a wavefront's blocks w, w + NW, ... have the parity of w
-    const u32x4_t xsrd = make_rsrc(X + static_cast<int64_t>(m0) * K, static_cast<int64_t>(M - m0) * K * ES);
-    const u32x4_t wsrd = make_rsrc(W + static_cast<int64_t>(n0) * K, static_cast<int64_t>(N - n0) * K * ES);
+    const int64_t k0 = static_cast<int64_t>(part) * nk * (kRowBytes / ES);
+    const u32x4_t xsrd = make_rsrc(X + static_cast<int64_t>(m0) * K + k0, (static_cast<int64_t>(M - m0) * K - k0) * ES);
+    const u32x4_t wsrd = make_rsrc(W + static_cast<int64_t>(n0) * K + k0, (static_cast<int64_t>(N - n0) * K - k0) * ES);
     const int voff = (lane >> 3) * K * ES + (((lane & 7) ^ (((wave & 1) << 2) | (lane >> 4))) << 4);
     const uint32_t lds_base = lds_address(lds);
     auto issue = [&](int kt, int stage, int lo, int hi) {               // blocks [lo, hi) of this wavefront's share
@@ -99,12 +108,16 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
     const int x_row0 = (wm * TM * 32 + l32) * kRowBytes, w_row0 = (BM + wn * TN * 32 + l32) * kRowBytes;
     u32x4_t fx[2][4][TM], fw[2][4][TN];                                 // two slices of fragments
     f32x16_t acc[TM][TN];
+    [[maybe_unused]] f32x16_t sum[kSeg ? TM : 1][TN];                   // kSeg: the finished parts of K
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+            for (int e = 0; e < 16; ++e) {
+                acc[i][j][e] = 0.f;
+                if constexpr (kSeg) sum[i][j][e] = 0.f;
+            }
     auto load_frags = [&](int stage, int buf, int ks) {
         const char* base = lds + stage * kStageBytes;
         const int choff = (((ks << 1) | lhi) ^ sw) << 4;
@@ -189,6 +202,25 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
     const std::false_type no{};
     int kt = 0;
     const int n_steady = nk > S ? nk - S : 0;                           // slices whose stage is refilled
+    if constexpr (kSeg) {
+        // the parts before the last one: an even number of slices each, at least S (linear_split_covers)
+        const int seg = nk / kSplitParts;
+        for (int end = seg; end < nk; end += seg) {
+            for (; kt < end; kt += 2) {
+                step(kt, b0, yes);
+                step(kt + 1, b1, yes);
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        sum[i][j][e] += acc[i][j][e];
+                        acc[i][j][e] = 0.f;
+                    }
+        }
+    }
     for (; kt + 1 < n_steady; kt += 2) {
         step(kt, b0, yes);
         step(kt + 1, b1, yes);
@@ -208,8 +240,32 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
     }
 
     // ---- epilogue
+    if constexpr (!kPart && !kPreBias) load_bias();
     if constexpr (kResid && !kPreResid) load_resid();
-    if constexpr (kResid || kF32) {
+    if constexpr (kPart) {
+        // 32-row blocks of the fp32 sums transposed through the idle stages: 128 TN bytes of a row per store, not 32
+        __syncthreads();
+        constexpr int CH = TN * 8, kStageRow = (CH + 1) * 16;
+        static_assert(NW * 32 * kStageRow <= S * kStageBytes && (32 * CH) % 64 == 0, "output staging must fit in the stages");
+        char* wave_lds = lds + wave * 32 * kStageRow;
+        float* dst = resid + static_cast<int64_t>(part) * M * N;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<f32x4_t*>(wave_lds + l32 * kStageRow + ((8 * j + 2 * q + lhi) << 4)) =
+                        f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+#pragma unroll
+            for (int q = 0; q < 32 * CH / 64; ++q) {
+                const int f = q * 64 + lane, row = f / CH, ch = f % CH;
+                const f32x4_t o = *reinterpret_cast<const f32x4_t*>(wave_lds + row * kStageRow + (ch << 4));
+                const int gm = m0 + wm * TM * 32 + i * 32 + row, gn = n0 + wn * TN * 32 + ch * 4;
+                if (gm < M && gn < N) *reinterpret_cast<f32x4_t*>(dst + static_cast<int64_t>(gm) * N + gn) = o;
+            }
+        }
+    } else if constexpr (kResid || kF32) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -221,7 +277,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
                     f32x4_t o;
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float v = acc[i][j][4 * q + c] + pre_b[j][q][c];
+                        float a = acc[i][j][4 * q + c];
+                        if constexpr (kSeg) a = sum[i][j][4 * q + c] + a;
+                        const float v = a + pre_b[j][q][c];
                         if constexpr (kResid) o[c] = fmaf(pre_g[i][j][q][c], v, pre_r[i][j][q][c]);
                         else o[c] = kGelu ? gelu_fast(v) : v;
                     }
@@ -285,7 +343,8 @@ int32_t launch_one(const Args<T>& a) {
             return FREE_ERR_HIP;
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(WGM * WGN * 64), lds, a.s, a.X, a.W, a.bias, a.M, a.N, a.K, tiles_m,
+    constexpr int kParts = EPI == FREE_EPI_PARTIAL ? kSplitParts : 1;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * kParts), dim3(WGM * WGN * 64), lds, a.s, a.X, a.W, a.bias, a.M, a.N, a.K, tiles_m,
                        tiles_n, a.out, a.resid, a.gate);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
@@ -296,6 +355,12 @@ int32_t launch_tile(const Args<T>& a, int32_t epi) {
         case FREE_EPI_BIAS: return launch_one<T, BM, BN, WGM, WGN, S, FREE_EPI_BIAS>(a);
         case FREE_EPI_BIAS_GELU: return launch_one<T, BM, BN, WGM, WGN, S, FREE_EPI_BIAS_GELU>(a);
         case FREE_EPI_GATE_RESID: return launch_one<T, BM, BN, WGM, WGN, S, FREE_EPI_GATE_RESID>(a);
+        case FREE_EPI_PARTIAL:
+            if constexpr (!std::is_same<T, float>::value) return launch_one<T, BM, BN, WGM, WGN, S, FREE_EPI_PARTIAL>(a);
+            return FREE_ERR_RANGE;
+        case FREE_EPI_GATE_RESID_SEG:
+            if constexpr (!std::is_same<T, float>::value) return launch_one<T, BM, BN, WGM, WGN, S, FREE_EPI_GATE_RESID_SEG>(a);
+            return FREE_ERR_RANGE;
         default: return FREE_ERR_RANGE;
     }
 }

@@ -64,6 +64,30 @@ def test_drafter_embedding_edges(lat_h, lat_w, B, hidden, mode):
     target.close()
 
 
+@pytest.mark.parametrize("hidden,heads,lat_h,lat_w,B", [(1152, 16, 32, 32, 6), (768, 12, 30, 34, 5), (1536, 24, 20, 20, 3)])
+def test_drafter_alone_or_packed_same_bits(hidden, heads, lat_h, lat_w, B):
+    """The fusion layer and the second layers of the MLPs sum K in parts, in one workgroup or in several with the parts added up by
+    the LayerNorm behind (or, after the last block, by a launch of its own): which it is depends on the rows, the sums do not."""
+    import torch
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("small", hidden=hidden, heads=heads, mlp_hidden=4 * hidden, depth=1, lat_h=lat_h, lat_w=lat_w)
+    w, wd = pu.weights_for(cfg, "bf16", seed=21), synth.make_drafter_weights(cfg, 2, seed=22, bf16_values=True)
+    target = binding.FreeDit(cfg, w, "bf16")
+    drafter = binding.FreeDrafter(target, wd, 2)
+    rng = np.random.default_rng(23)
+    x = pu.to_dev(rng.standard_normal((B, cfg["in_ch"], lat_h, lat_w)).astype(np.float32))
+    f = pu.to_dev(rng.standard_normal((B, synth.n_tokens(cfg), hidden)).astype(np.float32))
+    t, y = (pu.to_dev(rng.integers(0, n, B).astype(np.int32)) for n in (1000, cfg["num_classes"] + 1))
+    eps, feat = (v.clone() for v in drafter.drafter_forward(x, f, t, y))
+    eps1, feat1 = drafter.drafter_forward(*(v[1:2].contiguous() for v in (x, f, t, y)))
+    assert torch.equal(eps1.reshape(-1), eps[1].reshape(-1)) and torch.equal(feat1.reshape(-1), feat.reshape(B, -1)[1])
+    ref_eps, ref_feat = fo.drafter_forward(wd, w, dict(cfg, drafter_depth=2), *(v[1:2].cpu().numpy() for v in (x, f, t, y)))
+    assert pu.rel_l2(eps1.cpu().numpy(), ref_eps) <= pu.DIT_REL_L2["bf16"]
+    assert pu.rel_l2(feat1.cpu().numpy(), ref_feat) <= pu.DIT_REL_L2["bf16"]
+    drafter.close()
+    target.close()
+
+
 def _draft_inputs(cfg, K, seed, cfg_scale):
     sched = fo.ddpm_schedule()
     di = synth.make_draft_inputs(cfg, K, seed, cfg_scale)
