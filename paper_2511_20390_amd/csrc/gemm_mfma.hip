@@ -5,7 +5,8 @@
 // v_mfma_f32_32x32x16_bf16 (lane l: row/col l%32, 8 consecutive k at 8*(l/32)).
 //
 // Design for gfx950 (64-wide wavefronts, 160 KB LDS per CU, 512 registers per lane):
-//  * used for fp32 operands and for bf16 with K no multiple of the slice; bf16 problems of whole slices are chosen between
+//  * used for fp32 operands (of models where K is no multiple of 32, else gemm_f32.hip; of free_op_linear always) and for bf16 with
+//    K no multiple of the slice; bf16 problems of whole slices are chosen between
 //    the tiles of gemm_pipe.hip and gemm_rows.hip at the end of this file.  Rates quoted below for bf16 were measured when
 //    this kernel took those as well.
 //  * workgroup = 4 or 8 wavefronts in a WGM x WGN grid, macro tile BM x BN (256x256 and

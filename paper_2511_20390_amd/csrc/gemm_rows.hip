@@ -1,5 +1,6 @@
 // GEMM of the dense projections for problems of few token rows (single guided steps, the drafter, short packs):
 //   C[M,N] = X[M,K] . W[N,K]^T  (+bias, fused epilogue), bf16 or fp32 operands, fp32 accumulation, K a whole number of slices.
+// (fp32: free_op_linear; the linear layers of fp32 models run on gemm_f32.hip.)
 // Operand layout, accumulation order, LDS swizzle and results are those of gemm_mfma.hip bit for bit; this kernel is
 // organised for latency.
 //
@@ -12,6 +13,8 @@
 //    group of products; one barrier per slice;
 //  * fragments of slice t + 1 are read under the products of slice t (a whole slice in registers: the tiles are small);
 //  * what the epilogue needs from memory (bias; gate and residual of the smallest tile) is requested before the first slice.
+// K in parts (kSplitParts; narrow outputs of long K, where even small tiles leave CUs idle): one workgroup per tile and part with the
+// fp32 sums to memory (FREE_EPI_PARTIAL), or one per tile that adds the same parts in the same order (FREE_EPI_GATE_RESID_SEG).
 // Rows are walked fastest within an XCD, so every weight panel is fetched by one XCD only.
 // Measured back to back, weights from HBM, against the 96 x 128 / 160 x 128 register-staged tiles (us; QKV, out-projection,
 // MLP-1, MLP-2):   256 rows 13.3, 15.8, 14.5, 43.8 -> 8.2, 8.7, 11.2, 23.2
