@@ -154,10 +154,10 @@ def bench_round(args):
             ent["tflops"] = per[name] / (ms / n * 1e-3) / 1e12
         kernels[name] = ent
     dom = max((k for k in kernels if k in per), key=lambda k: kernels[k]["ms_per_step"])
-    # both modes run the GEMMs and attention on the matrix cores: bf16 against the dense bf16 peak; the fp32 linear layers (six
-    # bf16 products per fp32 product) against a sixth of it, fp32 attention (v_mfma_f32_32x32x2_f32) against the fp32 matrix peak of
+    # both modes run the GEMMs and attention on the matrix cores: bf16 against the dense bf16 peak; the fp32 linear layers (eight
+    # bf16 products per fp32 product) against an eighth of it, fp32 attention (v_mfma_f32_32x32x2_f32) against the fp32 matrix peak of
     # 157.3 TFLOP/s (256 CUs x 4 SIMDs x 64 lanes x 2 flop x 2.4 GHz); the whole fp32 step against the linear layers' peak
-    peak = PEAK_BF16_TFLOPS if mode == "bf16" else PEAK_FP32_TFLOPS if dom == "attention" else PEAK_BF16_TFLOPS / 6
+    peak = PEAK_BF16_TFLOPS if mode == "bf16" else PEAK_FP32_TFLOPS if dom == "attention" else PEAK_BF16_TFLOPS / 8
     roofline = {"kernel": dom, "bound": "mfma", "achieved": kernels[dom]["tflops"], "peak": peak,
                 "unit": "TFLOP/s", "frac": kernels[dom]["tflops"] / peak,
                 "traffic": (measured_traffic(dom, bool(model.ln_fold_active(B)))
@@ -201,7 +201,7 @@ def bench_round(args):
         "forward": {"algorithmic_tflop": total_flops / 1e12, "ms_sum_of_kernels": fwd_ms,
                     "tflops_whole_step": total_flops / (ms_per_step * 1e-3) / 1e12,
                     "frac_of_peak_whole_step": total_flops / (ms_per_step * 1e-3) / 1e12
-                    / (PEAK_BF16_TFLOPS if mode == "bf16" else PEAK_BF16_TFLOPS / 6)},
+                    / (PEAK_BF16_TFLOPS if mode == "bf16" else PEAK_BF16_TFLOPS / 8)},
         "tokens_per_round": B * synth.n_tokens(cfg), "setup_s": setup_s,
         "n_accept": int(out["n_accept"].item()), "B": B,
     }

@@ -2,11 +2,14 @@
 //
 // The fp32 matrix instructions run at 157 TFLOP/s, the bf16 ones at 2.5 PFLOP/s.  An fp32 value is the exact sum of three bf16
 // values (its 24 significant bits cut in three eights, v = h + m + l, each part the leading bits of what is left), so that
-//     x w = xh wh + (xh wm + xm wh + xm wm + xh wl + xl wh) + (xm wl + xl wm + xl wl)
-// and the last bracket is below 2^-21 of the product: six bf16 products give what one fp32 product gives, in 192 cycles per
-// 32 x 32 x 16 against 512.  The leading products have an accumulator of their own, which is rounded once per 32 k and not at
-// every second one, and the five small ones another, whose rounding is 2^-7 of that.  2-norm error against 64 bits, normal X and
-// W, fp32 instructions -> here: K = 96 4.4e-8 -> 3.0e-8, K = 1152 3.4e-7 -> 8.9e-8, K = 1536 4.3e-7 -> 1.1e-7, K = 4608 9.8e-7 -> 2.4e-7.
+//     x w = xh wh + (xh wm + xm wh + xm wm + xh wl + xl wh + xm wl + xl wm) + xl wl
+// and the last product, below 2^-30 of the whole, is the only one left out: eight bf16 products, 256 cycles per 32 x 32 x 16 against
+// 512.  (Without xm wl and xl wm, up to 2^-21 of a product, sums of few terms were further off than those of the fp32 instructions:
+// one term 5.5e-8 against 2.5e-8; what the two cost: width 1152, MLP-2, 512 rows 58.5 -> 64.6 us, 12288 rows 689 -> 850.)  The leading
+// products have an accumulator of their own, which is rounded once per 32 k and not at every second one, and the seven small ones
+// another, whose rounding is 2^-7 of that.  2-norm error against 64 bits, fp32 instructions -> here: normal X and W, K = 32 1.0e-7 ->
+// 4.2e-8, K = 96 1.8e-7 -> 5.2e-8, K = 1152 6.1e-7 -> 1.4e-7, K = 4608 1.2e-6 -> 2.9e-7; one non-zero per row 2.5e-8, both, and no element
+// further off than one rounding; 5 % non-zeros over half a row, K = 32 2.9e-8 -> 2.5e-8, K = 96 3.7e-8 -> 3.3e-8.
 // Values that are not finite have no such parts (inf - inf): they give a NaN, and a wavefront that finds one in its tile computes
 // the tile again with fp32 products.  Parts below the smallest bf16 (2^-133) are lost: full precision needs |v| >= 2^-110.
 //
@@ -15,11 +18,12 @@
 // conflict counter reads zero); two stages, one barrier per slice.  Every value is cut once per workgroup, eleven instructions per
 // pair.  Eight wavefronts: 2 x 2 parts of the tile, and of every slice one wavefront of a SIMD takes k-step 0, the other k-step 1 -
 // with four wavefronts, one per SIMD, the cutting and the products of a wavefront hardly overlap (512 x 1152 x 4608 on 64 x 64 tiles
-// 76 us with four, 58 with eight; fp32 instructions 86).
-// What bounds it now: matrix and vector pipe and LDS are each busy a third of the time (64 x 64 tiles at 512 rows: 0.35, 0.38,
-// 0.35) to a half (128 x 128 at 12288 rows: 0.59, 0.36, 0.30) and overlap only in part.
+// six products: 76 us with four, 58 with eight; fp32 instructions 86).
+// What bounds it now: matrix and vector pipe and LDS, which overlap only in part (with six products each busy a third of the time on 64 x
+// 64 tiles at 512 rows, 0.35, 0.38, 0.35, to a half on 128 x 128 at 12288 rows, 0.59, 0.36, 0.30; the matrix pipe a third more now).
 #include <algorithm>
 #include <cmath>
+#include <utility>
 
 #include "free_internal.h"
 #include "gemm_dma.h"
@@ -30,6 +34,7 @@ namespace {
 
 constexpr int kSlice = 32;                   // fp32 values per row and slice (kRowBytes of them)
 constexpr int kPlaneRow = kSlice * 2;        // bytes of a row of one plane
+constexpr int kProducts = 8;                 // of the nine products of two times three parts
 constexpr int kWaves = 8;                    // 2 x 2 parts of the tile, each by two wavefronts: k-steps 0 and 1 of every slice
 
 // two fp32 values -> their leading, middle and last eight bits as pairs of bf16
@@ -42,6 +47,11 @@ __device__ __forceinline__ void cut2(float v0, float v1, uint32_t (&out)[3]) {
         r0 = __float_as_uint(__uint_as_float(r0) - __uint_as_float(r0 & 0xffff0000u));
         r1 = __float_as_uint(__uint_as_float(r1) - __uint_as_float(r1 & 0xffff0000u));
     }
+}
+
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
 }
 
 template <int BM, int BN, int SETS, int EPI>
@@ -112,24 +122,24 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_f32_kernel(
                 hi[i][j][e] = 0.f;
                 lo[i][j][e] = 0.f;
             }
-    constexpr int MF = 6 * TM * TN, NR = 3 * (TM + TN);
+    constexpr int MF = kProducts * TM * TN, NR = 3 * (TM + TN);
     auto buffer = [](int buf, int p) { return p == 0 || kTwo ? buf : 0; };
-    auto load_frag = [&](int stage, int buf, int r) {                   // fragment r of a slice, plane by plane
+    auto load_frag = [&](int stage, int buf, int r) {                   // fragment r of a slice: leading, last, middle plane
         const char* base = lds + stage * kStage;
-        const int p = r / (TM + TN), f = r % (TM + TN), at = buffer(buf, p);
+        const int p = (3 - r / (TM + TN)) % 3, f = r % (TM + TN), at = buffer(buf, p);
         if (f < TM) fx[at][p][f] = *reinterpret_cast<const u32x4_t*>(base + p * kPlane + x_row + f * 32 * kPlaneRow);
         else fw[at][p][f - TM] = *reinterpret_cast<const u32x4_t*>(base + p * kPlane + w_row + (f - TM) * 32 * kPlaneRow);
     };
-    // the reads of the next slice's fragments behind product t: evenly, or as the planes are used up (middle 3, last 5, of the six)
+    // the reads of the next slice's fragments behind product t: evenly, or as the planes are used up (last 4, middle 7, of the eight)
     auto reads_until = [](int t) {
         if (kTwo) return t * NR / MF;
-        constexpr int u = MF / 6, f = TM + TN;
-        return t <= 3 * u ? t * f / (3 * u) : t <= 5 * u ? f + (t - 3 * u) * f / (2 * u) : 2 * f + (t - 5 * u) * f / u;
+        constexpr int u = MF / kProducts, f = TM + TN;
+        return t <= 4 * u ? t * f / (4 * u) : t <= 7 * u ? f + (t - 4 * u) * f / (3 * u) : 2 * f + (t - 7 * u) * f / u;
     };
     auto mma = [&](int buf, int t) {
-        constexpr int pw[6] = {1, 0, 1, 0, 2, 0}, px[6] = {1, 1, 0, 2, 0, 0};
+        constexpr int pw[kProducts] = {2, 1, 0, 2, 1, 0, 1, 0}, px[kProducts] = {1, 2, 2, 0, 1, 1, 0, 0};
         const int p = t / (TM * TN), i = t / TN % TM, j = t % TN;
-        f32x16_t& acc = p == 5 ? hi[i][j] : lo[i][j];
+        f32x16_t& acc = p == kProducts - 1 ? hi[i][j] : lo[i][j];
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fw[buffer(buf, pw[p])][pw[p]][j]),
                                                       __builtin_bit_cast(bf16x8_t, fx[buffer(buf, px[p])][px[p]][i]), acc, 0, 0, 0);
     };
@@ -140,15 +150,17 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_f32_kernel(
     auto slice = [&](int kt, auto buf_c, auto set_c) {                  // register set of slice kt + 2
         constexpr int buf = decltype(buf_c)::value;
         wait_lds_barrier();
-#pragma unroll
-        for (int t = 0; t < MF; ++t) {
+        // (a loop over t has too much in it for `#pragma unroll`)
+        auto share = [&](auto t_c) {
+            constexpr int t = decltype(t_c)::value;
             mma(buf, t);
 #pragma unroll
             for (int r = reads_until(t); r < reads_until(t + 1); ++r) load_frag((kt + 1) & 1, buf ^ 1, r);
 #pragma unroll
             for (int q = t * 2 * UP / MF; q < (t + 1) * 2 * UP / MF; ++q) stash(kt + 2, set_c, q / 2, q % 2);
             __builtin_amdgcn_sched_barrier(0);
-        }
+        };
+        unrolled(share, std::make_integer_sequence<int, MF>{});
     };
     const integral_constant<int, 0> c0{};
     const integral_constant<int, 1> c1{};

@@ -4,7 +4,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# three parts carry all 24 bits and the products left out are below 3 * 2^-22 of each: what remains are fp32 sums, sqrt(K) 2^-24 of
+# three parts carry all 24 bits and the one product left out is below 2^-30 of each: what remains are fp32 sums, sqrt(K) 2^-24 of
 # the result where errors are independent (4e-6 at K = 4608); five times that, as for the fp32 instructions
 F32_TOL = 2e-5
 
@@ -42,6 +42,29 @@ def test_parts(M, N, K):
     ref = resid + gate * ref
     assert _rel(got, ref) < F32_TOL
     assert ((got - ref).norm(dim=1).max() / ref.norm(dim=1).mean()).item() < 5 * F32_TOL
+
+
+# 64 x 64 tiles and 128 x 128 ones; fewer and more slices than the loop takes per pass
+@pytest.mark.parametrize("M,N,K", [(300, 200, 32), (513, 1152, 1152), (3000, 1160, 352)])
+def test_few_terms(M, N, K):
+    """Sums that no averaging helps.  One non-zero per row: every result is one product and must be it, rounded once (2^-24; the seven
+    products below the leading one have sums of 2^-7 of it, each rounded: 2^-31; the ninth, left out, is below 2^-30).  A few
+    non-zeros: no further off than the fp32 instructions."""
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, _, _ = _data(M, N, K, seed=2)
+    bias.zero_()
+    g = torch.Generator(device="cuda").manual_seed(3)
+    one = torch.zeros_like(x)
+    at = torch.randint(0, K, (M, 1), generator=g, device="cuda")
+    one.scatter_(1, at, x.gather(1, at))
+    ref = one.double() @ w.double().T
+    err = (binding.op_linear_f32(one, w, bias).double() - ref).abs() / ref.abs().clamp_min(1e-300)
+    assert err.max().item() <= 2 ** -24 + 8 * 2 ** -31 + 2 ** -30
+    few = x * (torch.rand(M, K, generator=g, device="cuda") < 0.05)
+    few[:, K // 2:] = 0
+    ref = few.double() @ w.double().T
+    assert _rel(binding.op_linear_f32(few, w, bias), ref) <= 1.02 * _rel(binding.op_linear(few, w, bias, "fp32"), ref)
 
 
 def test_rows_do_not_depend_on_the_pack():
