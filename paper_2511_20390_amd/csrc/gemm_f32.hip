@@ -10,8 +10,11 @@
 // another, whose rounding is 2^-7 of that.  2-norm error against 64 bits, fp32 instructions -> here: normal X and W, K = 32 1.0e-7 ->
 // 4.2e-8, K = 96 1.8e-7 -> 5.2e-8, K = 1152 6.1e-7 -> 1.4e-7, K = 4608 1.2e-6 -> 2.9e-7; one non-zero per row 2.5e-8, both, and no element
 // further off than one rounding; 5 % non-zeros over half a row, K = 32 2.9e-8 -> 2.5e-8, K = 96 3.7e-8 -> 3.3e-8.
-// Values that are not finite have no such parts (inf - inf): they give a NaN, and a wavefront that finds one in its tile computes
-// the tile again with fp32 products.  Parts below the smallest bf16 (2^-133) are lost: full precision needs |v| >= 2^-110.
+// Values that are not finite have no such parts (inf - inf): they give a NaN.  And what is below the smallest bf16 (2^-133) has no
+// part: values below 2^-110 lose bits, K values at most K 2^-132 max(|x|, |w|) of a sum, which counts in small sums only.  A wavefront
+// that finds a sum that is not finite or below 2^-64 computes its tile again with fp32 products and takes those sums from there.  What is
+// left: a value below 2^-110 in a sum of 2^-64 and more, which needs values of some 2^42 / K beside it to be seen in 24 bits; and values
+// below 2^-133 where all of a sum consists of them, which are zero.
 //
 // A slice is 32 k.  Its fp32 values go through registers, two to four slices ahead, are cut there and stored to LDS as three planes
 // of 64-byte rows (16-byte chunks swizzled by (row / 4) % 4: neither the stores nor the fragment reads of 16 lanes share a bank; the
@@ -34,6 +37,7 @@ namespace {
 
 constexpr int kSlice = 32;                   // fp32 values per row and slice (kRowBytes of them)
 constexpr int kPlaneRow = kSlice * 2;        // bytes of a row of one plane
+constexpr float kSmall = 0x1p-64f;
 constexpr int kProducts = 8;                 // of the nine products of two times three parts
 constexpr int kWaves = 8;                    // 2 x 2 parts of the tile, each by two wavefronts: k-steps 0 and 1 of every slice
 
@@ -227,16 +231,19 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_f32_kernel(
             }
 
     // ---- epilogue
-    bool bad = false;
+    // Sums that need fp32 products: not finite, or so small that bits below the parts (2^-133 of a value) may count.  Each on its own:
+    // what a row is packed with has no part in it.
+    auto needs = [](float v) { return !(fabsf(v) >= kSmall && fabsf(v) < INFINITY) && v != 0.f; };
+    bool any = false;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) bad |= hi[i][j][e] != hi[i][j][e];
-    if (__builtin_expect(__any(bad), 0)) {
-        // something here is not finite: fp32 products of the same values (lane group 0 / 1 holds the two k of a product).  Rows past
-        // the end repeat the last one: they are not stored, and a product has its own row and column only.
+            for (int e = 0; e < 16; ++e) any |= needs(hi[i][j][e]);
+    if (__builtin_expect(__any(any), 0)) {
+        // (lane group 0 / 1 holds the two k of a product.)  Rows past the end repeat the last one: they are not stored, and a product has
+        // its own row and column only.
 #pragma unroll 1
         for (int i = 0; i < TM; ++i)
 #pragma unroll 1
@@ -257,7 +264,9 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_f32_kernel(
                 for (int a = 0; a < TM; ++a)
 #pragma unroll
                     for (int b = 0; b < TN; ++b)
-                        if (a == i && b == j) hi[a][b] = acc;
+                        if (a == i && b == j)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) hi[a][b][e] = needs(hi[a][b][e]) ? acc[e] : hi[a][b][e];
             }
     }
     float ln_scale[TM];                                                 // (used by the folded-LayerNorm epilogues only)

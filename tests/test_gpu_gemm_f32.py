@@ -90,6 +90,37 @@ def test_values_without_three_parts(M, N):
     assert ((out - ref).abs()[ok] <= 64 * 2 ** -24 * (x.abs() @ w.abs().T + bias.abs())[ok]).all()
 
 
+@pytest.mark.parametrize("M,N", [(100, 72), (3000, 1160)])
+def test_small_magnitudes(M, N):
+    """Values whose last bits are below the smallest bf16, down to fp32's own smallest: their small sums are rounded once (in steps of
+    2^-149 where fp32 has no smaller ones)."""
+    import torch
+    from paper_2511_20390_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K = 64
+    mant = lambda *s: (1 + torch.rand(*s, generator=g, device="cuda")).double()
+    x = torch.zeros(M, K, dtype=torch.float64, device="cuda")
+    at = torch.randint(0, K, (M, 1), generator=g, device="cuda")
+    x.scatter_(1, at, mant(M, 1) * 2.0 ** torch.arange(-126, -100, device="cuda", dtype=torch.float64).repeat(M)[:M, None])
+    for w_exp in (-20, 0, 30):
+        w = (mant(N, K) * 2.0 ** w_exp).float()
+        ref = x.float().double() @ w.double().T
+        out = binding.op_linear_f32(x.float(), w, torch.zeros(N, device="cuda")).double()
+        assert ((out - ref).abs() <= ref.abs() * 2 ** -24 + 2.0 ** -150).all(), w_exp
+
+
+def test_other_rows_keep_their_bits():
+    """One row whose sums are not finite or tiny sends its tile to the fp32 products; the rows beside it stay as they were."""
+    import torch
+    from paper_2511_20390_amd import binding
+    x, w, bias, _, _ = _data(200, 136, 96, seed=4)
+    ref = binding.op_linear_f32(x, w, bias)
+    x[70], x[131, 3] = 1e-36, float("nan")
+    out = binding.op_linear_f32(x, w, bias)
+    keep = [m for m in range(200) if m not in (70, 131)]
+    assert torch.equal(out[keep], ref[keep]) and out[131].isnan().all()
+
+
 def test_refused():
     import torch
     from paper_2511_20390_amd import binding
