@@ -325,10 +325,12 @@ bool linear_f32_covers(const float* X, const float* W, int32_t M, int32_t N, int
 }
 
 // Which tile: 128 x 128 takes half as many bytes from LDS per product, 64 x 64 gives few rows to more CUs (two or three share a
-// CU and then take 0.43 us per slice each).  Constants from launches back to back, us, width 1152 (QKV, out-projection, MLP-1, MLP-2),
-// fp32 instructions / 64 x 64 / 128 x 128:   256 rows 25 24 42 83 / 21 18 30 58 / 39 40 41 132
-//      512 rows 45 24 62 86 / 34 19 48 60 / 44 40 44 132      2048 rows 146 60 190 215 / 122 48 150 170 / 97 45 144 148
-//      12288 rows 805 290 922 1045 / 639 225 850 810 / 543 204 713 695
+// CU).  Constants from both tiles, launches back to back, at 17 values of M from 64 to 12288 and the four layers at widths 384, 768 and
+// 1152: the faster tile is chosen within 0.4 % everywhere (those fitted to six products at width 1152 alone chose tiles up to 26 %
+// slower, 0.6 % on average: 4096 x 1152 x 1152 114 us for 90).  us at width 1152 (QKV, out-projection, MLP-1, MLP-2), 64 x 64 /
+// 128 x 128; the fp32 instructions at the first:   256 rows 22 20 34 63 / 49 49 51 166 (25 24 42 83)
+//      512 rows 36 22 53 65 / 52 49 55 167 (45 24 62 86)     2048 rows 125 53 164 190 / 117 55 176 174 (146 60 190 215)
+//      12288 rows 717 250 953 931 / 650 245 850 841 (805 290 922 1045)
 // Both add in the same order: the result does not depend on the choice.
 int32_t launch_linear_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
                           float* out, float* resid, RowVec gate, hipStream_t s, int cu_share) {
@@ -336,7 +338,7 @@ int32_t launch_linear_f32(const float* X, const float* W, const float* bias, int
     const Args a{X, W, bias, M, N, K, out, resid, gate, s};
     const double cus = std::max(1, device_cus() / std::max(1, cu_share)), nk = K / kSlice;
     const auto rounds = [&](int b) { return std::ceil(static_cast<double>((M + b - 1) / b) * ((N + b - 1) / b) / cus); };
-    const double n64 = rounds(64), t64 = 4.0 + nk * (n64 <= 1.0 ? 0.385 : 0.43 * n64), t128 = rounds(128) * (8.5 + 0.88 * nk);
+    const double n64 = rounds(64), t64 = 4.4 + nk * (n64 <= 1.0 ? 0.526 : 0.499 * n64), t128 = rounds(128) * (7.5 + 1.455 * nk);
     return t64 <= t128 ? launch_tile<64, 64, 4>(a, epi) : launch_tile<128, 128, 2>(a, epi);
 }
 

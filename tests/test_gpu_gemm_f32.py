@@ -20,10 +20,12 @@ def _rel(a, b):
     return ((a.double() - b.double()).norm() / b.double().norm()).item()
 
 
-# one row, one column group, one to 144 slices (the loop takes four per pass), ragged rows and columns of both tiles (64 x 64 up to
-# some 500 rows, 128 x 128 above), 1150 columns: element-wise epilogue
+# one row, one column group, one to 144 slices (the loop takes four per pass), ragged rows and columns, 1150 and 4597 columns:
+# element-wise epilogue; the last four on 128 x 128 tiles (one round of them against four of 64 x 64, from eight slices on), the others on
+# 64 x 64
 @pytest.mark.parametrize("M,N,K", [(1, 8, 32), (65, 72, 64), (130, 200, 96), (63, 1152, 128), (64, 64, 160), (257, 1152, 4608),
-                                   (450, 1150, 384), (512, 4608, 1152), (600, 3464, 1152), (2050, 1160, 32), (3000, 4600, 224)])
+                                   (450, 1150, 384), (512, 4608, 1152), (600, 3464, 1152), (2050, 1160, 32), (3000, 4600, 224),
+                                   (770, 4600, 1152), (771, 4597, 288), (769, 4608, 320), (770, 4600, 352)])
 def test_parts(M, N, K):
     import torch
     from paper_2511_20390_amd import binding
@@ -75,29 +77,29 @@ def test_rows_do_not_depend_on_the_pack():
     assert torch.equal(binding.op_linear_f32(x[:70].contiguous(), w, bias), binding.op_linear_f32(x, w, bias)[:70])
 
 
-@pytest.mark.parametrize("M,N", [(100, 72), (3000, 1160)])
-def test_values_without_three_parts(M, N):
+# 64 x 64 tiles; 128 x 128 ones at K = 352
+@pytest.mark.parametrize("M,N,K", [(100, 72, 64), (3000, 1160, 64), (3000, 1160, 352)])
+def test_values_without_three_parts(M, N, K):
     """Infinities, NaN, magnitudes near both ends of fp32: what fp32 products give."""
     import torch
     from paper_2511_20390_amd import binding
-    x, w, bias, _, _ = _data(M, N, 64, seed=1)
+    x, w, bias, _, _ = _data(M, N, K, seed=1)
     x[3, 5], x[40, 7], x[70, 0], x[71, :], w[9, 1] = float("inf"), float("nan"), 3e38, 1e-42, float("-inf")
     out, ref = binding.op_linear_f32(x, w, bias), x @ w.T + bias
     assert torch.equal(out.isnan(), ref.isnan()) and torch.equal(out.isinf(), ref.isinf())
     assert torch.equal(out[ref.isinf()], ref[ref.isinf()])
     ok = ref.isfinite()
-    # 64 products: errors of 64 2^-24 of the largest partial sum at worst
-    assert ((out - ref).abs()[ok] <= 64 * 2 ** -24 * (x.abs() @ w.abs().T + bias.abs())[ok]).all()
+    # K products: errors of K 2^-24 of the largest partial sum at worst
+    assert ((out - ref).abs()[ok] <= K * 2 ** -24 * (x.abs() @ w.abs().T + bias.abs())[ok]).all()
 
 
-@pytest.mark.parametrize("M,N", [(100, 72), (3000, 1160)])
-def test_small_magnitudes(M, N):
+@pytest.mark.parametrize("M,N,K", [(100, 72, 64), (3000, 1160, 352)])
+def test_small_magnitudes(M, N, K):
     """Values whose last bits are below the smallest bf16, down to fp32's own smallest: their small sums are rounded once (in steps of
     2^-149 where fp32 has no smaller ones)."""
     import torch
     from paper_2511_20390_amd import binding
     g = torch.Generator(device="cuda").manual_seed(5)
-    K = 64
     mant = lambda *s: (1 + torch.rand(*s, generator=g, device="cuda")).double()
     x = torch.zeros(M, K, dtype=torch.float64, device="cuda")
     at = torch.randint(0, K, (M, 1), generator=g, device="cuda")
