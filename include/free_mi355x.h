@@ -182,8 +182,12 @@ int32_t free_dit_stream_choice(free_dit_t h, int32_t B);
  *   FREE_LN_FOLD_AUTO (initial state): folded when covered and the batch has at
  *     least 4096 token rows (its GEMMs use the two large tile shapes only),
  *     the separate LayerNorm kernel otherwise.
- *   FREE_LN_FOLD_OFF: always the separate kernel.  Outputs then do not depend on how many states a batch holds, bit for bit;
- *     otherwise they do not up to 4095 token rows (smaller batches may add their sums in another order than larger ones).
+ *   FREE_LN_FOLD_OFF: always the separate kernel.
+ * What a state is packed with changes no bit of its result: at every batch size
+ * with FREE_LN_FOLD_OFF and in models that are not covered; with
+ * FREE_LN_FOLD_AUTO in covered models among all batches below 4096 token rows.
+ * (From there on the LayerNorms are folded; below, the sums of such models may
+ * be added in another order than with FREE_LN_FOLD_OFF.)
  *   FREE_LN_FOLD_REQUIRE: always folded; free_dit_set_ln_fold returns
  *     FREE_ERR_SHAPE when the model is not covered - never a silent switch.
  * free_dit_ln_fold_active(h, B): 1 if a forward on B packed states would take

@@ -28,6 +28,26 @@ def test_alone_or_packed_same_bits(hidden, heads, lat_h, lat_w, B, mode):
     model.close()
 
 
+# 450 tokens are no multiple of 32, 576 columns none of 128; few heads and many keys, long K of a narrow layer, both of them
+@pytest.mark.parametrize("hidden,heads,lat_h,lat_w,B", [(384, 6, 36, 50, 10), (1152, 16, 36, 50, 10), (576, 8, 32, 34, 16)])
+def test_never_folded_same_bits_at_every_size(hidden, heads, lat_h, lat_w, B):
+    """Models whose LayerNorms are folded at no size: alone, in a pack of just under 4096 token rows and in one of more."""
+    import torch
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("small", hidden=hidden, heads=heads, mlp_hidden=4 * hidden, depth=2, lat_h=lat_h, lat_w=lat_w)
+    model = binding.FreeDit(cfg, pu.weights_for(cfg, "bf16", 15), "bf16")
+    assert (B - 1) * synth.n_tokens(cfg) < 4096 <= B * synth.n_tokens(cfg) and not model.ln_fold_active(B)
+    rng = np.random.default_rng(16)
+    x = pu.to_dev(rng.standard_normal((B, cfg["in_ch"], lat_h, lat_w)).astype(np.float32))
+    t, y = (pu.to_dev(rng.integers(0, n, B).astype(np.int32)) for n in (1000, cfg["num_classes"] + 1))
+    eps, feat = (v.clone() for v in model.dit_forward_packed(x, t, y, want_feat=True))
+    for n in (1, B - 1):
+        eps1, feat1 = model.dit_forward_packed(*(v[:n].contiguous() for v in (x, t, y)), want_feat=True)
+        assert torch.equal(eps1.reshape(-1), eps[:n].reshape(-1)), n
+        assert torch.equal(feat1.reshape(-1), feat.reshape(B, -1)[:n].reshape(-1)), n
+    model.close()
+
+
 @pytest.mark.parametrize("hidden,heads,depth", [(512, 8, 44), (1152, 16, 5), (2048, 16, 3)])
 def test_reading_weights_ahead_changes_no_bit(hidden, heads, depth):
     """Models whose weights do not stay in the caches have them read ahead by the LayerNorm and attention launches of small
