@@ -192,7 +192,8 @@ int32_t free_dit_stream_choice(free_dit_t h, int32_t B);
  *     FREE_ERR_SHAPE when the model is not covered - never a silent switch.
  * free_dit_ln_fold_active(h, B): 1 if a forward on B packed states would take
  * the folded path now, else 0.  The drafter's blocks always use the separate
- * kernel. */
+ * kernel, the switch does not change them, and what a drafter's state is packed
+ * with changes no bit of its result at any batch size. */
 #define FREE_LN_FOLD_OFF     0
 #define FREE_LN_FOLD_AUTO    1
 #define FREE_LN_FOLD_REQUIRE 2

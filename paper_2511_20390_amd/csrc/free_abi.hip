@@ -36,6 +36,7 @@ constexpr int kTuneSlots = 8;                 // batch sizes a handle remembers 
 constexpr int64_t kMinSplitRows = 2048;       // token rows per part below which the split does not pay
 // token rows from which the folded-LayerNorm path is taken by default: its residual updates run on the 256-column tiles only
 constexpr int64_t kMinFoldRows = 4096;
+static_assert(kMinFoldRows <= kMaxPartRows + 1, "a target's batches with cut sums must fit in the room for parts");
 // Weights of a block stack from which its LayerNorms read them ahead below kMinFoldRows rows: the line between 221 MB, where that
 // costs up to 1 % of the forward, and 234 MB, where it gains as much (the Infinity Cache holds 256 MB).
 constexpr int64_t kReadAheadBytes = 220ll << 20;
@@ -103,11 +104,11 @@ struct WsLayout {
 // floats per sample of the fold vectors: c1 of every block's QKV and MLP-1 rows, then c0 of the same
 int64_t fold_stride(const Dims& d) { return 2 * static_cast<int64_t>(d.depth) * (3 * d.D + d.F); }
 
-// Sums over the parts of K that a split linear layer (of that many inputs) leaves to the kernel behind it (ResidJoin): fewer than
-// kMinFoldRows rows.  (Larger batches, which use none, reserve as much: a workspace for some B serves every smaller one.)
+// Sums over the parts of K that a split linear layer (of that many inputs) leaves to the kernel behind it (ResidJoin): up to
+// kMaxPartRows rows.  (Larger batches, which use none, reserve as much: a workspace for some B serves every smaller one.)
 size_t split_bytes(const Dims& d, int32_t k, size_t rows) {
     if (d.mode != FREE_BF16 || !linear_split_covers(d.D, k)) return 0;
-    return kSplitParts * std::min(rows, static_cast<size_t>(kMinFoldRows - 1)) * d.D * 4;
+    return kSplitParts * std::min(rows, static_cast<size_t>(kMaxPartRows)) * d.D * 4;
 }
 
 WsLayout make_layout(const Dims& d, int32_t B) {
@@ -207,9 +208,13 @@ struct free_dit_s {
     // still agree bit for bit on either side of that line.  A model that is never folded has no such line, and with FREE_LN_FOLD_OFF
     // there is none: nothing is cut.  (Cut at every size such models would lose more than they gain: width 1152, 450 tokens 1920 ->
     // 2010 us for one state without, 9.72 -> 10.28 ms for 20 with; width 384 1.25 -> 1.38 ms for 22.)
-    bool few_rows_for(int64_t rows) const {
+    bool target_cuts(int64_t rows) const {
         return dims.mode == FREE_BF16 && ln_fold == FREE_LN_FOLD_AUTO && rows < kMinFoldRows && ln_fold_covers();
     }
+    // Whether the target's drafters cut theirs.  Their LayerNorms are never folded and the switch has no part in it: by the tokens of a
+    // state alone, where a drafting step of a guided chain (two samples) has few rows.  (A pack of more rows than that pays for it: one
+    // block at width 1152, 8 x 1024 rows 473 -> 520 us, 5 x 1024 330 -> 343; one sample gains 109 -> 98 us at 256 rows, 158 -> 151 at 1024.)
+    bool draft_cuts() const { return dims.mode == FREE_BF16 && 2ll * dims.ntok < kMinFoldRows; }
     bool ln_fold_for(int32_t B) const {
         if (ln_fold == FREE_LN_FOLD_OFF || !ln_fold_covers()) return false;
         return ln_fold == FREE_LN_FOLD_REQUIRE || static_cast<int64_t>(B) * dims.ntok >= kMinFoldRows;
@@ -259,7 +264,7 @@ int32_t model_linear(const Dims& d, const void* A, const void* W, const float* b
     return linear_dispatch(d, A, W, bias, M, N, K, epi, out, resid, gate, s, cu_share, ln);
 }
 
-// split_keys: the keys of a query over two wavefronts (bf16, few token rows)
+// split_keys: the keys of a query over two wavefronts (bf16)
 int32_t attention_dispatch(const Dims& d, const void* qkv, int32_t B, void* out, hipStream_t s, const Prefetch& pf, bool split_keys) {
     if (d.mode == FREE_BF16 && mfma_attention_supported(d.ntok, d.dh))
         return launch_attention_mfma(static_cast<const bf16_t*>(qkv), B, d.ntok, d.heads, d.dh,
@@ -289,7 +294,7 @@ struct ActBufs {
 // `nblk` adaLN-Zero blocks on samples [b0, b0 + nb) of a batch.  blkw holds 10 pointers per block
 // (B_* order); block l's six modulation vectors of sample b are mod[b * mod_rows + l * 6D ..].
 // cu_share: number of such stacks running side by side on different streams (tile choice of the GEMMs).
-// few: the batch has few token rows (few_rows_for): sums over the keys and over K may be cut where that fills the chip; part then
+// cut: sums over the keys and over K may be cut where that fills the chip (target_cuts, draft_cuts); part then
 // is room for the sums of split linear layers, [kSplitParts, B*ntok, D] fp32, and join what such a layer in front of the stack left.
 // chained: the stack runs again at once on the same weights (the steps of a drafting chain).
 // fold_ready (nullable): event after which fold->vec is complete; waited for on `s` before the first use.
@@ -304,7 +309,7 @@ struct FoldBufs {
 };
 int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const float* mod, int32_t mod_rows,
                         const ActBufs& a, int b0, int nb, hipStream_t s, Profiler* pf, int cu_share = 1,
-                        bool few = false, float* part = nullptr, ResidJoin join = ResidJoin{},
+                        bool cut = false, float* part = nullptr, ResidJoin join = ResidJoin{},
                         const FoldBufs* fold = nullptr, hipEvent_t fold_ready = nullptr, bool chained = false) {
     const size_t esz = d.mode == FREE_BF16 ? 2 : 4;
     const int32_t M = nb * d.ntok;
@@ -365,7 +370,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     // holds up to kMinFoldRows rows, from five tiles of keys on (6 heads, 450 and 1024 tokens: 1.035-1.045; 100 and 256 tokens 1.02-1.03,
     // left as it is), and the drafter's one or two samples.
     const int64_t places = 2 * device_cus();
-    const bool split_keys = few && ((d.ntok > 256 && d.heads * (kMinFoldRows / 64) <= places) || (chained && d.heads * ((2ll * d.ntok + 63) / 64) <= places));
+    const bool split_keys = cut && ((d.ntok > 256 && d.heads * (kMinFoldRows / 64) <= places) || (chained && d.heads * ((2ll * d.ntok + 63) / 64) <= places));
     const int64_t DD = static_cast<int64_t>(d.D) * d.D, DF = static_cast<int64_t>(d.D) * d.F;
     const int64_t stack_bytes = nblk * (10 * DD + 2 * DF) * static_cast<int64_t>(esz);
     const bool may_ahead = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;
@@ -381,7 +386,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         return p;
     };
-    const bool split_fc2 = few && linear_split_covers(d.D, d.F);
+    const bool split_fc2 = cut && linear_split_covers(d.D, d.F);
     for (int l = 0; l < nblk; ++l) {
         // x += gate1 * Proj(Attn(LN(x)(1+scale1)+shift1))
         if (fold && l > 0) {
@@ -516,7 +521,7 @@ int32_t forward_impl(free_dit_t h, const float* x, int32_t x_mod, const int32_t*
     const void* const* blkw = h->w.data() + 7;
     auto run_blocks = [&](int b0, int nb, hipStream_t st, int cu_share) -> int32_t {
         return run_block_stack(d, blkw, d.depth, mod, d.mod_rows, act, b0, nb, st, &h->prof, cu_share,
-                               h->few_rows_for(M), reinterpret_cast<float*>(ws + L.part), ResidJoin{}, folded ? &fb : nullptr, fold_ready);
+                               h->target_cuts(M), reinterpret_cast<float*>(ws + L.part), ResidJoin{}, folded ? &fb : nullptr, fold_ready);
     };
     // The samples of a packed batch are independent through all blocks, so the batch can be cut in two halves
     // or three thirds that run on as many streams forked from (and joined back into) the caller's stream: while
@@ -1213,8 +1218,8 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     const RowVec ones{dr->ones, 0, 1};
     const float* fuse_b = static_cast<const float*>(dr->w[1]);
     float* part = reinterpret_cast<float*>(ws + L.part);
-    const bool few = h->few_rows_for(M);
-    const bool split = few && linear_split_covers(d.D, 2 * d.D), left = split && linear_split_pays(rows, d.D, 2 * d.D, false);
+    const bool cut = h->draft_cuts();
+    const bool split = cut && linear_split_covers(d.D, 2 * d.D), left = split && linear_split_pays(rows, d.D, 2 * d.D, false);
     ResidJoin join;
     FREE_TRY(launch_draft_embed(x, x_mod, B, d.C, d.H, d.W, d.p, d.D, static_cast<const float*>(h->w[W_PATCH_W]),
                                 static_cast<const float*>(h->w[W_PATCH_B]), h->pos, f_prev, d.mode, fin, left ? nullptr : f_out, emb, s));
@@ -1226,7 +1231,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
         FREE_TRY(model_linear(d, fin, dr->w[0], fuse_b, rows, d.D, 2 * d.D, FREE_EPI_GATE_RESID, nullptr, f_out, ones, s));
     }
     const ActBufs act{f_out, ws + L.xn, ws + L.qkv, ws + L.att, ws + L.hmid};
-    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, few, part, join, nullptr, nullptr,
+    FREE_TRY(run_block_stack(d, dr->blkw(), dr->depth, mod, mod_stride, act, 0, B, s, &h->prof, 1, cut, part, join, nullptr, nullptr,
                              true));
     RowVec fsh{mod + static_cast<int64_t>(dr->depth) * 6 * d.D, mod_stride, d.ntok};
     RowVec fsc{mod + static_cast<int64_t>(dr->depth) * 6 * d.D + d.D, mod_stride, d.ntok};

@@ -105,6 +105,7 @@ struct LnFold {
 // update is left to the next kernel:
 //   x = gate (((part 0 + part 1) + part 2) + bias) + x        (x taken as zero with from_zero).
 constexpr int kSplitParts = 3;
+constexpr int32_t kMaxPartRows = 4095;     // rows of a layer whose parts may be left to the next kernel: what workspaces have room for
 struct ResidJoin {
     const float* part = nullptr;           // [kSplitParts, M, D]; nullptr: nothing to add
     const float* bias = nullptr;

@@ -585,6 +585,7 @@ const TileTime* best_split_tile(int32_t M, int32_t N, int32_t K, double* t_best)
 // launch of its own takes three more.  Second layer of the MLP at width 1152, one launch -> parts, and the LayerNorm behind it (us):
 // 256 rows 17 -> 8.4, 4.2 -> 6.2; 512 rows 16.6 -> 11.8, 6.0 -> 8.2; 2048 rows 36 -> 36, 5.6 -> 10.8 (not taken).
 bool linear_split_pays(int32_t M, int32_t N, int32_t K, bool own_launch) {
+    if (M > kMaxPartRows) return false;
     double t_split = 0.0, t_one = 0.0;
     best_split_tile(M, N, K, &t_split);
     choose(M, N, K, 2, FREE_EPI_GATE_RESID_SEG, true, 1, &t_one);

@@ -64,7 +64,11 @@ def test_drafter_embedding_edges(lat_h, lat_w, B, hidden, mode):
     target.close()
 
 
-@pytest.mark.parametrize("hidden,heads,lat_h,lat_w,B", [(1152, 16, 32, 32, 6), (768, 12, 30, 34, 5), (1536, 24, 20, 20, 3)])
+# few rows: parts; 1275 and 1536: one workgroup per tile, on tiles for few rows; 2800, 3840: on 160 x 128 and 192 x 128; 4352: more than
+# parts have room for.  450 tokens of few heads: the keys in parts at every size
+@pytest.mark.parametrize("hidden,heads,lat_h,lat_w,B", [(1152, 16, 32, 32, 6), (768, 12, 30, 34, 5), (1536, 24, 20, 20, 3),
+                                                        (384, 6, 36, 50, 10), (1152, 16, 32, 32, 15), (1536, 24, 20, 20, 28),
+                                                        (1152, 16, 32, 32, 17)])
 def test_drafter_alone_or_packed_same_bits(hidden, heads, lat_h, lat_w, B):
     """The fusion layer and the second layers of the MLPs sum K in parts, in one workgroup or in several with the parts added up by
     the LayerNorm behind (or, after the last block, by a launch of its own): which it is depends on the rows, the sums do not."""
@@ -84,6 +88,11 @@ def test_drafter_alone_or_packed_same_bits(hidden, heads, lat_h, lat_w, B):
     ref_eps, ref_feat = fo.drafter_forward(wd, w, dict(cfg, drafter_depth=2), *(v[1:2].cpu().numpy() for v in (x, f, t, y)))
     assert pu.rel_l2(eps1.cpu().numpy(), ref_eps) <= pu.DIT_REL_L2["bf16"]
     assert pu.rel_l2(feat1.cpu().numpy(), ref_feat) <= pu.DIT_REL_L2["bf16"]
+    # the target's LayerNorm switch is the target's alone
+    for mode in (binding.LN_FOLD_OFF, binding.LN_FOLD_REQUIRE if target.ln_fold_active(1 << 12) else binding.LN_FOLD_AUTO):
+        target.set_ln_fold(mode)
+        eps1, feat1 = drafter.drafter_forward(x, f, t, y)
+        assert torch.equal(eps1, eps) and torch.equal(feat1, feat), mode
     drafter.close()
     target.close()
 
