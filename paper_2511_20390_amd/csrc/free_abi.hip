@@ -319,6 +319,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     void* qkv_h = static_cast<char*>(a.qkv) + r0 * 3 * d.D * esz;
     void* att_h = static_cast<char*>(a.att) + r0 * d.D * esz;
     void* hmid_h = static_cast<char*>(a.hmid) + r0 * d.F * esz;
+    if (part) part += kSplitParts * r0 * d.D;             // (stacks side by side on several streams: room of their own)
     auto vec = [&](int l, int which) {
         RowVec r;
         r.base = mod + static_cast<int64_t>(b0) * mod_rows + static_cast<int64_t>(l) * 6 * d.D +

@@ -68,3 +68,23 @@ def test_reading_weights_ahead_changes_no_bit(hidden, heads, depth):
         assert torch.equal(eps1.reshape(-1), eps[lo:hi].reshape(-1)), lo
         assert torch.equal(feat1.reshape(-1), feat.reshape(17, -1)[lo:hi].reshape(-1)), lo
     model.close()
+
+
+def test_forced_streams_change_no_bit_of_small_batches():
+    """Below 4096 token rows the sums of the split layers go through one workspace region: with two or three streams forced such a
+    batch gives the bits of one stream."""
+    import torch
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("small", hidden=1152, heads=16, mlp_hidden=4608, depth=2, lat_h=32, lat_w=32)
+    model = binding.FreeDit(cfg, pu.weights_for(cfg, "bf16", 17), "bf16")
+    rng = np.random.default_rng(18)
+    for B in (2, 15):
+        x = pu.to_dev(rng.standard_normal((B, cfg["in_ch"], 32, 32)).astype(np.float32))
+        t, y = (pu.to_dev(rng.integers(0, n, B).astype(np.int32)) for n in (1000, cfg["num_classes"] + 1))
+        res = []
+        for n in (1, 2, 3):
+            model.set_streams(n)
+            res.append([v.clone() for v in model.dit_forward_packed(x, t, y, want_feat=True)])
+        for r in res[1:]:
+            assert torch.equal(r[0], res[0][0]) and torch.equal(r[1], res[0][1]), B
+    model.close()
