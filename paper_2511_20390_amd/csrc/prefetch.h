@@ -16,8 +16,9 @@ namespace freemi {
 // From some 1500 rows on QKV and MLP-1 run on tiles whose order gives every XCD all of the weights: what the read-ahead brings
 // then is in the Infinity Cache rather than in the right L2, and buys 6 to 9 % of the forward instead of 11 to 14 (2560 to 3840
 // against 256 to 1024 rows).  LayerNorm and attention each contribute: 4 and 8 % of those 11 to 14.
-// Eight loads of a thread are in flight together, from both matrices, and the share of a workgroup takes a 32-bit division per
-// matrix (a wait behind every load and four 64-bit divisions before: at 512 rows LayerNorm 6.15 -> 6.03, attention 12.0 -> 11.9 us).
+// A thread has two lines over both matrices (Prefetch::blocks), at most two of one and mostly no second round; its loads are in
+// flight together, and the share of a workgroup takes a 32-bit division per matrix (a wait behind every load and four 64-bit
+// divisions before: at 512 rows LayerNorm 6.15 -> 6.03, attention 12.0 -> 11.9 us).
 __device__ inline void prefetch_lines(const Prefetch& pf, int first) {
     const uint32_t xcd = blockIdx.x & 7, rank = (blockIdx.x - first) >> 3, n = (gridDim.x - first) >> 3;
     const char* base[2];
@@ -33,16 +34,16 @@ __device__ inline void prefetch_lines(const Prefetch& pf, int first) {
     }
     uint32_t acc = 0;
     while (at[0] < end[0] || at[1] < end[1]) {
-        uint32_t v[2][4];
+        uint32_t v[2][2];
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int k = 0; k < 4; ++k, at[m] += blockDim.x)
+            for (int k = 0; k < 2; ++k, at[m] += blockDim.x)
                 v[m][k] = at[m] < end[m] ? *reinterpret_cast<const uint32_t*>(base[m] + (static_cast<int64_t>(at[m]) << 7)) : 0u;
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) acc ^= v[m][k];
+            for (int k = 0; k < 2; ++k) acc ^= v[m][k];
     }
     asm volatile("" ::"v"(acc));                             // the loads are for the caches: keep them, drop the value
 }
