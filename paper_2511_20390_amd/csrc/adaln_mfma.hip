@@ -213,13 +213,8 @@ int32_t launch_adaln_mfma(const float* sc, int32_t B, int32_t D, const void* con
                                         adaln_mfma_kernel<false, true>, adaln_mfma_kernel<true, true>};
     const int which = 2 * f32 + exact;
     const kernel_t kernel = kernels[which];
-    static bool attr_set[4] = {false, false, false, false};
-    if (!attr_set[which]) {
-        if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024)))
-            return FREE_ERR_HIP;
-        attr_set[which] = true;
-    }
+    static LdsLimit limit[4];
+    if (!limit[which].allow(reinterpret_cast<const void*>(kernel), 150 * 1024)) return FREE_ERR_HIP;
     for (int b0 = 0; b0 < B; b0 += kBatch) {
         const int nb = (B - b0 < kBatch) ? B - b0 : kBatch;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, sc + static_cast<int64_t>(b0) * D,

@@ -1310,13 +1310,8 @@ int32_t launch_final_layer(const float* x, RowVec shift, RowVec scale, int32_t B
 #define FREE_FIN_CASE(WT, NV)                                                                                  \
     do {                                                                                                       \
         auto kern = final_layer_vec_kernel<WT, NV, true>;                                                      \
-        static bool attr_set = false;                                                                          \
-        if (stage && !attr_set) {                                                                              \
-            if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                               \
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, kMaxFinalLds)))        \
-                return FREE_ERR_HIP;                                                                           \
-            attr_set = true;                                                                                   \
-        }                                                                                                      \
+        static LdsLimit limit;                                                                                 \
+        if (stage && !limit.allow(reinterpret_cast<const void*>(kern), kMaxFinalLds)) return FREE_ERR_HIP;     \
         hipLaunchKernelGGL(kern, dim3(vblocks), dim3(kThreads), stage ? lds_bytes : 0, s, x, shift, scale, M,  \
                            gh, gw, p,                                                                          \
                            c_out, D, static_cast<const WT*>(w), bias, out);                                    \

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/free_mi355x.h"
 
 namespace freemi {
@@ -131,6 +133,24 @@ inline bool hip_ok(hipError_t e) {
     return true;
 }
 inline bool launch_ok() { return hip_ok(hipGetLastError()); }
+
+// More than 64 KB of dynamic LDS has to be allowed per kernel and device.  One object per kernel, asked in front of every launch, from
+// any thread.
+class LdsLimit {
+public:
+    bool allow(const void* kernel, size_t bytes) {
+        int dev = 0;
+        if (!hip_ok(hipGetDevice(&dev))) return false;
+        const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
+        if (allowed.load(std::memory_order_relaxed) & bit) return true;
+        if (!hip_ok(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes)))) return false;
+        allowed.fetch_or(bit, std::memory_order_relaxed);
+        return true;
+    }
+
+private:
+    std::atomic<uint64_t> allowed{0};
+};
 
 // ---- optional per-kernel timing (free_profile_begin / free_profile_end) --------
 // A Profiler belongs to a model handle.  While it is on, a ProfScope records a HIP event on the

@@ -289,13 +289,8 @@ int32_t launch_one(const Args& a) {
     const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN, total = tiles_m * tiles_n;
     const size_t lds = 2 * static_cast<size_t>(BM + BN) * 3 * kPlaneRow;
     auto kern = gemm_f32_kernel<BM, BN, SETS, EPI>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        static_cast<int>(lds))))
-            return FREE_ERR_HIP;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    if (!limit.allow(reinterpret_cast<const void*>(kern), lds)) return FREE_ERR_HIP;
     // the vector epilogue needs 16-byte aligned rows of out / resid / bias / gate
     auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     const bool vec = ((a.N & 7) == 0) && al16(a.bias) && al16(a.out) && al16(a.resid) && al16(a.gate.base) && ((a.gate.stride & 3) == 0);

@@ -296,13 +296,8 @@ int32_t launch_one(const T* X, const T* W, const float* bias, int32_t M, int32_t
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const size_t lds = 2 * static_cast<size_t>(BM + BN) * kRowBytes;
     auto kern = gemm_bf16_kernel<T, BM, BN, WGM, WGN, EPI, EVEN_K>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds))))
-            return FREE_ERR_HIP;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    if (!limit.allow(reinterpret_cast<const void*>(kern), lds)) return FREE_ERR_HIP;
     // the vector epilogue needs 16-byte aligned rows of out / resid / bias / gate
     auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     const bool vec = ((N & 7) == 0) && al16(bias) && al16(out) && al16(resid) && al16(gate.base) &&

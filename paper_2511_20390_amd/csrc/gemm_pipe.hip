@@ -335,13 +335,8 @@ int32_t launch_one(const Args& a, const LnFold& ln) {
     const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     const size_t lds = 2 * static_cast<size_t>(BM + BN) * kRowBytes;
     auto kern = gemm_pipe_kernel<BM, BN, WGM, WGN, EPI>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        static_cast<int>(lds))))
-            return FREE_ERR_HIP;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    if (!limit.allow(reinterpret_cast<const void*>(kern), lds)) return FREE_ERR_HIP;
     // the vector epilogue needs 16-byte aligned rows of out / resid / bias / gate
     auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     const bool vec = ((a.N & 7) == 0) && al16(a.bias) && al16(a.out) && al16(a.resid) && al16(a.gate.base) && ((a.gate.stride & 3) == 0);

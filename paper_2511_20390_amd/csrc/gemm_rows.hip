@@ -339,13 +339,8 @@ int32_t launch_one(const Args<T>& a) {
     const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     const size_t lds = S * static_cast<size_t>(BM + BN) * kRowBytes;
     auto kern = gemm_rows_kernel<T, BM, BN, WGM, WGN, S, EPI>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        static_cast<int>(lds))))
-            return FREE_ERR_HIP;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    if (!limit.allow(reinterpret_cast<const void*>(kern), lds)) return FREE_ERR_HIP;
     constexpr int kParts = EPI == FREE_EPI_PARTIAL ? kSplitParts : 1;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * kParts), dim3(WGM * WGN * 64), lds, a.s, a.X, a.W, a.bias, a.M, a.N, a.K, tiles_m,
                        tiles_n, a.out, a.resid, a.gate);

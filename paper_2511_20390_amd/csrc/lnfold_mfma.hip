@@ -181,13 +181,8 @@ int32_t launch_ln_fold(const float* mod, int32_t B, int32_t D, int32_t mod_strid
     const size_t lds = 2 * static_cast<size_t>(kBatch) * (static_cast<size_t>(D) * 2 + 16);
     const bool exact = D >= 64 * kChunk && (D / 32) % (2 * kChunk) == 0;
     auto kernel = exact ? ln_fold_kernel<true> : ln_fold_kernel<false>;
-    static bool attr_set[2] = {false, false};
-    if (!attr_set[exact]) {
-        if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))
-            return FREE_ERR_HIP;
-        attr_set[exact] = true;
-    }
+    static LdsLimit limit[2];
+    if (!limit[exact].allow(reinterpret_cast<const void*>(kernel), 160 * 1024)) return FREE_ERR_HIP;
     const int per_block = (rows_qkv + kSegRows - 1) / kSegRows + (rows_fc1 + kSegRows - 1) / kSegRows;
     for (int b0 = 0; b0 < B; b0 += kBatch) {
         const int nb = (B - b0 < kBatch) ? B - b0 : kBatch;
