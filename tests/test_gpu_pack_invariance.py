@@ -70,6 +70,25 @@ def test_reading_weights_ahead_changes_no_bit(hidden, heads, depth):
     model.close()
 
 
+def test_reading_weights_ahead_with_parts_changes_no_bit():
+    """The same in what small packs run by default: the LayerNorm that reads ahead also adds up the parts of the MLP's second layer (one
+    and two states: one and four wavefronts per workgroup), which one workgroup per tile adds in larger packs."""
+    import torch
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("small", hidden=1152, heads=16, mlp_hidden=4608, depth=5, lat_h=32, lat_w=32)
+    assert 5 * 18 * 1152 * 1152 * 2 >= 220 << 20 and 15 * synth.n_tokens(cfg) < 4096
+    model = binding.FreeDit(cfg, pu.weights_for(cfg, "bf16", 19), "bf16")
+    rng = np.random.default_rng(20)
+    x = pu.to_dev(rng.standard_normal((15, cfg["in_ch"], 32, 32)).astype(np.float32))
+    t, y = (pu.to_dev(rng.integers(0, n, 15).astype(np.int32)) for n in (1000, cfg["num_classes"] + 1))
+    eps, feat = (v.clone() for v in model.dit_forward_packed(x, t, y, want_feat=True))
+    for lo, hi in ((0, 1), (1, 3), (3, 6), (2, 14)):
+        eps1, feat1 = model.dit_forward_packed(*(v[lo:hi].contiguous() for v in (x, t, y)), want_feat=True)
+        assert torch.equal(eps1.reshape(-1), eps[lo:hi].reshape(-1)), lo
+        assert torch.equal(feat1.reshape(-1), feat.reshape(15, -1)[lo:hi].reshape(-1)), lo
+    model.close()
+
+
 def test_forced_streams_change_no_bit_of_small_batches():
     """Below 4096 token rows the sums of the split layers go through one workspace region: with two or three streams forced such a
     batch gives the bits of one stream."""
