@@ -366,12 +366,14 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     // drafting round of one block (48 MB) 1.01 at 256^2 and 512^2.
     // (fp32 GEMMs are bound by the matrix cores: no gain, 0.4 % lost on 2 x 256 tokens.)
     // Attention with the keys of a query over two wavefronts: twice the workgroups of half the work, faster while two of them per CU
-    // hold the launch, slower beyond (16 heads: 256 rows 1.03, 1024 rows 1.015, 2048 rows 0.985, 3840 rows 0.97 of the forward).  The
-    // choice may not depend on the number of samples, or a state alone and in a pack would differ: models of few heads, where that
-    // holds up to kMinFoldRows rows, from five tiles of keys on (6 heads, 450 and 1024 tokens: 1.035-1.045; 100 and 256 tokens 1.02-1.03,
-    // left as it is), and the drafter's one or two samples.
-    const int64_t places = 2 * device_cus();
-    const bool split_keys = cut && ((d.ntok > 256 && d.heads * (kMinFoldRows / 64) <= places) || (chained && d.heads * ((2ll * d.ntok + 63) / 64) <= places));
+    // hold the launch, slower beyond (forward, 12 blocks; workgroups with split keys, gain: 8 heads of 64, 1024 tokens 128 1.10, 384
+    // 1.03; 512 tokens 64 1.06, 448 1.01; 12 heads 576 0.97; 16 heads 256 1.04, 512 1.005, 768 0.98; 8 heads, 288 tokens 560 0.97;
+    // 6 heads, 576 tokens 54 1.06, 378 1.00; 288 tokens 30 1.035, 420 0.99; 128 and 16 per head as 64).  The choice may not depend on the
+    // number of samples, or a state alone and in a pack would differ: it is taken where the largest batch that is cut, or the two
+    // samples of a drafting step (16 heads: 1024 tokens 1.01, one sample 1.03; 1156 tokens 608 workgroups 0.97), fits.  A target's short
+    // sequences stay whole (256 tokens, 6 heads: 1.02 but 0.98 at 3840 rows): with FREE_LN_FOLD_AUTO and _OFF they give the same bits.
+    const int64_t places = 2 * device_cus(), most = chained ? 2 : (kMinFoldRows - 1) / d.ntok;
+    const bool split_keys = cut && (chained || d.ntok > 256) && most * ((d.ntok + 63) / 64) * d.heads <= places;
     const int64_t DD = static_cast<int64_t>(d.D) * d.D, DF = static_cast<int64_t>(d.D) * d.F;
     const int64_t stack_bytes = nblk * (10 * DD + 2 * DF) * static_cast<int64_t>(esz);
     const bool may_ahead = d.mode == FREE_BF16 && M < kMinFoldRows && cu_share == 1;

@@ -553,7 +553,8 @@ int32_t launch_linear_mfma(const bf16_t* X, const bf16_t* W, const float* bias, 
 
 // A part has at least twelve slices: below that a workgroup is all prologue and epilogue, and with one part less to wait for there
 // is little to gain (K = 1536 to 384 columns 8.6 -> 7.6 us at 2250 rows, which the LayerNorm behind gives back).  And an even number:
-// gemm_rows_kernel takes two per pass.
+// gemm_rows_kernel takes two per pass.  So K is a multiple of 384 from 2304 on: the second layer of four-fold MLPs at widths that are
+// multiples of 96 from 576 on; at width 1024 (64 slices) K stays in one.
 bool linear_split_covers(int32_t N, int32_t K) {
     return N % 8 == 0 && N <= 2048 && K % (kSplitParts * 2 * BK) == 0 && K >= kSplitParts * 12 * BK;
 }
@@ -579,6 +580,9 @@ const TileTime* best_split_tile(int32_t M, int32_t N, int32_t K, double* t_best)
 // The next kernel reads the parts and updates the residual stream, out of the caches at 8.5 TB/s, and takes a microsecond longer; a
 // launch of its own takes three more.  Second layer of the MLP at width 1152, one launch -> parts, and the LayerNorm behind it (us):
 // 256 rows 17 -> 8.4, 4.2 -> 6.2; 512 rows 16.6 -> 11.8, 6.0 -> 8.2; 2048 rows 36 -> 36, 5.6 -> 10.8 (not taken).
+// Where it does not pay one workgroup adds the same parts for the sake of equal bits alone, with a second set of accumulators.  Forward
+// of a target, K in one -> in parts, us: width 1152 1536 rows 3015 -> 3018, 2048 3591 -> 3622, 3072 4459 -> 4431, 3840 5063 -> 5070;
+// width 768 1536 905 -> 916, 2048 1007 -> 1018, 3072 1227 -> 1229 (256 rows 590 -> 536, 512 645 -> 621, 1024 729 -> 716).
 bool linear_split_pays(int32_t M, int32_t N, int32_t K, bool own_launch) {
     if (M > kMaxPartRows) return false;
     double t_split = 0.0, t_one = 0.0;
