@@ -475,7 +475,7 @@ int32_t free_linear_tile(int32_t M, int32_t N, int32_t Kdim, int32_t dtype, int3
  * qkv [B*N, 3*heads*dh] rows ordered q | k | v, out [B*N, heads*dh]; dh <= 128. */
 int32_t free_op_attention(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
                           int32_t dtype, void* out, void* stream);
-/* The same in bf16 as small batches run it (below 4096 token rows, few heads or the drafter): the keys of a query over two wavefronts,
+/* The same in bf16 as small batches of models of few heads and long sequences run it, and drafters: the keys of a query over two wavefronts,
  * whose partial results are added at the end.  dh 16, 64, 72 or 128 (FREE_ERR_SHAPE otherwise). */
 int32_t free_op_attention_split(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh, void* out, void* stream);
 /* out[m, :] = LayerNorm(x[m, :]) * (1 + scale[m / rows_per_sample, :]) + shift[...]

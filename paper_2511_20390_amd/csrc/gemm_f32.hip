@@ -22,8 +22,8 @@
 // pair.  Eight wavefronts: 2 x 2 parts of the tile, and of every slice one wavefront of a SIMD takes k-step 0, the other k-step 1 -
 // with four wavefronts, one per SIMD, the cutting and the products of a wavefront hardly overlap (512 x 1152 x 4608 on 64 x 64 tiles
 // six products: 76 us with four, 58 with eight; fp32 instructions 86).
-// What bounds it now: matrix and vector pipe and LDS, which overlap only in part (with six products each busy a third of the time on 64 x
-// 64 tiles at 512 rows, 0.35, 0.38, 0.35, to a half on 128 x 128 at 12288 rows, 0.59, 0.36, 0.30; the matrix pipe a third more now).
+// What bounds it now: the matrix pipe, 0.77 busy on 128 x 128 tiles at 12288 rows (vector pipe 0.37, LDS 0.29); on 64 x 64 tiles at 512
+// rows matrix pipe 0.49, vector pipe 0.41, LDS 0.37, which overlap only in part.
 #include <algorithm>
 #include <cmath>
 #include <utility>
