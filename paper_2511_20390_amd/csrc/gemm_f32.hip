@@ -1,7 +1,8 @@
 // fp32 GEMM of the dense projections (FREE_FP32): C[M,N] = X[M,K] . W[N,K]^T  (+bias, fused epilogue), K a multiple of 32.
 //
 // The fp32 matrix instructions run at 157 TFLOP/s, the bf16 ones at 2.5 PFLOP/s.  An fp32 value is the exact sum of three bf16
-// values (its 24 significant bits cut in three eights, v = h + m + l, each part the leading bits of what is left), so that
+// values (its 24 significant bits cut in three eights, v = h + m + l, each part the leading bits of what is left; the technique is that of
+// Henry, Tang and Heinecke, Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations, 2019), so that
 //     x w = xh wh + (xh wm + xm wh + xm wm + xh wl + xl wh + xm wl + xl wm) + xl wl
 // and the last product, below 2^-30 of the whole, is the only one left out: eight bf16 products, 256 cycles per 32 x 32 x 16 against
 // 512.  (Without xm wl and xl wm, up to 2^-21 of a product, sums of few terms were further off than those of the fp32 instructions:
