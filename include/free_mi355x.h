@@ -460,9 +460,9 @@ int32_t free_op_linear(const void* A, const void* W, const float* bias, int32_t 
 /* The same with fp32 operands and results as a FREE_FP32 model runs its linear layers: Kdim % 32 == 0, A and W 16-byte aligned
  * (FREE_ERR_SHAPE otherwise; such layers of a model run as free_op_linear does).  Every fp32 value is cut into three bf16 values
  * whose sum it is, and eight of the nine products of two values run on the bf16 matrix instructions with fp32 accumulation; the
- * ninth is below 2^-30 of the whole.  Sums of one term are off by one rounding, like free_op_linear's; the more terms, the closer to
- * the exact result than free_op_linear's.  Sums that are not finite or below 2^-64 are those of fp32
- * products.  In the others values below 2^-110 keep 2^-133, in sums of nothing but values below 2^-133 these count as zero. */
+ * ninth is below 2^-30 of the whole.  A sum of one term is off by one rounding, like free_op_linear's; the more terms, the closer to
+ * the exact result than free_op_linear's.  Sums that are not finite, or not zero and below 2^-64, are those of fp32 products.  Bits of a
+ * value below 2^-133 do not count in the others. */
 int32_t free_op_linear_f32(const float* A, const float* W, const float* bias, int32_t M, int32_t N, int32_t Kdim,
                            int32_t epilogue, float* out, float* resid, const float* gate, int32_t gate_stride,
                            int32_t rows_per_sample, void* stream);
