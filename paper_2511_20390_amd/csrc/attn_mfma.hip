@@ -54,7 +54,7 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) { return pack_bf16_pa
 // launch lasts as long as the chain of tiles in one wavefront; here every wavefront takes one 32-key block of each tile, and the
 // two partial results of a query (O^T, its reference maximum and sum) are added through LDS at the end.  A second K/V register set
 // instead of the third workgroup per CU, which such launches do not fill.  us per launch, KS = 1 -> 2: 16 heads of 72, 256 rows
-// 10.2 -> 8.2, 2 x 1024 rows 24.3 -> 21.7; 6 heads of 64, 5 x 450 rows 12.7 -> 10.8.
+// 8.0 -> 6.7, 2 x 1024 rows 23.9 -> 23.0; 6 heads of 64, 5 x 450 rows 11.5 -> 9.5.
 template <int DH, int QT, int KS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 72 && KS == 1 ? 3 : 2, DH <= 72 && KS == 1 ? 3 : 2))) void attn_mfma_kernel(const bf16_t* __restrict__ qkv, int32_t N,
                                                              int32_t heads, float scale_log2,
@@ -105,37 +105,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     const size_t row_bytes = static_cast<size_t>(3) * D * 2;
     const char* qkv_b = reinterpret_cast<const char*>(qkv);
 
-    // zero the pad chunks of K (d in [DH, 16*KSTEPS)) and the pad rows of V^T once
-    for (int i = tid; i < 2 * BKV * (KROW / 16); i += kThreads) {
-        const int c = i % (KROW / 16);
-        if (c >= DCH) *reinterpret_cast<u32x4_t*>(sKbuf + (i / (KROW / 16)) * KROW + c * 16) = u32x4_t{0, 0, 0, 0};
-    }
-    // ... except, when the head dimension leaves pad columns (kSumByMfma), column DH of V, which is one
-    // (bf16 0x3F80) for every key: row DH of O^T then accumulates the sum of the probabilities in the matrix
-    // pipe, rescaled together with O^T, instead of one VALU addition per score
-    for (int i = tid; i < 2 * BKV * (VROW / 16); i += kThreads) {
-        const int c = i % (VROW / 16);
-        if (c >= DCH)
-            *reinterpret_cast<u32x4_t*>(sVbuf + (i / (VROW / 16)) * VROW + c * 16) =
-                u32x4_t{(kSumByMfma && c == DCH) ? 0x3F80u : 0u, 0, 0, 0};
-    }
-
-    // Q^T fragments (B operand of S^T): lane holds query column l32, k-slots d = 16 ks + 8 g + j
-    bf16x8_t qf[QT][KSTEPS];
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        int q = q_base + qt * 32 + l32;
-        if (q >= N) q = N - 1;
-        const char* src = qkv_b + (row0 + q) * row_bytes + static_cast<size_t>(h) * DH * 2;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int c = 2 * ks + g;
-            u32x4_t v = {0, 0, 0, 0};
-            if (c < DCH) v = *reinterpret_cast<const u32x4_t*>(src + c * 16);
-            qf[qt][ks] = __builtin_bit_cast(bf16x8_t, v);
-        }
-    }
-
+    // The first K/V tile and Q are requested before anything else: a launch of one workgroup per CU is a chain of waits, and the
+    // larger ones begin every round of workgroups with it.  Same bits; us per launch with the pads written first -> now: 16 heads
+    // of 72, 2 x 256 rows 9.3 -> 8.2, 8 x 256 11.0 -> 10.0, 12 x 1024 94 -> 85; 6 heads of 64, 5 x 450 12.6 -> 11.5; 2 of 128, 256 rows
+    // 11.8 -> 10.1.
+    //
     // global -> register staging of one K/V tile: thread chunk idx = tid + 256 i -> key row idx / DCH,
     // 16-byte chunk idx % DCH of that row, for K and for V alike (lanes walk the chunks of a row).
     // Buffer loads over the rows of this sample: keys past N read as zero (on gfx950 the scalar offset
@@ -163,6 +137,41 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
             }
         }
     };
+    const std::integral_constant<int, 0> set0{};
+    const std::integral_constant<int, kSets - 1> set1{};
+    fetch(0, set0);
+
+    // Q^T fragments (B operand of S^T): lane holds query column l32, k-slots d = 16 ks + 8 g + j
+    bf16x8_t qf[QT][KSTEPS];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+        int q = q_base + qt * 32 + l32;
+        if (q >= N) q = N - 1;
+        const char* src = qkv_b + (row0 + q) * row_bytes + static_cast<size_t>(h) * DH * 2;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            const int c = 2 * ks + g;
+            u32x4_t v = {0, 0, 0, 0};
+            if (c < DCH) v = *reinterpret_cast<const u32x4_t*>(src + c * 16);
+            qf[qt][ks] = __builtin_bit_cast(bf16x8_t, v);
+        }
+    }
+
+    // pad chunks that the fragment reads touch, written while the first loads are under way: of K (d in [DH, 16 KSTEPS)) zero; of V
+    // (columns [DH, 32 DT)) zero, except, when the head dimension leaves pad columns (kSumByMfma), column DH, which is one
+    // (bf16 0x3F80) for every key: row DH of O^T then accumulates the sum of the probabilities in the matrix
+    // pipe, rescaled together with O^T, instead of one VALU addition per score
+    constexpr int kPadK = 2 * KSTEPS - DCH, kPadV = 4 * DT - DCH;
+    if constexpr (kPadK > 0) {
+        for (int i = tid; i < 2 * BKV * kPadK; i += kThreads)
+            *reinterpret_cast<u32x4_t*>(sKbuf + (i / kPadK) * KROW + (DCH + i % kPadK) * 16) = u32x4_t{0, 0, 0, 0};
+    }
+    if constexpr (kPadV > 0) {
+        for (int i = tid; i < 2 * BKV * kPadV; i += kThreads)
+            *reinterpret_cast<u32x4_t*>(sVbuf + (i / kPadV) * VROW + (DCH + i % kPadV) * 16) =
+                u32x4_t{(kSumByMfma && i % kPadV == 0) ? 0x3F80u : 0u, 0, 0, 0};
+    }
+
     auto stash = [&](int stage, auto set) {
         constexpr int S = decltype(set)::value;
         char* sK = sKbuf + stage * kKBytes;
@@ -204,9 +213,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
     for (int qt = 0; qt < QT; ++qt) { m_ref[qt] = -INFINITY; l_run[qt] = 0.f; }
 
     const int ntiles = (N + BKV - 1) / BKV;
-    const std::integral_constant<int, 0> set0{};
-    const std::integral_constant<int, kSets - 1> set1{};
-    fetch(0, set0);
     stash(0, set0);
     if (ntiles > 1) fetch(1, set1);
     if (kSets == 2 && ntiles > 2) fetch(2, set0);
