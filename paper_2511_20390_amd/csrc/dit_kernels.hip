@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "free_internal.h"
+#include "lanes.h"
 #include "prefetch.h"
 
 namespace freemi {
@@ -17,12 +18,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxFinalLds = 160 * 1024;          // LDS of one CU: the final projection matrix must fit
-
-__device__ inline float wave_sum_f(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 // ---------------------------------------------------------------------------
 // Conditioning: c = W2 silu(W1 temb(t) + b1) + b2 + table[y];  sc = silu(c)
@@ -55,7 +50,7 @@ __global__ __launch_bounds__(kThreads) void small_linear_kernel(
     const float* w = W + static_cast<int64_t>(j) * K;
     float acc = 0.f;
     for (int i = lane; i < K; i += 64) acc = fmaf(x[i], w[i], acc);
-    acc = wave_sum_f(acc);
+    acc = wave_sum(acc);
     if (lane == 0) {
         float v = acc + bias[j];
         if (table) v += table[static_cast<int64_t>(row[b]) * N + j];
@@ -94,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void small_linear_rows_kernel(
         float mine = 0.f;
 #pragma unroll
         for (int q = 0; q < kSamples; ++q) {
-            const float t = wave_sum_f(acc[q]);
+            const float t = wave_sum(acc[q]);
             if (lane == q) mine = t;
         }
         const int b = b0 + lane;
@@ -180,7 +175,7 @@ __global__ __launch_bounds__(kThreads) void adaln_kernel(
 #pragma unroll
             for (int b = 0; b < kAdaBatch; ++b) {
                 if (b < nb) {
-                    const float v = wave_sum_f(acc[b]);
+                    const float v = wave_sum(acc[b]);
                     if (lane == 0) mod[static_cast<int64_t>(b0 + b) * total_rows + r] = v + bias;
                 }
             }
@@ -419,13 +414,13 @@ __global__ __launch_bounds__(kThreads) void ln_modulate_kernel(
     const float* xr = x + row * D;
     float s = 0.f;
     for (int i = lane; i < D; i += 64) s += xr[i];
-    const float mean = wave_sum_f(s) / static_cast<float>(D);
+    const float mean = wave_sum(s) / static_cast<float>(D);
     float q = 0.f;
     for (int i = lane; i < D; i += 64) {
         const float c = xr[i] - mean;
         q = fmaf(c, c, q);
     }
-    const float rstd = rsqrtf(wave_sum_f(q) / static_cast<float>(D) + kLnEps);
+    const float rstd = rsqrtf(wave_sum(q) / static_cast<float>(D) + kLnEps);
     const float* sh = shift.base + (row / shift.rows_per_sample) * shift.stride;
     const float* sc = scale.base + (row / scale.rows_per_sample) * scale.stride;
     OT* o = out + row * D;
@@ -515,7 +510,7 @@ __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, co
         float s = 0.f;
 #pragma unroll
         for (int k = 0; k < NV; ++k) s += (xv[k].x + xv[k].y) + (xv[k].z + xv[k].w);
-        const float mean = wave_sum_f(s) / static_cast<float>(D);
+        const float mean = wave_sum(s) / static_cast<float>(D);
         float q = 0.f;
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
@@ -524,7 +519,7 @@ __device__ __forceinline__ void ln_modulate_rows(const float* __restrict__ x, co
                 q += (a * a + b * b) + (c * c + d * d);
             }
         }
-        const float rstd = rsqrtf(wave_sum_f(q) / static_cast<float>(D) + kLnEps);
+        const float rstd = rsqrtf(wave_sum(q) / static_cast<float>(D) + kLnEps);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const int v = lane + 64 * k;
@@ -750,13 +745,13 @@ __global__ __launch_bounds__(kThreads) void final_layer_kernel(
     const float* xr = x + row * D;
     float s = 0.f;
     for (int i = lane; i < D; i += 64) s += xr[i];
-    const float mean = wave_sum_f(s) / static_cast<float>(D);
+    const float mean = wave_sum(s) / static_cast<float>(D);
     float q = 0.f;
     for (int i = lane; i < D; i += 64) {
         const float c = xr[i] - mean;
         q = fmaf(c, c, q);
     }
-    const float rstd = rsqrtf(wave_sum_f(q) / static_cast<float>(D) + kLnEps);
+    const float rstd = rsqrtf(wave_sum(q) / static_cast<float>(D) + kLnEps);
     const float* sh = shift.base + (row / shift.rows_per_sample) * shift.stride;
     const float* sc = scale.base + (row / scale.rows_per_sample) * scale.stride;
     const int ntok = gh * gw;
@@ -776,7 +771,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_kernel(
         }
 #pragma unroll
         for (int k = 0; k < OC; ++k) {
-            const float v = wave_sum_f(acc[k]);
+            const float v = wave_sum(acc[k]);
             const int o = o0 + k;
             if (lane == 0 && o < P) {
                 const int c = o % c_out, pq = (o / c_out) % p, ph = o / (c_out * p);
@@ -807,7 +802,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_row_kernel(
         xv[k] = (v < nvec) ? xr[v] : make_float4(0.f, 0.f, 0.f, 0.f);
         s += (xv[k].x + xv[k].y) + (xv[k].z + xv[k].w);
     }
-    const float mean = wave_sum_f(s) / static_cast<float>(D);
+    const float mean = wave_sum(s) / static_cast<float>(D);
     float q = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -816,7 +811,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_row_kernel(
             q += (a * a + b * b) + (c * c + d * d);
         }
     }
-    const float rstd = rsqrtf(wave_sum_f(q) / static_cast<float>(D) + kLnEps);
+    const float rstd = rsqrtf(wave_sum(q) / static_cast<float>(D) + kLnEps);
     const float4* sh = reinterpret_cast<const float4*>(shift.base + (row / shift.rows_per_sample) * shift.stride);
     const float4* sc = reinterpret_cast<const float4*>(scale.base + (row / scale.rows_per_sample) * scale.stride);
 #pragma unroll
@@ -861,7 +856,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_row_kernel(
                 acc = fmaf(xv[k].w, w3, acc);
             }
         }
-        acc = wave_sum_f(acc);
+        acc = wave_sum(acc);
         if (lane == 0) {
             const int c = o % c_out, pq = (o / c_out) % p, ph = o / (c_out * p);
             out[((static_cast<int64_t>(b) * c_out + c) * H + gi * p + ph) * Wd + gj * p + pq] = acc + bias[o];
@@ -909,7 +904,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_vec_kernel(
         xv[k] = (v < nvec) ? xr[v] : make_float4(0.f, 0.f, 0.f, 0.f);
         s += (xv[k].x + xv[k].y) + (xv[k].z + xv[k].w);
     }
-    const float mean = wave_sum_f(s) / static_cast<float>(D);
+    const float mean = wave_sum(s) / static_cast<float>(D);
     float q = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -918,7 +913,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_vec_kernel(
             q += (a * a + b * b) + (c * c + d * d);
         }
     }
-    const float rstd = rsqrtf(wave_sum_f(q) / static_cast<float>(D) + kLnEps);
+    const float rstd = rsqrtf(wave_sum(q) / static_cast<float>(D) + kLnEps);
     const float4* sh = reinterpret_cast<const float4*>(shift.base + (row / shift.rows_per_sample) * shift.stride);
     const float4* sc = reinterpret_cast<const float4*>(scale.base + (row / scale.rows_per_sample) * scale.stride);
 #pragma unroll

@@ -15,6 +15,7 @@
 // token row and reduced each of the 32 outputs across the wavefront separately: 120 us at 12288
 // rows against 10 us for reading the rows once.
 #include "free_internal.h"
+#include "lanes.h"
 
 namespace freemi {
 
@@ -48,8 +49,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
     }
     // a row lives in the four lanes l16 + 16 lq of each of the four wavefronts
     auto row_total = [&](float v, int slot) {
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
+        v = add_lane_xor<32>(add_lane_xor<16>(v));
         if (lq == 0) red[slot][wave][l16] = v;
         __syncthreads();
         return (red[slot][0][l16] + red[slot][1][l16]) + (red[slot][2][l16] + red[slot][3][l16]);

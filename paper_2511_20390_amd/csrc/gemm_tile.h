@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "free_internal.h"
+#include "lanes.h"
 
 namespace freemi {
 
@@ -283,20 +284,20 @@ __device__ __forceinline__ void write_tile(const f32x16_t (&acc)[TM][TN], int gm
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         const float keep = b3 ? ps[8 + k] : ps[k], give = b3 ? ps[k] : ps[8 + k];
-                        w8[k] = keep + __shfl_xor(give, 8, 64);
+                        w8[k] = keep + lane_xor<8>(give);
                     }
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const float keep = b2 ? w8[4 + k] : w8[k], give = b2 ? w8[k] : w8[4 + k];
-                        w4[k] = keep + __shfl_xor(give, 4, 64);
+                        w4[k] = keep + lane_xor<4>(give);
                     }
 #pragma unroll
                     for (int k = 0; k < 2; ++k) {
                         const float keep = b1 ? w4[2 + k] : w4[k], give = b1 ? w4[k] : w4[2 + k];
-                        w2[k] = keep + __shfl_xor(give, 2, 64);
+                        w2[k] = keep + lane_xor<2>(give);
                     }
                     const float keep = b0 ? w2[1] : w2[0], give = b0 ? w2[0] : w2[1];
-                    const float total = keep + __shfl_xor(give, 1, 64);
+                    const float total = keep + lane_xor<1>(give);
                     const int k = lane & 15;                       // = 2 q + (0: sum, 1: sum of squares)
                     row_sums[(i * 32 + 4 * (k >> 1) + (lane >> 4)) * row_sums_stride + (k & 1)] = total;
                 }

@@ -28,6 +28,7 @@
 #include <mutex>
 
 #include "free_internal.h"
+#include "lanes.h"
 
 // Scratch memory of spec_verify_static, the entry point for callers that cannot allocate: the partial sums of
 // the streaming launch.  One copy per GPU the library runs on, held until the process ends.  In host code
@@ -74,12 +75,6 @@ __device__ inline const float* draft_ptr(const float* x_draft, const float* x_la
         return (k < K - 1) ? x_draft + static_cast<int64_t>(k + 1) * d : x_last;
     }
     return x_draft + pair * d;
-}
-
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
 }
 
 __device__ inline void accum(double& s2, double& s3, float m, float mh, float xh) {
