@@ -13,11 +13,20 @@
 // The contraction over the head dim uses 16-byte fragments like the fp32 GEMM: lane group g reads
 // chunk 2 j + g of its K row (and holds the same chunks of its Q row in registers); element e of
 // the chunk pair (2 j, 2 j + 1) is one 32x32x2 product.
-// One workgroup = 4 wavefronts x 32 queries; key tiles of 32; the K/V tile t+1 is in flight from
-// global memory in registers while tile t is multiplied.
+// One workgroup = 32 queries of one head; its four wavefronts take the key tiles (32 keys) t = wave, wave + 4, ... with an LDS tile
+// and an online softmax of their own - no barrier in the loop - and their maxima, sums and O^T are put together at the end in
+// wavefront order, whatever the batch.  (Head dim 128 has no LDS for that with two workgroups per CU: four query blocks that share the
+// tiles.)  What bounds it: a key tile is 36 + 32 products of 64 cycles at head dim 72, so that a wavefront with all 256 keys of a state
+// is a chain of 15 us, and such a state has 8 x heads query blocks, on 1024 SIMDs; with many samples the matrix pipe.  us per launch,
+// all keys in each wavefront, the third 32-row tile of O^T at head dim 72 in products too -> here: 16 heads of 72, 2 x 256 tokens
+// 31.3 -> 11.5, 600 68.8 -> 34, 1024 115 -> 56, 16 x 256 58.0 -> 59.5, 12 x 1024 620 -> 592; 12 heads of 64, 2 x 256 24.2 -> 9.4,
+// 12 x 1024 349 -> 331; 8 heads of 128, 8 x 1024 335 -> 289.  2-norm error against 64 bits 4.1e-7 -> 3.4e-7 (256 tokens), 6.6e-7 ->
+// 4.2e-7 (1024).
+#include <algorithm>
 #include <cmath>
 
 #include "free_internal.h"
+#include "lanes.h"
 
 namespace freemi {
 
@@ -26,32 +35,55 @@ namespace {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kThreads = 256;
+constexpr int kWaves = 4, kThreads = kWaves * 64;
+constexpr int BQ = 32;                    // queries per workgroup
 constexpr int BKV = 32;                   // keys per tile
 
-template <int DH>
-__global__ __launch_bounds__(kThreads) void attn_f32_mfma_kernel(const float* __restrict__ qkv, int32_t N,
+// KS: wavefronts that share the keys of a query block, 4 (an LDS tile each) or 1 (four query blocks, one tile and a barrier).
+template <int DH, int KS>
+struct Tile {
+    static constexpr int NC = DH / 4;            // 16-byte chunks per row
+    static constexpr int NP = DH / 8;            // chunk pairs: groups of four 32x32x2 products
+    static constexpr int kRest = DH > 32 && DH % 32 <= 8 ? DH % 32 : 0;   // last columns of O, on the vector ALU
+    static constexpr int DT = (DH - kRest + 31) / 32;         // 32-row tiles of O^T
+    static constexpr int KP = DH + 4;            // K row pitch in floats: an odd number of chunks (conflict-free b128 reads)
+    static constexpr int VP = (DH % 16 == 8) ? DH : DH + 8;   // V row pitch = 8 mod 16: rows 4 apart land on the other 32 banks
+    static constexpr int kKeys = BKV * (KP + VP) + 32 * DT;   // floats per wavefront; the pad rows of O^T read past a row's end
+    static constexpr int kSums = KS > 1 ? 32 * DH : 0;        // floats of O^T
+    static constexpr int kWaveFloats = kKeys > kSums ? kKeys : kSums;
+    static constexpr size_t kLds = sizeof(float) * KS * (kWaveFloats + (KS > 1 ? 2 * BQ : 0));
+};
+
+template <int DH, int KS>
+__global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float* __restrict__ qkv, int32_t N,
                                                                  int32_t heads, float scale_log2,
                                                                  float* __restrict__ out) {
     static_assert(DH % 8 == 0 && DH <= 128, "whole chunk pairs");
-    constexpr int NC = DH / 4;            // 16-byte chunks per row
-    constexpr int NP = DH / 8;            // chunk pairs: groups of four 32x32x2 products
-    constexpr int DT = (DH + 31) / 32;    // 32-row tiles of O^T
-    constexpr int KP = DH + 4;            // K row pitch in floats: an odd number of chunks (conflict-free b128 reads)
-    constexpr int VP = (DH % 16 == 8) ? DH : DH + 8;   // V row pitch = 8 mod 16: rows 4 apart land on the other 32 banks
-    constexpr int NLD = (BKV * NC + kThreads - 1) / kThreads;
-    __shared__ __attribute__((aligned(16))) float sK[BKV * KP];
-    __shared__ __attribute__((aligned(16))) float sV[BKV * VP + 32 * DT];   // the pad rows of O^T read past a row's end
+    static_assert(KS == 1 || KS == kWaves, "whole workgroups");
+    using L = Tile<DH, KS>;
+    constexpr int NC = L::NC, NP = L::NP, DT = L::DT, KP = L::KP, VP = L::VP, kRest = L::kRest;
+    constexpr int kGroup = kThreads / KS;            // threads that fill a tile
+    constexpr int NLD = BKV * NC / kGroup;           // chunks per thread of a K (and a V) tile
+    constexpr int kPieces = NC / 8, kRows = kGroup / 8, kWhole = BKV / kRows * kPieces;    // 128-byte pieces of a row; passes of them
+    constexpr int kTail = NC % 8 ? NC % 8 : 8;       // chunks behind the last piece
+    static_assert(BKV * NC % kGroup == 0 && kGroup % kTail == 0 && kRest % 4 == 0, "whole passes");
+    extern __shared__ __attribute__((aligned(16))) float lds[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, g = lane >> 5;
-    const int nq = (N + 127) / 128;
-    const int pair_idx = blockIdx.x / nq, q_tile = blockIdx.x % nq;
+    constexpr int kQueries = BQ * kWaves / KS;
+    const int nq = (N + kQueries - 1) / kQueries, group = KS > 1 ? wave : 0, in_group = KS > 1 ? lane : tid;
+    // all query tiles of one (sample, head) on one XCD, back to back (attn_mfma.hip)
+    const int id = blockIdx.x;
+    const bool by_xcd = gridDim.x / nq % 8 == 0;
+    const int pair_idx = by_xcd ? (id & 7) + 8 * (id / (8 * nq)) : id / nq, q_tile = by_xcd ? (id >> 3) % nq : id % nq;
     const int h = pair_idx % heads, b = pair_idx / heads;
     const int D = heads * DH;
     const int64_t row0 = static_cast<int64_t>(b) * N;
     const int64_t row_stride = static_cast<int64_t>(3) * D;       // floats
-    const int q_base = q_tile * 128 + wave * 32;
+    const int q_base = q_tile * kQueries + (KS > 1 ? 0 : wave * BQ);
+    float* const sK = lds + group * L::kWaveFloats;
+    float* const sV = sK + BKV * KP;
 
     // Q fragments: lane holds query column l32, chunks 2 j + g
     f32x4_t qf[NP];
@@ -63,32 +95,34 @@ __global__ __launch_bounds__(kThreads) void attn_f32_mfma_kernel(const float* __
         for (int j = 0; j < NP; ++j) qf[j] = *reinterpret_cast<const f32x4_t*>(src + 4 * (2 * j + g));
     }
 
-    // staging of one K/V tile: chunk idx = tid + 256 i -> key row idx / NC, chunk idx % NC (rows past N are clamped:
+    // staging of a K or V tile: whole 128-byte pieces of kRows rows per pass, then what is left of the rows (rows past N read as zero:
     // their scores are masked, and their probabilities are zero)
-    f32x4_t kreg[NLD], vreg[NLD];
-    auto fetch = [&](int t) {
+    const int row_bytes = 12 * D;
+    const int piece = (in_group >> 3) * row_bytes + (in_group & 7) * 16, tail = (in_group / kTail) * row_bytes + (kPieces * 8 + in_group % kTail) * 16;
+    auto fetch = [&](f32x4_t (&reg)[NLD], int t, int which) {         // 1: K, 2: V
+        const int left = N - t * BKV;
+        const float* base = qkv + (row0 + t * BKV) * row_stride + which * D + h * DH;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0,
+            (std::min(left, BKV) - 1) * row_bytes + DH * 4, 0x00020000);
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
-            const int idx = tid + kThreads * i;
-            if (idx < BKV * NC) {
-                int kv = t * BKV + idx / NC;
-                if (kv >= N) kv = N - 1;
-                const float* src = qkv + (row0 + kv) * row_stride + h * DH + (idx % NC) * 4;
-                kreg[i] = *reinterpret_cast<const f32x4_t*>(src + D);
-                vreg[i] = *reinterpret_cast<const f32x4_t*>(src + 2 * D);
-            }
+            const bool whole = i < kWhole;
+            const int soff = whole ? i / std::max(kPieces, 1) * kRows * row_bytes + i % std::max(kPieces, 1) * 128 : (i - kWhole) * (kGroup / kTail) * row_bytes;
+            reg[i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, whole ? piece : tail, soff, 0));
         }
     };
-    auto stash = [&]() {
+    // With KS > 1 a wavefront's LDS operations keep their order, and the fences keep the compiler's.  With KS == 1 the barrier behind
+    // the K tile says that every wavefront is done with the V tile before, the one behind the V tile the same of the K tile.
+    auto stash = [&](const f32x4_t (&reg)[NLD], float* dst, int pitch) {
+        if constexpr (KS > 1) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
-            const int idx = tid + kThreads * i;
-            if (idx < BKV * NC) {
-                const int r = idx / NC, c = idx % NC;
-                *reinterpret_cast<f32x4_t*>(sK + r * KP + c * 4) = kreg[i];
-                *reinterpret_cast<f32x4_t*>(sV + r * VP + c * 4) = vreg[i];
-            }
+            float* at = i < kWhole ? dst + ((in_group >> 3) + i / std::max(kPieces, 1) * kRows) * pitch + (in_group & 7) * 4 + i % std::max(kPieces, 1) * 32
+                                   : dst + (in_group / kTail + (i - kWhole) * (kGroup / kTail)) * pitch + (kPieces * 8 + in_group % kTail) * 4;
+            *reinterpret_cast<f32x4_t*>(at) = reg[i];
         }
+        if constexpr (KS > 1) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        else __syncthreads();
     };
 
     f32x16_t o[DT];
@@ -96,15 +130,18 @@ __global__ __launch_bounds__(kThreads) void attn_f32_mfma_kernel(const float* __
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+    // columns DH - kRest .. DH - 1 of this lane's query over its keys (g): a third product of 32 rows per key pair, of which head dim
+    // 72 uses 8, would be a fifth of the matrix pipe's time; the vector ALU does them beside it
+    [[maybe_unused]] float rest[kRest > 0 ? kRest : 1] = {};
     float m_run = -INFINITY, l_run = 0.f;
 
     const int ntiles = (N + BKV - 1) / BKV;
-    fetch(0);
-    for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();                      // every wavefront is done with the previous tile
-        stash();
-        __syncthreads();
-        if (t + 1 < ntiles) fetch(t + 1);
+    // K of a tile is on its way while the tile before is multiplied with V, V while the scores are computed: one set of registers
+    f32x4_t kreg[NLD], vreg[NLD];
+    if (group < ntiles) fetch(kreg, group, 1);
+    for (int t = group; t < ntiles; t += KS) {
+        fetch(vreg, t, 2);
+        stash(kreg, sK, KP);
 
         // ---- S^T = K Q^T for the 32 keys of the tile
         f32x16_t st;
@@ -119,6 +156,8 @@ __global__ __launch_bounds__(kThreads) void attn_f32_mfma_kernel(const float* __
                 st = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, qv, st, 0, 0, 0);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + KS < ntiles) fetch(kreg, t + KS, 1);
         if ((t + 1) * BKV > N) {              // ragged last tile: keys past N
 #pragma unroll
             for (int e = 0; e < 16; ++e)
@@ -129,10 +168,12 @@ __global__ __launch_bounds__(kThreads) void attn_f32_mfma_kernel(const float* __
         float mx = st[0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, st[e]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m_run, mx);           // finite: the first key of every tile exists
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2);
-        const float mb = m_new * scale_log2;
+        mx = max_lane_xor32(mx);
+        const float m_new = fmaxf(m_run, mx);
+        // (scores of -inf only, so far: they weigh nothing, and the keys of the other wavefronts may be finite)
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_ref) * scale_log2);
+        const float mb = m_ref * scale_log2;
         float p[16], sum = 0.f;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
@@ -145,45 +186,94 @@ __global__ __launch_bounds__(kThreads) void attn_f32_mfma_kernel(const float* __
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
+        if constexpr (kRest > 0)
+#pragma unroll
+            for (int d = 0; d < kRest; ++d) rest[d] *= alpha;
 
+        __builtin_amdgcn_sched_barrier(0);
+        stash(vreg, sV, VP);
         // ---- O^T += V^T P^T: register e pairs the keys 8 (e / 4) + e % 4 (+ 4 for the upper half-wave)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const float* vrow = sV + (8 * (e >> 2) + 4 * g + (e & 3)) * VP + l32;
+            const float* vrow = sV + (8 * (e >> 2) + 4 * g + (e & 3)) * VP;
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                const float vv = vrow[32 * dt];
+                const float vv = vrow[l32 + 32 * dt];
                 o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, p[e], o[dt], 0, 0, 0);
             }
+            if constexpr (kRest > 0)
+#pragma unroll
+                for (int c = 0; c < kRest / 4; ++c) {
+                    const f32x4_t vv = *reinterpret_cast<const f32x4_t*>(vrow + 32 * DT + 4 * c);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) rest[4 * c + i] = fmaf(vv[i], p[e], rest[4 * c + i]);
+                }
         }
     }
 
-    // ---- normalise and store: register e of O^T tile dt is row d = 32 dt + 8 (e / 4) + 4 g + e % 4, column l32
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    l_run = add_lane_xor<32>(l_run);
+    if constexpr (kRest > 0)
+#pragma unroll
+        for (int d = 0; d < kRest; ++d) rest[d] = add_lane_xor<32>(rest[d]);
+    // ---- register e of O^T tile dt is row d = 32 dt + 8 (e / 4) + 4 g + e % 4, column l32: groups of eight columns of a query, four in
+    // either half-wave
+    auto columns = [&](int c) -> f32x4_t {
+        const int dt = c >> 2, e4 = c & 3;
+        if constexpr (kRest > 0) {
+            if (c * 8 >= 32 * DT)
+                return g == 0 ? f32x4_t{rest[0], rest[1], rest[2], rest[3]} : f32x4_t{rest[4 % kRest], rest[5 % kRest], rest[6 % kRest], rest[7 % kRest]};
+        }
+        return f32x4_t{o[dt][4 * e4], o[dt][4 * e4 + 1], o[dt][4 * e4 + 2], o[dt][4 * e4 + 3]};
+    };
     const int q = q_base + l32;
+    float* dst = out + (row0 + q) * D + h * DH + 4 * g;
+    if constexpr (KS == 1) {
+        if (q >= N) return;
+        const float inv = 1.0f / l_run;
+#pragma unroll
+        for (int c = 0; c < DH / 8; ++c) *reinterpret_cast<f32x4_t*>(dst + 8 * c) = columns(c) * inv;
+        return;
+    }
+    // ---- the four parts: every wavefront scales its sums to the common maximum (one without keys has weight zero) and leaves them
+    // in its LDS tile
+    float* const maxima = lds + KS * L::kWaveFloats;
+    float* const sums = maxima + KS * BQ;
+    if (g == 0) {
+        maxima[wave * BQ + l32] = m_run;
+        sums[wave * BQ + l32] = l_run;
+    }
+    __syncthreads();
+    float m_all = maxima[l32];
+#pragma unroll
+    for (int w = 1; w < KS; ++w) m_all = fmaxf(m_all, maxima[w * BQ + l32]);
+    auto weight = [&](float m) { return __builtin_amdgcn_exp2f((m - m_all) * scale_log2); };
+    const float own = weight(m_run);
+#pragma unroll
+    for (int c = 0; c < DH / 8; ++c) *reinterpret_cast<f32x4_t*>(sK + c * 256 + lane * 4) = columns(c) * own;
+    float l_tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) l_tot = fmaf(sums[w * BQ + l32], weight(maxima[w * BQ + l32]), l_tot);
+    __syncthreads();
     if (q >= N) return;
     const float inv = 1.0f / l_tot;
-    float* dst = out + (row0 + q) * D + h * DH;
+    for (int c = wave; c < DH / 8; c += KS) {
+        f32x4_t v = *reinterpret_cast<const f32x4_t*>(lds + c * 256 + lane * 4);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            const int d = 32 * dt + 8 * e4 + 4 * g;
-            if (d < DH) {
-                const f32x4_t v = {o[dt][4 * e4] * inv, o[dt][4 * e4 + 1] * inv, o[dt][4 * e4 + 2] * inv,
-                                   o[dt][4 * e4 + 3] * inv};
-                *reinterpret_cast<f32x4_t*>(dst + d) = v;
-            }
-        }
+        for (int w = 1; w < KS; ++w) v += *reinterpret_cast<const f32x4_t*>(lds + w * L::kWaveFloats + c * 256 + lane * 4);
+        *reinterpret_cast<f32x4_t*>(dst + 8 * c) = v * inv;
+    }
 }
 
-template <int DH>
+template <int DH, int KS>
 int32_t launch_dh(const float* qkv, int32_t B, int32_t N, int32_t heads, float* out, hipStream_t s) {
+    constexpr int kQueries = BQ * kWaves / KS;
     const float scale_log2 = 1.4426950408889634f / std::sqrt(static_cast<float>(DH));
-    const int64_t total = static_cast<int64_t>((N + 127) / 128) * heads * B;
+    const int64_t total = static_cast<int64_t>((N + kQueries - 1) / kQueries) * heads * B;
     if (total > 0x7fffffff) return FREE_ERR_SHAPE;
-    hipLaunchKernelGGL((attn_f32_mfma_kernel<DH>), dim3(static_cast<unsigned>(total)), dim3(kThreads), 0, s, qkv, N,
-                       heads, scale_log2, out);
+    auto kern = attn_f32_mfma_kernel<DH, KS>;
+    static LdsLimit limit;
+    if (!limit.allow(reinterpret_cast<const void*>(kern), Tile<DH, KS>::kLds)) return FREE_ERR_HIP;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(total)), dim3(kThreads), (Tile<DH, KS>::kLds), s, qkv, N, heads, scale_log2, out);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 
@@ -197,10 +287,10 @@ int32_t launch_attention_mfma_f32(const float* qkv, int32_t B, int32_t N, int32_
                                   hipStream_t s) {
     if ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(out)) & 15u) return FREE_ERR_SHAPE;
     switch (dh) {
-        case 16: return launch_dh<16>(qkv, B, N, heads, out, s);
-        case 64: return launch_dh<64>(qkv, B, N, heads, out, s);
-        case 72: return launch_dh<72>(qkv, B, N, heads, out, s);
-        case 128: return launch_dh<128>(qkv, B, N, heads, out, s);
+        case 16: return launch_dh<16, 4>(qkv, B, N, heads, out, s);
+        case 64: return launch_dh<64, 4>(qkv, B, N, heads, out, s);
+        case 72: return launch_dh<72, 4>(qkv, B, N, heads, out, s);
+        case 128: return launch_dh<128, 1>(qkv, B, N, heads, out, s);
         default: return FREE_ERR_SHAPE;
     }
 }

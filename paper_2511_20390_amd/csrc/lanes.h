@@ -62,6 +62,15 @@ __device__ __forceinline__ double add_lane_xor(double v) {
     }
 }
 
+// the larger of v and the value of lane ^ 32
+__device__ __forceinline__ float max_lane_xor32(float v) {
+    typedef uint32_t pair_t __attribute__((ext_vector_type(2)));
+    const uint32_t b = __float_as_uint(v);
+    const pair_t r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    return fmaxf(__uint_as_float(r0), __uint_as_float(r1));
+}
+
 // the sum over the 64 lanes, in every lane: halves added from the widest distance down
 __device__ __forceinline__ float wave_sum(float v) {
     v = add_lane_xor<32>(v);
