@@ -302,6 +302,7 @@ __global__ __launch_bounds__(kThreads) void patch_embed16_kernel(
 constexpr int kPeThreads = 320;            // 288 of them carry columns at D = 1152
 constexpr int kPeTok = 4;
 constexpr int kPeSamples = 16;
+static_assert(kPeThreads % (kPeTok * 16) == 0, "a thread gathers one pixel of every sample");
 template <typename FT>
 __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
     const float* __restrict__ x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p, int32_t D,
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
     const int gw = W / p;
     const int n0 = blockIdx.x * kPeTok, b0 = blockIdx.y * kPeSamples;
     const int nb = B - b0 < kPeSamples ? B - b0 : kPeSamples;
-    const int j0 = 4 * static_cast<int>(threadIdx.x);
+    const int j0 = 4 * static_cast<int>(blockIdx.z * blockDim.x + threadIdx.x);
     const bool col_on = j0 < D;
     const int jc = col_on ? j0 : 0;                     // idle lanes re-read column 0 and store nothing
     float4 w[4][4];
@@ -327,17 +328,23 @@ __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
         const int n = n0 + u < ntok ? n0 + u : ntok - 1;
         pe[u] = *reinterpret_cast<const float4*>(pos + static_cast<int64_t>(n) * D + jc);
     }
-    for (int e = threadIdx.x; e < nb * kPeTok * 16; e += kPeThreads) {
-        const int sb = e / (kPeTok * 16), tk = (e >> 4) % kPeTok, q = e & 15;
-        const int n = n0 + tk;
-        float v = 0.f;
-        if (n < ntok) {
-            const float* xb = x + static_cast<int64_t>((b0 + sb) % x_mod) * C * H * W;
-            const int gi = n / gw, gj = n % gw;
-            const int c = q / (p * p), ph = (q / p) % p, pq = q % p;
-            v = xb[(static_cast<int64_t>(c) * H + gi * p + ph) * W + gj * p + pq];
+    // (a workgroup has a whole multiple of kPeTok * 16 threads: a thread gathers the same pixel of every sample, four samples in flight)
+    {
+        const int e = threadIdx.x % (kPeTok * 16), tk = e >> 4, q = e & 15, n = n0 + tk, nc = n < ntok ? n : ntok - 1;
+        const int gi = nc / gw, gj = nc - gi * gw, qp = q / p, pq = q - qp * p, c = qp / p, ph = qp - c * p;
+        const int64_t at = (static_cast<int64_t>(c) * H + gi * p + ph) * W + gj * p + pq, latent = static_cast<int64_t>(C) * H * W;
+        const int step = blockDim.x / (kPeTok * 16);
+        for (int sb = threadIdx.x / (kPeTok * 16); sb < nb; sb += 4 * step) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int s1 = sb + u * step < nb ? sb + u * step : nb - 1;
+                v[u] = x[static_cast<uint32_t>(b0 + s1) % static_cast<uint32_t>(x_mod) * latent + at];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (sb + u * step < nb) patch[sb + u * step][tk][q] = n < ntok ? v[u] : 0.f;
         }
-        patch[sb][tk][q] = v;
     }
     float4 fv[kPeTok];                                  // kFuse: this thread's columns of feat, a sample ahead
     auto load_feat = [&](int sb) {
@@ -1092,9 +1099,14 @@ template <typename FT>
 static int32_t launch_patch_embed16v(const float* x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p,
                                      int32_t D, const float* pw, const float* pb, const float* pos, void* out, const float* feat,
                                      float* zero_out, hipStream_t s) {
-    const int ntok = (H / p) * (W / p);
-    hipLaunchKernelGGL(patch_embed16v_kernel<FT>, dim3((ntok + kPeTok - 1) / kPeTok, (B + kPeSamples - 1) / kPeSamples),
-                       dim3(kPeThreads), 0, s, x, x_mod, B, C, H, W, p, D, pw, pb, pos, out, ntok, feat, zero_out);
+    // Fewer workgroups than CUs: the columns over several, of one wavefront each.  Every weight load of a wavefront touches 64 lines (a
+    // thread's four rows are 256 bytes), which for all columns is 2 us of line lookups in the CU that has them.  (The weights through
+    // LDS instead, whole lines per load: 2 x 1024 tokens 1.6 % of a drafting round slower.)
+    const int ntok = (H / p) * (W / p), bx = (ntok + kPeTok - 1) / kPeTok, by = (B + kPeSamples - 1) / kPeSamples;
+    const bool narrow = static_cast<int64_t>(bx) * by < device_cus();
+    const int threads = narrow ? kPeTok * 16 : kPeThreads, bz = narrow ? (D / 4 + 63) / 64 : 1;
+    hipLaunchKernelGGL(patch_embed16v_kernel<FT>, dim3(bx, by, bz), dim3(threads), 0, s, x, x_mod, B, C, H, W, p, D, pw, pb, pos, out,
+                       ntok, feat, zero_out);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 

@@ -47,6 +47,21 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
         xa[s][0] = *reinterpret_cast<const f32x4_t*>(xr + 32 * s);
         xa[s][1] = *reinterpret_cast<const f32x4_t*>(xr + 32 * s + 4);
     }
+    // Where this thread's sums go (the first two wavefronts: outputs 16 t + 4 (lane / 16) + i of token row lane % 16) and their bias:
+    // some twenty divisions, done while the loads above are under way.
+    const int P = p * p * c_out, r_out = row0 + l16;
+    float* dst[4];
+    float bias_out[4];
+    if (wave < 2) {
+        const int ntok = gh * gw, b = row / ntok, n = row - b * ntok, gi = n / gw, gj = n - gi * gw;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = 16 * wave + 4 * lq + i, oc = o < P ? o : 0;
+            const int pp = oc / c_out, c = oc - pp * c_out, ph = pp / p, pq = pp - ph * p;
+            dst[i] = o < P && r_out < M ? out + ((static_cast<int64_t>(b) * c_out + c) * gh * p + gi * p + ph) * gw * p + gj * p + pq : nullptr;
+            bias_out[i] = bias[oc];
+        }
+    }
     // a row lives in the four lanes l16 + 16 lq of each of the four wavefronts
     auto row_total = [&](float v, int slot) {
         v = add_lane_xor<32>(add_lane_xor<16>(v));
@@ -72,7 +87,6 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
 
     const float* shr = shift.base + static_cast<int64_t>(row / shift.rows_per_sample) * shift.stride + k0;
     const float* scr = scale.base + static_cast<int64_t>(row / scale.rows_per_sample) * scale.stride + k0;
-    const int P = p * p * c_out;
     f32x4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     // k-steps in groups of kG: the shift, scale and weight pieces of a whole group are requested together and
     // only then used - one memory round trip per group on the critical path of the workgroup instead of two per
@@ -134,30 +148,17 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
 #pragma unroll
     for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4_t*>(part[wave][t][lane]) = acc[t];
     __syncthreads();
-    if (tid < 128) {
-        const int t = tid >> 6, ln = tid & 63;
-        f32x4_t v = *reinterpret_cast<const f32x4_t*>(part[0][t][ln]);
+    if (wave < 2) {
+        f32x4_t v = *reinterpret_cast<const f32x4_t*>(part[0][wave][lane]);
 #pragma unroll
         for (int wv = 1; wv < 4; ++wv) {
-            const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part[wv][t][ln]);
+            const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part[wv][wave][lane]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] += u[i];
         }
-        const int r = row0 + (ln & 15);
-        if (r < M) {
-            const int ntok = gh * gw;
-            const int b = r / ntok, n = r % ntok;
-            const int gi = n / gw, gj = n % gw;
-            const int H = gh * p, Wd = gw * p;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int o = 16 * t + 4 * (ln >> 4) + i;
-                if (o < P) {
-                    const int c = o % c_out, pq = (o / c_out) % p, ph = o / (c_out * p);
-                    out[((static_cast<int64_t>(b) * c_out + c) * H + gi * p + ph) * Wd + gj * p + pq] = v[i] + bias[o];
-                }
-            }
-        }
+        for (int i = 0; i < 4; ++i)
+            if (dst[i]) *dst[i] = v[i] + bias_out[i];
     }
 }
 
