@@ -1,5 +1,5 @@
 // Final layer of the DiT (LayerNorm without affine, per-sample modulate, linear D -> p*p*C_out,
-// unpatchify to [B, C_out, H, W]) for bf16 weights, on the matrix cores.
+// unpatchify to [B, C_out, H, W]) on the matrix cores, bf16 or fp32 weights.
 //
 // One workgroup per 16 token rows, four wavefronts that split the hidden dimension in four
 // contiguous quarters: a lane holds its 8-float pieces of the quarter in registers (72 floats at
@@ -10,12 +10,16 @@
 // activations lose nothing that matters against the fp32 accumulation; weight rows are the A
 // operand, read from global memory (L2) in operand layout.  The four partial 32 x 16 products are
 // added through LDS and scattered to the image layout.
+// With fp32 weights the same pieces feed v_mfma_f32_16x16x4_f32, eight per k-step and output tile (2 x 256 rows of 1152 43 -> 11 us
+// against the kernel of one wavefront per row).
 //
 // The per-row kernel this replaces re-read the whole weight matrix (74 KB) from cache for every
 // token row and reduced each of the 32 outputs across the wavefront separately: 120 us at 12288
 // rows against 10 us for reading the rows once.
 #include "free_internal.h"
 #include "lanes.h"
+
+#include <type_traits>
 
 namespace freemi {
 
@@ -24,15 +28,17 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef float float8_t __attribute__((ext_vector_type(8), aligned(16)));
 
 constexpr int kThreads = 256;
 constexpr int kRows = 16;                 // token rows per workgroup (the N dimension of the MFMA)
 
-template <int NS>                         // k-steps of 32 per wavefront: D = 128 NS
+template <typename WT, int NS>            // k-steps of 32 per wavefront: D = 128 NS
 __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
     const float* __restrict__ x, RowVec shift, RowVec scale, int32_t M, int32_t gh, int32_t gw, int32_t p,
-    int32_t c_out, const bf16_t* __restrict__ w, const float* __restrict__ bias, float* __restrict__ out) {
+    int32_t c_out, const WT* __restrict__ w, const float* __restrict__ bias, float* __restrict__ out) {
     constexpr int D = 128 * NS;
+    constexpr bool kF32 = std::is_same<WT, float>::value;
     __shared__ float red[2][4][kRows];
     __shared__ __attribute__((aligned(16))) float part[4][2][64][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -97,7 +103,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
 #pragma unroll
     for (int g0 = 0; g0 < NS; g0 += kG) {
         f32x4_t shv[kG][2], scv[kG][2];
-        u32x4_t wv[kG][2];
+        std::conditional_t<kF32, float8_t, u32x4_t> wv[kG][2];          // eight weights
 #pragma unroll
         for (int u = 0; u < kG; ++u) {
             const int s = g0 + u;
@@ -111,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
             for (int t = 0; t < 2; ++t) {
                 const int o = 16 * t + l16;
                 // (outputs past P re-read row 0 and are multiplied into columns that are never stored)
-                wv[u][t] = *reinterpret_cast<const u32x4_t*>(w + static_cast<int64_t>(o < P ? o : 0) * D + k0 + 32 * s);
+                wv[u][t] = *reinterpret_cast<decltype(&wv[0][0])>(const_cast<WT*>(w + static_cast<int64_t>(o < P ? o : 0) * D + k0 + 32 * s));
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -119,28 +125,34 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
         for (int u = 0; u < kG; ++u) {
             const int s = g0 + u;
             if (s >= NS) continue;
-            uint32_t hi[4], lo[4];
+            float v[8];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                float v[4];
+            for (int c = 0; c < 8; ++c) v[c] = fmaf((xa[s][c >> 2][c & 3] - mean) * rstd, 1.0f + scv[u][c >> 2][c & 3], shv[u][c >> 2][c & 3]);
+            if constexpr (kF32) {
+                // element e: the four lane groups hold four k of one product
 #pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = fmaf((xa[s][h][c] - mean) * rstd, 1.0f + scv[u][h][c], shv[u][h][c]);
+                for (int e = 0; e < 8; ++e)
 #pragma unroll
-                for (int c2 = 0; c2 < 2; ++c2) {
+                    for (int t = 0; t < 2; ++t) {
+                        const float a = wv[u][t][e];
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(16 * t + l16 < P ? a : 0.f, v[e], acc[t], 0, 0, 0);
+                    }
+            } else {
+                uint32_t hi[4], lo[4];
+#pragma unroll
+                for (int c2 = 0; c2 < 4; ++c2) {
                     const uint32_t hp = pack_bf16_pair(v[2 * c2], v[2 * c2 + 1]);
-                    hi[2 * h + c2] = hp;
-                    lo[2 * h + c2] = pack_bf16_pair(v[2 * c2] - __uint_as_float(hp << 16),
-                                                    v[2 * c2 + 1] - __uint_as_float(hp & 0xffff0000u));
+                    hi[c2] = hp;
+                    lo[c2] = pack_bf16_pair(v[2 * c2] - __uint_as_float(hp << 16), v[2 * c2 + 1] - __uint_as_float(hp & 0xffff0000u));
                 }
-            }
-            const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[0], hi[1], hi[2], hi[3]});
-            const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
+                const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, u32x4_t{hi[0], hi[1], hi[2], hi[3]});
+                const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, u32x4_t{lo[0], lo[1], lo[2], lo[3]});
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int o = 16 * t + l16;
-                const bf16x8_t a = __builtin_bit_cast(bf16x8_t, o < P ? wv[u][t] : u32x4_t{0, 0, 0, 0});
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, acc[t], 0, 0, 0);
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc[t], 0, 0, 0);
+                for (int t = 0; t < 2; ++t) {
+                    const bf16x8_t a = __builtin_bit_cast(bf16x8_t, 16 * t + l16 < P ? wv[u][t] : u32x4_t{0, 0, 0, 0});
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc[t], 0, 0, 0);
+                }
             }
         }
     }
@@ -164,18 +176,23 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
 
 }  // namespace
 
-// bf16 weights, D one of 384 / 768 / 1024 / 1152 (the DiT-S/B/L/XL widths), at most 32 outputs per
+// bf16 or fp32 weights, D one of 384 / 768 / 1024 / 1152 (the DiT-S/B/L/XL widths), at most 32 outputs per
 // token, 16-byte aligned rows of x, the weights and the modulation vectors.
 bool final_mfma_supported(int32_t D, int32_t P) {
     return (D == 384 || D == 768 || D == 1024 || D == 1152) && P >= 1 && P <= 32;
 }
 
 int32_t launch_final_layer_mfma(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t gh, int32_t gw,
-                                int32_t p, int32_t c_out, int32_t D, const bf16_t* w, const float* bias, float* out,
-                                hipStream_t s) {
+                                int32_t p, int32_t c_out, int32_t D, const void* w, int32_t dtype, const float* bias,
+                                float* out, hipStream_t s) {
     const dim3 grid((M + kRows - 1) / kRows), block(kThreads);
-#define FREE_FIN_MFMA(NS)                                                                                        \
-    hipLaunchKernelGGL(final_layer_mfma_kernel<NS>, grid, block, 0, s, x, shift, scale, M, gh, gw, p, c_out, w, bias, out)
+#define FREE_FIN_MFMA(NS)                                                                                                        \
+    if (dtype == FREE_BF16)                                                                                                      \
+        hipLaunchKernelGGL((final_layer_mfma_kernel<bf16_t, NS>), grid, block, 0, s, x, shift, scale, M, gh, gw, p, c_out,       \
+                           static_cast<const bf16_t*>(w), bias, out);                                                            \
+    else                                                                                                                         \
+        hipLaunchKernelGGL((final_layer_mfma_kernel<float, NS>), grid, block, 0, s, x, shift, scale, M, gh, gw, p, c_out,        \
+                           static_cast<const float*>(w), bias, out)
     switch (D) {
         case 384: FREE_FIN_MFMA(3); break;
         case 768: FREE_FIN_MFMA(6); break;
