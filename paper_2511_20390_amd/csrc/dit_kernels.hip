@@ -1277,17 +1277,12 @@ int32_t launch_attention_simple(const void* qkv, int32_t B, int32_t N, int32_t h
     return attention_simple_t(static_cast<const float*>(qkv), B, N, heads, dh, static_cast<float*>(out), s);
 }
 
-int32_t launch_final_layer(const float* x, RowVec shift, RowVec scale, int32_t B, int32_t gh, int32_t gw,
-                           int32_t p, int32_t c_out, int32_t D, const void* w, const float* bias, int32_t dtype,
-                           float* out, hipStream_t s) {
-    const int M = B * gh * gw;
+// the noise estimates, for shapes that final_mfma.hip does not have (or has not in this alignment)
+static int32_t launch_final_layer_rows(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t gh, int32_t gw, int32_t p,
+                                       int32_t c_out, int32_t D, const void* w, const float* bias, int32_t dtype, bool vec,
+                                       float* out, hipStream_t s) {
     const int blocks = (M + kWaves - 1) / kWaves;
-    auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
-    bool vec = (D % 4 == 0) && D <= 2048 && al16(x) && al16(w) && al16(shift.base) && al16(scale.base) &&
-                     (shift.stride % 4 == 0) && (scale.stride % 4 == 0);
     const size_t lds_bytes = static_cast<size_t>(p) * p * c_out * D * (dtype == FREE_BF16 ? 2 : 4);
-    if (vec && final_mfma_supported(D, p * p * c_out))
-        return launch_final_layer_mfma(x, shift, scale, M, gh, gw, p, c_out, D, w, dtype, bias, out, s);
     if (vec) {
         const int nv = (D / 4 + 63) / 64;
         // few rows: stage the weights in LDS, as many workgroups as fit on the chip at once (LDS-limited),
@@ -1343,6 +1338,24 @@ int32_t launch_final_layer(const float* x, RowVec shift, RowVec scale, int32_t B
         hipLaunchKernelGGL(final_layer_kernel<float>, dim3(blocks), dim3(kThreads), 0, s, x, shift, scale, M, gh,
                            gw, p, c_out, D, static_cast<const float*>(w), bias, out);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
+}
+
+int32_t launch_final_layer(const float* x, RowVec shift, RowVec scale, int32_t B, int32_t gh, int32_t gw,
+                           int32_t p, int32_t c_out, int32_t D, const void* w, const float* bias, int32_t dtype,
+                           float* out, hipStream_t s, const FinalMean* mean) {
+    const int M = B * gh * gw;
+    auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
+    const bool vec = (D % 4 == 0) && D <= 2048 && al16(x) && al16(w) && al16(shift.base) && al16(scale.base) &&
+                     (shift.stride % 4 == 0) && (scale.stride % 4 == 0);
+    if (vec && final_mfma_supported(D, p * p * c_out))
+        return launch_final_layer_mfma(x, shift, scale, M, gh, gw, p, c_out, D, w, dtype, bias, out, s, mean);
+    const int32_t st = launch_final_layer_rows(x, shift, scale, M, gh, gw, p, c_out, D, w, bias, dtype, vec, out, s);
+    if (st != FREE_OK || !mean) return st;
+    const int64_t hw = static_cast<int64_t>(gh) * p * gw * p;
+    if (mean->x_copy && !hip_ok(hipMemcpyAsync(mean->x_copy, mean->x, static_cast<size_t>(mean->C * hw) * 4, hipMemcpyDeviceToDevice, s)))
+        return FREE_ERR_HIP;
+    return launch_eps_to_mean(out, mean->x, mean->coef_x, mean->coef_eps, mean->cfg_scale, 1, mean->C, c_out, hw, mean->m, s, nullptr,
+                              mean->sigma, mean->xi, mean->x_next);
 }
 
 // ---- drafter helpers (Sec. 3.2: FC layer on [embedding | propagated feature]; Alg. 1 drafting loop) ----

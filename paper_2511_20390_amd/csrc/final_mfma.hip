@@ -33,18 +33,29 @@ typedef float float8_t __attribute__((ext_vector_type(8), aligned(16)));
 constexpr int kThreads = 256;
 constexpr int kRows = 16;                 // token rows per workgroup (the N dimension of the MFMA)
 
-template <typename WT, int NS>            // k-steps of 32 per wavefront: D = 128 NS
+// kMean: what a drafting step computes from the noise estimates (FinalMean) in their place.  The rows of a workgroup are then 16 / dup
+// tokens of each state, so that both estimates of a pixel are in one wavefront, eight lanes apart.  A launch less per step, of 2.9 us
+// at 256 tokens and 4.7 at 2 x 1024.
+template <typename WT, int NS, bool kMean>            // NS: k-steps of 32 per wavefront, D = 128 NS
 __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
     const float* __restrict__ x, RowVec shift, RowVec scale, int32_t M, int32_t gh, int32_t gw, int32_t p,
-    int32_t c_out, const WT* __restrict__ w, const float* __restrict__ bias, float* __restrict__ out) {
+    int32_t c_out, const WT* __restrict__ w, const float* __restrict__ bias, float* __restrict__ out,
+    FinalMean step) {
     constexpr int D = 128 * NS;
     constexpr bool kF32 = std::is_same<WT, float>::value;
     __shared__ float red[2][4][kRows];
     __shared__ __attribute__((aligned(16))) float part[4][2][64][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, lq = lane >> 4;
-    const int row0 = blockIdx.x * kRows;
-    const int row = row0 + l16 < M ? row0 + l16 : M - 1;          // rows past M repeat the last one, never stored
+    const int ntok = gh * gw;
+    int row = blockIdx.x * kRows + l16;
+    bool stored = row < M;
+    row = stored ? row : M - 1;                                    // rows past M repeat the last one, never stored
+    if constexpr (kMean) {
+        const int per = kRows / step.dup, state = l16 / per, n = blockIdx.x * per + l16 - state * per;
+        stored = state == 0 && n < ntok;
+        row = state * ntok + (n < ntok ? n : ntok - 1);
+    }
     const int k0 = wave * NS * 32 + lq * 8;                        // + 32 s: this lane's 8 columns of k-step s
     const float* xr = x + static_cast<int64_t>(row) * D + k0;
     f32x4_t xa[NS][2];
@@ -55,17 +66,28 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
     }
     // Where this thread's sums go (the first two wavefronts: outputs 16 t + 4 (lane / 16) + i of token row lane % 16) and their bias:
     // some twenty divisions, done while the loads above are under way.
-    const int P = p * p * c_out, r_out = row0 + l16;
-    float* dst[4];
+    const int P = p * p * c_out;
+    int64_t dst[4];
     float bias_out[4];
+    [[maybe_unused]] float x_in[4], xi_in[4], cx, ce, sg;
     if (wave < 2) {
-        const int ntok = gh * gw, b = row / ntok, n = row - b * ntok, gi = n / gw, gj = n - gi * gw;
+        if constexpr (kMean) {
+            cx = *step.coef_x;
+            ce = *step.coef_eps;
+            sg = *step.sigma;
+        }
+        const int b = row / ntok, n = row - b * ntok, gi = n / gw, gj = n - gi * gw;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int o = 16 * wave + 4 * lq + i, oc = o < P ? o : 0;
             const int pp = oc / c_out, c = oc - pp * c_out, ph = pp / p, pq = pp - ph * p;
-            dst[i] = o < P && r_out < M ? out + ((static_cast<int64_t>(b) * c_out + c) * gh * p + gi * p + ph) * gw * p + gj * p + pq : nullptr;
+            const bool on = o < P && stored && (!kMean || c < step.C);
+            dst[i] = on ? ((static_cast<int64_t>(b) * c_out + c) * gh * p + gi * p + ph) * gw * p + gj * p + pq : -1;
             bias_out[i] = bias[oc];
+            if constexpr (kMean) {
+                x_in[i] = step.x[on ? dst[i] : 0];
+                xi_in[i] = step.xi[on ? dst[i] : 0];
+            }
         }
     }
     // a row lives in the four lanes l16 + 16 lq of each of the four wavefronts
@@ -169,8 +191,20 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
             for (int i = 0; i < 4; ++i) v[i] += u[i];
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (dst[i]) *dst[i] = v[i] + bias_out[i];
+        for (int i = 0; i < 4; ++i) {
+            float e = v[i] + bias_out[i];
+            if constexpr (!kMean) {
+                if (dst[i] >= 0) out[dst[i]] = e;
+            } else {
+                const float null = lane_xor<8>(e);
+                if (step.dup == 2) e = fmaf(step.cfg_scale, e - null, null);
+                const float m = fmaf(cx, x_in[i], ce * e);
+                if (dst[i] < 0) continue;
+                step.m[dst[i]] = m;
+                step.x_next[dst[i]] = fmaf(sg, xi_in[i], m);
+                if (step.x_copy) step.x_copy[dst[i]] = x_in[i];
+            }
+        }
     }
 }
 
@@ -184,22 +218,28 @@ bool final_mfma_supported(int32_t D, int32_t P) {
 
 int32_t launch_final_layer_mfma(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t gh, int32_t gw,
                                 int32_t p, int32_t c_out, int32_t D, const void* w, int32_t dtype, const float* bias,
-                                float* out, hipStream_t s) {
-    const dim3 grid((M + kRows - 1) / kRows), block(kThreads);
-#define FREE_FIN_MFMA(NS)                                                                                                        \
-    if (dtype == FREE_BF16)                                                                                                      \
-        hipLaunchKernelGGL((final_layer_mfma_kernel<bf16_t, NS>), grid, block, 0, s, x, shift, scale, M, gh, gw, p, c_out,       \
-                           static_cast<const bf16_t*>(w), bias, out);                                                            \
-    else                                                                                                                         \
-        hipLaunchKernelGGL((final_layer_mfma_kernel<float, NS>), grid, block, 0, s, x, shift, scale, M, gh, gw, p, c_out,        \
-                           static_cast<const float*>(w), bias, out)
+                                float* out, hipStream_t s, const FinalMean* mean) {
+    const int per = mean ? kRows / mean->dup : kRows, rows = mean ? gh * gw : M;
+    const dim3 grid((rows + per - 1) / per), block(kThreads);
+    const FinalMean fm = mean ? *mean : FinalMean{};
+#define FREE_FIN_MFMA(WT, NS, MEAN)                                                                                            \
+    hipLaunchKernelGGL((final_layer_mfma_kernel<WT, NS, MEAN>), grid, block, 0, s, x, shift, scale, M, gh, gw, p, c_out,       \
+                       static_cast<const WT*>(w), bias, out, fm)
+#define FREE_FIN_CASE(NS)                                                   \
+    do {                                                                    \
+        if (dtype == FREE_BF16 && mean) FREE_FIN_MFMA(bf16_t, NS, true);    \
+        else if (dtype == FREE_BF16) FREE_FIN_MFMA(bf16_t, NS, false);      \
+        else if (mean) FREE_FIN_MFMA(float, NS, true);                      \
+        else FREE_FIN_MFMA(float, NS, false);                               \
+    } while (0)
     switch (D) {
-        case 384: FREE_FIN_MFMA(3); break;
-        case 768: FREE_FIN_MFMA(6); break;
-        case 1024: FREE_FIN_MFMA(8); break;
-        case 1152: FREE_FIN_MFMA(9); break;
+        case 384: FREE_FIN_CASE(3); break;
+        case 768: FREE_FIN_CASE(6); break;
+        case 1024: FREE_FIN_CASE(8); break;
+        case 1152: FREE_FIN_CASE(9); break;
         default: return FREE_ERR_SHAPE;
     }
+#undef FREE_FIN_CASE
 #undef FREE_FIN_MFMA
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }

@@ -1197,10 +1197,10 @@ int32_t drafter_modulation(free_drafter_t dr, const int32_t* t, const int32_t* y
 }
 
 // mod_pre (nullable): modulation vectors computed by the caller, sample b at mod_pre + b * mod_stride; then t
-// and y are not read.
+// and y are not read.  mean (nullable): instead of the noise estimates, which then only eps_out may hold.
 int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, const float* f_prev, const int32_t* t,
                              const int32_t* y, int32_t B, float* eps_out, float* f_out, char* ws, hipStream_t s,
-                             const float* mod_pre = nullptr, int32_t mod_stride = 0) {
+                             const float* mod_pre = nullptr, int32_t mod_stride = 0, const FinalMean* mean = nullptr) {
     free_dit_t h = dr->target;
     const Dims& d = h->dims;
     const DraftLayout L = make_draft_layout(d, dr->mod_rows, B);
@@ -1239,7 +1239,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     RowVec fsh{mod + static_cast<int64_t>(dr->depth) * 6 * d.D, mod_stride, d.ntok};
     RowVec fsc{mod + static_cast<int64_t>(dr->depth) * 6 * d.D + d.D, mod_stride, d.ntok};
     return launch_final_layer(f_out, fsh, fsc, B, d.gh, d.gw, d.p, d.c_out, d.D, dr->fin(F_W),
-                              static_cast<const float*>(dr->fin(F_B)), d.mode, eps_out, s);
+                              static_cast<const float*>(dr->fin(F_B)), d.mode, eps_out, s, mean);
 }
 
 }  // namespace
@@ -1349,12 +1349,6 @@ int32_t draft_round(free_drafter_t dr, const float* x_a, const float* f_a, const
     int32_t* yp = reinterpret_cast<int32_t*>(ws + L.ypack);
     float* eps = reinterpret_cast<float*>(ws + L.eps);
     float* feat = f_last ? f_last : reinterpret_cast<float*>(ws + L.feat);
-    const size_t feat_bytes = static_cast<size_t>(dup) * d.ntok * d.D * 4;
-    const int64_t hw = static_cast<int64_t>(d.H) * d.W;
-    if (!hip_ok(hipMemcpyAsync(x_states, x_a, static_cast<size_t>(d.d) * 4, hipMemcpyDeviceToDevice, s)))
-        return FREE_ERR_HIP;
-    if (feat != f_a && !hip_ok(hipMemcpyAsync(feat, f_a, feat_bytes, hipMemcpyDeviceToDevice, s)))
-        return FREE_ERR_HIP;
     // The timesteps of all K steps are known: their conditioning and modulation vectors are computed in one
     // pass (packed as [cond x K | null x K], so step k reads samples k and K + k), not once per step.
     const bool hoist = K * dup <= kHoistRows;
@@ -1366,18 +1360,20 @@ int32_t draft_round(free_drafter_t dr, const float* x_a, const float* f_a, const
         mod_all = reinterpret_cast<const float*>(ws + L.mod);
     }
     for (int k = 0; k < K; ++k) {
-        const float* xk = x_states + static_cast<int64_t>(k) * d.d;
+        // the first step reads the state and the feature where they are, and writes the state to its place in the pack
+        const float* xk = k == 0 ? x_a : x_states + static_cast<int64_t>(k) * d.d;
+        const float* fk = k == 0 ? f_a : feat;
         float* mk = m_draft + static_cast<int64_t>(k) * d.d;
         float* xn = k + 1 < K ? x_states + static_cast<int64_t>(k + 1) * d.d : x_last;
+        const FinalMean mean{xk, coef_x + k, coef_eps + k, sigma + k, cfg_scale, dup, d.C, xi + static_cast<int64_t>(k) * d.d, mk, xn,
+                             k == 0 && x_a != x_states ? x_states : nullptr};
         if (hoist) {
-            FREE_TRY(drafter_forward_impl(dr, xk, 1, feat, nullptr, nullptr, dup, eps, feat, ws, s,
-                                          mod_all + static_cast<int64_t>(k) * dr->mod_rows, K * dr->mod_rows));
+            FREE_TRY(drafter_forward_impl(dr, xk, 1, fk, nullptr, nullptr, dup, eps, feat, ws, s,
+                                          mod_all + static_cast<int64_t>(k) * dr->mod_rows, K * dr->mod_rows, &mean));
         } else {
             FREE_TRY(launch_pack_cond(t + k, y, d.classes, 1, dup, tp, yp, s));
-            FREE_TRY(drafter_forward_impl(dr, xk, 1, feat, tp, yp, dup, eps, feat, ws, s));
+            FREE_TRY(drafter_forward_impl(dr, xk, 1, fk, tp, yp, dup, eps, feat, ws, s, nullptr, 0, &mean));
         }
-        FREE_TRY(launch_eps_to_mean(eps, xk, coef_x + k, coef_eps + k, cfg_scale, 1, d.C, d.c_out, hw, mk, s, nullptr,
-                                    sigma + k, xi + static_cast<int64_t>(k) * d.d, xn));
     }
     return FREE_OK;
 }

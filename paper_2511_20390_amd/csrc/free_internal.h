@@ -215,9 +215,20 @@ int32_t launch_linear_simple(const void* A, const void* W, const float* bias, in
                              RowVec gate, hipStream_t s);
 int32_t launch_attention_simple(const void* qkv, int32_t B, int32_t N, int32_t heads, int32_t dh,
                                 int32_t dtype, void* out, hipStream_t s);
+// What follows the output layer in a drafting step, on the one latent x [C, H, W]: the guided noise estimate (dup = 2: conditional and
+// null state, cfg_scale), m = coef_x x + coef_eps eps and x_next = m + sigma xi.  x_copy: nullptr, or where x goes too.
+struct FinalMean {
+    const float* x;
+    const float *coef_x, *coef_eps, *sigma;
+    float cfg_scale;
+    int32_t dup, C;
+    const float* xi;
+    float *m, *x_next, *x_copy;
+};
+// mean: nullptr (the noise estimates go to out), or the step's mean and next draft, out being room for the estimates of dup states
 int32_t launch_final_layer(const float* x, RowVec shift, RowVec scale, int32_t B, int32_t gh, int32_t gw,
                            int32_t p, int32_t c_out, int32_t D, const void* w, const float* bias,
-                           int32_t dtype, float* out, hipStream_t s);
+                           int32_t dtype, float* out, hipStream_t s, const FinalMean* mean = nullptr);
 int32_t launch_eps_to_mean(const float* eps_out, const float* x_states, const float* coef_x,
                            const float* coef_eps, float cfg_scale, int32_t K, int32_t C, int32_t c_out,
                            int64_t hw, float* m_out, hipStream_t s, float* eps_guided = nullptr,
@@ -251,7 +262,7 @@ bool adaln_mfma_supported(int32_t D, int32_t total_rows);
 bool final_mfma_supported(int32_t D, int32_t P);
 int32_t launch_final_layer_mfma(const float* x, RowVec shift, RowVec scale, int32_t M, int32_t gh, int32_t gw,
                                 int32_t p, int32_t c_out, int32_t D, const void* w, int32_t dtype, const float* bias,
-                                float* out, hipStream_t s);
+                                float* out, hipStream_t s, const FinalMean* mean);
 int32_t launch_adaln_mfma(const float* sc, int32_t B, int32_t D, const void* const* w_tab,
                           const float* const* b_tab, const int32_t* row_start, int32_t n_mats,
                           int32_t total_rows, int32_t mode, float* mod, hipStream_t s);

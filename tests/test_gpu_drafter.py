@@ -144,6 +144,51 @@ def test_draft_round_parity(name, K, cfg_scale, depth, mode):
     target.close()
 
 
+# tokens that are no multiple of a workgroup's 16 (8 per state under guidance), fewer than one workgroup's, a width whose output layer
+# has no matrix-core kernel (64); the state in place (the first of the pack already)
+@pytest.mark.parametrize("mode", ["fp32", "bf16"])
+@pytest.mark.parametrize("hidden,lat_h,lat_w,K,cfg_scale,in_place", [(384, 18, 22, 3, 4.0, False), (384, 18, 22, 2, 1.0, False), (768, 2, 6, 2, 1.5, False),
+                                                                     (1152, 10, 14, 1, 4.0, True), (64, 18, 22, 3, 4.0, False)])
+def test_draft_round_step_by_step(hidden, lat_h, lat_w, K, cfg_scale, in_place, mode):
+    """The output layer of a drafting step computes the step's mean and next draft; the first step reads the state and the feature where
+    the caller has them.  Every step against the drafter's forward on the same state and the update in 64 bits."""
+    import torch
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("tiny", lat_h=lat_h, lat_w=lat_w, hidden=hidden, heads=max(1, hidden // 64), mlp_hidden=2 * hidden, depth=1)
+    w, wd = pu.weights_for(cfg, mode, seed=31), synth.make_drafter_weights(cfg, 1, seed=32, bf16_values=(mode == "bf16"))
+    target = binding.FreeDit(cfg, w, mode)
+    drafter = binding.FreeDrafter(target, wd, 1)
+    _, di, cx, ce, sigma = _draft_inputs(cfg, K, 33, cfg_scale)
+    buf = dict(x_states=torch.zeros(K, cfg["in_ch"], lat_h, lat_w, device="cuda"), x_last=torch.zeros(synth.latent_dim(cfg), device="cuda"),
+               m_draft=torch.zeros(K, synth.latent_dim(cfg), device="cuda"), f_last=torch.zeros(tuple(di["f_a"].shape), device="cuda"))
+    x_a = pu.to_dev(di["x_a"])
+    if in_place:
+        buf["x_states"][0] = x_a
+        x_a = buf["x_states"][0]
+    coef = [pu.to_dev(np.asarray(v, np.float32)) for v in (cx, ce, sigma)]
+    out = drafter.draft_round(x_a, pu.to_dev(di["f_a"]), pu.to_dev(di["t"]), di["y"], cfg_scale, *coef, pu.to_dev(di["xi"]), out=buf)
+    states = torch.cat([out["x_states"].reshape(K, -1), out["x_last"].reshape(1, -1)]).double().cpu().numpy()
+    assert np.array_equal(states[0].astype(np.float32), np.asarray(di["x_a"], np.float32).reshape(-1))
+    dup = 2 if cfg_scale > 1.0 else 1
+    feat = pu.to_dev(np.asarray(di["f_a"], np.float32)).reshape(dup, synth.n_tokens(cfg), hidden)
+    shape = (1, cfg["in_ch"], lat_h, lat_w)
+    for k in range(K):
+        x = out["x_states"].reshape(K, *shape[1:])[k:k + 1].repeat(dup, 1, 1, 1).contiguous()
+        t = pu.to_dev(np.full(dup, di["t"][k], np.int32))
+        y = pu.to_dev(np.array([di["y"], cfg["num_classes"]][:dup], np.int32))
+        eps, feat = drafter.drafter_forward(x, feat.contiguous(), t, y)
+        e = eps.double().cpu().numpy().reshape(dup, -1, lat_h, lat_w)[:, :cfg["in_ch"]].reshape(dup, -1)
+        guided = e[1] + np.float64(np.float32(cfg_scale)) * (e[0] - e[1]) if dup == 2 else e[0]
+        m = np.float64(np.float32(cx[k])) * states[k] + np.float64(np.float32(ce[k])) * guided
+        nxt = m + np.float64(np.float32(sigma[k])) * np.asarray(di["xi"], np.float32).reshape(K, -1)[k].astype(np.float64)
+        got = out["m_draft"].reshape(K, -1)[k].double().cpu().numpy()
+        # three fp32 roundings of terms of the size of m; the noise estimates are the same bits
+        assert pu.rel_l2(got, m) < 3 * 2.0 ** -23 and pu.rel_l2(states[k + 1], nxt) < 3 * 2.0 ** -23, k
+    assert torch.equal(out["f_last"].reshape(-1), feat.reshape(-1))
+    drafter.close()
+    target.close()
+
+
 def test_draft_then_verify_round_chain():
     """Drafting loop -> verification round on the GPU, against the same chain in the oracle: the outputs
     of draft_round are exactly the inputs of spec_round (Alg. 1)."""
