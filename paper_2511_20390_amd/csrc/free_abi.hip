@@ -390,6 +390,10 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         return p;
     };
     const bool split_fc2 = cut && linear_split_covers(d.D, d.F);
+    // the order in which the workgroups of the MLP's second layer take its weights
+    const int32_t lines = d.F * 2 / 128 / kSplitParts;
+    const int32_t lines_last = split_fc2 && attn_ahead && linear_split_pays(M, d.D, d.F, true) ? lines : 0;
+    const int32_t lines_other = split_fc2 && attn_ahead && linear_split_pays(M, d.D, d.F, false) ? lines : 0;
     for (int l = 0; l < nblk; ++l) {
         // x += gate1 * Proj(Attn(LN(x)(1+scale1)+shift1))
         if (fold && l > 0) {
@@ -414,7 +418,9 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
         }
         {
             ProfScope prof(pf, PROF_ATTN, s);
-            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, ahead(attn_ahead, l, B_FC1_W, DF, B_FC2_W, DF), split_keys));
+            Prefetch pre = ahead(attn_ahead, l, B_FC1_W, DF, B_FC2_W, DF);
+            pre.part_lines = l + 1 == nblk ? lines_last : lines_other;
+            FREE_TRY(attention_dispatch(d, qkv_h, nb, att_h, s, pre, split_keys));
         }
         if (fold) {
             // the out-projection also prepares the second LayerNorm: z = x (1 + scale2), partial row sums

@@ -120,6 +120,7 @@ struct ResidJoin {
 struct Prefetch {
     const void* p[2] = {nullptr, nullptr};
     int64_t bytes[2] = {0, 0};
+    int32_t part_lines = 0;                                  // p[1] is used in kSplitParts parts of its rows: 128-byte lines of each; 0: whole
     int blocks(int threads = 256) const {                    // workgroups of that many threads, a multiple of 8
         const int64_t per_block = static_cast<int64_t>(threads) << 8;
         return static_cast<int>(((bytes[0] + bytes[1] + per_block - 1) / per_block + 7) / 8 * 8);

@@ -60,11 +60,14 @@ __device__ __forceinline__ void sched_hints() {
 // XCD-aware tile order: workgroup ids are dealt round-robin to the 8 XCDs, so the
 // ids of one XCD are made contiguous first, then walked in groups of kGroupM row
 // tiles (column-major inside a group) so concurrent workgroups share X and W panels.
-__device__ inline void tile_coords(int kGroupM, int pid, int tiles_m, int tiles_n, int* tm, int* tn) {
-    const int total = tiles_m * tiles_n;
+__device__ inline int xcd_tile(int pid, int total) {
     const int q = total / kNumXcd, r = total % kNumXcd;
     const int x = pid % kNumXcd, j = pid / kNumXcd;
-    const int npid = x * q + (x < r ? x : r) + j;
+    return x * q + (x < r ? x : r) + j;
+}
+
+__device__ inline void tile_coords(int kGroupM, int pid, int tiles_m, int tiles_n, int* tm, int* tn) {
+    const int npid = xcd_tile(pid, tiles_m * tiles_n);
     const int per_group = kGroupM * tiles_n;
     const int group = npid / per_group;
     const int first_m = group * kGroupM;

@@ -32,6 +32,13 @@ __device__ inline void prefetch_lines(const Prefetch& pf, int first) {
         at[m] = xcd * eighth + lo + threadIdx.x;
         end[m] = xcd * eighth + hi < lines ? xcd * eighth + hi : lines;
     }
+    // line i of a matrix; where its GEMM takes it in parts of K: the lines of part 0 of all rows, then those of part 1, ...
+    auto where = [&](int m, uint32_t i) -> int64_t {
+        if (m == 0 || pf.part_lines == 0) return static_cast<int64_t>(i) << 7;
+        const uint32_t per = pf.part_lines, lines = static_cast<uint32_t>(pf.bytes[1] >> 7) / kSplitParts;
+        const uint32_t part = i / lines, in_part = i - part * lines, row = in_part / per;
+        return static_cast<int64_t>((row * kSplitParts + part) * per + (in_part - row * per)) << 7;
+    };
     uint32_t acc = 0;
     while (at[0] < end[0] || at[1] < end[1]) {
         uint32_t v[2][2];
@@ -39,7 +46,7 @@ __device__ inline void prefetch_lines(const Prefetch& pf, int first) {
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int k = 0; k < 2; ++k, at[m] += blockDim.x)
-                v[m][k] = at[m] < end[m] ? *reinterpret_cast<const uint32_t*>(base[m] + (static_cast<int64_t>(at[m]) << 7)) : 0u;
+                v[m][k] = at[m] < end[m] ? *reinterpret_cast<const uint32_t*>(base[m] + where(m, at[m])) : 0u;
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
