@@ -24,24 +24,22 @@ constexpr int kMaxFinalLds = 160 * 1024;          // LDS of one CU: the final pr
 // ---------------------------------------------------------------------------
 // temb[b, :] = [cos(t w_j) | sin(t w_j)], w_j = 10000^(-j/half).  The angle is
 // formed in fp64 (t up to 999 times w_0 = 1 would lose 4 digits in fp32).
-__global__ void timestep_embed_kernel(const int32_t* __restrict__ t, int32_t B, int32_t tfreq,
-                                      float* __restrict__ temb) {
+__global__ void timestep_embed_kernel(CondIn in, int32_t B, int32_t tfreq, float* __restrict__ temb) {
     const int half = tfreq / 2;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= B * half) return;
     const int b = idx / half, j = idx % half;
     const double w = exp(-9.210340371976184 * static_cast<double>(j) / static_cast<double>(half));
-    const double ang = static_cast<double>(t[b]) * w;
+    const double ang = static_cast<double>(in.timestep(b)) * w;
     temb[b * tfreq + j] = static_cast<float>(cos(ang));
     temb[b * tfreq + half + j] = static_cast<float>(sin(ang));
 }
 
-// out[b, j] = act(sum_i in[b, i] W[j, i] + bias[j] + table[row[b], j]); one wavefront per (b, j).
+// out[b, j] = act(sum_i in[b, i] W[j, i] + bias[j] + table[label of b, j]); one wavefront per (b, j).
 template <bool SILU>
 __global__ __launch_bounds__(kThreads) void small_linear_kernel(
     const float* __restrict__ in, int32_t B, int32_t K, int32_t N, const float* __restrict__ W,
-    const float* __restrict__ bias, const float* __restrict__ table, const int32_t* __restrict__ row,
-    float* __restrict__ out) {
+    const float* __restrict__ bias, const float* __restrict__ table, CondIn row, float* __restrict__ out) {
     const int j = blockIdx.x * kWaves + (threadIdx.x >> 6);
     const int b = blockIdx.y;
     const int lane = threadIdx.x & 63;
@@ -53,7 +51,7 @@ __global__ __launch_bounds__(kThreads) void small_linear_kernel(
     acc = wave_sum(acc);
     if (lane == 0) {
         float v = acc + bias[j];
-        if (table) v += table[static_cast<int64_t>(row[b]) * N + j];
+        if (table) v += table[static_cast<int64_t>(row.label_of(b)) * N + j];
         out[static_cast<int64_t>(b) * N + j] = SILU ? silu_f(v) : v;
     }
 }
@@ -64,8 +62,7 @@ __global__ __launch_bounds__(kThreads) void small_linear_kernel(
 template <bool SILU>
 __global__ __launch_bounds__(kThreads) void small_linear_rows_kernel(
     const float* __restrict__ in, int32_t B, int32_t K, int32_t N, const float* __restrict__ W,
-    const float* __restrict__ bias, const float* __restrict__ table, const int32_t* __restrict__ row,
-    float* __restrict__ out) {
+    const float* __restrict__ bias, const float* __restrict__ table, CondIn row, float* __restrict__ out) {
     constexpr int kSamples = 8;
     const int j = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -95,7 +92,7 @@ __global__ __launch_bounds__(kThreads) void small_linear_rows_kernel(
         const int b = b0 + lane;
         if (lane < kSamples && b < B) {
             float v = mine + bias[j];
-            if (table) v += table[static_cast<int64_t>(row[b]) * N + j];
+            if (table) v += table[static_cast<int64_t>(row.label_of(b)) * N + j];
             out[static_cast<int64_t>(b) * N + j] = SILU ? silu_f(v) : v;
         }
     }
@@ -1025,41 +1022,33 @@ __global__ void eps_to_mean_kernel(const float* __restrict__ eps_out, const floa
     if (x_next) x_next[idx] = fmaf(sigma_step[k], xi[idx], m);
 }
 
-__global__ void pack_cond_kernel(const int32_t* __restrict__ t, int32_t y, int32_t null_label, int32_t K,
-                                 int32_t dup, int32_t* __restrict__ t_out, int32_t* __restrict__ y_out) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= K * dup) return;
-    t_out[b] = t[b % K];
-    y_out[b] = (b < K) ? y : null_label;
-}
-
 }  // namespace
 
 // ============================ host launch wrappers ============================
 
-int32_t launch_conditioning(const int32_t* t, const int32_t* y, int32_t B, int32_t D, int32_t tfreq,
+int32_t launch_conditioning(const CondIn& in, int32_t B, int32_t D, int32_t tfreq,
                             const float* w1, const float* b1, const float* w2, const float* b2,
                             const float* ytab, float* h1, float* sc, hipStream_t s) {
     // h1 doubles as [B, tfreq] timestep embedding followed by [B, D] hidden
     float* temb = h1;
     float* hid = h1 + static_cast<int64_t>(B) * tfreq;
     const int n = B * (tfreq / 2);
-    hipLaunchKernelGGL(timestep_embed_kernel, dim3((n + 255) / 256), dim3(256), 0, s, t, B, tfreq, temb);
+    hipLaunchKernelGGL(timestep_embed_kernel, dim3((n + 255) / 256), dim3(256), 0, s, in, B, tfreq, temb);
     if (!launch_ok()) return FREE_ERR_HIP;
     auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
     if (tfreq % 4 == 0 && D % 4 == 0 && al16(h1) && al16(w1) && al16(w2)) {
         const dim3 g((D + kWaves - 1) / kWaves);
         hipLaunchKernelGGL(small_linear_rows_kernel<true>, g, dim3(kThreads), 0, s, temb, B, tfreq, D, w1, b1,
-                           static_cast<const float*>(nullptr), static_cast<const int32_t*>(nullptr), hid);
+                           static_cast<const float*>(nullptr), in, hid);
         if (!launch_ok()) return FREE_ERR_HIP;
-        hipLaunchKernelGGL(small_linear_rows_kernel<true>, g, dim3(kThreads), 0, s, hid, B, D, D, w2, b2, ytab, y, sc);
+        hipLaunchKernelGGL(small_linear_rows_kernel<true>, g, dim3(kThreads), 0, s, hid, B, D, D, w2, b2, ytab, in, sc);
         return launch_ok() ? FREE_OK : FREE_ERR_HIP;
     }
     dim3 g((D + kWaves - 1) / kWaves, B);
     hipLaunchKernelGGL(small_linear_kernel<true>, g, dim3(kThreads), 0, s, temb, B, tfreq, D, w1, b1,
-                       static_cast<const float*>(nullptr), static_cast<const int32_t*>(nullptr), hid);
+                       static_cast<const float*>(nullptr), in, hid);
     if (!launch_ok()) return FREE_ERR_HIP;
-    hipLaunchKernelGGL(small_linear_kernel<true>, g, dim3(kThreads), 0, s, hid, B, D, D, w2, b2, ytab, y, sc);
+    hipLaunchKernelGGL(small_linear_kernel<true>, g, dim3(kThreads), 0, s, hid, B, D, D, w2, b2, ytab, in, sc);
     if (!launch_ok()) return FREE_ERR_HIP;
     return FREE_OK;
 }
@@ -1450,14 +1439,6 @@ int32_t launch_eps_to_mean(const float* eps_out, const float* x_states, const fl
     hipLaunchKernelGGL(eps_to_mean_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, eps_out,
                        x_states, coef_x, coef_eps, cfg_scale, use_cfg, K, C, c_out, hw, m_out, eps_guided, sigma_step,
                        xi, x_next);
-    return launch_ok() ? FREE_OK : FREE_ERR_HIP;
-}
-
-int32_t launch_pack_cond(const int32_t* t, int32_t y, int32_t null_label, int32_t K, int32_t dup,
-                         int32_t* t_out, int32_t* y_out, hipStream_t s) {
-    const int n = K * dup;
-    hipLaunchKernelGGL(pack_cond_kernel, dim3((n + 63) / 64), dim3(64), 0, s, t, y, null_label, K, dup, t_out,
-                       y_out);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 

@@ -98,7 +98,7 @@ bool make_dims(const free_dit_config* c, Dims* o) {
 
 // Workspace carve-up for a forward on B packed states (offsets in bytes).
 struct WsLayout {
-    size_t cond_h, sc, mod, tpack, ypack, xres, xn, qkv, att, hmid, eps, mtarget, vpart, vpart_bytes, fold, stats, part, total;
+    size_t cond_h, sc, mod, xres, xn, qkv, att, hmid, eps, mtarget, vpart, vpart_bytes, fold, stats, part, total;
 };
 
 // floats per sample of the fold vectors: c1 of every block's QKV and MLP-1 rows, then c0 of the same
@@ -120,8 +120,6 @@ WsLayout make_layout(const Dims& d, int32_t B) {
     L.cond_h = take(static_cast<size_t>(B) * (d.tfreq + d.D) * 4);
     L.sc = take(static_cast<size_t>(B) * d.D * 4);
     L.mod = take(static_cast<size_t>(B) * d.mod_rows * 4);
-    L.tpack = take(static_cast<size_t>(B) * 4);
-    L.ypack = take(static_cast<size_t>(B) * 4);
     L.xres = take(M * d.D * 4);
     L.xn = take(M * d.D * es);
     L.qkv = take(M * 3 * d.D * es);
@@ -472,7 +470,7 @@ int32_t run_block_stack(const Dims& d, const void* const* blkw, int nblk, const 
     return FREE_OK;
 }
 
-int32_t forward_impl(free_dit_t h, const float* x, int32_t x_mod, const int32_t* t, const int32_t* y, int32_t B,
+int32_t forward_impl(free_dit_t h, const float* x, int32_t x_mod, const CondIn& cond, int32_t B,
                      float* eps_out, float* top_feat, char* ws, hipStream_t s) {
     const Dims& d = h->dims;
     const WsLayout L = make_layout(d, B);
@@ -488,7 +486,7 @@ int32_t forward_impl(free_dit_t h, const float* x, int32_t x_mod, const int32_t*
 
     {
     ProfScope prof(&h->prof, PROF_COND, s);
-    FREE_TRY(launch_conditioning(t, y, B, d.D, d.tfreq, static_cast<const float*>(h->w[W_T_W1]),
+    FREE_TRY(launch_conditioning(cond, B, d.D, d.tfreq, static_cast<const float*>(h->w[W_T_W1]),
                                  static_cast<const float*>(h->w[W_T_B1]), static_cast<const float*>(h->w[W_T_W2]),
                                  static_cast<const float*>(h->w[W_T_B2]),
                                  static_cast<const float*>(h->w[W_Y_TABLE]), cond_h, sc, s));
@@ -841,7 +839,7 @@ int32_t dit_forward_packed(free_dit_t h, const float* x, const int32_t* t, const
     if (!h || !x || !t || !y || !eps_out) return FREE_ERR_NULL;
     if (B < 1 || static_cast<int64_t>(B) * h->dims.ntok > INT32_MAX / 4) return FREE_ERR_SHAPE;
     FREE_TRY(check_ws(workspace, ws_bytes, make_layout(h->dims, B).total));
-    return forward_impl(h, x, B, t, y, B, eps_out, top_feat, static_cast<char*>(workspace),
+    return forward_impl(h, x, B, CondIn{t, y}, B, eps_out, top_feat, static_cast<char*>(workspace),
                         static_cast<hipStream_t>(stream));
 }
 
@@ -868,7 +866,7 @@ int32_t free_dit_tune(free_dit_t h, const float* x, const int32_t* t, const int3
         h->forced_streams = sched[i % ns];
         for (int r = 0; r < kTuneRun && st == FREE_OK; ++r) {
             if (r == 1 && !hip_ok(hipEventRecord(h->tune_ev[i][0], s))) st = FREE_ERR_HIP;
-            if (st == FREE_OK) st = forward_impl(h, x, B, t, y, B, eps_out, nullptr, static_cast<char*>(workspace), s);
+            if (st == FREE_OK) st = forward_impl(h, x, B, CondIn{t, y}, B, eps_out, nullptr, static_cast<char*>(workspace), s);
         }
         if (st == FREE_OK && !hip_ok(hipEventRecord(h->tune_ev[i][1], s))) st = FREE_ERR_HIP;
     }
@@ -990,12 +988,9 @@ int32_t spec_round(free_dit_t h, const float* x_states, const float* x_last, con
     FREE_TRY(check_ws(workspace, ws_bytes, L.total));
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t* tp = reinterpret_cast<int32_t*>(ws + L.tpack);
-    int32_t* yp = reinterpret_cast<int32_t*>(ws + L.ypack);
     float* eps = reinterpret_cast<float*>(ws + L.eps);
     float* mt = m_target_out ? m_target_out : reinterpret_cast<float*>(ws + L.mtarget);
-    FREE_TRY(launch_pack_cond(t, y, d.classes, K, dup, tp, yp, s));
-    FREE_TRY(forward_impl(h, x_states, K, tp, yp, B, eps, nullptr, ws, s));
+    FREE_TRY(forward_impl(h, x_states, K, CondIn{t, nullptr, K, y, d.classes}, B, eps, nullptr, ws, s));
     {
         ProfScope prof(&h->prof, PROF_EPS2MEAN, s);
         FREE_TRY(launch_eps_to_mean(eps, x_states, coef_x, coef_eps, cfg_scale, K, d.C, d.c_out,
@@ -1153,7 +1148,7 @@ namespace {
 constexpr int kHoistRows = 16;          // samples of one adaLN pass
 
 struct DraftLayout {
-    size_t cond_h, sc, mod, tpack, ypack, emb, fin, xn, qkv, att, hmid, eps, feat, part, total;
+    size_t cond_h, sc, mod, emb, fin, xn, qkv, att, hmid, eps, feat, part, total;
 };
 
 DraftLayout make_draft_layout(const Dims& d, int32_t mod_rows, int32_t B) {
@@ -1168,8 +1163,6 @@ DraftLayout make_draft_layout(const Dims& d, int32_t mod_rows, int32_t B) {
     L.cond_h = take(CB * (d.tfreq + d.D) * 4);
     L.sc = take(CB * d.D * 4);
     L.mod = take(CB * mod_rows * 4);
-    L.tpack = take(CB * 4);
-    L.ypack = take(CB * 4);
     L.emb = take(M * d.D * 4);
     L.fin = take(M * 2 * d.D * es);
     L.xn = take(M * d.D * es);
@@ -1187,11 +1180,11 @@ DraftLayout make_draft_layout(const Dims& d, int32_t mod_rows, int32_t B) {
 // residual stream of the drafter's blocks (it IS the predicted feature when they are done), and
 // f_prev is consumed before f_out is first written, so the two may alias.
 // Conditioning (shared embedding layers of the target) and the drafter's modulation vectors for B samples.
-int32_t drafter_modulation(free_drafter_t dr, const int32_t* t, const int32_t* y, int32_t B, float* cond_h, float* sc,
+int32_t drafter_modulation(free_drafter_t dr, const CondIn& cond, int32_t B, float* cond_h, float* sc,
                            float* mod, hipStream_t s) {
     free_dit_t h = dr->target;
     const Dims& d = h->dims;
-    FREE_TRY(launch_conditioning(t, y, B, d.D, d.tfreq, static_cast<const float*>(h->w[W_T_W1]),
+    FREE_TRY(launch_conditioning(cond, B, d.D, d.tfreq, static_cast<const float*>(h->w[W_T_W1]),
                                  static_cast<const float*>(h->w[W_T_B1]), static_cast<const float*>(h->w[W_T_W2]),
                                  static_cast<const float*>(h->w[W_T_B2]),
                                  static_cast<const float*>(h->w[W_Y_TABLE]), cond_h, sc, s));
@@ -1204,8 +1197,8 @@ int32_t drafter_modulation(free_drafter_t dr, const int32_t* t, const int32_t* y
 
 // mod_pre (nullable): modulation vectors computed by the caller, sample b at mod_pre + b * mod_stride; then t
 // and y are not read.  mean (nullable): instead of the noise estimates, which then only eps_out may hold.
-int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, const float* f_prev, const int32_t* t,
-                             const int32_t* y, int32_t B, float* eps_out, float* f_out, char* ws, hipStream_t s,
+int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, const float* f_prev, const CondIn& cond,
+                             int32_t B, float* eps_out, float* f_out, char* ws, hipStream_t s,
                              const float* mod_pre = nullptr, int32_t mod_stride = 0, const FinalMean* mean = nullptr) {
     free_dit_t h = dr->target;
     const Dims& d = h->dims;
@@ -1215,7 +1208,7 @@ int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, c
     float* sc = reinterpret_cast<float*>(ws + L.sc);
     const float* mod = mod_pre;
     if (!mod_pre) {
-        FREE_TRY(drafter_modulation(dr, t, y, B, cond_h, sc, reinterpret_cast<float*>(ws + L.mod), s));
+        FREE_TRY(drafter_modulation(dr, cond, B, cond_h, sc, reinterpret_cast<float*>(ws + L.mod), s));
         mod = reinterpret_cast<float*>(ws + L.mod);
         mod_stride = dr->mod_rows;
     }
@@ -1331,7 +1324,7 @@ int32_t drafter_forward(free_drafter_t dr, const float* x, const float* f_prev, 
     const Dims& d = dr->target->dims;
     FREE_TRY(check_ws(workspace, ws_bytes, make_draft_layout(d, dr->mod_rows, B).total));
     if ((reinterpret_cast<uintptr_t>(f_prev) | reinterpret_cast<uintptr_t>(f_out)) & 15u) return FREE_ERR_SHAPE;
-    return drafter_forward_impl(dr, x, B, f_prev, t, y, B, eps_out, f_out, static_cast<char*>(workspace),
+    return drafter_forward_impl(dr, x, B, f_prev, CondIn{t, y}, B, eps_out, f_out, static_cast<char*>(workspace),
                                 static_cast<hipStream_t>(stream));
 }
 
@@ -1351,8 +1344,6 @@ int32_t draft_round(free_drafter_t dr, const float* x_a, const float* f_a, const
     if ((reinterpret_cast<uintptr_t>(f_a) | reinterpret_cast<uintptr_t>(f_last)) & 15u) return FREE_ERR_SHAPE;
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t* tp = reinterpret_cast<int32_t*>(ws + L.tpack);
-    int32_t* yp = reinterpret_cast<int32_t*>(ws + L.ypack);
     float* eps = reinterpret_cast<float*>(ws + L.eps);
     float* feat = f_last ? f_last : reinterpret_cast<float*>(ws + L.feat);
     // The timesteps of all K steps are known: their conditioning and modulation vectors are computed in one
@@ -1360,8 +1351,7 @@ int32_t draft_round(free_drafter_t dr, const float* x_a, const float* f_a, const
     const bool hoist = K * dup <= kHoistRows;
     const float* mod_all = nullptr;
     if (hoist) {
-        FREE_TRY(launch_pack_cond(t, y, d.classes, K, dup, tp, yp, s));
-        FREE_TRY(drafter_modulation(dr, tp, yp, K * dup, reinterpret_cast<float*>(ws + L.cond_h),
+        FREE_TRY(drafter_modulation(dr, CondIn{t, nullptr, K, y, d.classes}, K * dup, reinterpret_cast<float*>(ws + L.cond_h),
                                     reinterpret_cast<float*>(ws + L.sc), reinterpret_cast<float*>(ws + L.mod), s));
         mod_all = reinterpret_cast<const float*>(ws + L.mod);
     }
@@ -1374,11 +1364,10 @@ int32_t draft_round(free_drafter_t dr, const float* x_a, const float* f_a, const
         const FinalMean mean{xk, coef_x + k, coef_eps + k, sigma + k, cfg_scale, dup, d.C, xi + static_cast<int64_t>(k) * d.d, mk, xn,
                              k == 0 && x_a != x_states ? x_states : nullptr};
         if (hoist) {
-            FREE_TRY(drafter_forward_impl(dr, xk, 1, fk, nullptr, nullptr, dup, eps, feat, ws, s,
+            FREE_TRY(drafter_forward_impl(dr, xk, 1, fk, CondIn{}, dup, eps, feat, ws, s,
                                           mod_all + static_cast<int64_t>(k) * dr->mod_rows, K * dr->mod_rows, &mean));
         } else {
-            FREE_TRY(launch_pack_cond(t + k, y, d.classes, 1, dup, tp, yp, s));
-            FREE_TRY(drafter_forward_impl(dr, xk, 1, fk, tp, yp, dup, eps, feat, ws, s, nullptr, 0, &mean));
+            FREE_TRY(drafter_forward_impl(dr, xk, 1, fk, CondIn{t + k, nullptr, 1, y, d.classes}, dup, eps, feat, ws, s, nullptr, 0, &mean));
         }
     }
     return FREE_OK;
@@ -1391,7 +1380,7 @@ namespace {
 // Workspace of the sampler: the target's and the drafter's own workspaces plus the round's buffers.
 struct LoopLayout {
     size_t ws_target, ws_draft, x_cur, x_states, x_last, m_draft, m_target, log_ratio, accept, n_accept, x_refl,
-        top_feat, feat, tp, yp, eps, eps_guided, dist, total;
+        top_feat, feat, eps, eps_guided, dist, total;
 };
 
 LoopLayout make_loop_layout(const Dims& d, int32_t drafter_mod_rows, int32_t L, int32_t dup) {
@@ -1412,8 +1401,6 @@ LoopLayout make_loop_layout(const Dims& d, int32_t drafter_mod_rows, int32_t L, 
     o.x_refl = take(dd);
     o.top_feat = take(drafter_mod_rows > 0 ? fd * L * dup : 0);
     o.feat = take(drafter_mod_rows > 0 ? fd * dup : dd);      // top-block features, or one frozen noise estimate
-    o.tp = take(static_cast<size_t>(L) * dup * 4);
-    o.yp = take(static_cast<size_t>(L) * dup * 4);
     o.eps = take(static_cast<size_t>(L) * dup * d.c_out * d.H * d.W * 4);
     o.eps_guided = take(dd * L);
     o.dist = take(sizeof(double) * FREE_MAX_DRAFTS);
@@ -1453,8 +1440,6 @@ int32_t sample_loop(free_dit_t h, free_drafter_t dr, const float* x_init, int32_
     float* x_cur = F(o.x_cur);
     float* feat = F(o.feat);
     float* top = F(o.top_feat);
-    int32_t* tp = reinterpret_cast<int32_t*>(ws + o.tp);
-    int32_t* yp = reinterpret_cast<int32_t*>(ws + o.yp);
     int32_t* n_acc_dev = reinterpret_cast<int32_t*>(ws + o.n_accept);
     const size_t dd = static_cast<size_t>(d.d) * 4, fd = static_cast<size_t>(d.ntok) * d.D * 4;
     const int64_t hw = static_cast<int64_t>(d.H) * d.W;
@@ -1468,8 +1453,8 @@ int32_t sample_loop(free_dit_t h, free_drafter_t dr, const float* x_init, int32_
     while (i < S) {
         if (!have_feat || i >= n_spec) {
             // plain target step: x_{i+1} = m_i + sigma_i xi_i; its top-block feature starts the next round
-            FREE_TRY(launch_pack_cond(tmap + i, y, d.classes, 1, dup, tp, yp, s));
-            FREE_TRY(forward_impl(h, x_cur, 1, tp, yp, dup, F(o.eps), frozen ? nullptr : feat, ws + o.ws_target, s));
+            FREE_TRY(forward_impl(h, x_cur, 1, CondIn{tmap + i, nullptr, 1, y, d.classes}, dup, F(o.eps), frozen ? nullptr : feat,
+                                  ws + o.ws_target, s));
             FREE_TRY(launch_eps_to_mean(F(o.eps), x_cur, coef_x + i, coef_eps + i, cfg_scale, 1, d.C, d.c_out, hw,
                                         F(o.m_target), s, frozen ? feat : nullptr, sigma + i,
                                         xi + static_cast<int64_t>(i) * d.d, x_cur));
@@ -1489,8 +1474,8 @@ int32_t sample_loop(free_dit_t h, free_drafter_t dr, const float* x_init, int32_
                                  xi + static_cast<int64_t>(i) * d.d, K, F(o.x_states), F(o.x_last), F(o.m_draft), feat,
                                  ws + o.ws_draft, make_draft_layout(d, dr->mod_rows, dup).total, s));
         const WsLayout TL = make_layout(d, B);
-        FREE_TRY(launch_pack_cond(tmap + i, y, d.classes, K, dup, tp, yp, s));
-        FREE_TRY(forward_impl(h, F(o.x_states), K, tp, yp, B, F(o.eps), frozen ? nullptr : top, ws + o.ws_target, s));
+        FREE_TRY(forward_impl(h, F(o.x_states), K, CondIn{tmap + i, nullptr, K, y, d.classes}, B, F(o.eps), frozen ? nullptr : top,
+                              ws + o.ws_target, s));
         FREE_TRY(launch_eps_to_mean(F(o.eps), F(o.x_states), coef_x + i, coef_eps + i, cfg_scale, K, d.C, d.c_out, hw,
                                     F(o.m_target), s, frozen ? eps_g : nullptr));
         if (eps_delta) FREE_TRY(launch_sqdist(F(o.m_draft), F(o.m_target), K, d.d, dist, s));

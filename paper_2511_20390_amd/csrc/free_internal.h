@@ -192,7 +192,15 @@ int32_t static_verify_scratch(void** ptr);
 int32_t launch_verify(const VerifyArgs& a, void* ws, size_t ws_bytes, hipStream_t s, hipEvent_t* ev4 = nullptr);
 
 // ---- simple DiT kernels, both dtypes (dit_kernels.hip) ---------------------------
-int32_t launch_conditioning(const int32_t* t, const int32_t* y, int32_t B, int32_t D, int32_t tfreq,
+// Timestep and label of every sample of a batch: t[b] and y[b], or, with steps > 0, those of a guided pack [conditional x steps | null
+// x steps]: t[b % steps], and label or null_label.
+struct CondIn {
+    const int32_t *t, *y;
+    int32_t steps = 0, label = 0, null_label = 0;
+    __host__ __device__ int32_t timestep(int b) const { return t[steps > 0 ? b % steps : b]; }
+    __host__ __device__ int32_t label_of(int b) const { return steps == 0 ? y[b] : b < steps ? label : null_label; }
+};
+int32_t launch_conditioning(const CondIn& in, int32_t B, int32_t D, int32_t tfreq,
                             const float* w1, const float* b1, const float* w2, const float* b2,
                             const float* ytab, float* h1, float* sc, hipStream_t s);
 // mod[b, r] = sum_i sc[b, i] W_r[i] + bias_r; rows r come from n_mats matrices of
@@ -234,8 +242,6 @@ int32_t launch_eps_to_mean(const float* eps_out, const float* x_states, const fl
                            const float* coef_eps, float cfg_scale, int32_t K, int32_t C, int32_t c_out,
                            int64_t hw, float* m_out, hipStream_t s, float* eps_guided = nullptr,
                            const float* sigma_step = nullptr, const float* xi = nullptr, float* x_next = nullptr);
-int32_t launch_pack_cond(const int32_t* t, int32_t y, int32_t null_label, int32_t K, int32_t dup,
-                         int32_t* t_out, int32_t* y_out, hipStream_t s);
 
 // drafter: fin = [emb | feat] in the compute type with emb the patch embedding, zero_out (nullable, may be feat) cleared.  One
 // launch where the patch embedding has its 16-byte form, else emb goes through `emb_buf`.
