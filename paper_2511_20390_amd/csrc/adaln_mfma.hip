@@ -21,8 +21,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8;                  // per workgroup: they share one staged copy of the activations
-constexpr int kThreads = 64 * kWaves;
 constexpr int kChunk = 6;                  // k-steps (1 KB of weights per wavefront each) per register set
 constexpr int kBatch = 16;
 
@@ -30,46 +28,45 @@ constexpr int kBatch = 16;
 // 2 * kChunk, so every load and product below is issued
 // unconditionally.  With the guards of the general form the compiler cannot count the loads in flight and waits
 // for all of them (vmcnt(0)) before the first product of a register set - the other set's loads included.
-template <bool kExact, bool kF32>
-__global__ __launch_bounds__(kThreads) void adaln_mfma_kernel(
+// kWaves per workgroup share one staged copy of the activations.
+template <bool kExact, bool kF32, int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void adaln_mfma_kernel(
     const float* __restrict__ sc, int32_t B, int32_t D, const void* const* __restrict__ w_tab,
     const float* const* __restrict__ b_tab, const int32_t* __restrict__ row_start, int32_t n_mats,
     int32_t total_rows, int32_t blocks_per_wave, float* __restrict__ mod) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int kThreads = 64 * kWaves;
     constexpr int kEl = kF32 ? 4 : 2;                       // bytes per weight
     const int row_bytes = D * kEl + 16;                     // odd number of 16-byte chunks per row
     char* s_hi = lds;                                       // (fp32 weights: the fp32 vector itself, one set)
-    char* s_lo = lds + kBatch * row_bytes;
+    char* s_lo = lds + B * row_bytes;
     // (the wavefront index is made a scalar: row blocks, matrix index and table lookups then stay in scalar
     // registers - as per-lane values every table lookup is a vector load whose wait drains the weight loads)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // stage SiLU(c) as hi + lo bf16 parts; rows past B are zero.  Every thread requests its (up to kStage) 16-byte
+    // stage SiLU(c) as hi + lo bf16 parts.  Every thread requests its (up to kStage) 16-byte
     // pieces before it converts the first one: one memory round trip per batch instead of one per piece, and this
     // prologue is exposed - all workgroups of the launch are resident at once and start with it.
     {
-        constexpr int kStage = 9;
-        const int per_row = D / 4, nvec = kBatch * per_row;
+        constexpr int kStage = kWaves == 2 ? 18 : 9;
+        const int per_row = D / 4, nvec = B * per_row;
         for (int base = tid; base < nvec; base += kThreads * kStage) {
             float4 v[kStage];
 #pragma unroll
             for (int u = 0; u < kStage; ++u) {
                 const int i = base + u * kThreads;
-                const int b = i / per_row, p = i - b * per_row;
-                const bool live = i < nvec && b < B;
-                v[u] = reinterpret_cast<const float4*>(sc + static_cast<int64_t>(live ? b : 0) * D)[live ? p : 0];
+                v[u] = reinterpret_cast<const float4*>(sc)[i < nvec ? i : 0];
             }
 #pragma unroll
             for (int u = 0; u < kStage; ++u) {
                 const int i = base + u * kThreads;
                 if (i < nvec) {
                     const int b = i / per_row, p = i - b * per_row;
-                    const bool live = b < B;
-                    const float x0 = live ? v[u].x : 0.f, x1 = live ? v[u].y : 0.f, x2 = live ? v[u].z : 0.f, x3 = live ? v[u].w : 0.f;
                     if constexpr (kF32) {
-                        *reinterpret_cast<float4*>(s_hi + b * row_bytes + p * 16) = float4{x0, x1, x2, x3};
+                        *reinterpret_cast<float4*>(s_hi + b * row_bytes + p * 16) = v[u];
                         continue;
                     }
+                    const float x0 = v[u].x, x1 = v[u].y, x2 = v[u].z, x3 = v[u].w;
                     const uint32_t h0 = pack_bf16_pair(x0, x1), h1 = pack_bf16_pair(x2, x3);
                     const uint32_t l0 = pack_bf16_pair(x0 - __uint_as_float(h0 << 16), x1 - __uint_as_float(h0 & 0xffff0000u));
                     const uint32_t l1 = pack_bf16_pair(x2 - __uint_as_float(h1 << 16), x3 - __uint_as_float(h1 & 0xffff0000u));
@@ -84,8 +81,10 @@ __global__ __launch_bounds__(kThreads) void adaln_mfma_kernel(
     const int l16 = lane & 15, lq = lane >> 4;
     const int nblocks = total_rows / 16;
     const int first = (blockIdx.x * kWaves + wave) * blocks_per_wave;
-    const char* bh = s_hi + l16 * row_bytes + lq * 16;
-    const char* bl = s_lo + l16 * row_bytes + lq * 16;
+    // (columns past B repeat the last sample and are not stored)
+    const int column = l16 < B ? l16 : B - 1;
+    const char* bh = s_hi + column * row_bytes + lq * 16;
+    const char* bl = s_lo + column * row_bytes + lq * 16;
     const int steps = D * kEl / 64;
     // Weight rows stream through two register sets of kChunk k-steps each: the loads of one set are in
     // flight while the other is multiplied, across row blocks too (the first chunk of the next block is
@@ -202,22 +201,28 @@ int32_t launch_adaln_mfma(const float* sc, int32_t B, int32_t D, const void* con
     // about 16 wavefronts per CU at the DiT-XL size (12096 row blocks): measured best among 2, 3, 6, 12
     const int blocks_per_wave = nblocks >= 8192 ? 3 : 1;
     const int waves = (nblocks + blocks_per_wave - 1) / blocks_per_wave;
-    const int grid = (waves + kWaves - 1) / kWaves;
+    // Eight wavefronts per workgroup, or two where eight would leave half of the CUs without one: a CU takes in 46 KB/us from HBM, a
+    // workgroup of two stages the activations in more round trips.  One block at width 1152 (576 wavefronts) 14.4 -> 9.5 us for 4
+    // samples, 13.8 -> 11.3 for 12; twelve blocks at width 384 (1776) 9.0 with eight, 10.2 with two.
+    const bool narrow = waves < 4 * device_cus();
+    const int per_group = narrow ? 2 : 8, grid = (waves + per_group - 1) / per_group;
     const int el = f32 ? 4 : 2;
-    const size_t lds = (f32 ? 1 : 2) * static_cast<size_t>(kBatch) * (D * el + 16);
     const int steps = D * el / 64;
     const bool exact = steps >= 2 * kChunk && steps % (2 * kChunk) == 0;
     using kernel_t = void (*)(const float*, int32_t, int32_t, const void* const*, const float* const*, const int32_t*,
                               int32_t, int32_t, int32_t, float*);
-    static const kernel_t kernels[4] = {adaln_mfma_kernel<false, false>, adaln_mfma_kernel<true, false>,
-                                        adaln_mfma_kernel<false, true>, adaln_mfma_kernel<true, true>};
-    const int which = 2 * f32 + exact;
+    static const kernel_t kernels[8] = {adaln_mfma_kernel<false, false, 8>, adaln_mfma_kernel<true, false, 8>,
+                                        adaln_mfma_kernel<false, true, 8>,  adaln_mfma_kernel<true, true, 8>,
+                                        adaln_mfma_kernel<false, false, 2>, adaln_mfma_kernel<true, false, 2>,
+                                        adaln_mfma_kernel<false, true, 2>,  adaln_mfma_kernel<true, true, 2>};
+    const int which = 4 * narrow + 2 * f32 + exact;
     const kernel_t kernel = kernels[which];
-    static LdsLimit limit[4];
+    static LdsLimit limit[8];
     if (!limit[which].allow(reinterpret_cast<const void*>(kernel), 150 * 1024)) return FREE_ERR_HIP;
     for (int b0 = 0; b0 < B; b0 += kBatch) {
         const int nb = (B - b0 < kBatch) ? B - b0 : kBatch;
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, sc + static_cast<int64_t>(b0) * D,
+        const size_t lds = (f32 ? 1 : 2) * static_cast<size_t>(nb) * (D * el + 16);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * per_group), lds, s, sc + static_cast<int64_t>(b0) * D,
                            nb, D, w_tab, b_tab, row_start, n_mats, total_rows, blocks_per_wave,
                            mod + static_cast<int64_t>(b0) * total_rows);
         if (!launch_ok()) return FREE_ERR_HIP;
