@@ -289,7 +289,7 @@ int32_t launch_linear_pipe(const bf16_t* X, const bf16_t* W, const float* bias, 
 // ... and gemm_rows.hip (few rows; N % 8 == 0 and 16-byte aligned operands, checked by linear_rows_covers)
 enum RowsTile { ROWS_64x64, ROWS_128x64, ROWS_128x128 };
 int32_t launch_linear_rows(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile, bool from_zero = false);
 int32_t launch_linear_rows(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
                            float* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile);
 bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* bias, const void* out, const float* resid,
@@ -300,7 +300,9 @@ bool linear_rows_covers(int32_t N, int32_t K, int32_t elem_bytes, const float* b
 bool linear_split_covers(int32_t N, int32_t K);
 bool linear_split_pays(int32_t M, int32_t N, int32_t K, bool own_launch);
 int32_t launch_linear_split(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, float* resid,
-                            RowVec gate, float* part, bool own_launch, ResidJoin* join, hipStream_t s);
+                            RowVec gate, float* part, bool own_launch, ResidJoin* join, hipStream_t s, bool from_zero = false);
+// whether it can take resid as zero instead of reading it (from_zero; where the parts are left, the next kernel can)
+bool linear_split_from_zero(int32_t M, int32_t N, int32_t K, bool own_launch);
 // fp32 operands and results, K a multiple of 32, products on the bf16 matrix instructions (gemm_f32.hip)
 bool linear_f32_covers(const float* X, const float* W, int32_t M, int32_t N, int32_t K);
 int32_t launch_linear_f32(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,

@@ -592,21 +592,27 @@ bool linear_split_pays(int32_t M, int32_t N, int32_t K, bool own_launch) {
     return t_split + t_join < t_one;
 }
 
+bool linear_split_from_zero(int32_t M, int32_t N, int32_t K, bool own_launch) {
+    return linear_split_pays(M, N, K, own_launch) || choose(M, N, K, 2, FREE_EPI_GATE_RESID_SEG, true, 1).family == TILE_ROWS;
+}
+
 int32_t launch_linear_split(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, float* resid,
-                            RowVec gate, float* part, bool own_launch, ResidJoin* join, hipStream_t s) {
+                            RowVec gate, float* part, bool own_launch, ResidJoin* join, hipStream_t s, bool from_zero) {
     if (!mfma_linear_supported(M, N, K) || !linear_split_covers(N, K) || !linear_rows_covers(N, K, 2, bias, part, resid, gate))
         return FREE_ERR_SHAPE;
     if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(W)) & 15u) return FREE_ERR_SHAPE;
     if (linear_split_pays(M, N, K, own_launch)) {
         double t;
         const TileTime* tile = best_split_tile(M, N, K, &t);
-        *join = ResidJoin{part, bias, gate, 0};
+        *join = ResidJoin{part, bias, gate, from_zero};
         return launch_linear_rows(X, W, nullptr, M, N, K, FREE_EPI_PARTIAL, nullptr, part, RowVec{nullptr, 0, 1}, s,
                                   static_cast<RowsTile>(tile->tile));
     }
     const Choice c = choose(M, N, K, 2, FREE_EPI_GATE_RESID_SEG, true, 1);
     if (c.family == TILE_ROWS)
-        return launch_linear_rows(X, W, bias, M, N, K, FREE_EPI_GATE_RESID_SEG, nullptr, resid, gate, s, static_cast<RowsTile>(c.tile));
+        return launch_linear_rows(X, W, bias, M, N, K, FREE_EPI_GATE_RESID_SEG, nullptr, resid, gate, s, static_cast<RowsTile>(c.tile),
+                                  from_zero);
+    if (from_zero) return FREE_ERR_SHAPE;
     return launch_linear_pipe(X, W, bias, M, N, K, FREE_EPI_GATE_RESID_SEG, nullptr, resid, gate, s, static_cast<PipeTile>(c.tile),
                               nullptr);
 }

@@ -34,7 +34,7 @@ namespace {
 template <typename T, int BM, int BN, int WGM, int WGN, int S, int EPI>
 __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
     const T* __restrict__ X, const T* __restrict__ W, const float* __restrict__ bias, int32_t M, int32_t N, int32_t K,
-    int32_t tiles_m, int32_t tiles_n, T* __restrict__ out, float* __restrict__ resid, RowVec gate) {
+    int32_t tiles_m, int32_t tiles_n, T* __restrict__ out, float* __restrict__ resid, RowVec gate, int32_t from_zero) {
     constexpr bool kF32 = std::is_same<T, float>::value;
     constexpr bool kSeg = EPI == FREE_EPI_GATE_RESID_SEG, kResid = EPI == FREE_EPI_GATE_RESID || kSeg;
     constexpr bool kGelu = EPI == FREE_EPI_BIAS_GELU, kPart = EPI == FREE_EPI_PARTIAL;
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_rows_kernel(
                 for (int q = 0; q < 4; ++q) {
                     const int gm = gm_lane + i * 32, gn = gn_lane + j * 32 + 8 * q;
                     const bool ok = gm < M && gn < N;
-                    pre_r[i][j][q] = ok ? *reinterpret_cast<const f32x4_t*>(resid + static_cast<int64_t>(gm) * N + gn) : zero4;
+                    pre_r[i][j][q] = ok && !from_zero ? *reinterpret_cast<const f32x4_t*>(resid + static_cast<int64_t>(gm) * N + gn) : zero4;
                     pre_g[i][j][q] = ok ? *reinterpret_cast<const f32x4_t*>(gate.base + static_cast<int64_t>(gm / gate.rows_per_sample) * gate.stride + gn) : zero4;
                 }
     };
@@ -333,6 +333,7 @@ struct Args {
     float* resid;
     RowVec gate;
     hipStream_t s;
+    bool from_zero;                        // the residual stream counts as zero and is not read
 };
 
 template <typename T, int BM, int BN, int WGM, int WGN, int S, int EPI>
@@ -344,7 +345,7 @@ int32_t launch_one(const Args<T>& a) {
     if (!limit.allow(reinterpret_cast<const void*>(kern), lds)) return FREE_ERR_HIP;
     constexpr int kParts = EPI == FREE_EPI_PARTIAL ? kSplitParts : 1;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * kParts), dim3(WGM * WGN * 64), lds, a.s, a.X, a.W, a.bias, a.M, a.N, a.K, tiles_m,
-                       tiles_n, a.out, a.resid, a.gate);
+                       tiles_n, a.out, a.resid, a.gate, a.from_zero ? 1 : 0);
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 
@@ -386,13 +387,13 @@ static int32_t launch_rows(const Args<T>& a, int32_t epi, RowsTile tile) {
 }
 
 int32_t launch_linear_rows(const bf16_t* X, const bf16_t* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
-                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile) {
-    return launch_rows(Args<bf16_t>{X, W, bias, M, N, K, out, resid, gate, s}, epi, tile);
+                           bf16_t* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile, bool from_zero) {
+    return launch_rows(Args<bf16_t>{X, W, bias, M, N, K, out, resid, gate, s, from_zero}, epi, tile);
 }
 
 int32_t launch_linear_rows(const float* X, const float* W, const float* bias, int32_t M, int32_t N, int32_t K, int32_t epi,
                            float* out, float* resid, RowVec gate, hipStream_t s, RowsTile tile) {
-    return launch_rows(Args<float>{X, W, bias, M, N, K, out, resid, gate, s}, epi, tile);
+    return launch_rows(Args<float>{X, W, bias, M, N, K, out, resid, gate, s, false}, epi, tile);
 }
 
 }  // namespace freemi
