@@ -145,10 +145,11 @@ def test_draft_round_parity(name, K, cfg_scale, depth, mode):
 
 
 # tokens that are no multiple of a workgroup's 16 (8 per state under guidance), fewer than one workgroup's, a width whose output layer
-# has no matrix-core kernel (64); the state in place (the first of the pack already)
+# has no matrix-core kernel (64); the state in place (the first of the pack already); rows for which the fusion layer is one workgroup per
+# tile (1250).  Nothing that is written may have been read before: the outputs start as NaN
 @pytest.mark.parametrize("mode", ["fp32", "bf16"])
 @pytest.mark.parametrize("hidden,lat_h,lat_w,K,cfg_scale,in_place", [(384, 18, 22, 3, 4.0, False), (384, 18, 22, 2, 1.0, False), (768, 2, 6, 2, 1.5, False),
-                                                                     (1152, 10, 14, 1, 4.0, True), (64, 18, 22, 3, 4.0, False)])
+                                                                     (1152, 10, 14, 1, 4.0, True), (64, 18, 22, 3, 4.0, False), (1152, 50, 50, 2, 4.0, False)])
 def test_draft_round_step_by_step(hidden, lat_h, lat_w, K, cfg_scale, in_place, mode):
     """The output layer of a drafting step computes the step's mean and next draft; the first step reads the state and the feature where
     the caller has them.  Every step against the drafter's forward on the same state and the update in 64 bits."""
@@ -159,8 +160,9 @@ def test_draft_round_step_by_step(hidden, lat_h, lat_w, K, cfg_scale, in_place, 
     target = binding.FreeDit(cfg, w, mode)
     drafter = binding.FreeDrafter(target, wd, 1)
     _, di, cx, ce, sigma = _draft_inputs(cfg, K, 33, cfg_scale)
-    buf = dict(x_states=torch.zeros(K, cfg["in_ch"], lat_h, lat_w, device="cuda"), x_last=torch.zeros(synth.latent_dim(cfg), device="cuda"),
-               m_draft=torch.zeros(K, synth.latent_dim(cfg), device="cuda"), f_last=torch.zeros(tuple(di["f_a"].shape), device="cuda"))
+    nan = lambda *shape: torch.full(shape, float("nan"), device="cuda")
+    buf = dict(x_states=nan(K, cfg["in_ch"], lat_h, lat_w), x_last=nan(synth.latent_dim(cfg)), m_draft=nan(K, synth.latent_dim(cfg)),
+               f_last=nan(*di["f_a"].shape))
     x_a = pu.to_dev(di["x_a"])
     if in_place:
         buf["x_states"][0] = x_a
