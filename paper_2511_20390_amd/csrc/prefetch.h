@@ -7,7 +7,7 @@ namespace freemi {
 
 // Workgroups first .. gridDim.x - 1 of a launch (first and their number multiples of 8) read one word of every
 // 128-byte line of the matrices.  Workgroup ids are dealt round-robin to the 8 XCDs, and the few-row GEMMs give each XCD a
-// contiguous eighth of the weight rows, so XCD x reads eighth x.
+// contiguous eighth of the weight rows (where K is summed in parts: of the rows of part 0, then of part 1, ...), so XCD x reads eighth x.
 // What it buys: a CU takes in 46 KB/us from HBM, 85 from the Infinity Cache, 120 from its L2, and the few-row GEMMs are bound
 // by that.  The LayerNorm in front of QKV (latency-bound, 5 us) loads the QKV and out-projection weights of its block, the
 // attention kernel (idle CUs at few rows) those of the MLP.  512 rows at width 1152, us per launch without -> with: QKV 10.7
