@@ -56,18 +56,15 @@ __global__ __launch_bounds__(kThreads) void small_linear_kernel(
     }
 }
 
-// The same with one wavefront per output column j for ALL samples: the weight row is read once per four samples
+// The same with one wavefront per output column j for ALL samples: the weight row is read once per kSamples samples
 // instead of once per sample, in 16-byte pieces, and a launch has N / 4 workgroups instead of B N / 4
 // (K % 4 == 0, 16-byte aligned rows).  Sample b0 + q is reduced in lane order and written by lane q.
-// A chain of memory round trips: kPieces pieces of the row and of the samples are in flight together (K = 1152 is one pass), and what is
-// added to the sum - bias, and the label's row of the table behind the label - is requested in front of them.
-// us per launch at width 1152, two pieces in flight and eight samples per pass -> here: 4 samples 5.5 -> 4.1, 12 samples 8.5 -> 7.2 (mean of
-// K = 256 and 1152).
-template <bool SILU>
+// A chain of memory round trips, one or two per pass over kSamples samples: kPieces pieces of the row and of the samples are in flight
+// together, and what is added to the sum - bias, and the label's row of the table behind the label - is requested in front of them.
+template <bool SILU, int kSamples, int kPieces>
 __global__ __launch_bounds__(kThreads) void small_linear_rows_kernel(
     const float* __restrict__ in, int32_t B, int32_t K, int32_t N, const float* __restrict__ W,
     const float* __restrict__ bias, const float* __restrict__ table, CondIn row, float* __restrict__ out) {
-    constexpr int kSamples = 4, kPieces = 5;
     const int j = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (j >= N) return;
@@ -93,12 +90,16 @@ __global__ __launch_bounds__(kThreads) void small_linear_rows_kernel(
                     xv[u][q] = reinterpret_cast<const float4*>(in + static_cast<int64_t>(bq) * K)[i];
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);                  // (requested together: the compiler would take them one by one)
 #pragma unroll
-            for (int u = 0; u < kPieces; ++u)
-                if (i0 + 64 * u < k4)
+            for (int u = 0; u < kPieces; ++u) {
+                const bool on = i0 + 64 * u < k4;               // (a select: behind a branch the compiler would request piece u there)
 #pragma unroll
-                    for (int q = 0; q < kSamples; ++q)
-                        acc[q] = fmaf(xv[u][q].w, wv[u].w, fmaf(xv[u][q].z, wv[u].z, fmaf(xv[u][q].y, wv[u].y, fmaf(xv[u][q].x, wv[u].x, acc[q]))));
+                for (int q = 0; q < kSamples; ++q) {
+                    const float t = fmaf(xv[u][q].w, wv[u].w, fmaf(xv[u][q].z, wv[u].z, fmaf(xv[u][q].y, wv[u].y, fmaf(xv[u][q].x, wv[u].x, acc[q]))));
+                    acc[q] = on ? t : acc[q];
+                }
+            }
         }
         float mine = 0.f;
 #pragma unroll
@@ -1042,6 +1043,30 @@ __global__ void eps_to_mean_kernel(const float* __restrict__ eps_out, const floa
 
 // ============================ host launch wrappers ============================
 
+static void launch_small_linear_rows(const float* x, int32_t B, int32_t K, int32_t N, const float* W, const float* bias, const float* table,
+                                     const CondIn& row, float* out, hipStream_t s) {
+    const dim3 g((N + kWaves - 1) / kWaves);
+#define FREE_ROWS(SAMPLES, PIECES) \
+    hipLaunchKernelGGL((small_linear_rows_kernel<true, SAMPLES, PIECES>), g, dim3(kThreads), 0, s, x, B, K, N, W, bias, table, row, out)
+    // Four samples per pass where eight would leave half a pass empty, up to three passes: all of a row of 1152 in flight; else eight, a
+    // pass less for every two, and as many pieces as the row has, up to three (108 registers).
+    // us per launch, eight samples and two pieces throughout / four and five throughout / here:
+    //             K = 256 (N = 1152)   K = 1152              K = 768              K = 384
+    //   1-4       4.3 / 3.9 / 3.3      6.7 / 4.7 / 4.8       5.0 / 3.9 / 3.9      4.5 / 3.7 / 3.7
+    //   8         4.4 / 5.4 / 3.9      6.7 / 7.0 / 7.3       5.2 / 5.5 / 4.6      4.6 / 5.2 / 3.8
+    //   12        5.6 / 6.8 / 4.8      10.9 / 9.1 / 9.6      7.8 / 7.2 / 7.2      7.0 / 6.7 / 6.7
+    //   16        5.5 / 8.2 / 5.0      11.7 / 11.7 / 10.9    7.8 / 8.7 / 6.7      7.0 / 8.1 / 5.5
+    //   32        7.8 / 14.1 / 7.7     17.8 / 18.6 / 18.2    12.7 / 14.3 / 11.0   12.2 / 13.9 / 8.7
+    //   64        12.5 / 23.7 / 11.9   31.3 / 34.0 / 32.8    22.0 / 26.1 / 18.3   21.7 / 24.7 / 14.7
+    const bool fours = B <= 12 && (B - 1) % 8 < 4;
+    if (fours && K <= 256) FREE_ROWS(4, 1);
+    else if (fours) FREE_ROWS(4, 5);
+    else if (K <= 256) FREE_ROWS(8, 1);
+    else if (K <= 512) FREE_ROWS(8, 2);
+    else FREE_ROWS(8, 3);
+#undef FREE_ROWS
+}
+
 int32_t launch_conditioning(const CondIn& in, int32_t B, int32_t D, int32_t tfreq,
                             const float* w1, const float* b1, const float* w2, const float* b2,
                             const float* ytab, float* h1, float* sc, hipStream_t s) {
@@ -1053,11 +1078,9 @@ int32_t launch_conditioning(const CondIn& in, int32_t B, int32_t D, int32_t tfre
     if (!launch_ok()) return FREE_ERR_HIP;
     auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; };
     if (tfreq % 4 == 0 && D % 4 == 0 && al16(h1) && al16(w1) && al16(w2)) {
-        const dim3 g((D + kWaves - 1) / kWaves);
-        hipLaunchKernelGGL(small_linear_rows_kernel<true>, g, dim3(kThreads), 0, s, temb, B, tfreq, D, w1, b1,
-                           static_cast<const float*>(nullptr), in, hid);
+        launch_small_linear_rows(temb, B, tfreq, D, w1, b1, nullptr, in, hid, s);
         if (!launch_ok()) return FREE_ERR_HIP;
-        hipLaunchKernelGGL(small_linear_rows_kernel<true>, g, dim3(kThreads), 0, s, hid, B, D, D, w2, b2, ytab, in, sc);
+        launch_small_linear_rows(hid, B, D, D, w2, b2, ytab, in, sc, s);
         return launch_ok() ? FREE_OK : FREE_ERR_HIP;
     }
     dim3 g((D + kWaves - 1) / kWaves, B);

@@ -107,3 +107,28 @@ def test_forced_streams_change_no_bit_of_small_batches():
         for r in res[1:]:
             assert torch.equal(r[0], res[0][0]) and torch.equal(r[1], res[0][1]), B
     model.close()
+
+
+# the conditioning's linear layers take four or eight samples per pass and one to five pieces of a row at once: rows of one piece, of a whole
+# number of pieces, of more than one pass; the modulation's and the embedding's launches go by the samples too (17: two modulation passes)
+@pytest.mark.parametrize("mode", ["bf16", "fp32"])
+@pytest.mark.parametrize("hidden,heads,t_freq", [(384, 6, 256), (512, 8, 64), (576, 8, 260), (1152, 16, 256), (2048, 16, 256)])
+def test_small_packs_of_every_size_same_bits(hidden, heads, t_freq, mode):
+    import torch
+    from oracle import free_oracle as fo
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("tiny", hidden=hidden, heads=heads, mlp_hidden=2 * hidden, depth=1, lat_h=2, lat_w=6, t_freq_dim=t_freq)
+    w = pu.weights_for(cfg, mode, 21)
+    model = binding.FreeDit(cfg, w, mode)
+    rng = np.random.default_rng(22)
+    x = rng.standard_normal((17, cfg["in_ch"], 2, 6)).astype(np.float32)
+    t, y = (rng.integers(0, n, 17).astype(np.int32) for n in (1000, cfg["num_classes"] + 1))
+    dev = [pu.to_dev(v) for v in (x, t, y)]
+    eps, feat = (v.clone() for v in model.dit_forward_packed(*dev, want_feat=True))
+    ref = fo.dit_forward(w, cfg, x, t, y)
+    assert pu.rel_l2(eps.cpu().numpy(), ref[0]) <= pu.DIT_REL_L2[mode] and pu.rel_l2(feat.cpu().numpy(), ref[1]) <= pu.DIT_REL_L2[mode]
+    for B in (1, 4, 5, 8, 9, 12, 13, 16):
+        eps1, feat1 = model.dit_forward_packed(*(v[:B].contiguous() for v in dev), want_feat=True)
+        assert torch.equal(eps1.reshape(-1), eps[:B].reshape(-1)), B
+        assert torch.equal(feat1.reshape(-1), feat.reshape(17, -1)[:B].reshape(-1)), B
+    model.close()
