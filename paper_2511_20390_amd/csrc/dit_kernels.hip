@@ -316,9 +316,9 @@ __global__ __launch_bounds__(kThreads) void patch_embed16_kernel(
 constexpr int kPeThreads = 320;            // 288 of them carry columns at D = 1152
 constexpr int kPeTok = 4;
 constexpr int kPeSamples = 16;
-static_assert(kPeThreads % (kPeTok * 16) == 0, "a thread gathers one pixel of every sample");
-template <typename FT>
-__global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
+// kGroup: threads of a workgroup.  (Aiming at four wavefronts per SIMD, the compiler puts feat's columns of the fp32 form into scratch memory.)
+template <typename FT, int kGroup>
+__global__ __launch_bounds__(kGroup) __attribute__((amdgpu_waves_per_eu(3, std::is_same<FT, float>::value ? 3 : 8))) void patch_embed16v_kernel(
     const float* __restrict__ x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p, int32_t D,
     const float* __restrict__ pw, const float* __restrict__ pb, const float* __restrict__ pos,
     void* __restrict__ out, int32_t ntok, const float* feat, float* zero_out) {
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
     const int gw = W / p;
     const int n0 = blockIdx.x * kPeTok, b0 = blockIdx.y * kPeSamples;
     const int nb = B - b0 < kPeSamples ? B - b0 : kPeSamples;
-    const int j0 = 4 * static_cast<int>(blockIdx.z * blockDim.x + threadIdx.x);
+    const int j0 = 4 * static_cast<int>(blockIdx.z * kGroup + threadIdx.x);
     const bool col_on = j0 < D;
     const int jc = col_on ? j0 : 0;                     // idle lanes re-read column 0 and store nothing
     float4 w[4][4];
@@ -342,21 +342,22 @@ __global__ __launch_bounds__(kPeThreads) void patch_embed16v_kernel(
         const int n = n0 + u < ntok ? n0 + u : ntok - 1;
         pe[u] = *reinterpret_cast<const float4*>(pos + static_cast<int64_t>(n) * D + jc);
     }
-    // (a workgroup has a whole multiple of kPeTok * 16 threads: a thread gathers the same pixel of every sample, four samples in flight)
-    {
-        const int e = threadIdx.x % (kPeTok * 16), tk = e >> 4, q = e & 15, n = n0 + tk, nc = n < ntok ? n : ntok - 1;
+    // a thread gathers the same pixel of every step-th sample, kAhead samples in flight
+    constexpr int kPixels = kPeTok * 16, step = kGroup / kPixels, kAhead = step == 1 ? 4 : 1;
+    static_assert(kGroup % kPixels == 0, "whole sets of pixels");
+    if (int sb = threadIdx.x / kPixels; sb < nb) {
+        const int e = threadIdx.x % kPixels, tk = e >> 4, q = e & 15, n = n0 + tk, nc = n < ntok ? n : ntok - 1;
         const int gi = nc / gw, gj = nc - gi * gw, qp = q / p, pq = q - qp * p, c = qp / p, ph = qp - c * p;
         const int64_t at = (static_cast<int64_t>(c) * H + gi * p + ph) * W + gj * p + pq, latent = static_cast<int64_t>(C) * H * W;
-        const int step = blockDim.x / (kPeTok * 16);
-        for (int sb = threadIdx.x / (kPeTok * 16); sb < nb; sb += 4 * step) {
-            float v[4];
+        for (; sb < nb; sb += kAhead * step) {
+            float v[kAhead];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kAhead; ++u) {
                 const int s1 = sb + u * step < nb ? sb + u * step : nb - 1;
                 v[u] = x[static_cast<uint32_t>(b0 + s1) % static_cast<uint32_t>(x_mod) * latent + at];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < kAhead; ++u)
                 if (sb + u * step < nb) patch[sb + u * step][tk][q] = n < ntok ? v[u] : 0.f;
         }
     }
@@ -1127,14 +1128,23 @@ template <typename FT>
 static int32_t launch_patch_embed16v(const float* x, int32_t x_mod, int32_t B, int32_t C, int32_t H, int32_t W, int32_t p,
                                      int32_t D, const float* pw, const float* pb, const float* pos, void* out, const float* feat,
                                      float* zero_out, hipStream_t s) {
-    // Fewer workgroups than CUs: the columns over several, of one wavefront each.  Every weight load of a wavefront touches 64 lines (a
+    // Few tokens: the columns over several workgroups, of one wavefront each.  Every weight load of a wavefront touches 64 lines (a
     // thread's four rows are 256 bytes), which for all columns is 2 us of line lookups in the CU that has them.  (The weights through
-    // LDS instead, whole lines per load: 2 x 1024 tokens 1.6 % of a drafting round slower.)
+    // LDS instead, whole lines per load: 2 x 1024 tokens 1.6 % of a drafting round slower.)  Each of them gathers the pixels of all its
+    // samples by itself, so that it pays for few samples, and for few workgroups as a whole.  us per launch, all columns / columns over
+    // several, at width 1152, 768, 384:
+    //   256 tokens   1 sample 4.8 / 4.0, 4.2 / 3.9, 4.1 / 3.6     4 samples 8.5 / 7.2, 7.6 / 7.0, 7.0 / 6.7     8 samples 12.1 / 11.8, 13.8 / 13.7, 11.1 / 11.7
+    //   400 tokens   1 sample 4.8 / 4.4, 4.9 / 4.7, 4.3 / 4.2     4 samples 9.0 / 7.6, 9.8 / 9.4, 7.4 / 7.2     8 samples 14.1 / 14.3, 15.4 / 16.1, 13.3 / 13.2
+    //   961 tokens   1 sample 5.4 / 6.0, 5.4 / 5.6, 4.6 / 4.8     2 samples 7.1 / 8.0, 8.8 / 9.0, 5.8 / 5.9
+    // and 16 x 256 tokens 24 / 28, 23 / 26, 20.5 / 21; 4 tokens of 16 samples 17.5 / 19, 16.6 / 17.3, 16.5 / 18.
     const int ntok = (H / p) * (W / p), bx = (ntok + kPeTok - 1) / kPeTok, by = (B + kPeSamples - 1) / kPeSamples;
-    const bool narrow = static_cast<int64_t>(bx) * by < device_cus();
-    const int threads = narrow ? kPeTok * 16 : kPeThreads, bz = narrow ? (D / 4 + 63) / 64 : 1;
-    hipLaunchKernelGGL(patch_embed16v_kernel<FT>, dim3(bx, by, bz), dim3(threads), 0, s, x, x_mod, B, C, H, W, p, D, pw, pb, pos, out,
-                       ntok, feat, zero_out);
+    const int bz = (D / 4 + 63) / 64, cus = device_cus();
+    const bool narrow = bx <= 3 * cus / 4 && B <= (bz > 2 ? 8 : 4) && bx * B <= 2 * cus;
+#define FREE_PE(GROUP, Z) \
+    hipLaunchKernelGGL((patch_embed16v_kernel<FT, GROUP>), dim3(bx, by, Z), dim3(GROUP), 0, s, x, x_mod, B, C, H, W, p, D, pw, pb, pos, out, ntok, feat, zero_out)
+    if (narrow) FREE_PE(64, bz);
+    else FREE_PE(kPeThreads, 1);
+#undef FREE_PE
     return launch_ok() ? FREE_OK : FREE_ERR_HIP;
 }
 

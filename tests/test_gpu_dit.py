@@ -136,6 +136,25 @@ def test_forward_parity_standard_widths(hidden, heads, learn_sigma):
     model.close()
 
 
+# 99 tokens of 4 samples, 35 of 8: the embedding's columns over several workgroups; 1089 tokens (no multiple of the tokens of a workgroup),
+# 9 and 17 samples: all of them in one, the last with a second block of samples
+@pytest.mark.parametrize("mode", ["fp32", "bf16"])
+@pytest.mark.parametrize("lat_h,lat_w,B,hidden", [(18, 22, 4, 64), (66, 66, 1, 64), (66, 66, 17, 64), (10, 14, 8, 768), (10, 14, 9, 768)])
+def test_patch_embedding_edges(lat_h, lat_w, B, hidden, mode):
+    from paper_2511_20390_amd import binding
+    cfg = synth.dit_config("tiny", lat_h=lat_h, lat_w=lat_w, hidden=hidden, heads=hidden // 64, mlp_hidden=2 * hidden, depth=1)
+    w = pu.weights_for(cfg, mode, seed=51)
+    model = binding.FreeDit(cfg, w, mode)
+    rng = np.random.default_rng(52)
+    x = rng.standard_normal((B, cfg["in_ch"], lat_h, lat_w)).astype(np.float32)
+    t, y = (rng.integers(0, n, B).astype(np.int32) for n in (1000, cfg["num_classes"] + 1))
+    eps, feat = model.dit_forward_packed(*(pu.to_dev(v) for v in (x, t, y)), want_feat=True)
+    ref_eps, ref_feat = fo.dit_forward(w, cfg, x, t, y)
+    assert pu.rel_l2(eps.cpu().numpy(), ref_eps) <= pu.DIT_REL_L2[mode]
+    assert pu.row_rel_l2(feat.cpu().numpy(), ref_feat, hidden) <= pu.ROW_REL_L2[mode]
+    model.close()
+
+
 @pytest.mark.parametrize("mode", ["fp32", "bf16"])
 def test_forward_adaln_zero_blocks_are_identity(mode):
     """With zero modulation the GPU blocks must leave the token stream untouched:

@@ -43,10 +43,12 @@ def test_drafter_forward_parity(name, B, depth, mode):
 
 
 @pytest.mark.parametrize("mode", ["fp32", "bf16"])
-@pytest.mark.parametrize("lat_h,lat_w,B,hidden", [(18, 22, 17, 64), (2, 6, 1, 64), (6, 10, 3, 1280)])
+@pytest.mark.parametrize("lat_h,lat_w,B,hidden", [(18, 22, 17, 64), (2, 6, 1, 64), (6, 10, 3, 1280), (18, 22, 4, 64), (66, 66, 1, 64), (66, 66, 17, 64),
+                                                  (10, 14, 8, 768), (10, 14, 9, 768)])
 def test_drafter_embedding_edges(lat_h, lat_w, B, hidden, mode):
     """The patch embedding and the features go to the fusion layer in one launch: token counts that are no multiple of the tokens
-    of a workgroup, more samples than one workgroup takes, the widest rows.  The forward's tolerance."""
+    of a workgroup, more samples than one workgroup takes, the widest rows.  Few tokens of few samples have their columns over several
+    workgroups, 1089 tokens, 9 and 17 samples all of them in one.  The forward's tolerance."""
     from paper_2511_20390_amd import binding
     cfg = synth.dit_config("tiny", lat_h=lat_h, lat_w=lat_w, hidden=hidden, heads=hidden // 64 or 1, mlp_hidden=2 * hidden, depth=1)
     w, wd = pu.weights_for(cfg, mode, seed=6), synth.make_drafter_weights(cfg, 1, seed=7, bf16_values=(mode == "bf16"))
