@@ -11,6 +11,8 @@
 // fp32 weights (FREE_FP32 mode) take the same route with v_mfma_f32_16x16x4_f32: a lane's 16 bytes are four
 // consecutive k of its row and feed four products, the activation operand is 16 bytes of the fp32 vector in LDS
 // at the same offset (lane group q of product j contracts k = 16 s + 4 q + j on both sides).
+#include <algorithm>
+
 #include "free_internal.h"
 
 namespace freemi {
@@ -201,14 +203,24 @@ int32_t launch_adaln_mfma(const float* sc, int32_t B, int32_t D, const void* con
     // about 16 wavefronts per CU at the DiT-XL size (12096 row blocks): measured best among 2, 3, 6, 12
     const int blocks_per_wave = nblocks >= 8192 ? 3 : 1;
     const int waves = (nblocks + blocks_per_wave - 1) / blocks_per_wave;
-    // Eight wavefronts per workgroup, or two where eight would leave half of the CUs without one: a CU takes in 46 KB/us from HBM, a
-    // workgroup of two stages the activations in more round trips.  One block at width 1152 (576 wavefronts) 14.4 -> 9.5 us for 4
-    // samples, 13.8 -> 11.3 for 12; twelve blocks at width 384 (1776) 9.0 with eight, 10.2 with two.
-    const bool narrow = waves < 4 * device_cus();
-    const int per_group = narrow ? 2 : 8, grid = (waves + per_group - 1) / per_group;
     const int el = f32 ? 4 : 2;
     const int steps = D * el / 64;
     const bool exact = steps >= 2 * kChunk && steps % (2 * kChunk) == 0;
+    auto staged = [&](int nb) { return (f32 ? 1 : 2) * static_cast<size_t>(nb) * (D * el + 16); };
+    // Eight wavefronts per workgroup, or two where eight would leave half of the CUs without one: a CU takes in 46 KB/us from HBM, a
+    // workgroup of two stages the activations in more round trips.  One block at width 1152 (576 wavefronts) 14.4 -> 9.5 us for 4
+    // samples, 13.8 -> 11.3 for 12; twelve blocks at width 384 (1776) 9.0 with eight, 10.2 with two.  Not where the CUs cannot hold all
+    // workgroups of two at once (one block at width 1280, 16 samples of 82 KB: 15.2 us with eight, 24.8 with two; fp32 24.7, 51.2), nor
+    // where the staging takes longer than the spread saves: samples x width x wavefronts above a figure fitted to, us with eight / two,
+    //   fp32, two blocks at width 1152: 4 samples 21.4 / 17.3, 8 21.4 / 20.4, 12 21.3 / 22.6, 16 21.4 / 24.5; one block 16 samples 21.2 / 22.2;
+    //         three at 768: 12 samples 15.9 / 14.7, 16 15.9 / 16.6; six at 384: 16 samples 11.0 / 10.1
+    //   fp32, widths whose rows are no whole number of register sets: one block at 1024 4 samples 19.6 / 17.1, 8 19.6 / 18.6, 12 19.6 / 21.3, two
+    //         blocks 4 19.9 / 19.7, 8 20.0 / 22.2; 640 one block 12 samples 14.4 / 13.8, 16 14.5 / 15.4, two 4 14.6 / 13.5, 8 14.6 / 14.9
+    //   bf16, such widths: two blocks at 1024 8 samples 12.9 / 12.0, 12 11.9 / 12.2, 16 12.4 / 12.8; one block 16 12.0 / 11.6
+    const int nb0 = std::min(B, kBatch), cus = device_cus();
+    const int64_t most = exact ? (f32 ? 10500000 : INT64_MAX) : (f32 ? 3000000 : 10500000);
+    const bool narrow = waves < 4 * cus && (waves <= 2 * cus || 2 * staged(nb0) <= 160 * 1024) && static_cast<int64_t>(nb0) * D * waves <= most;
+    const int per_group = narrow ? 2 : 8, grid = (waves + per_group - 1) / per_group;
     using kernel_t = void (*)(const float*, int32_t, int32_t, const void* const*, const float* const*, const int32_t*,
                               int32_t, int32_t, int32_t, float*);
     static const kernel_t kernels[8] = {adaln_mfma_kernel<false, false, 8>, adaln_mfma_kernel<true, false, 8>,
@@ -221,8 +233,7 @@ int32_t launch_adaln_mfma(const float* sc, int32_t B, int32_t D, const void* con
     if (!limit[which].allow(reinterpret_cast<const void*>(kernel), 150 * 1024)) return FREE_ERR_HIP;
     for (int b0 = 0; b0 < B; b0 += kBatch) {
         const int nb = (B - b0 < kBatch) ? B - b0 : kBatch;
-        const size_t lds = (f32 ? 1 : 2) * static_cast<size_t>(nb) * (D * el + 16);
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * per_group), lds, s, sc + static_cast<int64_t>(b0) * D,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * per_group), staged(nb), s, sc + static_cast<int64_t>(b0) * D,
                            nb, D, w_tab, b_tab, row_start, n_mats, total_rows, blocks_per_wave,
                            mod + static_cast<int64_t>(b0) * total_rows);
         if (!launch_ok()) return FREE_ERR_HIP;

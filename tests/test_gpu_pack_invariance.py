@@ -110,14 +110,16 @@ def test_forced_streams_change_no_bit_of_small_batches():
 
 
 # the conditioning's linear layers take four or eight samples per pass and one to five pieces of a row at once: rows of one piece, of a whole
-# number of pieces, of more than one pass; the modulation's and the embedding's launches go by the samples too (17: two modulation passes)
+# number of pieces, of more than one pass; the modulation's and the embedding's launches go by the samples too (17: two
+# modulation passes; larger workgroups from 10 samples on in fp32 at two blocks of width 1152, at width 1280 from 16 on and in fp32 from 4)
 @pytest.mark.parametrize("mode", ["bf16", "fp32"])
-@pytest.mark.parametrize("hidden,heads,t_freq", [(384, 6, 256), (512, 8, 64), (576, 8, 260), (1152, 16, 256), (2048, 16, 256)])
-def test_small_packs_of_every_size_same_bits(hidden, heads, t_freq, mode):
+@pytest.mark.parametrize("hidden,heads,t_freq,depth", [(384, 6, 256, 1), (512, 8, 64, 1), (576, 8, 260, 1), (1152, 16, 256, 1), (1152, 16, 256, 2),
+                                                       (1280, 20, 256, 1), (2048, 16, 256, 1)])
+def test_small_packs_of_every_size_same_bits(hidden, heads, t_freq, depth, mode):
     import torch
     from oracle import free_oracle as fo
     from paper_2511_20390_amd import binding
-    cfg = synth.dit_config("tiny", hidden=hidden, heads=heads, mlp_hidden=2 * hidden, depth=1, lat_h=2, lat_w=6, t_freq_dim=t_freq)
+    cfg = synth.dit_config("tiny", hidden=hidden, heads=heads, mlp_hidden=2 * hidden, depth=depth, lat_h=2, lat_w=6, t_freq_dim=t_freq)
     w = pu.weights_for(cfg, mode, 21)
     model = binding.FreeDit(cfg, w, mode)
     rng = np.random.default_rng(22)
