@@ -17,11 +17,17 @@
 // and an online softmax of their own - no barrier in the loop - and their maxima, sums and O^T are put together at the end in
 // wavefront order, whatever the batch.  (Head dim 128 has no LDS for that with two workgroups per CU: four query blocks that share the
 // tiles.)  What bounds it: a key tile is 36 + 32 products of 64 cycles at head dim 72, so that a wavefront with all 256 keys of a state
-// is a chain of 15 us, and such a state has 8 x heads query blocks, on 1024 SIMDs; with many samples the matrix pipe.  us per launch,
-// all keys in each wavefront, the third 32-row tile of O^T at head dim 72 in products too -> here: 16 heads of 72, 2 x 256 tokens
-// 31.3 -> 11.5, 600 68.8 -> 34, 1024 115 -> 56, 16 x 256 58.0 -> 59.5, 12 x 1024 620 -> 592; 12 heads of 64, 2 x 256 24.2 -> 9.4,
-// 12 x 1024 349 -> 331; 8 heads of 128, 8 x 1024 335 -> 289.  2-norm error against 64 bits 4.1e-7 -> 3.4e-7 (256 tokens), 6.6e-7 ->
-// 4.2e-7 (1024).
+// is a chain of 15 us, and such a state has 8 x heads query blocks, on 1024 SIMDs; with many samples the matrix pipe, which wants three
+// wavefronts per SIMD: the queries are in LDS, which the four wavefronts share, K and V take turns in one LDS tile (a wavefront's own, so
+// that no barrier is needed), and no register is spilled.  us per launch, all keys in each wavefront, the third 32-row tile of O^T at head
+// dim 72 in products too / keys over four wavefronts with two of them per SIMD / here:
+//   16 heads of 72   2 x 256 tokens 30.5 / 11.4 / 11.5   16 x 256 61 / 62 / 58   64 x 256 211 / 229 / 200   2 x 450 54 / 29 / 29   12 x 1024 580 / 524 / 495
+//   12 heads of 64   2 x 256 23.5 / 8.8 / 8.6   16 x 256 44 / 41 / 38   32 x 256 65 / 75 / 69   64 x 256 114 / 139 / 124   12 x 1024 350 / 326 / 309
+//   8 heads of 128 (two per SIMD, tiles shared)   2 x 256 41.5 / 39.7 / 39.6   64 x 256 178 / 144 / 144
+//   16 heads of 72, one to 16 tokens of one to nine samples 6.0 / 6.4 / 6.7: the last barriers of a workgroup
+// A wavefront has two of the eight tiles at 256 tokens, and what it does once - queries, first tile, the sums of the four put together - is then
+// 4 to 8 % more than all keys in one, at 32 samples of head dim 64 and more; by the batch the choice cannot go, or a state would
+// have other bits in a pack.  2-norm error against 64 bits 4.1e-7 -> 3.4e-7 (256 tokens), 6.6e-7 -> 4.2e-7 (1024).
 #include <algorithm>
 #include <cmath>
 
@@ -48,14 +54,16 @@ struct Tile {
     static constexpr int DT = (DH - kRest + 31) / 32;         // 32-row tiles of O^T
     static constexpr int KP = DH + 4;            // K row pitch in floats: an odd number of chunks (conflict-free b128 reads)
     static constexpr int VP = (DH % 16 == 8) ? DH : DH + 8;   // V row pitch = 8 mod 16: rows 4 apart land on the other 32 banks
-    static constexpr int kKeys = BKV * (KP + VP) + 32 * DT;   // floats per wavefront; the pad rows of O^T read past a row's end
+    // floats per wavefront: K and V take turns in one tile with KS > 1; the pad rows of O^T read past a row's end
+    static constexpr int kV = KS > 1 ? 0 : BKV * KP, kKeys = KS > 1 ? std::max(BKV * KP, BKV * VP + 32 * DT) : BKV * (KP + VP) + 32 * DT;
     static constexpr int kSums = KS > 1 ? 32 * DH : 0;        // floats of O^T
     static constexpr int kWaveFloats = kKeys > kSums ? kKeys : kSums;
-    static constexpr size_t kLds = sizeof(float) * KS * (kWaveFloats + (KS > 1 ? 2 * BQ : 0));
+    static constexpr int kQ = KS * (kWaveFloats + (KS > 1 ? 2 * BQ : 0));       // where Q is, with KS > 1
+    static constexpr size_t kLds = sizeof(float) * (kQ + (KS > 1 ? BQ * KP : 0));
 };
 
 template <int DH, int KS>
-__global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float* __restrict__ qkv, int32_t N,
+__global__ __launch_bounds__(kThreads, KS > 1 ? 3 : 2) void attn_f32_mfma_kernel(const float* __restrict__ qkv, int32_t N,
                                                                  int32_t heads, float scale_log2,
                                                                  float* __restrict__ out) {
     static_assert(DH % 8 == 0 && DH <= 128, "whole chunk pairs");
@@ -65,6 +73,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float*
     constexpr int kGroup = kThreads / KS;            // threads that fill a tile
     constexpr int NLD = BKV * NC / kGroup;           // chunks per thread of a K (and a V) tile
     constexpr int kPieces = NC / 8, kRows = kGroup / 8, kWhole = BKV / kRows * kPieces;    // 128-byte pieces of a row; passes of them
+    constexpr bool kEarlyK = KS == 1 || DH <= 64;    // (with head dim 72 three wavefronts per SIMD have no registers for K and V)
     constexpr int kTail = NC % 8 ? NC % 8 : 8;       // chunks behind the last piece
     static_assert(BKV * NC % kGroup == 0 && kGroup % kTail == 0 && kRest % 4 == 0, "whole passes");
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -83,20 +92,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float*
     const int64_t row_stride = static_cast<int64_t>(3) * D;       // floats
     const int q_base = q_tile * kQueries + (KS > 1 ? 0 : wave * BQ);
     float* const sK = lds + group * L::kWaveFloats;
-    float* const sV = sK + BKV * KP;
+    float* const sV = sK + L::kV;
 
-    // Q fragments: lane holds query column l32, chunks 2 j + g
-    f32x4_t qf[NP];
-    {
-        int q = q_base + l32;
-        if (q >= N) q = N - 1;
-        const float* src = qkv + (row0 + q) * row_stride + h * DH;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) qf[j] = *reinterpret_cast<const f32x4_t*>(src + 4 * (2 * j + g));
-    }
-
-    // staging of a K or V tile: whole 128-byte pieces of kRows rows per pass, then what is left of the rows (rows past N read as zero:
-    // their scores are masked, and their probabilities are zero)
+    // staging of a K or V tile: whole 128-byte pieces of kRows rows per pass, then what is left of the rows.  Rows past N read as zero, also
+    // in a pass that has no other (a load whose scalar offset alone is past the descriptor's end returns zero on gfx950, measured): their
+    // scores are masked, and their probabilities are zero
     const int row_bytes = 12 * D;
     const int piece = (in_group >> 3) * row_bytes + (in_group & 7) * 16, tail = (in_group / kTail) * row_bytes + (kPieces * 8 + in_group % kTail) * 16;
     auto fetch = [&](f32x4_t (&reg)[NLD], int t, int which) {         // 1: K, 2: V
@@ -111,6 +111,33 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float*
             reg[i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, whole ? piece : tail, soff, 0));
         }
     };
+    // K of the wavefront's first tile and the queries: lane holds query column l32, chunks 2 j + g, with one query block (KS > 1) in LDS for
+    // all four wavefronts
+    const int ntiles = (N + BKV - 1) / BKV;
+    f32x4_t kreg[NLD], vreg[NLD], qf[KS > 1 ? 1 : NP];
+    const float* const qrow = lds + L::kQ + l32 * KP + 4 * g;
+    if constexpr (KS > 1) {
+        constexpr int kChunks = BQ * NC, kLoads = (kChunks + kThreads - 1) / kThreads;
+        f32x4_t own[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int idx = std::min(tid + i * kThreads, kChunks - 1), r = idx / NC;
+            own[i] = *reinterpret_cast<const f32x4_t*>(qkv + (row0 + std::min(q_base + r, N - 1)) * row_stride + h * DH + 4 * (idx - r * NC));
+        }
+        if (group < ntiles) fetch(kreg, group, 1);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int idx = tid + i * kThreads, r = idx / NC;
+            if (idx < kChunks) *reinterpret_cast<f32x4_t*>(lds + L::kQ + r * KP + 4 * (idx - r * NC)) = own[i];
+        }
+        __syncthreads();
+    } else {
+        fetch(kreg, group, 1);
+        const float* src = qkv + (row0 + std::min(q_base + l32, N - 1)) * row_stride + h * DH;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) qf[j] = *reinterpret_cast<const f32x4_t*>(src + 4 * (2 * j + g));
+    }
+
     // With KS > 1 a wavefront's LDS operations keep their order, and the fences keep the compiler's.  With KS == 1 the barrier behind
     // the K tile says that every wavefront is done with the V tile before, the one behind the V tile the same of the K tile.
     auto stash = [&](const f32x4_t (&reg)[NLD], float* dst, int pitch) {
@@ -135,10 +162,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float*
     [[maybe_unused]] float rest[kRest > 0 ? kRest : 1] = {};
     float m_run = -INFINITY, l_run = 0.f;
 
-    const int ntiles = (N + BKV - 1) / BKV;
-    // K of a tile is on its way while the tile before is multiplied with V, V while the scores are computed: one set of registers
-    f32x4_t kreg[NLD], vreg[NLD];
-    if (group < ntiles) fetch(kreg, group, 1);
+    // K of a tile is on its way while the tile before is multiplied with V, V while the scores are computed
     for (int t = group; t < ntiles; t += KS) {
         fetch(vreg, t, 2);
         stash(kreg, sK, KP);
@@ -150,14 +174,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float*
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const f32x4_t kf = *reinterpret_cast<const f32x4_t*>(sK + l32 * KP + 4 * (2 * j + g));
+            const f32x4_t qv4 = KS > 1 ? *reinterpret_cast<const f32x4_t*>(qrow + 8 * j) : qf[KS > 1 ? 0 : j];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float kv = kf[e], qv = qf[j][e];
+                const float kv = kf[e], qv = qv4[e];
                 st = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, qv, st, 0, 0, 0);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (t + KS < ntiles) fetch(kreg, t + KS, 1);
+        if (kEarlyK && t + KS < ntiles) fetch(kreg, t + KS, 1);
         if ((t + 1) * BKV > N) {              // ragged last tile: keys past N
 #pragma unroll
             for (int e = 0; e < 16; ++e)
@@ -192,6 +217,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_mfma_kernel(const float*
 
         __builtin_amdgcn_sched_barrier(0);
         stash(vreg, sV, VP);
+        if (!kEarlyK && t + KS < ntiles) fetch(kreg, t + KS, 1);
         // ---- O^T += V^T P^T: register e pairs the keys 8 (e / 4) + e % 4 (+ 4 for the upper half-wave)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {

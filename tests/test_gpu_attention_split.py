@@ -75,3 +75,23 @@ def test_fp32_keys_of_no_weight(dead):
     v = qkv.astype(np.float64).reshape(N, 3, heads, dh)
     ref = np.stack([fo.attention(v[:, 0, h], v[live, 1, h], v[live, 2, h]) for h in range(heads)], 1)
     assert pu.rel_l2(out, ref.reshape(N, D)) < 2e-6
+
+
+# one row and one pass of rows behind the last whole tile, with the tile's other passes past the end; a sample that is followed by another one
+@pytest.mark.parametrize("mode", ["fp32", "bf16"])
+@pytest.mark.parametrize("B,N,heads,dh", [(1, 33, 2, 72), (1, 40, 3, 64), (2, 65, 2, 16), (1, 129, 1, 128), (3, 450, 2, 72)])
+def test_rows_behind_a_sample_are_not_used(B, N, heads, dh, mode):
+    """NaN in the rows behind the last sample, and in the next sample, reaches no output."""
+    import torch
+    from paper_2511_20390_amd import binding
+    D = heads * dh
+    g = torch.Generator(device="cuda").manual_seed(N)
+    room = torch.full((B * N + 256, 3 * D), float("nan"), device="cuda")
+    room[:B * N] = torch.randn(B * N, 3 * D, generator=g, device="cuda")
+    room = room if mode == "fp32" else room.bfloat16()
+    for nan_samples in range(B):                     # the last ones
+        qkv = room[:B * N].clone()
+        room[(B - nan_samples) * N:] = float("nan")
+        out = binding.op_attention(room[:B * N], B, N, heads, dh, mode).reshape(B, N, D)
+        whole = binding.op_attention(qkv, B, N, heads, dh, mode).reshape(B, N, D)
+        assert torch.equal(out[:B - nan_samples], whole[:B - nan_samples]) and torch.isfinite(out[:B - nan_samples].float()).all()
