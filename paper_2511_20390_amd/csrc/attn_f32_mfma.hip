@@ -23,10 +23,11 @@
 // dim 72 in products too / keys over four wavefronts with two of them per SIMD / here:
 //   16 heads of 72   2 x 256 tokens 30.5 / 11.4 / 11.5   16 x 256 61 / 62 / 58   64 x 256 211 / 229 / 200   2 x 450 54 / 29 / 29   12 x 1024 580 / 524 / 495
 //   12 heads of 64   2 x 256 23.5 / 8.8 / 8.6   16 x 256 44 / 41 / 38   32 x 256 65 / 75 / 69   64 x 256 114 / 139 / 124   12 x 1024 350 / 326 / 309
+//   16 heads of 64   8 x 256 30 / 32 / 33.5 (1024 workgroups on 256, 512, 768 places)
 //   8 heads of 128 (two per SIMD, tiles shared)   2 x 256 41.5 / 39.7 / 39.6   64 x 256 178 / 144 / 144
 //   16 heads of 72, one to 16 tokens of one to nine samples 6.0 / 6.4 / 6.7: the last barriers of a workgroup
 // A wavefront has two of the eight tiles at 256 tokens, and what it does once - queries, first tile, the sums of the four put together - is then
-// 4 to 8 % more than all keys in one, at 32 samples of head dim 64 and more; by the batch the choice cannot go, or a state would
+// 4 to 8 % more than all keys in one, at 32 samples of head dim 64 and more, 12 % there; by the batch the choice cannot go, or a state would
 // have other bits in a pack.  2-norm error against 64 bits 4.1e-7 -> 3.4e-7 (256 tokens), 6.6e-7 -> 4.2e-7 (1024).
 #include <algorithm>
 #include <cmath>

@@ -10,8 +10,11 @@
 // activations lose nothing that matters against the fp32 accumulation; weight rows are the A
 // operand, read from global memory (L2) in operand layout.  The four partial 32 x 16 products are
 // added through LDS and scattered to the image layout.
-// With fp32 weights the same pieces feed v_mfma_f32_16x16x4_f32, eight per k-step and output tile (2 x 256 rows of 1152 43 -> 11 us
-// against the kernel of one wavefront per row).
+// With fp32 weights the same pieces feed v_mfma_f32_16x16x4_f32, eight per k-step and output tile (2 x 256 rows of 1152 35 -> 11.6 us
+// against the kernel of one wavefront per row, 12 x 1024 rows 122 -> 30).  The instruction adds its products one after the other, so that
+// all of a wavefront's in one accumulator are a chain of 288 roundings; two instructions at a time and their sums pair by pair are
+// as short a chain as the other kernel's: 2-norm error against 64 bits at width 384 / 768 / 1024 / 1152 one wavefront per row 1.30e-7 /
+// 1.29e-7 / 1.19e-7 / 1.40e-7, one accumulator 2.2e-7 / 2.9e-7 / 3.1e-7 / 3.5e-7 (10.6 us), here 1.29e-7 / 1.28e-7 / 1.15e-7 / 1.33e-7.
 //
 // The per-row kernel this replaces re-read the whole weight matrix (74 KB) from cache for every
 // token row and reduced each of the 32 outputs across the wavefront separately: 120 us at 12288
@@ -29,6 +32,29 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float float8_t __attribute__((ext_vector_type(8), aligned(16)));
+
+// Sum of N values added pair by pair, pairs pair by pair, ...: a value passes log2 N roundings instead of up to N.  add() in order, i known
+// at compile time.
+template <int N, typename T>
+struct PairSum {
+    T level[32 - __builtin_clz(N)] = {};           // level l: 2^l values, where bit l of the number of values is set
+    __device__ __forceinline__ void add(int i, T v) {
+        int l = 0;
+        for (; (i >> l) & 1; ++l) v = level[l] + v;
+        level[l] = v;
+    }
+    __device__ __forceinline__ T result() const {
+        T v = {};
+        bool first = true;
+#pragma unroll
+        for (int l = 0; l < 32 - __builtin_clz(N); ++l) {
+            if (!((N >> l) & 1)) continue;
+            v = first ? level[l] : level[l] + v;
+            first = false;
+        }
+        return v;
+    }
+};
 
 constexpr int kThreads = 256;
 constexpr int kRows = 16;                 // token rows per workgroup (the N dimension of the MFMA)
@@ -97,25 +123,28 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
         __syncthreads();
         return (red[slot][0][l16] + red[slot][1][l16]) + (red[slot][2][l16] + red[slot][3][l16]);
     };
-    float sum = 0.f;
+    // this lane's pieces of a sum: one after the other, in fp32 pair by pair (PairSum)
+    auto lane_total = [&](auto&& piece) {
+        std::conditional_t<kF32, PairSum<2 * NS, float>, float> total{};
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) sum += (xa[s][h][0] + xa[s][h][1]) + (xa[s][h][2] + xa[s][h][3]);
-    const float mean = row_total(sum, 0) / static_cast<float>(D);
-    float q = 0.f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float a = xa[s][h][0] - mean, b = xa[s][h][1] - mean, c = xa[s][h][2] - mean, d = xa[s][h][3] - mean;
-            q += (a * a + b * b) + (c * c + d * d);
+        for (int j = 0; j < 2 * NS; ++j) {
+            if constexpr (kF32) total.add(j, piece(xa[j >> 1][j & 1]));
+            else total += piece(xa[j >> 1][j & 1]);
         }
+        if constexpr (kF32) return total.result();
+        else return total;
+    };
+    const float mean = row_total(lane_total([](const f32x4_t& v) { return (v[0] + v[1]) + (v[2] + v[3]); }), 0) / static_cast<float>(D);
+    const float q = lane_total([&](const f32x4_t& v) {
+        const float a = v[0] - mean, b = v[1] - mean, c = v[2] - mean, d = v[3] - mean;
+        return (a * a + b * b) + (c * c + d * d);
+    });
     const float rstd = rsqrtf(row_total(q, 1) / static_cast<float>(D) + kLnEps);
 
     const float* shr = shift.base + static_cast<int64_t>(row / shift.rows_per_sample) * shift.stride + k0;
     const float* scr = scale.base + static_cast<int64_t>(row / scale.rows_per_sample) * scale.stride + k0;
     f32x4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    [[maybe_unused]] PairSum<4 * NS, f32x4_t> sums[2];       // fp32: of eight products each, see below
     // k-steps in groups of kG: the shift, scale and weight pieces of a whole group are requested together and
     // only then used - one memory round trip per group on the critical path of the workgroup instead of two per
     // k-step (left to itself the compiler keeps 72 registers and waits for every piece where it is used)
@@ -153,11 +182,14 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
             if constexpr (kF32) {
                 // element e: the four lane groups hold four k of one product
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
+                for (int e = 0; e < 8; e += 2)
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
-                        const float a = wv[u][t][e];
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(16 * t + l16 < P ? a : 0.f, v[e], acc[t], 0, 0, 0);
+                        const float a0 = wv[u][t][e], a1 = wv[u][t][e + 1];
+                        const bool on = 16 * t + l16 < P;
+                        f32x4_t r = __builtin_amdgcn_mfma_f32_16x16x4f32(on ? a0 : 0.f, v[e], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                        r = __builtin_amdgcn_mfma_f32_16x16x4f32(on ? a1 : 0.f, v[e + 1], r, 0, 0, 0);
+                        sums[t].add(4 * s + e / 2, r);
                     }
             } else {
                 uint32_t hi[4], lo[4];
@@ -178,18 +210,19 @@ __global__ __launch_bounds__(kThreads) void final_layer_mfma_kernel(
             }
         }
     }
+    if constexpr (kF32) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = sums[t].result();
+    }
     // accumulator register i of lane l: output 16 t + 4 (l / 16) + i, token row l % 16
 #pragma unroll
     for (int t = 0; t < 2; ++t) *reinterpret_cast<f32x4_t*>(part[wave][t][lane]) = acc[t];
     __syncthreads();
     if (wave < 2) {
-        f32x4_t v = *reinterpret_cast<const f32x4_t*>(part[0][wave][lane]);
+        f32x4_t from[4], v;
 #pragma unroll
-        for (int wv = 1; wv < 4; ++wv) {
-            const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part[wv][wave][lane]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] += u[i];
-        }
+        for (int wv = 0; wv < 4; ++wv) from[wv] = *reinterpret_cast<const f32x4_t*>(part[wv][wave][lane]);
+        v = kF32 ? (from[0] + from[1]) + (from[2] + from[3]) : ((from[0] + from[1]) + from[2]) + from[3];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float e = v[i] + bias_out[i];
