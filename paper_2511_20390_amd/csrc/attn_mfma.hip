@@ -107,8 +107,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DH <= 
 
     // The first K/V tile and Q are requested before anything else: a launch of one workgroup per CU is a chain of waits, and the
     // larger ones begin every round of workgroups with it.  Same bits; us per launch with the pads written first -> now: 16 heads
-    // of 72, 2 x 256 rows 9.3 -> 8.2, 8 x 256 11.0 -> 10.0, 12 x 1024 94 -> 85; 6 heads of 64, 5 x 450 12.6 -> 11.5; 2 of 128, 256 rows
-    // 11.8 -> 10.1.
+    // of 72, 2 x 256 rows 8.8 -> 7.8, 8 x 256 10.3 -> 9.3, 32 x 256 27.3 -> 25.4, 12 x 1024 81.2 -> 79.1, 9 x 1089 84.6 -> 81.9; 6 heads of
+    // 64, 5 x 450 11.6 -> 10.4; 2 of 128, 256 rows 11.8 -> 10.1.
     //
     // global -> register staging of one K/V tile: thread chunk idx = tid + 256 i -> key row idx / DCH,
     // 16-byte chunk idx % DCH of that row, for K and for V alike (lanes walk the chunks of a row).

@@ -1195,8 +1195,9 @@ int32_t drafter_modulation(free_drafter_t dr, const CondIn& cond, int32_t B, flo
                         d.mode, mod, s);
 }
 
-// mod_pre (nullable): modulation vectors computed by the caller, sample b at mod_pre + b * mod_stride; then t
-// and y are not read.  mean (nullable): instead of the noise estimates, which then only eps_out may hold.
+// mod_pre (nullable): modulation vectors computed by the caller, sample b at mod_pre + b * mod_stride; then cond
+// is not read.  mean (nullable): the step's mean and next draft are written in place of the noise estimates; eps_out is then room for the
+// estimates, which the output layer of other widths than the matrix cores' leaves there for the launch that computes the mean from them.
 int32_t drafter_forward_impl(free_drafter_t dr, const float* x, int32_t x_mod, const float* f_prev, const CondIn& cond,
                              int32_t B, float* eps_out, float* f_out, char* ws, hipStream_t s,
                              const float* mod_pre = nullptr, int32_t mod_stride = 0, const FinalMean* mean = nullptr) {

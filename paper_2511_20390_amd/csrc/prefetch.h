@@ -18,7 +18,8 @@ namespace freemi {
 // against 256 to 1024 rows).  LayerNorm and attention each contribute: 4 and 8 % of those 11 to 14.
 // A thread has two lines over both matrices (Prefetch::blocks), at most two of one and mostly no second round; its loads are in
 // flight together, and the share of a workgroup takes a 32-bit division per matrix (a wait behind every load and four 64-bit
-// divisions before: at 512 rows LayerNorm 6.15 -> 6.03, attention 12.0 -> 11.9 us).
+// divisions before: at 512 rows LayerNorm 6.15 -> 6.03, attention 12.0 -> 11.9 us).  Where a matrix is taken in parts of K, each of its
+// lines takes two more, in front of its load.
 __device__ inline void prefetch_lines(const Prefetch& pf, int first) {
     const uint32_t xcd = blockIdx.x & 7, rank = (blockIdx.x - first) >> 3, n = (gridDim.x - first) >> 3;
     const char* base[2];
